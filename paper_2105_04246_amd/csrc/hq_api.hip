@@ -1,6 +1,6 @@
 // C-ABI entry points of the hq library: argument checks, dispatch, and the small kernels
 // around the GEMMs (range update, statistics reset, dynamic-baseline middle and second
-// pass, weight-side preparation).
+// pass).
 #include "hq_device.h"
 #include "hq_internal.h"
 
@@ -127,48 +127,6 @@ __global__ __launch_bounds__(HQ_THREADS) void dynamic_pass2_kernel(const int32_t
     hq_block_stats_commit(INT_MAX, INT_MIN, nlo, nhi, st_out, red);
 }
 
-// Weight-side preparation: per-output-channel and per-input-channel code sums and the
-// [C][R][S][Cout] re-layout.  Small tensors, run once per weight update: plain kernels.
-__global__ void weight_rowsum_kernel(const int8_t *W, int rows, int len, int32_t *sum)
-{
-    // one wavefront per row
-    int row = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= rows) return;
-    int s = 0;
-    for (int i = lane; i < len; i += 64) s += W[(size_t)row * len + i];
-    s = hq_wave_reduce(s, HqAdd());
-    if (lane == 0) sum[row] = s;
-}
-
-__global__ void weight_colsum_kernel(const int8_t *W, int rows, int taps, int C, int32_t *sum)
-{
-    // sum over (row, tap) for each channel c of W[rows][taps][C]: a workgroup takes a slab of 64
-    // (row, tap) lines, a thread one channel of it; the slabs meet with one atomic per channel
-    // (sum is zeroed before the launch)
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= C) return;
-    const int lines = rows * taps, l0 = blockIdx.y * 64, l1 = min(lines, l0 + 64);
-    int s = 0;
-    for (int i = l0; i < l1; i++) s += W[(size_t)i * C + c];
-    if (s != 0) atomicAdd(sum + c, s);
-}
-
-__global__ void zero_words_kernel(int32_t *p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
-__global__ void weight_relayout_kernel(const int8_t *W, int Cout, int taps, int C, int8_t *Wd)
-{
-    // Wd[c][tap][n] = W[n][tap][c]
-    size_t total = (size_t)Cout * taps * C;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-        int n = (int)(i % Cout); size_t t = i / Cout; int tap = (int)(t % taps); int c = (int)(t / taps);
-        Wd[i] = W[((size_t)n * taps + tap) * C + c];
-    }
-}
-
 // ---------------------------------------------------------------------------------------
 // Argument checks
 // ---------------------------------------------------------------------------------------
@@ -197,42 +155,6 @@ size_t out_elems(const hq_problem *p, bool dgrad)
 {
     const size_t OH = (p->H + 2 * p->pad - p->R) / p->stride + 1, OW = (p->W + 2 * p->pad - p->S) / p->stride + 1;
     return dgrad ? (size_t)p->B * p->H * p->W * p->C : (size_t)p->B * OH * OW * p->Cout;
-}
-
-// Q_W: |w| maximum of an FP32 tensor into *bits (non-negative floats order like their bit patterns).
-__global__ __launch_bounds__(HQ_THREADS) void weight_absmax_kernel(const float *__restrict__ w, size_t n, unsigned *bits)
-{
-    __shared__ unsigned red[HQ_THREADS / 64];
-    unsigned m = 0;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        m = max(m, __float_as_uint(fabsf(w[i])));
-#pragma unroll
-    for (int k = 32; k >= 1; k >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, k));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int k = 1; k < HQ_THREADS / 64; k++) m = max(m, red[k]);
-        if (m) atomicMax(bits, m);
-    }
-}
-
-__global__ void weight_scale_init_kernel(hq_qparams *wq) { wq->zero_point = 0; }      // the maximum is gathered in this field
-
-__global__ void weight_scale_kernel(hq_qparams *wq)
-{
-    const float amax = __uint_as_float((unsigned)wq->zero_point);
-    wq->scale = amax > 0.0f ? __fdiv_rn(amax, 127.0f) : 1.0f;
-    wq->zero_point = 0;
-}
-
-__global__ __launch_bounds__(HQ_THREADS) void weight_quantize_kernel(const float *__restrict__ w, size_t n,
-                                                                     const hq_qparams *wq, int8_t *__restrict__ out)
-{
-    const float s = wq->scale;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const float r = fminf(fmaxf(rintf(__fdiv_rn(w[i], s)), -127.0f), 127.0f);
-        out[i] = (int8_t)(int)r;
-    }
 }
 
 // Register-only int8 MFMA loop: eight independent accumulator chains per wavefront, so that the
@@ -472,36 +394,13 @@ int hq_weight_prepare(const hq_problem *p, const int8_t *W, int8_t *Wd, int32_t 
     int rc = check_problem(p);
     if (rc != HQ_OK) return rc;
     if (!W) return HQ_E_BADARG;
-    hipStream_t s = as_stream(stream);
-    const int taps = p->R * p->S;
-    auto colsum = [&](int rows, int32_t *sum) {
-        hipLaunchKernelGGL(zero_words_kernel, dim3((p->C + 255) / 256), dim3(256), 0, s, sum, p->C);
-        hipLaunchKernelGGL(weight_colsum_kernel, dim3((p->C + 63) / 64, (rows * taps + 63) / 64), dim3(64), 0, s,
-                           W, rows, taps, p->C, sum);
-    };
-    if (p->kind == HQ_DEPTHWISE) {
-        if (wsum) colsum(1, wsum);
-        if (wdsum) colsum(1, wdsum);
-        return launch_status();
-    }
-    if (wsum) hipLaunchKernelGGL(weight_rowsum_kernel, dim3((p->Cout + 3) / 4), dim3(256), 0, s, W, p->Cout, taps * p->C, wsum);
-    if (wdsum) colsum(p->Cout, wdsum);
-    if (Wd) hipLaunchKernelGGL(weight_relayout_kernel, dim3(1024), dim3(256), 0, s, W, p->Cout, taps, p->C, Wd);
-    return launch_status();
+    return hq_launch_weight_prepare(p, W, Wd, wsum, wdsum, as_stream(stream));
 }
 
 int hq_weight_quantize(const float *Wf, size_t n, int8_t *Wq, hq_qparams *wq, void *stream)
 {
     if (!Wf || !Wq || !wq || n == 0 || misaligned(Wf, 4) || misaligned(wq, 4)) return HQ_E_BADARG;
-    hipStream_t s = as_stream(stream);
-    size_t blocks = (n + HQ_THREADS - 1) / HQ_THREADS;
-    if (blocks > 256u * 16u) blocks = 256u * 16u;
-    hipLaunchKernelGGL(weight_scale_init_kernel, dim3(1), dim3(1), 0, s, wq);
-    hipLaunchKernelGGL(weight_absmax_kernel, dim3((unsigned)blocks), dim3(HQ_THREADS), 0, s, Wf, n,
-                       reinterpret_cast<unsigned *>(&wq->zero_point));
-    hipLaunchKernelGGL(weight_scale_kernel, dim3(1), dim3(1), 0, s, wq);
-    hipLaunchKernelGGL(weight_quantize_kernel, dim3((unsigned)blocks), dim3(HQ_THREADS), 0, s, Wf, n, wq, Wq);
-    return launch_status();
+    return hq_launch_weight_quantize(Wf, n, Wq, wq, as_stream(stream));
 }
 
 int hq_probe_mfma_rate(int32_t blocks, int32_t iters, int32_t *sink, void *stream)

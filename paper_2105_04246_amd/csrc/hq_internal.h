@@ -43,3 +43,7 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
 int hq_launch_depthwise_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY,
                               const hq_qparams *gq, float *dW, int32_t *dW_acc, void *ws, hipStream_t stream,
                               const HqRideAlong *ride = nullptr);
+
+// Weight side: re-laying and sums (one launch), Q_W (one or two launches).
+int hq_launch_weight_prepare(const hq_problem *p, const int8_t *W, int8_t *Wd, int32_t *wsum, int32_t *wdsum, hipStream_t s);
+int hq_launch_weight_quantize(const float *Wf, size_t n, int8_t *Wq, hq_qparams *wq, hipStream_t s);

@@ -317,6 +317,26 @@ def test_weight_prepare_layouts_and_sums(H, hq):
     assert np.array_equal(Wd.Wd.cpu().numpy().reshape(L.C, L.R, L.S, L.Cout), W.codes.transpose(3, 1, 2, 0))
 
 
+@pytest.mark.parametrize("shape", [(3, 1, 4, 4), (1, 7, 3, 64), (3, 3, 36, 100), (1, 1, 1024, 1000), (3, 3, 68, 8), (5, 2, 80, 132)],
+                         ids=lambda s: "%dx%d_c%d_n%d" % s)
+@pytest.mark.parametrize("offset", [0, 4, 1])
+def test_weight_prepare_edges(H, hq, shape, offset):
+    """Edges of the 64 x 64 tiles, channel counts off the 16-byte chunks, and buffers off 16- and 4-byte alignment."""
+    R, S, C, Cout = shape
+    p = hq.problem(hq.HQ_CONV2D, 1, R, S, C, R, S, 1, 0, Cout)
+    w = np.random.default_rng(C).integers(-127, 128, (Cout, R, S, C)).astype(np.int8)
+    W, Wd = (torch.zeros(w.size + 16, dtype=torch.int8, device="cuda") for _ in range(2))
+    W[offset:offset + w.size] = H.dev(w).view(-1)
+    wsum, wdsum = (torch.empty(k, dtype=torch.int32, device="cuda") for k in (Cout, C))
+    hq.hq_weight_prepare(p, W[offset:], Wd[offset:], wsum, wdsum)
+    torch.cuda.synchronize()
+    assert np.array_equal(wsum.cpu().numpy(), w.sum(axis=(1, 2, 3), dtype=np.int64))
+    assert np.array_equal(wdsum.cpu().numpy(), w.sum(axis=(0, 1, 2), dtype=np.int64))
+    got = Wd.cpu().numpy()
+    assert np.array_equal(got[offset:offset + w.size].reshape(C, R, S, Cout), w.transpose(3, 1, 2, 0))
+    assert not got[:offset].any() and not got[offset + w.size:].any()
+
+
 @pytest.mark.parametrize("n", [1, 3, 36864, 147456 + 5, 2359296])
 def test_weight_quantizer(H, hq, n):
     """Q_W with the tensor's current min-max (Sec. 3.1, Sec. 5): codes and scale bit for bit."""
@@ -332,6 +352,27 @@ def test_weight_quantizer(H, hq, n):
         q = H.read_qparams(wq)
         assert np.float32(q["scale"]) == s and int(q["zero_point"]) == 0
         assert np.array_equal(Wq.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("n", [4099, 160 * 1024, 160 * 1024 + 1, 1 << 20])
+def test_weight_quantizer_edges(H, hq, n, offset):
+    """Both sides of the line between one launch and two, aligned and off 16- and 4-byte alignment; values on and
+    next to half codes, where a product with the reciprocal would round the other way than the quotient."""
+    g = np.random.default_rng(n)
+    s = np.float32(0.37) / np.float32(127)
+    half = (g.integers(-127, 127, n) + 0.5).astype(np.float32) * s
+    w = np.nextafter(half, half * g.integers(0, 3, n).astype(np.float32))
+    w[n // 3] = 0.37
+    want, s = oracle.quantize_weights(w)
+    Wf, Wq = torch.empty(n + 1, device="cuda")[offset:], torch.empty(n + 1, dtype=torch.int8, device="cuda")[offset:]
+    Wf[:n] = H.dev(w)
+    wq = hq.new_qparams(123.0, 7)
+    hq.hq_weight_quantize(Wf, n, Wq, wq)
+    torch.cuda.synchronize()
+    q = H.read_qparams(wq)
+    assert np.float32(q["scale"]) == s and int(q["zero_point"]) == 0
+    assert np.array_equal(Wq[:n].cpu().numpy(), want)
 
 
 def test_asymmetric_gradients_and_symmetric_inputs(H, hq):
