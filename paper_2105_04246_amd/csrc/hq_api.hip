@@ -5,6 +5,7 @@
 #include "hq_internal.h"
 
 #include <mutex>
+#include <cstdlib>
 
 // Scratch memory of hq_gemm_wgrad_static: one array per GPU, held from the moment the library is
 // loaded on that GPU until the process ends.  In host code the array's name is only a handle for
@@ -222,6 +223,8 @@ static int gemm_common(const hq_problem *p, int dgrad, const int8_t *A, const hq
         if (dgrad || sr_seed) return HQ_E_BADSHAPE;
         return hq_try_launch_direct(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream));
     }
+    rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
+    if (rc != HQ_E_BADSHAPE) return rc;
     if (sr_seed) {
         // stochastic rounding: the two 3x3 / 1x1 fast paths, else the two general kernels
         if (p->kind == HQ_DEPTHWISE)

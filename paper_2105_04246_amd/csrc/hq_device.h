@@ -237,6 +237,16 @@ __device__ inline void hq_global_to_lds16(const void *src, void *wave_base)
                  : "=&s"(keep) : "v"(src), "s"(m) : "memory");
 }
 
+// The same for 4 bytes per lane: lane l lands at wave_base + 4 * l.
+__device__ inline void hq_global_to_lds4(const void *src, void *wave_base)
+{
+    const unsigned m = __builtin_amdgcn_readfirstlane(
+        (unsigned)(size_t)(__attribute__((address_space(3))) void *)wave_base);
+    unsigned keep;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(keep) : "v"(src), "s"(m) : "memory");
+}
+
 // Three-operand integer minimum / maximum (v_min3_i32 / v_max3_i32).  Written out because the compiler
 // balances a chain of two-operand minima into a tree and then needs 12 instructions for 16 values, not 8.
 __device__ inline int hq_min3(int a, int b, int c)

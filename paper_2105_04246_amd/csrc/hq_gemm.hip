@@ -566,15 +566,12 @@ int launch3(GemmArgs &a, hipStream_t s)
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }
 
-// mode: 0 / 1 / 2 as the kernel's MODE.  Stochastic rounding is built for the two tile shapes with 64-byte
-// stages only (the launcher below routes it there).
 template <int BM, int BN, int WGM, int WGN, int BKB, bool STRIDED, bool ALIGNED>
 int launch2m(GemmArgs &a, int mode, hipStream_t s)
 {
     if (mode == 0) return launch3<BM, BN, WGM, WGN, BKB, STRIDED, ALIGNED, 0>(a, s);
     if (mode == 1) return launch3<BM, BN, WGM, WGN, BKB, STRIDED, ALIGNED, 1>(a, s);
-    if constexpr (BKB == 64 && BN >= 64) return launch3<BM, BN, WGM, WGN, BKB, STRIDED, ALIGNED, 2>(a, s);
-    return HQ_E_BADSHAPE;
+    return launch3<BM, BN, WGM, WGN, BKB, STRIDED, ALIGNED, 2>(a, s);
 }
 
 template <int BM, int BN, int WGM, int WGN, int BKB>
@@ -633,11 +630,11 @@ int hq_launch_gemm(const hq_problem *p, int dgrad, const int8_t *A, const hq_qpa
         const long tiles = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
         // not even one 128 x 128 tile per compute unit (small images or batches under a long reduction,
         // fully connected layers): 64 x 64 tiles, four times as many workgroups
-        if (aligned && !strided && mode != 2 && a.nchunks >= 16 && tiles < 256)
+        if (aligned && !strided && a.nchunks >= 16 && tiles < 256)
             return launch2m<64, 64, 2, 2, 128, false, true>(a, mode, stream);
-        if (mode != 2 && a.nchunks >= 16 && !(aligned && tiles >= 3 * 256)) return launch2<128, 128, 2, 2, 128>(a, strided, aligned, mode, stream);
+        if (a.nchunks >= 16 && !(aligned && tiles >= 3 * 256)) return launch2<128, 128, 2, 2, 128>(a, strided, aligned, mode, stream);
         return launch2<128, 128, 2, 2, 64>(a, strided, aligned, mode, stream);
     }
-    if (a.N > 32 || mode == 2) return launch2<256, 64, 4, 1, 64>(a, strided, aligned, mode, stream);
+    if (a.N > 32) return launch2<256, 64, 4, 1, 64>(a, strided, aligned, mode, stream);
     return launch2<256, 32, 4, 1, 64>(a, strided, aligned, mode, stream);
 }

@@ -1,0 +1,396 @@
+// Small launches of hq_gemm_fwd / hq_gemm_dgrad and of pass 1 of the dynamic baseline: layers whose output has so few
+// tiles that the tile kernels leave most compute units idle while each tile walks its whole reduction stage by
+// stage (batch-1 inference, small images under many channels, fully connected layers, ragged layers).
+//
+// What bounds such a launch is the latency of one tile's serial chain: load, wait, barrier, multiply, once per stage
+// (about 1 us each; 46 us for 7x7x512 -> 512 at batch 1).  Here the wavefronts of a workgroup share a small
+// output tile and split its reduction: wavefront w takes the 64-byte steps w, w + NW, ..., loads both
+// operands' MFMA fragments straight from global memory into registers D steps ahead, and meets the others only once, when
+// the partial sums are added through LDS.  No barrier, no LDS traffic and no shared stage inside the reduction; every
+// wavefront keeps D x (TMB + TNB) KB in flight.  The price is that an operand byte is fetched once per tile
+// instead of once per larger tile, so the rate is bound by the 64 bytes a clock a compute unit loads:
+// (TM + TN) x K / 64 clocks per tile.  Measured (forward, before -> now): 7x7x512 -> 512 at batch 1 45 -> 8.4 us, 14x14x256
+// 25 -> 7.3, 28x28x128 16 -> 6.9; 256 x 512 -> 1000 with 1000 reduced 30 -> 10; 4x4x512 at batch 128 24 -> 17 us.
+//
+// Both operations are  out[m][n] = sum_{tap,c} A[pix(m,tap)][c] * Bw[n][tap][c]  as in the gather kernel, with the
+// same class form for strided input gradients (an output pixel's class fixes its taps; everything else is one class).
+// A lane holds, per 16x16 block, 16 bytes of the reduction of one pixel and of one channel; the weights are the first
+// operand, so that a lane ends up with 4 consecutive channels of one pixel.
+#include "hq_device.h"
+#include "hq_internal.h"
+
+#include <type_traits>
+
+namespace {
+
+// 16-byte rows of one repeated byte: where a lane without a source reads (padding taps: zero-point code; chunks past
+// the reduction's end: 0).
+struct KsFillRows {
+    unsigned w[256][4];
+    constexpr KsFillRows() : w()
+    {
+        for (int v = 0; v < 256; v++)
+            for (int k = 0; k < 4; k++) w[v][k] = (unsigned)v * 0x01010101u;
+    }
+};
+__device__ const KsFillRows ks_fill_rows = KsFillRows();
+
+struct KsClass {
+    int ph, pw, Hc, Wc;            // pixels (ph + ostep * y, pw + ostep * x) of the output image, y < Hc, x < Wc
+    int ns, taps;                  // taps per row of the class's tap grid, taps in all
+    int dh, dw;                    // source pixel of tap (0, 0) for y = x = 0
+    int w0;                        // weight tap of tap (0, 0)
+    int tile0;                     // first row tile
+    unsigned magic_Wc, magic_Hc, magic_ns;
+};
+
+struct KsArgs {
+    const int8_t *A, *Bw;
+    const int32_t *bsum;
+    const hq_qparams *aq, *bq;
+    const hq_range *range;
+    int8_t *out8;
+    int32_t *out32;
+    hq_qparams *outq;
+    hq_stats *st;
+    int M, N, B;
+    int Cs, cpt;                   // reduced channels per tap; 16-byte chunks per tap (aligned form)
+    unsigned magic_div;            // of cpt (aligned) or Cs
+    size_t wrow;                   // bytes per weight row
+    int Hs, Ws, Ho, Wo;            // source image, output image
+    int istep, ostep, sgn;         // source pixel = istep * y + dh + sgn * tr;  ostep: class stride in the output
+    int wr, wc;                    // weight tap = w0 + wr * tr + wc * ts
+    int m_tiles, n_tiles, m_fast;  // m_fast: consecutive workgroups share their weights, not their pixels
+    int classed, ncls;             // classed: the zero-point term is summed from the class's own weights
+    HqSr sr;
+    KsClass cls[16];
+};
+
+// TMB, TNB: 16-pixel and 16-channel blocks of the tile.  NW wavefronts, D steps in flight.  MODE as in the gather kernel:
+// 0 32-bit outputs, 1 round to nearest even, 2 stochastic rounding.  ALIGNED: Cs % 16 == 0, a 16-byte chunk is of one tap;
+// otherwise 4-byte words (Cs % 4 == 0).
+template <int TMB, int TNB, int NW, int D, bool ALIGNED, int MODE>
+__global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
+{
+    constexpr int TM = 16 * TMB, TN = 16 * TNB;
+    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+    constexpr int BUF = NW * 1024 * (TMB * TNB > D * (TMB + TNB) ? TMB * TNB : D * (TMB + TNB));
+    v4i *sums = reinterpret_cast<v4i *>(smem);                           // [NW][TNB][TMB][64]
+    int *bzs = reinterpret_cast<int *>(smem + BUF);                      // [TN]
+    int *red = bzs + TN;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
+    // Aligned form: a 1 KB block of a step, 16 rows of 64 bytes, goes to LDS directly.  Lane l of such a load lands at
+    // 16 * l, so consecutive lanes fetch consecutive chunks of one row (fragments loaded as the MFMA wants them, 16
+    // rows side by side, come at a quarter of the rate); the chunks of a row are XOR-swizzled by the row, which keeps the
+    // fragment reads free of bank conflicts.  4-byte form: fragments straight into registers.
+    const int lrow = ALIGNED ? lane >> 2 : r16;                          // row of the lane's loads in a block
+    const int lchunk = ALIGNED ? (lane & 3) ^ ((lrow >> 1) & 3) : g;     // and its 16-byte chunk of the step
+    const int frag = r16 * 64 + 16 * (g ^ ((r16 >> 1) & 3));
+
+    int tile_m, tile_n;
+    if (a.m_fast) { tile_n = blockIdx.x / a.m_tiles; tile_m = blockIdx.x - tile_n * a.m_tiles; }
+    else          { tile_m = blockIdx.x / a.n_tiles; tile_n = blockIdx.x - tile_m * a.n_tiles; }
+    int ci = 0;
+    while (ci + 1 < a.ncls && tile_m >= a.cls[ci + 1].tile0) ci++;
+    const KsClass &cl = a.cls[ci];
+    const int m0 = (tile_m - cl.tile0) * TM, n0 = tile_n * TN;
+    const int Wc = cl.Wc, Hc = cl.Hc, ns = cl.ns, taps = cl.taps, Mrows = a.B * Hc * Wc;
+    const int units = ALIGNED ? taps * a.cpt : taps * a.Cs / 4;          // 16-byte chunks / 4-byte words of the reduction
+    auto decode = [&](int m, int &x, int &y, int &b) {
+        const unsigned t = hq_magic_div((unsigned)m, cl.magic_Wc), bb = hq_magic_div(t, cl.magic_Hc);
+        x = (int)((unsigned)m - t * (unsigned)Wc); y = (int)(t - bb * (unsigned)Hc); b = (int)bb;
+    };
+
+    const int za = a.aq->zero_point;
+    const int8_t *fill = reinterpret_cast<const int8_t *>(ks_fill_rows.w[za & 0xff]);
+    const int8_t *zero = reinterpret_cast<const int8_t *>(ks_fill_rows.w[0]);
+    if (a.classed && tid < TN) bzs[tid] = 0;
+
+    // per pixel of the lane: address of tap (0, 0), a bit per tap that says whether it has a source
+    const int8_t *arow[TMB];
+    unsigned long long amask[TMB];
+#pragma unroll
+    for (int i = 0; i < TMB; i++) {
+        const int m = m0 + 16 * i + lrow;
+        int x, y, b;
+        decode(m < Mrows ? m : 0, x, y, b);              // rows past the end repeat row 0; nothing of them is stored
+        const int iy = y * a.istep + cl.dh, ix = x * a.istep + cl.dw;
+        arow[i] = a.A + ((ptrdiff_t)((ptrdiff_t)b * a.Hs + iy) * a.Ws + ix) * a.Cs;
+        unsigned long long mk = 0;
+        for (int t = 0, r = 0, c = 0; t < taps; t++) {
+            const int sy = iy + a.sgn * r, sx = ix + a.sgn * c;
+            if (sy >= 0 && sy < a.Hs && sx >= 0 && sx < a.Ws) mk |= 1ull << t;
+            if (++c == ns) { c = 0; r++; }
+        }
+        amask[i] = mk;
+    }
+    const int8_t *brow[TNB];
+#pragma unroll
+    for (int j = 0; j < TNB; j++) {
+        const int n = n0 + 16 * j + lrow;
+        brow[j] = a.Bw + (size_t)(n < a.N ? n : 0) * a.wrow;
+    }
+
+    // offsets of unit u (chunk or word): from a pixel's tap (0, 0), from a weight row, and its tap
+    auto locate = [&](int u, int &aoff, int &woff, int &tap) {
+        const int per = ALIGNED ? a.cpt : a.Cs;
+        const int k = ALIGNED ? u : 4 * u;
+        tap = (int)hq_magic_div((unsigned)k, a.magic_div);
+        const int tr = (int)hq_magic_div((unsigned)tap, cl.magic_ns), ts = tap - tr * ns;
+        const int c = (k - tap * per) * (ALIGNED ? 16 : 1);
+        aoff = a.sgn * (tr * a.Ws + ts) * a.Cs + c;
+        woff = (cl.w0 + tr * a.wr + ts * a.wc) * a.Cs + c;
+    };
+    int8_t *const stage0 = smem + wave * D * (TMB + TNB) * 1024;         // [D][TMB + TNB][1024], this wavefront's own
+    auto load_lds = [&](int step, int d) {
+        const int u = 4 * step + lchunk;
+        const bool ok = u < units;
+        int aoff, woff, tap;
+        locate(u, aoff, woff, tap);
+        int8_t *dst = stage0 + d * (TMB + TNB) * 1024;
+#pragma unroll
+        for (int i = 0; i < TMB; i++) {
+            const bool in = ok && ((amask[i] >> (tap & 63)) & 1ull) != 0;
+            hq_global_to_lds16(in ? arow[i] + aoff : fill, dst + 1024 * i);
+        }
+#pragma unroll
+        for (int j = 0; j < TNB; j++) hq_global_to_lds16(ok ? brow[j] + woff : zero, dst + 1024 * (TMB + j));
+    };
+    auto load_regs = [&](int step, v4i (&af)[TMB], v4i (&bf)[TNB]) {
+#pragma unroll
+        for (int d = 0; d < 4; d++) {
+            const int u = 16 * step + 4 * lchunk + d;
+            const bool ok = u < units;
+            int aoff, woff, tap;
+            locate(u, aoff, woff, tap);
+#pragma unroll
+            for (int i = 0; i < TMB; i++) {
+                const bool in = ok && ((amask[i] >> (tap & 63)) & 1ull) != 0;
+                af[i][d] = *reinterpret_cast<const int *>(in ? arow[i] + aoff : fill);
+            }
+#pragma unroll
+            for (int j = 0; j < TNB; j++) bf[j][d] = *reinterpret_cast<const int *>(ok ? brow[j] + woff : zero);
+        }
+    };
+
+    v4i acc[TNB][TMB];
+#pragma unroll
+    for (int j = 0; j < TNB; j++)
+#pragma unroll
+        for (int i = 0; i < TMB; i++) acc[j][i] = v4i{0, 0, 0, 0};
+    int wsum[TNB] = {};
+    const bool own_sums = a.classed && za != 0;
+
+    // Steps past the end read the fill rows and add nothing, so the loads need no branch.
+    const int nsteps = (units + (ALIGNED ? 3 : 15)) / (ALIGNED ? 4 : 16);
+    auto multiply = [&](const v4i (&af)[TMB], const v4i (&bf)[TNB]) {
+        if (own_sums)
+#pragma unroll
+            for (int j = 0; j < TNB; j++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) wsum[j] = __builtin_amdgcn_sdot4(bf[j][e], 0x01010101, wsum[j], false);
+#pragma unroll
+        for (int j = 0; j < TNB; j++)
+#pragma unroll
+            for (int i = 0; i < TMB; i++)
+                acc[j][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bf[j], af[i], acc[j][i], 0, 0, 0);
+    };
+    if (wave < nsteps) {
+        if constexpr (ALIGNED) {
+#pragma unroll
+            for (int d = 0; d < D; d++) load_lds(wave + NW * d, d);
+            int d = 0;
+            for (int s = wave; s < nsteps; s += NW) {
+                // this wavefront's own loads only: no barrier
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 1) * (TMB + TNB)) : "memory");
+                const int8_t *src = stage0 + d * (TMB + TNB) * 1024 + frag;
+                v4i af[TMB], bf[TNB];
+#pragma unroll
+                for (int i = 0; i < TMB; i++) af[i] = *reinterpret_cast<const v4i *>(src + 1024 * i);
+#pragma unroll
+                for (int j = 0; j < TNB; j++) bf[j] = *reinterpret_cast<const v4i *>(src + 1024 * (TMB + j));
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the stage has been read: it can be filled again
+                load_lds(s + NW * D, d);
+                multiply(af, bf);
+                d = d + 1 == D ? 0 : d + 1;
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        } else {
+            v4i af[D][TMB], bf[D][TNB];
+#pragma unroll
+            for (int d = 0; d < D; d++) load_regs(wave + NW * d, af[d], bf[d]);
+            for (int s = wave; s < nsteps; s += NW * D) {
+#pragma unroll
+                for (int d = 0; d < D; d++) {
+                    multiply(af[d], bf[d]);
+                    load_regs(s + NW * (d + D), af[d], bf[d]);
+                }
+            }
+        }
+    }
+    __syncthreads();                                     // the stages make room for the partial sums
+#pragma unroll
+    for (int j = 0; j < TNB; j++)
+#pragma unroll
+        for (int i = 0; i < TMB; i++) sums[((wave * TNB + j) * TMB + i) * 64 + lane] = acc[j][i];
+    if (own_sums)
+#pragma unroll
+        for (int j = 0; j < TNB; j++) atomicAdd(bzs + 16 * j + r16, wsum[j]);
+    __syncthreads();
+
+    // ---- epilogue: a thread = 4 consecutive channels of one pixel
+    const float acc_scale = __fmul_rn(a.aq->scale, a.bq->scale);
+    HqEpilogue ep = {1.0f, 0.0f, 0.0f, 0.0f, true};
+    if (MODE != 0) ep = hq_make_epilogue(acc_scale, a.range);
+    int mn = INT_MAX, mx = INT_MIN;
+    unsigned nlo = 0, nhi = 0;
+    auto epilogue = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        for (int u = tid; u < TMB * TNB * 64; u += NW * 64) {
+            const int l = u & 63, i = (u >> 6) % TMB, j = (u >> 6) / TMB;
+            int m = m0 + 16 * i + (l & 15);
+            const int nc = 16 * j + 4 * (l >> 4), n = n0 + nc;
+            if (m >= Mrows || n >= a.N) continue;        // N % 4 == 0
+            v4i c = sums[u];
+#pragma unroll
+            for (int w = 1; w < NW; w++) c += sums[w * (TMB * TNB * 64) + u];
+            if (a.classed) {
+                if (za != 0) c -= za * *reinterpret_cast<const v4i *>(bzs + nc);
+                int x, y, b;
+                decode(m, x, y, b);
+                m = (b * a.Ho + cl.ph + a.ostep * y) * a.Wo + cl.pw + a.ostep * x;
+            } else {
+                c -= za * *reinterpret_cast<const v4i *>(a.bsum + n);
+            }
+            const int cc[4] = {c[0], c[1], c[2], c[3]};
+            const size_t o = (size_t)m * a.N + n;
+            if constexpr (MODE == 0) {
+                hq_minmax_group<4>(cc, mn, mx);
+                *reinterpret_cast<v4i *>(a.out32 + o) = c;
+            } else {
+                int w;
+                if constexpr (MODE == 2) hq_requant_group_sr<4, FULL>(cc, ep, a.sr, o, mn, mx, nlo, nhi, &w);
+                else                     hq_requant_group<4, FULL>(cc, ep, mn, mx, nlo, nhi, &w);
+                *reinterpret_cast<int *>(a.out8 + o) = w;
+            }
+        }
+    };
+    if (ep.full_grid) epilogue(std::true_type()); else epilogue(std::false_type());
+    hq_block_stats_commit_n<NW * 64>(mn, mx, nlo, nhi, a.st, red);
+    if (blockIdx.x == 0 && tid == 0) {
+        a.st->acc_scale = acc_scale;
+        atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)a.M * (unsigned long long)a.N);
+        if (MODE != 0) *a.outq = a.range->qp;
+    }
+}
+
+template <int TMB, int TNB, int NW, int D, bool ALIGNED, int MODE>
+int launch3(KsArgs &a, hipStream_t s)
+{
+    int t = 0;
+    for (int c = 0; c < a.ncls; c++) {
+        a.cls[c].tile0 = t;
+        t += (a.B * a.cls[c].Hc * a.cls[c].Wc + 16 * TMB - 1) / (16 * TMB);
+    }
+    a.m_tiles = t;
+    a.n_tiles = (a.N + 16 * TNB - 1) / (16 * TNB);
+    const size_t lds = (size_t)NW * 1024 * (TMB * TNB > D * (TMB + TNB) ? TMB * TNB : D * (TMB + TNB)) + 4 * 16 * TNB + 16 * NW;
+    auto kern = hq_ksplit_kernel<TMB, TNB, NW, D, ALIGNED, MODE>;
+    static bool configured = false;
+    if (lds > 48 * 1024 && !configured) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess)
+            return HQ_E_HIP;
+        configured = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)(a.m_tiles * a.n_tiles)), dim3(NW * 64), lds, s, a);
+    return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
+}
+
+template <int TMB, int TNB, int NW, int D, bool ALIGNED>
+int launch2(KsArgs &a, int mode, hipStream_t s)
+{
+    if (mode == 0) return launch3<TMB, TNB, NW, D, ALIGNED, 0>(a, s);
+    if (mode == 1) return launch3<TMB, TNB, NW, D, ALIGNED, 1>(a, s);
+    return launch3<TMB, TNB, NW, D, ALIGNED, 2>(a, s);
+}
+
+} // namespace
+
+int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
+                         const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
+                         int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed)
+{
+    if (p->kind == HQ_DEPTHWISE || (!dgrad && p->C < 8)) return HQ_E_BADSHAPE;      // (first layers have their own kernels)
+    const int OH = (p->H + 2 * p->pad - p->R) / p->stride + 1, OW = (p->W + 2 * p->pad - p->S) / p->stride + 1;
+    KsArgs a;
+    a.A = A; a.Bw = Bw; a.bsum = bsum; a.aq = aq; a.bq = bq; a.range = range;
+    a.out8 = out8; a.out32 = out32; a.outq = outq; a.st = st; a.B = p->B;
+    const int taps = p->R * p->S;
+    if (taps > 64) return HQ_E_BADSHAPE;                 // a pixel's tap mask has 64 bits
+    if (!dgrad) { a.N = p->Cout; a.Cs = p->C; a.Hs = p->H; a.Ws = p->W; a.Ho = OH; a.Wo = OW; }
+    else        { a.N = p->C; a.Cs = p->Cout; a.Hs = OH; a.Ws = OW; a.Ho = p->H; a.Wo = p->W; }
+    const unsigned long long M = (unsigned long long)a.B * a.Ho * a.Wo, lim = 1ull << 32;
+    a.wrow = (size_t)taps * a.Cs;
+    // operands of hq_magic_div
+    if (M * (unsigned)(a.Ho > a.Wo ? a.Ho : a.Wo) >= lim || (a.wrow + 64) * a.Cs >= lim) return HQ_E_BADSHAPE;
+    a.M = (int)M;
+    const bool aligned = a.Cs % 16 == 0;
+    a.cpt = a.Cs / 16;
+    a.magic_div = hq_magic32((unsigned)(aligned ? a.cpt : a.Cs));
+    a.classed = dgrad && !(p->stride == 1 && p->R == p->S);
+    if (!a.classed) {
+        a.ncls = 1; a.ostep = 1; a.sgn = 1;
+        a.istep = dgrad ? 1 : p->stride;
+        KsClass &c = a.cls[0];
+        c.ph = c.pw = 0; c.Hc = a.Ho; c.Wc = a.Wo; c.ns = p->S; c.taps = taps;
+        c.dh = c.dw = dgrad ? -(p->R - 1 - p->pad) : -p->pad;
+        c.w0 = dgrad ? taps - 1 : 0; a.wr = dgrad ? -p->S : p->S; a.wc = dgrad ? -1 : 1;
+        c.magic_Wc = hq_magic32((unsigned)c.Wc); c.magic_Hc = hq_magic32((unsigned)c.Hc); c.magic_ns = hq_magic32((unsigned)c.ns);
+    } else {
+        const int S = p->stride;
+        if (S > 4) return HQ_E_BADSHAPE;
+        a.ncls = S * S; a.ostep = S; a.sgn = -1; a.istep = 1; a.wr = S * p->S; a.wc = S;
+        for (int k = 0; k < a.ncls; k++) {
+            KsClass &c = a.cls[k];
+            c.ph = k / S; c.pw = k % S;
+            c.Hc = (a.Ho - c.ph + S - 1) / S; c.Wc = (a.Wo - c.pw + S - 1) / S;
+            const int r0 = (c.ph + p->pad) % S, s0 = (c.pw + p->pad) % S;
+            const int nr = r0 < p->R ? (p->R - r0 + S - 1) / S : 0;
+            c.ns = s0 < p->S ? (p->S - s0 + S - 1) / S : 0;
+            c.taps = nr * c.ns;
+            if (c.ns == 0) c.ns = 1;
+            c.dh = (c.ph + p->pad - r0) / S; c.dw = (c.pw + p->pad - s0) / S;
+            c.w0 = r0 * p->S + s0;
+            c.magic_Wc = hq_magic32((unsigned)(c.Wc > 0 ? c.Wc : 1)); c.magic_Hc = hq_magic32((unsigned)(c.Hc > 0 ? c.Hc : 1));
+            c.magic_ns = hq_magic32((unsigned)c.ns);
+        }
+    }
+    if (sr_seed && out32) return HQ_E_BADARG;
+    const int mode = out32 ? 0 : sr_seed ? 2 : 1;
+    a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
+    a.m_fast = (size_t)a.N * a.wrow > (size_t)a.B * a.Hs * a.Ws * a.Cs;
+    // Which tile.  A launch is one round of tiles that run side by side, so its time is one tile's, and the smallest tile
+    // that still gives every compute unit at most one is the fastest.  Beyond one round the tile kernels' larger tiles win
+    // (fewer bytes fetched per multiply-add), earlier where the weights-resident kernel takes the layer and where the
+    // reduction is too short for a 64 x 64 tile to pay for adding its partial sums.
+    const size_t k = a.wrow / (a.classed ? (size_t)p->stride * p->stride : 1);      // reduction of an average tile
+    auto tiles = [&](int tm, int tn) { return (M + tm - 1) / tm * (unsigned long long)((a.N + tn - 1) / tn); };
+    if (!aligned) {
+        // two or more workgroups per compute unit here; always in the class form, whose exact-division test
+        // per word the tile kernel repeats for every tap
+        if (tiles(32, 32) <= 512) return launch2<2, 2, 8, 1, false>(a, mode, stream);
+        if (tiles(64, 64) > 512 && !(a.classed && p->stride > 1)) return HQ_E_BADSHAPE;
+        if (a.N <= 32) return launch2<4, 2, 4, 1, false>(a, mode, stream);
+        return launch2<4, 4, 4, 1, false>(a, mode, stream);
+    }
+    if (tiles(16, 16) <= 256) return launch2<1, 1, 8, 4, true>(a, mode, stream);
+    if (tiles(16, 32) <= 256) return launch2<1, 2, 8, 4, true>(a, mode, stream);
+    if (tiles(32, 32) <= 256) return launch2<2, 2, 8, 2, true>(a, mode, stream);
+    if (tiles(32, 64) <= 256 && k >= 512 && !(a.Cs == 64 && p->R == 3 && p->stride == 1))
+        return launch2<2, 4, 8, 2, true>(a, mode, stream);
+    if (tiles(64, 64) <= 256 && k >= 1152) return launch2<4, 4, 8, 2, true>(a, mode, stream);
+    return HQ_E_BADSHAPE;
+}
