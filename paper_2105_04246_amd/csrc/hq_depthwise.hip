@@ -6,6 +6,9 @@
 #include "hq_device.h"
 #include "hq_internal.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace {
 
 struct DwArgs {
@@ -93,17 +96,16 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_depthwise_kernel(const DwArgs a
 }
 
 // ---------------------------------------------------------------------------------------
-// 3x3, stride 1 (forward, and input gradient as the same stencil with mirrored taps): the
-// shape of the depthwise layers of MobileNetV2-style blocks (Table 5, DW rows).
-// A thread owns four channels of one output column and slides down a strip of rows, keeping
-// the 3x3 window in registers as one word per (window row, channel) with the three horizontally
-// adjacent values in its bytes (two v_perm_b32 per word), so that an output is three 4-way byte
-// dot products (v_dot4) instead of nine multiply-adds on unpacked values.  Per output row the
-// thread loads three new words (one input row of the window), so an input byte is requested 3 times (by the three neighbouring
-// columns, which sit in adjacent lanes and hit the same cache lines) instead of 9.  Lanes run
-// along (column, channel) of a row, which is how NHWC lies in memory: loads and the 4-code
-// stores are contiguous across the wavefront.  The next row's words are requested before the
-// current row is multiplied.
+// 3x3 with padding 1 and stride 1 or 2: the depthwise layers of MobileNetV2-style blocks (Table 5, DW rows).
+//
+// What bounds these kernels is the vector ALU (the earlier stride-1 kernel, one column per thread: 27.8 instructions per
+// output, 84 % busy, 71 us for 128 x 56 x 56 x 192 against 30 us of memory traffic; now 43 us, stride 2 18 instead of 67 and
+// its input gradient 25 instead of 239), so they are written for few instructions per output.  A thread owns four channels (one word) of two neighbouring output columns and slides down a
+// strip of rows.  Pixels come as packed words of four channels; the words of four adjacent columns are byte-transposed (8
+// v_perm_b32) into one word per channel, and a filter row on it is one 4-way byte dot product per output: the second column's
+// weights are the first's shifted by one byte.  Rows are addressed by a uniform pointer plus a fixed lane offset, so loads cost
+// no address arithmetic, and the fill of columns outside the image is one select per word.  Lanes run along (column,
+// channel) of a row, which is how NHWC lies in memory.
 // ---------------------------------------------------------------------------------------
 struct Dw3Args {
     const int8_t *A, *Wt;
@@ -114,44 +116,115 @@ struct Dw3Args {
     int32_t *out32;
     hq_qparams *outq;
     hq_stats *st;
-    int B, H, W, C;                // input and output have the same size (pad 1)
+    int B, H, W, OH, OW, C;        // H x W: image A for the stencil, dX for the strided input gradient; OH x OW: the other one
     int rows_per_strip, flip;
+    HqSr sr;                       // MODE 2
 };
 
-// Three packed words (four channels each of the pixels left, middle, right) -> four words, one per
-// channel, holding that channel's three horizontally adjacent values and a zero byte: the operand
-// of a 4-way byte dot product against the three taps of a filter row.
-__device__ inline void dw_transpose3(int l, int m, int r, int *t)
+// four words = four pixels of four channels -> t[e] = (pixel0[e], pixel1[e], pixel2[e], pixel3[e])
+__device__ inline void dw_transpose4(int a0, int a1, int a2, int a3, int *t)
 {
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-        // v_perm_b32: selector bytes 0..3 pick bytes of the second source, 4..7 of the first, 0x0c is zero
-        const unsigned lm = __builtin_amdgcn_perm((unsigned)m, (unsigned)l, 0x0c0c0000u | (unsigned)e | ((4u + e) << 8));
-        t[e] = (int)__builtin_amdgcn_perm((unsigned)r, lm, 0x0c000100u | ((4u + e) << 16));
+    // v_perm_b32: selector bytes 0..3 pick bytes of the second source, 4..7 of the first, 0x0c is zero
+    const unsigned p0 = __builtin_amdgcn_perm((unsigned)a1, (unsigned)a0, 0x05010400u);   // (a0.0, a1.0, a0.1, a1.1)
+    const unsigned p1 = __builtin_amdgcn_perm((unsigned)a1, (unsigned)a0, 0x07030602u);   // (a0.2, a1.2, a0.3, a1.3)
+    const unsigned q0 = __builtin_amdgcn_perm((unsigned)a3, (unsigned)a2, 0x05010400u);
+    const unsigned q1 = __builtin_amdgcn_perm((unsigned)a3, (unsigned)a2, 0x07030602u);
+    t[0] = (int)__builtin_amdgcn_perm(q0, p0, 0x05040100u);
+    t[1] = (int)__builtin_amdgcn_perm(q0, p0, 0x07060302u);
+    t[2] = (int)__builtin_amdgcn_perm(q1, p1, 0x05040100u);
+    t[3] = (int)__builtin_amdgcn_perm(q1, p1, 0x07060302u);
+}
+
+// Word e of the transposed four pixels moved one pixel on: (t.1, t.2, t.3, next[e]); and one back: (prev[e], t.0, t.1, t.2).
+template <int E> __device__ inline int dw_shift_in(int t, int next)
+{
+    return (int)__builtin_amdgcn_perm((unsigned)next, (unsigned)t, 0x00030201u | ((4u + E) << 24));
+}
+template <int E> __device__ inline int dw_shift_back(int t, int prev)
+{
+    return (int)__builtin_amdgcn_perm((unsigned)t, (unsigned)prev, 0x06050400u | (unsigned)E);
+}
+
+// A word at a uniform address plus a lane's offset.  The statement keeps the widening of the offset next to the access, where it
+// is part of the instruction; hoisted out of the row loop it would cost a 64-bit addition per word and row.
+__device__ inline int dw_load(const int8_t *p, unsigned off)
+{
+    asm volatile("" : "+v"(off));
+    return *reinterpret_cast<const int *>(p + off);
+}
+__device__ inline void dw_store(int8_t *p, unsigned off, int v)
+{
+    asm volatile("" : "+v"(off));
+    *reinterpret_cast<int *>(p + off) = v;
+}
+
+// Epilogue of two neighbouring pixels' four channels each (`both`: the second exists; `pair`: it exists in every lane).
+// Stores through a uniform base and lane offsets.
+template <int MODE, bool FULL>
+__device__ inline void dw_emit(const Dw3Args &a, const HqEpilogue &ep, int (&cv)[8], size_t base, unsigned off0, unsigned off1,
+                               bool pair, bool both, int &mn, int &mx, unsigned &nlo, unsigned &nhi)
+{
+    if constexpr (MODE == 0) {
+        int32_t *o = a.out32 + base;
+        hq_minmax_group<4>(cv, mn, mx);
+        *reinterpret_cast<v4i *>(o + off0) = v4i{cv[0], cv[1], cv[2], cv[3]};
+        if (both) {
+            hq_minmax_group<4>(cv + 4, mn, mx);
+            *reinterpret_cast<v4i *>(o + off1) = v4i{cv[4], cv[5], cv[6], cv[7]};
+        }
+    } else {
+        int8_t *o = a.out8 + base;
+        int w[2];
+        if constexpr (MODE == 2) {
+            hq_requant_group_sr<4, FULL>(cv, ep, a.sr, base + off0, mn, mx, nlo, nhi, w);
+            dw_store(o, off0, w[0]);
+            if (both) {
+                hq_requant_group_sr<4, FULL>(cv + 4, ep, a.sr, base + off1, mn, mx, nlo, nhi, w + 1);
+                dw_store(o, off1, w[1]);
+            }
+        } else if (pair) {
+            hq_requant_group<8, FULL>(cv, ep, mn, mx, nlo, nhi, w);
+            dw_store(o, off0, w[0]);
+            dw_store(o, off1, w[1]);
+        } else {
+            hq_requant_group<4, FULL>(cv, ep, mn, mx, nlo, nhi, w);
+            dw_store(o, off0, w[0]);
+            if (both) {
+                hq_requant_group<4, FULL>(cv + 4, ep, mn, mx, nlo, nhi, w + 1);
+                dw_store(o, off1, w[1]);
+            }
+        }
     }
 }
 
+template <int N> using dw_int = std::integral_constant<int, N>;
+
+// Forward, and with stride 1 the input gradient as the same stencil with mirrored taps.
+template <int STRIDE, int MODE>
 __global__ __launch_bounds__(HQ_THREADS) void hq_dw3x3_kernel(const Dw3Args a)
 {
+    constexpr int NW = STRIDE == 1 ? 4 : 5;                          // input columns of the two outputs
+    constexpr int NT = STRIDE;                                       // transposed words per channel and row
+    constexpr int NR = STRIDE;                                       // new input rows per output row
+    constexpr int RING = STRIDE == 1 ? 3 : 2;                        // output rows whose input is under way
     __shared__ int red[4 * (HQ_THREADS / 64)];
-    const int c4n = a.C >> 2, rowwords = a.W * c4n;
-    const int q = blockIdx.x * HQ_THREADS + threadIdx.x;           // word inside an output row
-    const bool live = q < rowwords;
-    const int qq = live ? q : 0;
-    const int ox = qq / c4n, c = (qq - ox * c4n) * 4;
-    const int y0 = blockIdx.y * a.rows_per_strip, y1 = min(a.H, y0 + a.rows_per_strip);
-    const int8_t *img = a.A + (size_t)blockIdx.z * a.H * a.W * a.C;
-    const size_t out_img = (size_t)blockIdx.z * a.H * a.W;
+    const int c4n = a.C >> 2, cols2 = (a.OW + 1) >> 1;
+    const unsigned q = blockIdx.x * HQ_THREADS + threadIdx.x;        // (image, column pair, word)
+    const bool live = q < (unsigned)a.B * cols2 * c4n;
+    const unsigned qx = (live ? q : 0) / c4n, b = qx / cols2;
+    const int x = 2 * (int)(qx - b * cols2), c = (int)((live ? q : 0) - qx * c4n) * 4;
+    const int y0 = blockIdx.y * a.rows_per_strip, y1 = min(a.OH, y0 + a.rows_per_strip);
+    const size_t rowbytes = (size_t)a.W * a.C, orow = (size_t)a.OW * a.C;
+    // (tensors have fewer than 2^32 elements)
+    const unsigned ibase = b * (unsigned)a.H * (unsigned)rowbytes + (unsigned)c, obase = b * (unsigned)a.OH * (unsigned)orow + (unsigned)c;
 
     const int za = a.aq->zero_point;
-    const int fill = (int)((unsigned)(za & 0xff) * 0x01010101u);   // unsigned: the product may set bit 31
-    const bool fused = a.out32 == nullptr;
+    const int fill = (int)((unsigned)(za & 0xff) * 0x01010101u);     // unsigned: the product may set bit 31
     const float acc_scale = __fmul_rn(a.aq->scale, a.bq->scale);
-    HqEpilogue ep = {1.0f, 0.0f, 0.0f, 0.0f, true};
-    if (fused) ep = hq_make_epilogue(acc_scale, a.range);
+    HqEpilogue ep = {};
+    if (MODE != 0) ep = hq_make_epilogue(acc_scale, a.range);
 
-    // weights of the four channels: per filter row and channel one word (w[r][0], w[r][1], w[r][2], 0);
-    // mirrored for the input gradient
+    // weights: per filter row and channel one word (w[r][0], w[r][1], w[r][2], 0), mirrored for the input gradient
     int wt[3][4];
 #pragma unroll
     for (int r = 0; r < 3; r++) {
@@ -161,76 +234,206 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_dw3x3_kernel(const Dw3Args a)
             const int t = r * 3 + sx, ts = a.flip ? 8 - t : t;
             pk[sx] = *reinterpret_cast<const int *>(a.Wt + (size_t)ts * a.C + c);
         }
-        dw_transpose3(pk[0], pk[1], pk[2], wt[r]);
+        dw_transpose4(pk[0], pk[1], pk[2], 0, wt[r]);
     }
     const v4i wsv = *reinterpret_cast<const v4i *>(a.wsum + c);
-    int zw[4];
+    int nz[4];
 #pragma unroll
-    for (int e = 0; e < 4; e++) zw[e] = za * wsv[e];
+    for (int e = 0; e < 4; e++) nz[e] = -(za * wsv[e]);
 
-    const bool okl = ox > 0, okr = ox + 1 < a.W;
-    const size_t rowbytes = (size_t)a.W * a.C;
-    const int8_t *pcol = img + (size_t)ox * a.C + c;                 // this thread's column in input row 0
-    auto load_row = [&](const int8_t *p, bool rowok, int *dst) {      // three packed words of one input row
-        dst[0] = (rowok && okl) ? *reinterpret_cast<const int *>(p - a.C) : fill;
-        dst[1] = rowok ? *reinterpret_cast<const int *>(p) : fill;
-        dst[2] = (rowok && okr) ? *reinterpret_cast<const int *>(p + a.C) : fill;
+    unsigned off[NW];
+    bool ok[NW];
+#pragma unroll
+    for (int k = 0; k < NW; k++) {
+        const int xi = STRIDE * x - 1 + k;
+        ok[k] = xi >= 0 && xi < a.W;
+        off[k] = ibase + (unsigned)(ok[k] ? xi : STRIDE * x) * (unsigned)a.C;
+    }
+    const bool both = x + 1 < a.OW, pair = (a.OW & 1) == 0;
+    const unsigned off0 = obase + (unsigned)x * (unsigned)a.C, off1 = off0 + (unsigned)a.C;
+
+    auto load_row = [&](int y, int (&raw)[NW]) {                     // y is the same for the whole workgroup
+        if (y >= 0 && y < a.H) {
+            const int8_t *p = a.A + (size_t)y * rowbytes;
+#pragma unroll
+            for (int k = 0; k < NW; k++) raw[k] = dw_load(p, off[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < NW; k++) raw[k] = fill;
+        }
     };
-    const int8_t *pn = pcol + (size_t)(y0 > 0 ? y0 - 1 : 0) * rowbytes;   // walks down the input rows
-    size_t o = (out_img + (size_t)y0 * a.W + ox) * a.C + c;           // output word of row oy, advanced per row
+    auto transpose = [&](int (&raw)[NW], int (&t)[NT][4]) {
+#pragma unroll
+        for (int k = 0; k < NW; k++)
+            if (k != 1) raw[k] = ok[k] ? raw[k] : fill;
+        dw_transpose4(raw[0], raw[1], raw[2], raw[3], t[0]);
+        if constexpr (STRIDE == 2)                                   // columns 2x+1, 2x+2, 2x+3
+            dw_transpose4(raw[2], raw[3], raw[4], 0, t[1]);
+    };
 
     int mn = INT_MAX, mx = INT_MIN;
     unsigned nlo = 0, nhi = 0;
-    int win[3][4];                                                   // [row slot][channel]: (left, middle, right, 0)
-    int ring[3][3];                                                  // packed words of the next three input rows
-    if (live) {
-        int tmp[3];
-        load_row(pn, y0 > 0, tmp);                                   // row y0 - 1
-        if (y0 > 0) pn += rowbytes;
-        dw_transpose3(tmp[0], tmp[1], tmp[2], win[0]);
-        load_row(pn, true, tmp);                                     // row y0
-        pn += rowbytes;
-        dw_transpose3(tmp[0], tmp[1], tmp[2], win[1]);
+    int win[3][NT][4], ring[RING][NR][NW];
+    auto run = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
+        {
+            int tmp[NW];
+            load_row(STRIDE * y0 - 1, tmp);
+            int tmp1[NW];
+            if constexpr (STRIDE == 1) load_row(y0, tmp1);
 #pragma unroll
-        for (int k = 0; k < 3; k++) {                                // rows y0 + 1 .. y0 + 3 in flight
-            load_row(pn, y0 + 1 + k < a.H, ring[k]);
-            pn += rowbytes;
+            for (int k = 0; k < RING; k++)
+#pragma unroll
+                for (int r = 0; r < NR; r++) load_row(STRIDE == 1 ? y0 + 1 + k : 2 * (y0 + k) + r, ring[k][r]);
+            transpose(tmp, win[0]);
+            if constexpr (STRIDE == 1) transpose(tmp1, win[1]);
         }
+        int oy = y0;
+        // window slots of the filter's rows rotate with the output row: by one of three, or (stride 2) by swapping two
+        auto step = [&](auto phase) {
+            constexpr int P = decltype(phase)::value;
+            constexpr int TOP = STRIDE == 1 ? P : 2 * P, MID = STRIDE == 1 ? (P + 1) % 3 : 1, BOT = STRIDE == 1 ? (P + 2) % 3 : 2 - 2 * P;
+            if constexpr (STRIDE == 1) {
+                transpose(ring[P][0], win[BOT]);
+            } else {
+                transpose(ring[P][0], win[MID]);
+                transpose(ring[P][1], win[BOT]);
+            }
+            if (oy + RING < y1)
+#pragma unroll
+                for (int r = 0; r < NR; r++) load_row(STRIDE == 1 ? oy + RING + 1 : 2 * (oy + RING) + r, ring[P][r]);
+            int cv[8];
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                int p = __builtin_amdgcn_sdot4(win[TOP][0][e], wt[0][e], nz[e], false);
+                p = __builtin_amdgcn_sdot4(win[MID][0][e], wt[1][e], p, false);
+                cv[e] = __builtin_amdgcn_sdot4(win[BOT][0][e], wt[2][e], p, false);
+                p = __builtin_amdgcn_sdot4(win[TOP][NT - 1][e], STRIDE == 1 ? wt[0][e] << 8 : wt[0][e], nz[e], false);
+                p = __builtin_amdgcn_sdot4(win[MID][NT - 1][e], STRIDE == 1 ? wt[1][e] << 8 : wt[1][e], p, false);
+                cv[4 + e] = __builtin_amdgcn_sdot4(win[BOT][NT - 1][e], STRIDE == 1 ? wt[2][e] << 8 : wt[2][e], p, false);
+            }
+            dw_emit<MODE, FULL>(a, ep, cv, (size_t)oy * orow, off0, off1, pair, both, mn, mx, nlo, nhi);
+            oy++;
+        };
+        while (true) {
+            step(dw_int<0>());
+            if (oy >= y1) break;
+            step(dw_int<1>());
+            if (oy >= y1) break;
+            if constexpr (STRIDE == 1) {
+                step(dw_int<2>());
+                if (oy >= y1) break;
+            }
+        }
+    };
+    if (live) {
+        if (MODE == 0 || ep.full_grid) run(std::true_type()); else run(std::false_type());
     }
-    // one output row; TOP / MID / BOT name the register slots of input rows oy-1, oy, oy+1
-#define DW_STEP(TOP, MID, BOT, RING)                                                                        \
-    if (live && oy < y1) {                                                                            \
-        dw_transpose3(ring[RING][0], ring[RING][1], ring[RING][2], win[BOT]);                           \
-        if (oy + 3 < y1) { load_row(pn, oy + 4 < a.H, ring[RING]); pn += rowbytes; }                   \
-        int cv[4];                                                                                    \
-        _Pragma("unroll") for (int e = 0; e < 4; e++) {                                                 \
-            int acc = __builtin_amdgcn_sdot4(win[TOP][e], wt[0][e], -zw[e], false);                   \
-            acc = __builtin_amdgcn_sdot4(win[MID][e], wt[1][e], acc, false);                          \
-            cv[e] = __builtin_amdgcn_sdot4(win[BOT][e], wt[2][e], acc, false);                        \
-        }                                                                                             \
-        if (fused) {                                                                                  \
-            int wd;                                                                                   \
-            if (ep.full_grid) hq_requant_group<4, true>(cv, ep, mn, mx, nlo, nhi, &wd);               \
-            else hq_requant_group<4, false>(cv, ep, mn, mx, nlo, nhi, &wd);                            \
-            *reinterpret_cast<int *>(a.out8 + o) = wd;                                                \
-        } else {                                                                                      \
-            hq_minmax_group<4>(cv, mn, mx);                                                           \
-            const v4i v = {cv[0], cv[1], cv[2], cv[3]};                                               \
-            *reinterpret_cast<v4i *>(a.out32 + o) = v;                                                \
-        }                                                                                             \
-    }                                                                                                 \
-    oy++; o += rowbytes;
-    for (int oy = y0; oy < y1;) {
-        DW_STEP(0, 1, 2, 0)
-        DW_STEP(1, 2, 0, 1)
-        DW_STEP(2, 0, 1, 2)
-    }
-#undef DW_STEP
     hq_block_stats_commit(mn, mx, nlo, nhi, a.st, red);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        a.st->acc_scale = acc_scale;
+        atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)a.B * a.OH * a.OW * (unsigned long long)a.C);
+        if (MODE != 0) *a.outq = a.range->qp;
+    }
+}
+
+// Input gradient of the stride-2 layer.  dX pixel (2p + i, 2q + j) sees the taps r with (i + 1 - r) even: the block of 2 x 2
+// pixels (p, q) depends on the gradient pixels (p, q), (p, q+1), (p+1, q), (p+1, q+1) alone, which are one transposed word per
+// channel, so each of the four outputs is one dot product with a word of that parity's weights.
+template <int MODE>
+__global__ __launch_bounds__(HQ_THREADS) void hq_dw3x3_s2_dgrad_kernel(const Dw3Args a)
+{
+    constexpr int RING = 3;
+    __shared__ int red[4 * (HQ_THREADS / 64)];
+    const int c4n = a.C >> 2;
+    const unsigned q = blockIdx.x * HQ_THREADS + threadIdx.x;        // (image, gradient column, word)
+    const bool live = q < (unsigned)a.B * a.OW * c4n;
+    const unsigned qx = (live ? q : 0) / c4n, b = qx / a.OW;
+    const int x = (int)(qx - b * a.OW), c = (int)((live ? q : 0) - qx * c4n) * 4;
+    const int y0 = blockIdx.y * a.rows_per_strip, y1 = min(a.OH, y0 + a.rows_per_strip);       // gradient rows
+    const size_t grow = (size_t)a.OW * a.C, orow = (size_t)a.W * a.C;
+    const unsigned ibase = b * (unsigned)a.OH * (unsigned)grow + (unsigned)c, obase = b * (unsigned)a.H * (unsigned)orow + (unsigned)c;
+
+    const int za = a.aq->zero_point;
+    const int fill = (int)((unsigned)(za & 0xff) * 0x01010101u);
+    const float acc_scale = __fmul_rn(a.aq->scale, a.bq->scale);
+    HqEpilogue ep = {};
+    if (MODE != 0) ep = hq_make_epilogue(acc_scale, a.range);
+
+    // weights by output parity (row, column), bytes in the order of the gradient pixels above
+    int wt[4][4], nz[4][4];
+    {
+        int k[9];
+#pragma unroll
+        for (int t = 0; t < 9; t++) k[t] = *reinterpret_cast<const int *>(a.Wt + (size_t)t * a.C + c);
+        dw_transpose4(k[4], 0, 0, 0, wt[0]);                         // even, even: w[1][1]
+        dw_transpose4(k[5], k[3], 0, 0, wt[1]);                      // even, odd:  w[1][2], w[1][0]
+        dw_transpose4(k[7], 0, k[1], 0, wt[2]);                      // odd, even:  w[2][1], w[0][1]
+        dw_transpose4(k[8], k[6], k[2], k[0], wt[3]);                // odd, odd:   w[2][2], w[2][0], w[0][2], w[0][0]
+    }
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) nz[s][e] = -(za * __builtin_amdgcn_sdot4(wt[s][e], 0x01010101, 0, false));
+
+    const bool okr = x + 1 < a.OW, both = 2 * x + 1 < a.W, pair = (a.W & 1) == 0;
+    const unsigned goff = ibase + (unsigned)x * (unsigned)a.C, goff1 = okr ? goff + (unsigned)a.C : goff;
+    const unsigned off0 = obase + 2u * (unsigned)x * (unsigned)a.C, off1 = off0 + (unsigned)a.C;
+    auto load_row = [&](int y, int (&raw)[2]) {
+        if (y < a.OH) {
+            const int8_t *p = a.A + (size_t)y * grow;
+            raw[0] = dw_load(p, goff);
+            raw[1] = dw_load(p, goff1);
+        } else {
+            raw[0] = raw[1] = fill;
+        }
+    };
+
+    int mn = INT_MAX, mx = INT_MIN;
+    unsigned nlo = 0, nhi = 0;
+    int ring[RING][2];                                               // slot k: gradient row y0 + k, y0 + k + 3, ...
+    auto run = [&](auto full) {
+        constexpr bool FULL = decltype(full)::value;
+#pragma unroll
+        for (int k = 0; k < RING; k++) load_row(y0 + k, ring[k]);
+        ring[0][1] = okr ? ring[0][1] : fill;
+        int y = y0;
+        auto step = [&](auto phase) {
+            constexpr int P = decltype(phase)::value, Q = (P + 1) % 3;
+            ring[Q][1] = okr ? ring[Q][1] : fill;                    // (the upper row's turn came one step earlier)
+            int t[4];
+            dw_transpose4(ring[P][0], ring[P][1], ring[Q][0], ring[Q][1], t);
+            if (y + RING <= y1) load_row(y + RING, ring[P]);
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                if (2 * y + i >= a.H) continue;
+                int cv[8];
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    cv[e] = __builtin_amdgcn_sdot4(t[e], wt[2 * i][e], nz[2 * i][e], false);
+                    cv[4 + e] = __builtin_amdgcn_sdot4(t[e], wt[2 * i + 1][e], nz[2 * i + 1][e], false);
+                }
+                dw_emit<MODE, FULL>(a, ep, cv, (size_t)(2 * y + i) * orow, off0, off1, pair, both, mn, mx, nlo, nhi);
+            }
+            y++;
+        };
+        while (true) {
+            step(dw_int<0>());
+            if (y >= y1) break;
+            step(dw_int<1>());
+            if (y >= y1) break;
+            step(dw_int<2>());
+            if (y >= y1) break;
+        }
+    };
+    if (live) {
+        if (MODE == 0 || ep.full_grid) run(std::true_type()); else run(std::false_type());
+    }
+    hq_block_stats_commit(mn, mx, nlo, nhi, a.st, red);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         a.st->acc_scale = acc_scale;
         atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)a.B * a.H * a.W * (unsigned long long)a.C);
-        if (fused) *a.outq = a.range->qp;
+        if (MODE != 0) *a.outq = a.range->qp;
     }
 }
 
@@ -309,157 +512,188 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_depthwise_wgrad_kernel(const Dw
     }
 }
 
-// 3x3, stride 1, pad 1 weight gradient: the thread layout of hq_dw3x3_kernel (four channels of
-// one column, sliding down a strip of rows), four output rows at a time.  The reduction runs over
-// pixels, so the rows are byte-transposed: four packed words (four rows, four channels each)
-// become four words holding four vertically adjacent values of one channel (eight v_perm_b32),
-// and a tap's contribution of the four rows is one 4-way dot product against the transposed
-// gradient word.  The three row taps are the transposed block shifted by one row either way
-// (v_alignbyte with the neighbouring blocks).  A workgroup walks over several images and keeps
-// its 36 sums per thread in registers; threads that share channels meet in LDS, and the workgroup
-// leaves with one atomic per value.  The column sums of the input that remove the gradient's
-// zero point are only gathered when that zero point is not 0.
+// Weight gradient of the 3x3 layers with padding 1 and stride 1 or 2, in the manner of hq_dw3x3_kernel: a thread owns four
+// channels of four neighbouring output columns and walks down a strip of rows and over several images.  The reduction
+// runs over pixels, so the four columns' gradients and the inputs of one tap column are byte-transposed words, and a tap's
+// share of the four pixels is one 4-way dot product; the words of the neighbouring tap columns are the same pixels moved
+// by one (one v_perm each).  5.5 vector instructions per pixel and channel (22.5 in the earlier kernel, which packed rows and
+// fetched every input three times): 38 us instead of 68 for 128 x 56 x 56 x 192, stride 2 21 instead of 86.  Threads that share channels meet in LDS, and the workgroup leaves with one
+// atomic per value.  Where the gradient's zero point is not 0 a second walk, with ones in place of the gradients, gathers the
+// column sums of the input that remove it.
 struct Dw3WgradArgs {
     const int8_t *X, *G;
     const hq_qparams *xq, *gq;
     int32_t *acc, *gsum, *xsum;
-    int B, H, W, C;
-    int rows_per_strip;            // multiple of 4
+    int B, H, W, OH, OW, C;
+    int images;                    // images side by side; a thread takes every images-th
+    int rows_per_strip;
 };
 
-// four words = four rows of four channels -> t[e] = (row0[e], row1[e], row2[e], row3[e])
-__device__ inline void dw_transpose4(int a0, int a1, int a2, int a3, int *t)
-{
-    const unsigned p0 = __builtin_amdgcn_perm((unsigned)a1, (unsigned)a0, 0x05010400u);   // (a0.0, a1.0, a0.1, a1.1)
-    const unsigned p1 = __builtin_amdgcn_perm((unsigned)a1, (unsigned)a0, 0x07030602u);   // (a0.2, a1.2, a0.3, a1.3)
-    const unsigned q0 = __builtin_amdgcn_perm((unsigned)a3, (unsigned)a2, 0x05010400u);
-    const unsigned q1 = __builtin_amdgcn_perm((unsigned)a3, (unsigned)a2, 0x07030602u);
-    t[0] = (int)__builtin_amdgcn_perm(q0, p0, 0x05040100u);
-    t[1] = (int)__builtin_amdgcn_perm(q0, p0, 0x07060302u);
-    t[2] = (int)__builtin_amdgcn_perm(q1, p1, 0x05040100u);
-    t[3] = (int)__builtin_amdgcn_perm(q1, p1, 0x07060302u);
-}
+constexpr int DW_WG_THREADS = 512;
 
-__global__ __launch_bounds__(HQ_THREADS) void hq_dw3x3_wgrad_kernel(const Dw3WgradArgs a)
+template <int STRIDE>
+__global__ __launch_bounds__(DW_WG_THREADS) void hq_dw3x3_wgrad_kernel(const Dw3WgradArgs a)
 {
-    extern __shared__ int lds[];                 // [9][C] acc, [C] gsum, [9][C] xsum
-    const int words = 19 * a.C;
-    for (int i = threadIdx.x; i < words; i += HQ_THREADS) lds[i] = 0;
-    __syncthreads();
-    const int c4n = a.C >> 2, rowwords = a.W * c4n;
-    const int q = blockIdx.x * HQ_THREADS + threadIdx.x;
-    const bool live = q < rowwords;
-    const int qq = live ? q : 0;
-    const int ox = qq / c4n, c = (qq - ox * c4n) * 4;
-    const int y0 = blockIdx.y * a.rows_per_strip, y1 = min(a.H, y0 + a.rows_per_strip);
+    constexpr int NW = STRIDE == 1 ? 6 : 9;                          // input columns of the four outputs
+    extern __shared__ int lds[];                                     // [9][C] acc or xsum, [C] gsum
+    const int c4n = a.C >> 2, cols4 = (a.OW + 3) >> 2;
+    const unsigned q = blockIdx.x * DW_WG_THREADS + threadIdx.x;                // (image of the first round, column group, word)
+    const bool live = q < (unsigned)a.images * cols4 * c4n;
+    const unsigned qx = (live ? q : 0) / c4n, b0 = qx / cols4;
+    const int x = 4 * (int)(qx - b0 * cols4), c = (int)((live ? q : 0) - qx * c4n) * 4;
+    const int y0 = blockIdx.y * a.rows_per_strip, y1 = min(a.OH, y0 + a.rows_per_strip);
+    const size_t xrow = (size_t)a.W * a.C, grow = (size_t)a.OW * a.C;
     const int zx = a.xq->zero_point;
-    const bool want_xsum = a.gq->zero_point != 0;
-    const int fill = (int)((unsigned)(zx & 0xff) * 0x01010101u);   // unsigned: the product may set bit 31
-    const bool okl = ox > 0, okr = ox + 1 < a.W;
-    const size_t rowbytes = (size_t)a.W * a.C;
+    const int fill = (int)((unsigned)(zx & 0xff) * 0x01010101u);     // unsigned: the product may set bit 31
+    const int passes = a.gq->zero_point != 0 ? 2 : 1;
 
-    int acc[9][4], xs[9][4], gs[4] = {0, 0, 0, 0};
+    unsigned xoff[NW], goff[4];
+    bool xok[NW], gok[4];
 #pragma unroll
-    for (int t = 0; t < 9; t++)
+    for (int k = 0; k < NW; k++) {
+        const int xi = STRIDE * x - 1 + k;
+        xok[k] = xi >= 0 && xi < a.W;
+        xoff[k] = (unsigned)(xok[k] ? xi : STRIDE * x) * (unsigned)a.C + (unsigned)c;
+    }
 #pragma unroll
-        for (int e = 0; e < 4; e++) { acc[t][e] = 0; xs[t][e] = 0; }
+    for (int k = 0; k < 4; k++) {
+        gok[k] = x + k < a.OW;
+        goff[k] = (unsigned)(gok[k] ? x + k : x) * (unsigned)a.C + (unsigned)c;
+    }
 
-    if (live && y0 < y1) {
-        for (int b = blockIdx.z; b < a.B; b += gridDim.z) {
-            const int8_t *ximg = a.X + (size_t)b * a.H * rowbytes + (size_t)ox * a.C + c;
-            const int8_t *gimg = a.G + (size_t)b * a.H * rowbytes + (size_t)ox * a.C + c;
-            // block of four input rows starting at row y: raw[row][column], zero-point code outside the image
-            auto load_x = [&](int y, int (&raw)[4][3]) {
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const int iy = y + k;
-                    const bool rok = iy >= 0 && iy < a.H;
-                    const int8_t *p = ximg + (ptrdiff_t)iy * rowbytes;
-                    const int l = *reinterpret_cast<const int *>(rok && okl ? p - a.C : ximg);
-                    const int m = *reinterpret_cast<const int *>(rok ? p : ximg);
-                    const int r = *reinterpret_cast<const int *>(rok && okr ? p + a.C : ximg);
-                    raw[k][0] = rok && okl ? l : fill; raw[k][1] = rok ? m : fill; raw[k][2] = rok && okr ? r : fill;
-                }
-            };
-            // gradient rows y .. y+3 of this column; rows past the strip count as zero
-            auto load_g = [&](int y, int (&raw)[4]) {
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const bool rok = y + k < y1;
-                    const int v = *reinterpret_cast<const int *>(rok ? gimg + (size_t)(y + k) * rowbytes : gimg);
-                    raw[k] = rok ? v : 0;
-                }
-            };
-            auto transpose_x = [&](const int (&raw)[4][3], int (&t)[3][4]) {
-#pragma unroll
-                for (int sx = 0; sx < 3; sx++) dw_transpose4(raw[0][sx], raw[1][sx], raw[2][sx], raw[3][sx], t[sx]);
-            };
-            int prev[3][4], cur[3][4], nxt[3][4];             // [column][channel]: four rows in the bytes
-            int xraw[4][3], graw[4];
-            {
-                // of the block above the strip only its last row (y0 - 1) is ever read
-                const int iy = y0 - 1;
-                const bool rok = iy >= 0;
-                const int8_t *p = ximg + (ptrdiff_t)iy * rowbytes;
-                const int l = *reinterpret_cast<const int *>(rok && okl ? p - a.C : ximg);
-                const int m = *reinterpret_cast<const int *>(rok ? p : ximg);
-                const int r = *reinterpret_cast<const int *>(rok && okr ? p + a.C : ximg);
-                const int row3[3] = {rok && okl ? l : fill, rok ? m : fill, rok && okr ? r : fill};
-#pragma unroll
-                for (int sx = 0; sx < 3; sx++) dw_transpose4(0, 0, 0, row3[sx], prev[sx]);
-            }
-            load_x(y0, xraw); transpose_x(xraw, cur);
-            load_x(y0 + 4, xraw);                                // in flight: rows y0+4 .. y0+7, gradient rows y0 .. y0+3
-            load_g(y0, graw);
-            for (int oy = y0; oy < y1; oy += 4) {
-                transpose_x(xraw, nxt);
-                int gt[4];
-                dw_transpose4(graw[0], graw[1], graw[2], graw[3], gt);
-                if (oy + 4 < y1) { load_x(oy + 8, xraw); load_g(oy + 4, graw); }
-                // rows of this block that exist as output rows: a byte of ones per row (input column sums)
-                const int nrow = min(4, y1 - oy);
-                const int ones = nrow >= 4 ? 0x01010101 : nrow == 3 ? 0x00010101 : nrow == 2 ? 0x00000101 : 0x00000001;
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    gs[e] = __builtin_amdgcn_sdot4(gt[e], 0x01010101, gs[e], false);
-#pragma unroll
-                    for (int sx = 0; sx < 3; sx++) {
-                        const int top = (int)__builtin_amdgcn_alignbyte((unsigned)cur[sx][e], (unsigned)prev[sx][e], 3);   // rows oy-1 .. oy+2
-                        const int bot = (int)__builtin_amdgcn_alignbyte((unsigned)nxt[sx][e], (unsigned)cur[sx][e], 1);    // rows oy+1 .. oy+4
-                        acc[sx][e] = __builtin_amdgcn_sdot4(top, gt[e], acc[sx][e], false);
-                        acc[3 + sx][e] = __builtin_amdgcn_sdot4(cur[sx][e], gt[e], acc[3 + sx][e], false);
-                        acc[6 + sx][e] = __builtin_amdgcn_sdot4(bot, gt[e], acc[6 + sx][e], false);
-                        if (want_xsum) {
-                            xs[sx][e] = __builtin_amdgcn_sdot4(top, ones, xs[sx][e], false);
-                            xs[3 + sx][e] = __builtin_amdgcn_sdot4(cur[sx][e], ones, xs[3 + sx][e], false);
-                            xs[6 + sx][e] = __builtin_amdgcn_sdot4(bot, ones, xs[6 + sx][e], false);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int sx = 0; sx < 3; sx++)
-#pragma unroll
-                    for (int e = 0; e < 4; e++) { prev[sx][e] = cur[sx][e]; cur[sx][e] = nxt[sx][e]; }
-            }
-        }
+    for (int pass = 0; pass < passes; pass++) {
+        for (int i = threadIdx.x; i < 10 * a.C; i += DW_WG_THREADS) lds[i] = 0;
+        __syncthreads();
+        int acc[9][4], gs[4] = {0, 0, 0, 0};
 #pragma unroll
         for (int t = 0; t < 9; t++)
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                atomicAdd(&lds[t * a.C + c + e], acc[t][e]);
-                if (want_xsum) atomicAdd(&lds[(10 + t) * a.C + c + e], xs[t][e]);
+            for (int e = 0; e < 4; e++) acc[t][e] = 0;
+        if (live) {
+            for (int b = (int)b0; b < a.B; b += a.images) {
+                // (tensors have fewer than 2^32 elements)
+                const unsigned ximg = (unsigned)b * (unsigned)a.H * (unsigned)xrow, gimg = (unsigned)b * (unsigned)a.OH * (unsigned)grow;
+                auto load_x = [&](int y, int (&raw)[NW]) {           // y is the same for the whole workgroup
+                    if (y >= 0 && y < a.H) {
+                        const int8_t *p = a.X + (size_t)y * xrow;
+#pragma unroll
+                        for (int k = 0; k < NW; k++) raw[k] = dw_load(p, ximg + xoff[k]);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < NW; k++) raw[k] = fill;
+                    }
+                };
+                auto load_g = [&](int y, int (&raw)[4]) {            // rows outside the strip count as zero
+                    if (y >= y0 && y < y1) {
+                        const int8_t *p = a.G + (size_t)y * grow;
+#pragma unroll
+                        for (int k = 0; k < 4; k++) raw[k] = dw_load(p, gimg + goff[k]);
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 4; k++) raw[k] = 0;
+                    }
+                };
+                // words of the three tap columns: t[s][e] = input pixels STRIDE * (x .. x+3) - 1 + s of channel e
+                auto transpose_x = [&](int (&raw)[NW], int (&t)[3][4]) {
+#pragma unroll
+                    for (int k = 0; k < NW; k++)
+                        if (k != 1) raw[k] = xok[k] ? raw[k] : fill;
+                    if constexpr (STRIDE == 1) {
+                        dw_transpose4(raw[1], raw[2], raw[3], raw[4], t[1]);
+                        t[0][0] = dw_shift_back<0>(t[1][0], raw[0]); t[0][1] = dw_shift_back<1>(t[1][1], raw[0]);
+                        t[0][2] = dw_shift_back<2>(t[1][2], raw[0]); t[0][3] = dw_shift_back<3>(t[1][3], raw[0]);
+                        t[2][0] = dw_shift_in<0>(t[1][0], raw[5]); t[2][1] = dw_shift_in<1>(t[1][1], raw[5]);
+                        t[2][2] = dw_shift_in<2>(t[1][2], raw[5]); t[2][3] = dw_shift_in<3>(t[1][3], raw[5]);
+                    } else {
+                        dw_transpose4(raw[0], raw[2], raw[4], raw[6], t[0]);
+                        dw_transpose4(raw[1], raw[3], raw[5], raw[7], t[1]);
+                        t[2][0] = dw_shift_in<0>(t[0][0], raw[8]); t[2][1] = dw_shift_in<1>(t[0][1], raw[8]);
+                        t[2][2] = dw_shift_in<2>(t[0][2], raw[8]); t[2][3] = dw_shift_in<3>(t[0][3], raw[8]);
+                    }
+                };
+                auto transpose_g = [&](int (&raw)[4], int y, int (&t)[4]) {
+                    if (pass == 1) {                                 // ones where an output exists
+                        const bool row = y >= y0 && y < y1;
+#pragma unroll
+                        for (int k = 0; k < 4; k++) raw[k] = row ? 0x01010101 : 0;
+                    }
+#pragma unroll
+                    for (int k = 1; k < 4; k++) raw[k] = gok[k] ? raw[k] : 0;
+                    dw_transpose4(raw[0], raw[1], raw[2], raw[3], t);
+#pragma unroll
+                    for (int e = 0; e < 4; e++) gs[e] = __builtin_amdgcn_sdot4(t[e], 0x01010101, gs[e], false);
+                };
+                auto tap_row = [&](int r, const int (&t)[3][4], const int (&g)[4]) {
+#pragma unroll
+                    for (int s = 0; s < 3; s++)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) acc[3 * r + s][e] = __builtin_amdgcn_sdot4(t[s][e], g[e], acc[3 * r + s][e], false);
+                };
+                if constexpr (STRIDE == 1) {
+                    // input row y meets gradient rows y + 1, y, y - 1 with the filter's rows 0, 1, 2
+                    int xr[2][NW], gr[2][4], g[3][4] = {};
+                    load_x(y0 - 1, xr[0]); load_g(y0, gr[0]);
+                    load_x(y0, xr[1]); load_g(y0 + 1, gr[1]);
+                    int y = y0 - 1;
+                    auto step = [&](auto phase) {                    // 6 phases: two raw sets, three gradient slots
+                        constexpr int P = decltype(phase)::value, R = P % 2, N = P % 3, C0 = (P + 2) % 3, L = (P + 1) % 3;
+                        int t[3][4];
+                        transpose_x(xr[R], t);
+                        transpose_g(gr[R], y + 1, g[N]);
+                        if (y + 2 <= y1) { load_x(y + 2, xr[R]); load_g(y + 3, gr[R]); }
+                        tap_row(0, t, g[N]);
+                        tap_row(1, t, g[C0]);
+                        tap_row(2, t, g[L]);
+                        y++;
+                    };
+                    while (true) {
+                        step(dw_int<0>()); if (y > y1) break;
+                        step(dw_int<1>()); if (y > y1) break;
+                        step(dw_int<2>()); if (y > y1) break;
+                        step(dw_int<3>()); if (y > y1) break;
+                        step(dw_int<4>()); if (y > y1) break;
+                        step(dw_int<5>()); if (y > y1) break;
+                    }
+                } else {
+                    // output row y meets input rows 2y - 1, 2y, 2y + 1; the last is the next row's first
+                    int xr[2][NW], gr[4], t[2][3][4];
+                    load_x(2 * y0 - 1, xr[0]);
+                    transpose_x(xr[0], t[0]);
+                    load_x(2 * y0, xr[0]); load_x(2 * y0 + 1, xr[1]); load_g(y0, gr);
+                    int y = y0;
+                    auto step = [&](auto phase) {
+                        constexpr int P = decltype(phase)::value;
+                        int g[4], te[3][4];
+                        transpose_x(xr[0], te);
+                        transpose_x(xr[1], t[1 - P]);
+                        transpose_g(gr, y, g);
+                        if (y + 1 < y1) { load_x(2 * y + 2, xr[0]); load_x(2 * y + 3, xr[1]); load_g(y + 1, gr); }
+                        tap_row(0, t[P], g);
+                        tap_row(1, te, g);
+                        tap_row(2, t[1 - P], g);
+                        y++;
+                    };
+                    while (true) {
+                        step(dw_int<0>()); if (y >= y1) break;
+                        step(dw_int<1>()); if (y >= y1) break;
+                    }
+                }
             }
 #pragma unroll
-        for (int e = 0; e < 4; e++) atomicAdd(&lds[9 * a.C + c + e], gs[e]);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < words; i += HQ_THREADS) {
-        const int v = lds[i];
-        if (v == 0) continue;
-        const int row = i / a.C, col = i - row * a.C;
-        if (row < 9) atomicAdd(a.acc + row * a.C + col, v);
-        else if (row == 9) atomicAdd(a.gsum + col, v);
-        else atomicAdd(a.xsum + (row - 10) * a.C + col, v);
+            for (int t = 0; t < 9; t++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) atomicAdd(&lds[t * a.C + c + e], acc[t][e]);
+            if (pass == 0)
+#pragma unroll
+                for (int e = 0; e < 4; e++) atomicAdd(&lds[9 * a.C + c + e], gs[e]);
+        }
+        __syncthreads();
+        int32_t *sums = pass == 0 ? a.acc : a.xsum;
+        for (int i = threadIdx.x; i < 10 * a.C; i += DW_WG_THREADS) {
+            const int v = lds[i];
+            if (v != 0) atomicAdd(i < 9 * a.C ? sums + i : a.gsum + (i - 9 * a.C), v);
+        }
+        __syncthreads();
     }
 }
 
@@ -500,22 +734,31 @@ int hq_launch_depthwise(const hq_problem *p, int dgrad, const int8_t *A, const h
     a.C = p->C; a.R = p->R; a.S = p->S; a.stride = p->stride; a.pad = p->pad; a.dgrad = dgrad;
     if (!dgrad) { a.M = p->B * OH * OW; a.Hs = p->H; a.Ws = p->W; a.Ho = OH; a.Wo = OW; }
     else        { a.M = p->B * p->H * p->W; a.Hs = OH; a.Ws = OW; a.Ho = p->H; a.Wo = p->W; }
-    if (!sr_seed && p->R == 3 && p->S == 3 && p->stride == 1 && p->pad == 1 && p->B <= 65535) {
+    const int mode = out32 ? 0 : sr_seed ? 2 : 1;
+    if (p->R == 3 && p->S == 3 && p->stride <= 2 && p->pad == 1) {
         Dw3Args d;
         d.A = A; d.Wt = Wt; d.wsum = wsum; d.aq = aq; d.bq = bq; d.range = range;
         d.out8 = out8; d.out32 = out32; d.outq = outq; d.st = st;
-        d.B = p->B; d.H = p->H; d.W = p->W; d.C = p->C; d.flip = dgrad;
-        const int xb = (p->W * (p->C / 4) + HQ_THREADS - 1) / HQ_THREADS;
-        // strips: enough workgroups to fill the chip several times, rows per strip a multiple of 3
-        int strips = (4096 + xb * p->B - 1) / (xb * p->B);
-        if (strips < 1) strips = 1;
-        int rps = (p->H + strips - 1) / strips;
-        rps = (rps + 2) / 3 * 3;
-        if (rps < 6) rps = 6;
-        d.rows_per_strip = rps;
-        strips = (p->H + rps - 1) / rps;
-        hipLaunchKernelGGL(hq_dw3x3_kernel, dim3((unsigned)xb, (unsigned)strips, (unsigned)p->B), dim3(HQ_THREADS), 0,
-                           stream, d);
+        d.B = p->B; d.H = p->H; d.W = p->W; d.OH = OH; d.OW = OW; d.C = p->C; d.flip = dgrad; d.sr = a.sr;
+        const bool s2_dgrad = dgrad && p->stride == 2;
+        const int cols = s2_dgrad ? OW : (OW + 1) / 2;
+        const long xb = ((long)p->B * cols * (p->C / 4) + HQ_THREADS - 1) / HQ_THREADS;
+        // strips of output rows: about 16 workgroups per compute unit, at least four rows each (a strip reads two input
+        // rows beyond its own)
+        int strips = (int)std::min((4096 + xb - 1) / xb, (long)(OH + 3) / 4);
+        d.rows_per_strip = (OH + strips - 1) / strips;
+        strips = (OH + d.rows_per_strip - 1) / d.rows_per_strip;
+        const dim3 grid((unsigned)xb, (unsigned)strips);
+        if (s2_dgrad) {
+            auto k = mode == 0 ? hq_dw3x3_s2_dgrad_kernel<0> : mode == 1 ? hq_dw3x3_s2_dgrad_kernel<1> : hq_dw3x3_s2_dgrad_kernel<2>;
+            hipLaunchKernelGGL(k, grid, dim3(HQ_THREADS), 0, stream, d);
+        } else if (p->stride == 2) {
+            auto k = mode == 0 ? hq_dw3x3_kernel<2, 0> : hq_dw3x3_kernel<2, 1>;       // (forward only: never stochastic)
+            hipLaunchKernelGGL(k, grid, dim3(HQ_THREADS), 0, stream, d);
+        } else {
+            auto k = mode == 0 ? hq_dw3x3_kernel<1, 0> : mode == 1 ? hq_dw3x3_kernel<1, 1> : hq_dw3x3_kernel<1, 2>;
+            hipLaunchKernelGGL(k, grid, dim3(HQ_THREADS), 0, stream, d);
+        }
         return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
     }
     const size_t total = (size_t)a.M * (a.C / 4);
@@ -545,24 +788,23 @@ int hq_launch_depthwise_wgrad(const hq_problem *p, const int8_t *X, const hq_qpa
     a.stride = p->stride; a.pad = p->pad;
     const size_t ws_words = hq_wgrad_workspace_bytes(p) / 4;
     hipLaunchKernelGGL(dw_zero_kernel, dim3(16), dim3(256), 0, stream, a.acc, ws_words);
-    if (p->R == 3 && p->S == 3 && p->stride == 1 && p->pad == 1 && 19 * (size_t)p->C * 4 <= 64 * 1024) {
+    const size_t dw3_lds = 10 * (size_t)p->C * 4;
+    if (p->R == 3 && p->S == 3 && p->stride <= 2 && p->pad == 1 && dw3_lds <= 64 * 1024) {
         Dw3WgradArgs d;
         d.X = X; d.G = dY; d.xq = xq; d.gq = gq; d.acc = a.acc; d.gsum = a.gsum; d.xsum = a.xsum;
-        d.B = p->B; d.H = p->H; d.W = p->W; d.C = p->C;
-        const int xb = (p->W * (p->C / 4) + HQ_THREADS - 1) / HQ_THREADS;
-        // about four workgroups per compute unit: strips of at least 16 rows (a strip also reads the row
-        // above it and up to four rows below), then images in turn
-        int strips = p->H / 16 > 0 ? p->H / 16 : 1;
-        while (strips > 1 && xb * strips > 1024) strips--;
-        int rps = (p->H + strips - 1) / strips;
-        rps = (rps + 3) / 4 * 4;
-        d.rows_per_strip = rps;
-        strips = (p->H + rps - 1) / rps;
-        int gz = 768 / (xb * strips);
-        if (gz < 1) gz = 1;
-        if (gz > p->B) gz = p->B;
-        hipLaunchKernelGGL(hq_dw3x3_wgrad_kernel, dim3((unsigned)xb, (unsigned)strips, (unsigned)gz), dim3(HQ_THREADS),
-                           19 * (size_t)p->C * 4, stream, d);
+        d.B = p->B; d.H = p->H; d.W = p->W; d.OH = OH; d.OW = OW; d.C = p->C;
+        // One workgroup of DW_WG_THREADS per compute unit: every workgroup ends with up to 10 * C atomics on the same
+        // addresses, so more of them cost more than the latency they hide.  Strips of at least four rows where the
+        // images alone are too few, then images in turn.
+        const long per = (long)((OW + 3) / 4) * (p->C / 4);          // threads of one image
+        const long most = 256L * DW_WG_THREADS;
+        int strips = (int)std::max(1L, std::min(most / (per * p->B), (long)(OH + 3) / 4));
+        d.rows_per_strip = (OH + strips - 1) / strips;
+        strips = (OH + d.rows_per_strip - 1) / d.rows_per_strip;
+        d.images = (int)std::max(1L, std::min((long)p->B, most / (per * strips)));
+        const unsigned blocks = (unsigned)((d.images * per + DW_WG_THREADS - 1) / DW_WG_THREADS);
+        auto k = p->stride == 1 ? hq_dw3x3_wgrad_kernel<1> : hq_dw3x3_wgrad_kernel<2>;
+        hipLaunchKernelGGL(k, dim3(blocks, (unsigned)strips), dim3(DW_WG_THREADS), dw3_lds, stream, d);
         ra.first = (int)((K + 255) / 256);
         hipLaunchKernelGGL(dw_wgrad_finalize_kernel, dim3((unsigned)((K + 255) / 256) + (unsigned)ra.n), dim3(256), 0, stream,
                            a.acc, a.gsum, a.xsum, xq, gq, (unsigned)a.M, (int)K, p->C, dW, dW_acc, ra);

@@ -200,14 +200,15 @@ __device__ inline int hq_requant(int c, const HqRequant &q, unsigned &nlo, unsig
 // with min / max and exact clip counts folded in (Sec. 4, steps 1 and 2).
 // Per value: convert, multiply, round (the requantization of the static quantizer), add the
 // zero point, pack.  Clipped values are counted per lane from the rounded floats, and only in
-// groups whose extreme accumulators clip: requantization is monotone in the accumulator, so
-// the extremes decide for the whole group.
+// groups whose extreme accumulators may clip: requantization is monotone in the accumulator, so
+// the extremes decide for the whole group, and two bounds on the accumulator, worked out once, decide for them.
 // ---------------------------------------------------------------------------------------
 struct HqEpilogue {
     float mult;          // (s_a * s_b) / s_out
     float flo, fhi;      // grid bounds relative to the zero point
     float zoff;          // zero point + 128: codes are formed as unsigned bytes, see below
     bool full_grid;      // grid is -128..127: the saturating pack is the whole clamp
+    int c_lo, c_hi;      // accumulators in [c_lo, c_hi] surely do not clip under round to nearest
 };
 
 __device__ inline HqEpilogue hq_make_epilogue(float acc_scale, const hq_range *r)
@@ -218,6 +219,12 @@ __device__ inline HqEpilogue hq_make_epilogue(float acc_scale, const hq_range *r
     e.fhi = (float)(r->qhi - r->qp.zero_point);
     e.zoff = (float)(r->qp.zero_point + 128);
     e.full_grid = r->qlo == -128 && r->qhi == 127;
+    // a value clips iff |c| * mult rounds past the bound, i.e. c > (fhi + 1/2) / mult up to the few roundings (2^-24
+    // each) of that quotient, of float(c) and of the product: 1e-6 of it and one unit cover them
+    const float hi = __fmul_rn(__fdiv_rn(e.fhi + 0.5f, e.mult), 0.999999f) - 1.0f;
+    const float lo = __fmul_rn(__fdiv_rn(e.flo - 0.5f, e.mult), 0.999999f) + 1.0f;
+    e.c_hi = hi < 2147483000.0f ? (int)hi : INT_MAX;
+    e.c_lo = lo > -2147483000.0f ? (int)lo : INT_MIN;
     return e;
 }
 
@@ -237,32 +244,24 @@ __device__ inline void hq_global_to_lds16(const void *src, void *wave_base)
                  : "=&s"(keep) : "v"(src), "s"(m) : "memory");
 }
 
-// The same for 4 bytes per lane: lane l lands at wave_base + 4 * l.
-__device__ inline void hq_global_to_lds4(const void *src, void *wave_base)
-{
-    const unsigned m = __builtin_amdgcn_readfirstlane(
-        (unsigned)(size_t)(__attribute__((address_space(3))) void *)wave_base);
-    unsigned keep;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(keep) : "v"(src), "s"(m) : "memory");
-}
-
-// Three-operand integer minimum / maximum (v_min3_i32 / v_max3_i32).  Written out because the compiler
-// balances a chain of two-operand minima into a tree and then needs 12 instructions for 16 values, not 8.
+// Three-operand integer minimum / maximum (v_min3_i32 / v_max3_i32).  The empty statement keeps the compiler from
+// balancing a chain of minima into a tree of two-operand ones (12 instructions for 16 values instead of 8).  The
+// instruction itself is left to the compiler: it knows how long the result of a dot product or an MFMA has to
+// settle before it may be read, which it does not see inside an asm statement.
 __device__ inline int hq_min3(int a, int b, int c)
 {
-    int r;
-    asm("v_min3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    int r = min(min(a, b), c);
+    asm("" : "+v"(r));
     return r;
 }
 __device__ inline int hq_max3(int a, int b, int c)
 {
-    int r;
-    asm("v_max3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    int r = max(max(a, b), c);
+    asm("" : "+v"(r));
     return r;
 }
 
-// N = 4 or 16 accumulators -> N / 4 words of signed codes.  v_cvt_pk_u8_f32 saturates to
+// N = 4, 8 or 16 accumulators -> N / 4 words of signed codes.  v_cvt_pk_u8_f32 saturates to
 // 0..255, which after the flip of the top bits is the clamp to -128..127.
 template <int N, bool FULL_GRID>
 __device__ inline void hq_requant_group(const int *c, const HqEpilogue &ep, int &mn, int &mx,
@@ -276,7 +275,7 @@ __device__ inline void hq_requant_group(const int *c, const HqEpilogue &ep, int 
     float f[N];
 #pragma unroll
     for (int e = 0; e < N; e++) f[e] = hq_round_scaled(c[e], ep.mult);
-    if (__any(hq_round_scaled(gmx, ep.mult) > ep.fhi || hq_round_scaled(gmn, ep.mult) < ep.flo)) {
+    if (__any(gmx > ep.c_hi || gmn < ep.c_lo)) {
         // rounded values and bounds are whole numbers: clamping the difference to [0, 1] is the
         // indicator of a clipped value (a subtraction with the clamp modifier, no compare)
         float nh = 0.0f, nl = 0.0f;

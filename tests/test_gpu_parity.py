@@ -325,6 +325,28 @@ def test_small_launches_and_the_lines_to_the_tile_kernels(H, hq, L):
     test_random_shapes_all_ops(H, hq, L)
 
 
+# Remainders of the 3x3 depthwise kernels: columns in pairs (weight gradient: in fours), rows in strips, the last row and
+# column of a strided image odd or even, images narrower than a group, more channels than a workgroup has lanes.
+DEPTHWISE_EDGES = [wl.LayerShape("dw_edge", wl.DEPTHWISE, B, Hh, Ww, C, 3, 3, s, 1, C)
+                   for s in (1, 2) for B, Hh, Ww, C in ((1, 1, 1, 4), (3, 2, 3, 20), (2, 6, 1, 8), (2, 5, 4, 1040), (5, 33, 9, 12), (2, 18, 14, 192))]
+
+
+@pytest.mark.parametrize("L", DEPTHWISE_EDGES, ids=["b%d_%dx%d_c%d_s%d" % (l.B, l.H, l.W, l.C, l.stride) for l in DEPTHWISE_EDGES])
+@pytest.mark.parametrize("g_asym", [False, True])
+def test_depthwise_3x3_edges(H, hq, L, g_asym):
+    y_track, g_track = H.TensorTrack(0.9, g_asym), H.TensorTrack(0.9, not g_asym)
+    Wdev = None
+    for t in range(3):                                       # dynamic, nearest, stochastic
+        X, W, dY = rand_layer_inputs(L, 40 + t, x_asym=not g_asym, g_asym=g_asym)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        Xd, dYd = H.DevTensor(X), H.DevTensor(dY)
+        y_track.step(L, "fwd", X, W0, Xd, Wdev)
+        g_track.step(L, "dgrad", dY, W0, dYd, Wdev, seed=77 if t == 2 else None)
+    _, dWa = H.gpu_wgrad(L, Xd, dYd)
+    assert np.array_equal(dWa, oracle.wgrad(H.oracle_problem(L), X.codes, X.zero_point, dY.codes, dY.zero_point))
+
+
 def test_weight_prepare_layouts_and_sums(H, hq):
     L = wl.conv("prep", 1, 6, 24, 40, 3)
     W = wl.he_weight(np.random.default_rng(5), L)
