@@ -244,6 +244,22 @@ __device__ inline void hq_global_to_lds16(const void *src, void *wave_base)
                  : "=&s"(keep) : "v"(src), "s"(m) : "memory");
 }
 
+typedef __attribute__((__vector_size__(2 * sizeof(int)))) int tr_v2i;
+#define LDS_PTR(T) __attribute__((address_space(3))) T *
+
+// Fragment of one 32-channel x 32-pixel operand block for the 32x32x32 MFMA, read transposed (ds_read_b64_tr_b8) from LDS
+// rows of one pixel's channels: lane l gets channel (l % 32) and the 16 pixels of half (l / 32).  `tile` points at row 0
+// of the k-step and column 0 of the 32-channel block; P is the pitch of a row.
+template <int P> __device__ inline v4i hq_read_frag_tr(const int8_t *tile, int lane)
+{
+    const int j = lane & 15, grp = (lane >> 4) & 1, half = lane >> 5;
+    const int8_t *p = tile + (half * 16 + (j >> 1)) * P + 16 * grp + 8 * (j & 1);
+    tr_v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(tr_v2i))(p));
+    tr_v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(tr_v2i))(p + 8 * P));
+    v4i f = {lo[0], lo[1], hi[0], hi[1]};
+    return f;
+}
+
 // Three-operand integer minimum / maximum (v_min3_i32 / v_max3_i32).  The empty statement keeps the compiler from
 // balancing a chain of minima into a tree of two-operand ones (12 instructions for 16 values instead of 8).  The
 // instruction itself is left to the compiler: it knows how long the result of a dot product or an MFMA has to

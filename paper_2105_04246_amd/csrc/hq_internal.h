@@ -47,6 +47,10 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
                     const hq_qparams *gq, float *dW, int32_t *dW_acc, void *ws, hipStream_t stream,
                     const HqRideAlong *ride = nullptr);
 
+// Weight gradients over few pixels, in one launch; HQ_E_BADSHAPE: not covered.
+int hq_try_launch_wgrad_small(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY,
+                              const hq_qparams *gq, float *dW, int32_t *dW_acc, hipStream_t stream, const HqRideAlong *ride);
+
 int hq_launch_depthwise_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY,
                               const hq_qparams *gq, float *dW, int32_t *dW_acc, void *ws, hipStream_t stream,
                               const HqRideAlong *ride = nullptr);

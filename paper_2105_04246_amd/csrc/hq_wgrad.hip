@@ -19,9 +19,6 @@
 
 namespace {
 
-typedef __attribute__((__vector_size__(2 * sizeof(int)))) int tr_v2i;
-#define LDS_PTR(T) __attribute__((address_space(3))) T *
-
 constexpr int MB = 64;             // pixels staged per step (two MFMA k-steps of 32)
 
 struct WgradArgs {
@@ -51,19 +48,6 @@ __device__ inline v4i load16(const int8_t *p, int nbytes, bool aligned16)
     v[2] = nbytes > 8 ? q[2] : 0;
     v[3] = nbytes > 12 ? q[3] : 0;
     return v;
-}
-
-// Fragment of one 32-channel x 32-pixel operand block for the 32x32x32 MFMA: lane l gets
-// channel (l % 32) and the 16 pixels of half (l / 32).  `tile` points at row 0 of the k-step
-// and column 0 of the 32-channel block.
-template <int P> __device__ inline v4i read_frag_tr(const int8_t *tile, int lane)
-{
-    const int j = lane & 15, grp = (lane >> 4) & 1, half = lane >> 5;
-    const int8_t *p = tile + (half * 16 + (j >> 1)) * P + 16 * grp + 8 * (j & 1);
-    tr_v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(tr_v2i))(p));
-    tr_v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(tr_v2i))(p + 8 * P));
-    v4i f = {lo[0], lo[1], hi[0], hi[1]};
-    return f;
 }
 
 // PACKED: layers with fewer than 16 input channels (a network's first layer).  The tile's columns
@@ -250,10 +234,10 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
                 v4i gf[NT], xf[KT];
 #pragma unroll
                 for (int i = 0; i < NT; i++)
-                    gf[i] = read_frag_tr<PG>(&Gs[buf][ks * 32 * PG + wn * WTN + i * 32], lane);
+                    gf[i] = hq_read_frag_tr<PG>(&Gs[buf][ks * 32 * PG + wn * WTN + i * 32], lane);
 #pragma unroll
                 for (int j = 0; j < KT; j++)
-                    xf[j] = read_frag_tr<PX>(&Xs[buf][ks * 32 * PX + wk * WTK + j * 32], lane);
+                    xf[j] = hq_read_frag_tr<PX>(&Xs[buf][ks * 32 * PX + wk * WTK + j * 32], lane);
 #pragma unroll
                 for (int i = 0; i < NT; i++)
 #pragma unroll
@@ -1021,6 +1005,8 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
     a.magic_OW = a.magic_ok ? hq_magic32((unsigned)OW) : 0u;
     a.magic_OH = a.magic_ok ? hq_magic32((unsigned)OH) : 0u;
 
+    const int rc = hq_try_launch_wgrad_small(p, X, xq, dY, gq, dW, dW_acc, stream, ride);
+    if (rc != HQ_E_BADSHAPE) return rc;
     const WbandPlan pl = wband_plan(p);
     if (pl.covered) {
         // every workgroup stores its sums to a slot of its own: nothing to zero, no atomics

@@ -325,6 +325,23 @@ def test_small_launches_and_the_lines_to_the_tile_kernels(H, hq, L):
     test_random_shapes_all_ops(H, hq, L)
 
 
+# Weight gradients in one launch: tiles of every size, channel counts off 16 and 32, pixels off 32, and past each line.
+WGRAD_LINES = [wl.linear("ws_1px", 1, 16, 4), wl.linear("ws_4w", 100, 52, 68), wl.linear("ws_64", 70, 2064, 1040), wl.conv("ws_8w", 3, 25, 48, 36, 3),
+               wl.linear("ws_32x64", 1030, 304, 848), wl.conv("ws_16w_s2", 9, 50, 32, 80, 3, stride=2), wl.LayerShape("ws_5x3", wl.CONV, 2, 19, 14, 20, 5, 3, 3, 2, 48),
+               wl.linear("past_ws_512", 520, 1040, 1040), wl.linear("past_ws_64", 300, 2064, 1040), wl.conv("past_ws_band", 12, 27, 64, 64, 3),
+               wl.conv("past_ws_s2", 9, 62, 32, 80, 3, stride=2), wl.conv("past_ws_c36", 4, 47, 36, 100, 3, stride=2), wl.conv("past_ws_big", 20, 29, 80, 96, 1, stride=1, pad=0)]
+
+
+@pytest.mark.parametrize("L", WGRAD_LINES, ids=[l.name for l in WGRAD_LINES])
+@pytest.mark.parametrize("g_asym", [False, True])
+def test_weight_gradient_lines(H, hq, L, g_asym):
+    X, _, dY = rand_layer_inputs(L, 60, g_asym=g_asym)
+    dW, dWa = H.gpu_wgrad(L, H.DevTensor(X), H.DevTensor(dY))
+    ref = oracle.wgrad(H.oracle_problem(L), X.codes, X.zero_point, dY.codes, dY.zero_point)
+    assert np.array_equal(dWa, ref)
+    assert np.array_equal(dW, oracle.wgrad_scale(ref, X.scale, dY.scale))
+
+
 # Remainders of the 3x3 depthwise kernels: columns in pairs (weight gradient: in fours), rows in strips, the last row and
 # column of a strided image odd or even, images narrower than a group, more channels than a workgroup has lanes.
 DEPTHWISE_EDGES = [wl.LayerShape("dw_edge", wl.DEPTHWISE, B, Hh, Ww, C, 3, 3, s, 1, C)
