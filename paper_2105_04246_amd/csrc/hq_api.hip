@@ -225,6 +225,8 @@ static int gemm_common(const hq_problem *p, int dgrad, const int8_t *A, const hq
     }
     rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
     if (rc != HQ_E_BADSHAPE) return rc;
+    rc = hq_try_launch_regw(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
+    if (rc != HQ_E_BADSHAPE) return rc;
     if (sr_seed) {
         // stochastic rounding: the two 3x3 / 1x1 fast paths, else the two general kernels
         if (p->kind == HQ_DEPTHWISE)

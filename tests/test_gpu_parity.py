@@ -325,6 +325,25 @@ def test_small_launches_and_the_lines_to_the_tile_kernels(H, hq, L):
     test_random_shapes_all_ops(H, hq, L)
 
 
+# Weights in registers: units of 256 pixels that span rows and images in every way, the last one short; widest image, two
+# channel blocks, the smallest launch that takes the kernel; an image too wide for it.
+REGW_SHAPES = [wl.LayerShape("regw", wl.CONV, B, Hh, Ww, 64, 3, 3, 1, 1, n)
+               for B, Hh, Ww, n in ((7, 31, 29, 64), (131, 7, 7, 64), (4200, 1, 1, 64), (1500, 3, 1, 64), (20, 2, 125, 128), (1, 40, 126, 64), (1, 40, 128, 64))]
+
+
+@pytest.mark.parametrize("L", REGW_SHAPES, ids=["b%d_%dx%d_n%d" % (l.B, l.H, l.W, l.Cout) for l in REGW_SHAPES])
+@pytest.mark.parametrize("g_asym", [False, True])
+def test_weights_in_registers(H, hq, L, g_asym):
+    y_track, g_track = H.TensorTrack(0.9, g_asym), H.TensorTrack(0.9, not g_asym)
+    Wdev = None
+    for t in range(3):                                       # dynamic, nearest, stochastic
+        X, W, dY = rand_layer_inputs(L, 90 + t, x_asym=not g_asym, g_asym=g_asym)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        y_track.step(L, "fwd", X, W0, H.DevTensor(X), Wdev)
+        g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
+
+
 # Weight gradients in one launch: tiles of every size, channel counts off 16 and 32, pixels off 32, and past each line.
 WGRAD_LINES = [wl.linear("ws_1px", 1, 16, 4), wl.linear("ws_4w", 100, 52, 68), wl.linear("ws_64", 70, 2064, 1040), wl.conv("ws_8w", 3, 25, 48, 36, 3),
                wl.linear("ws_32x64", 1030, 304, 848), wl.conv("ws_16w_s2", 9, 50, 32, 80, 3, stride=2), wl.LayerShape("ws_5x3", wl.CONV, 2, 19, 14, 20, 5, 3, 3, 2, 48),
