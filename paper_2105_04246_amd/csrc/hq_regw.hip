@@ -57,7 +57,7 @@ __device__ inline void global_to_lds16(const int8_t *base, unsigned off, void *w
 template <int MODE>
 __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a)
 {
-    constexpr int CB = 64, KC = CB / 32, STORES = MODE == 0 ? 8 : 2;
+    constexpr int CB = 64, KC = CB / 32, STORES = MODE == 0 ? 32 : 2;
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     __shared__ __attribute__((aligned(16))) int bias[64];
     __shared__ int red[4 * (RW_THREADS / 64)];
@@ -124,11 +124,12 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
     if (tid < 64) bias[tid] = -za * bz;
     // Weights of this workgroup's 64 channels.  A fragment's 32 rows lie far apart, so loading them costs 64 cache lines a
     // KB: every wavefront fetches an eighth of the 36 fragments into LDS, where all read them from.  Row i of a fragment is
-    // channel sigma32(i), so that a lane ends up with 16 consecutive output channels.
+    // channel sigma32(i), so that a lane ends up with 16 consecutive output channels; channel i for 32-bit outputs, whose
+    // products are formed transposed (see finish).
     v4i wf[9][KC][2];
     {
         int8_t *frags = smem + bufbytes;                             // the second buffer is not needed yet
-        const int8_t *wrow = a.Bw + (size_t)(n0 + sigma32(lane & 31)) * 9 * CB + 16 * half;
+        const int8_t *wrow = a.Bw + (size_t)(n0 + (MODE == 0 ? lane & 31 : sigma32(lane & 31))) * 9 * CB + 16 * half;
         for (int f = wave; f < 9 * KC * 2; f += RW_THREADS / 64) {
             const int nb = f & 1, kc = (f >> 1) % KC, t = (f >> 1) / KC;
             hq_global_to_lds16(wrow + (size_t)32 * nb * 9 * CB + (a.flip ? 8 - t : t) * CB + 32 * kc, frags + 1024 * f);
@@ -162,6 +163,11 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
             const int8_t *p0 = smem + buf * bufbytes + (rr + 2 * bb) * rowpitch + x * RW_PITCH + 16 * half;
 #pragma unroll
             for (int nb = 0; nb < 2; nb++)
+                if constexpr (MODE == 0) {
+                    const int bz = bias[32 * nb + (lane & 31)];
+#pragma unroll
+                    for (int e = 0; e < 16; e++) acc[nb][e] = bz;
+                } else
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
                     const v4i bz = *reinterpret_cast<const v4i *>(bias + 32 * nb + 16 * half + 4 * k);
@@ -184,11 +190,34 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
                 for (int kc = 0; kc < KC; kc++)
 #pragma unroll
                     for (int nb = 0; nb < 2; nb++)
-                        acc[nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[t][kc][nb], af[t & 1][kc], acc[nb], 0, 0, 0);
+                        acc[nb] = MODE == 0 ? __builtin_amdgcn_mfma_i32_32x32x32_i8(af[t & 1][kc], wf[t][kc][nb], acc[nb], 0, 0, 0)
+                                            : __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[t][kc][nb], af[t & 1][kc], acc[nb], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
+        // 32-bit outputs: a lane holds one channel of 16 pixels, so a store of the wavefront writes two whole 128-byte lines
+        // (with 16 channels of one pixel a lane it would touch 64 lines, a quarter of each: 44 us against 30 for
+        // 128 x 56 x 56 x 64).
+        auto finish32 = [&](int u) {
+            const int P0 = u * RW_UNIT + wave * 32, left = a.M - P0;
+            const unsigned lo = (unsigned)(4 * half * a.N + (lane & 31));
+#pragma unroll
+            for (int nb = 0; nb < 2; nb++) {
+                int c[16];
+#pragma unroll
+                for (int e = 0; e < 16; e++) c[e] = acc[nb][e];
+                if (left >= 32) hq_minmax_group<16>(c, mn, mx);
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    const int row = 8 * (e >> 2) + (e & 3);
+                    int32_t *dst = a.out32 + (size_t)(P0 + row) * a.N + n0 + 32 * nb;
+                    if (left >= 32) dst[lo] = c[e];
+                    else if (row + 4 * half < left) { dst[lo] = c[e]; mn = min(mn, c[e]); mx = max(mx, c[e]); }
+                }
+            }
+        };
         auto finish = [&](int u) {
+            if constexpr (MODE == 0) { finish32(u); return; }
             const int P = u * RW_UNIT + wave * 32 + (lane & 31);
             if (P >= a.M) return;
 #pragma unroll
@@ -197,17 +226,10 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
 #pragma unroll
                 for (int e = 0; e < 16; e++) c[e] = acc[nb][e];
                 const size_t o = (size_t)P * a.N + n0 + 32 * nb + 16 * half;
-                if constexpr (MODE == 0) {
-                    hq_minmax_group<16>(c, mn, mx);
-#pragma unroll
-                    for (int k = 0; k < 4; k++)
-                        *reinterpret_cast<v4i *>(a.out32 + o + 4 * k) = v4i{c[4 * k], c[4 * k + 1], c[4 * k + 2], c[4 * k + 3]};
-                } else {
-                    int w[4];
-                    if constexpr (MODE == 2) hq_requant_group_sr<16, FULL>(c, ep, a.sr, o, mn, mx, nlo, nhi, w);
-                    else                     hq_requant_group<16, FULL>(c, ep, mn, mx, nlo, nhi, w);
-                    *reinterpret_cast<v4i *>(a.out8 + o) = v4i{w[0], w[1], w[2], w[3]};
-                }
+                int w[4];
+                if constexpr (MODE == 2) hq_requant_group_sr<16, FULL>(c, ep, a.sr, o, mn, mx, nlo, nhi, w);
+                else                     hq_requant_group<16, FULL>(c, ep, mn, mx, nlo, nhi, w);
+                *reinterpret_cast<v4i *>(a.out8 + o) = v4i{w[0], w[1], w[2], w[3]};
             }
         };
         // Between two barriers one of a SIMD's two wavefronts multiplies first and requantizes then, the other (`late`)
