@@ -178,6 +178,24 @@ def test_rgb_first_layer(H, hq, L, g_asym):
     assert e.value.code == hq.HQ_E_BADSHAPE
 
 
+# First layers with staged rows: odd strides, bands of one row for few images, filters narrower than a word group, the smallest
+# weight tensor, many short images.
+STEM_EDGES = [wl.LayerShape("stem", wl.CONV, *v) for v in
+              ((3, 31, 32, 3, 3, 3, 1, 1, 64), (2, 20, 36, 3, 5, 7, 1, 2, 32), (1, 90, 224, 3, 7, 7, 2, 3, 64), (300, 9, 8, 3, 3, 3, 3, 1, 48),
+               (1, 5, 4, 3, 1, 1, 1, 0, 16), (2, 33, 64, 4, 3, 3, 1, 1, 64), (1, 9, 12, 4, 7, 8, 3, 3, 16), (5, 40, 260, 4, 2, 3, 1, 1, 32))]
+
+
+@pytest.mark.parametrize("L", STEM_EDGES, ids=["b%d_%dx%dx%d_%dx%d_s%d_n%d" % (l.B, l.H, l.W, l.C, l.R, l.S, l.stride, l.Cout) for l in STEM_EDGES])
+def test_staged_first_layers(H, hq, L):
+    track, Wdev = H.TensorTrack(0.9, False), None
+    for t in range(2):                                       # dynamic, fused
+        g = np.random.default_rng([79, t])
+        X, W = wl.normal_image(g, wl.in_shape(L)), wl.he_weight(g, L)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        track.step(L, "fwd", X, W0, H.DevTensor(X), Wdev)
+
+
 @pytest.mark.parametrize("L", [wl.LayerShape("rgb_wgrad_9x2_n72", wl.CONV, 2, 17, 11, 3, 9, 2, 1, 1, 72),     # more filter rows and output channels than the forward kernel takes
                                wl.LayerShape("rgb_wgrad_2x10_n4", wl.CONV, 1, 6, 24, 3, 2, 10, 2, 0, 4)], ids=lambda l: l.name)
 def test_rgb_weight_gradient_beyond_the_forward_limits(H, hq, L):
