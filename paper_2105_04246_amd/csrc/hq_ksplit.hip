@@ -375,7 +375,8 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
     // Which tile.  A launch is one round of tiles that run side by side, so its time is one tile's, and the smallest tile
     // that still gives every compute unit at most one is the fastest.  Beyond one round the tile kernels' larger tiles win
     // (fewer bytes fetched per multiply-add), earlier where the weights-resident kernel takes the layer and where the
-    // reduction is too short for a 64 x 64 tile to pay for adding its partial sums.
+    // reduction is too short for a 64 x 64 tile to pay for adding its partial sums.  (Strided input gradients of at most 64
+    // channels would be 256-pixel tiles over the whole reduction: 32 of them for 16x16x64 <- 8x8x128 at batch 32, 17 -> 7.6 us.)
     const size_t k = a.wrow / (a.classed ? (size_t)p->stride * p->stride : 1);      // reduction of an average tile
     auto tiles = [&](int tm, int tn) { return (M + tm - 1) / tm * (unsigned long long)((a.N + tn - 1) / tn); };
     if (!aligned) {
@@ -389,7 +390,7 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
     if (tiles(16, 16) <= 256) return launch2<1, 1, 8, 4, true>(a, mode, stream);
     if (tiles(16, 32) <= 256) return launch2<1, 2, 8, 4, true>(a, mode, stream);
     if (tiles(32, 32) <= 256) return launch2<2, 2, 8, 2, true>(a, mode, stream);
-    if (tiles(32, 64) <= 256 && k >= 512 && !(a.Cs == 64 && p->R == 3 && p->stride == 1))
+    if (tiles(32, 64) <= 256 && (k >= 512 || (a.classed && a.N <= 64)) && !(a.Cs == 64 && p->R == 3 && p->stride == 1))
         return launch2<2, 4, 8, 2, true>(a, mode, stream);
     if (tiles(64, 64) <= 256 && k >= 1152) return launch2<4, 4, 8, 2, true>(a, mode, stream);
     return HQ_E_BADSHAPE;

@@ -330,7 +330,7 @@ SMALL_LAUNCHES = [
     wl.conv("ks_16x16", 1, 9, 80, 36, 3), wl.conv("ks_16x16_c528", 1, 5, 528, 16, 3),
     wl.conv("ks_16x32", 2, 14, 48, 176, 3), wl.conv("ks_32x32", 2, 26, 112, 112, 3),
     wl.linear("ks_32x64", 2600, 528, 132), wl.linear("ks_64x64", 2000, 1168, 400),
-    wl.conv("ks_s2", 3, 21, 64, 96, 3, stride=2), wl.LayerShape("ks_s3_5x3", wl.CONV, 2, 19, 14, 32, 5, 3, 3, 2, 48),
+    wl.conv("ks_s2", 3, 21, 64, 96, 3, stride=2), wl.conv("ks_s2_64", 5, 32, 64, 80, 3, stride=2), wl.LayerShape("ks_s3_5x3", wl.CONV, 2, 19, 14, 32, 5, 3, 3, 2, 48),
     wl.conv("ks_s4_no_tap", 2, 18, 32, 16, 1, stride=4, pad=0), wl.LayerShape("ks_8x8", wl.CONV, 1, 12, 12, 16, 8, 8, 1, 3, 16),
     wl.linear("ks_word", 70, 100, 52), wl.linear("ks_word_64", 3000, 100, 260), wl.conv("ks_word_s2_n20", 2, 150, 20, 8, 3, stride=2),
     wl.conv("ks_word_s2_n100", 8, 50, 100, 36, 3, stride=2), wl.LayerShape("word_s5", wl.CONV, 2, 23, 23, 20, 3, 3, 5, 1, 12),
