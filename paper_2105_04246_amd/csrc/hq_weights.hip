@@ -27,10 +27,13 @@ constexpr int QW_THREADS = 1024;
 constexpr size_t QW_ONE = 160 * 1024;
 constexpr int QW_PARTS = 512;                        // workgroups of the maximum pass of larger tensors
 
-// Maximum of |w| over elements first, first + step, ... (groups of four where `vec`), as non-negative float bits.
+__device__ inline unsigned abs_bits(float w) { return __float_as_uint(w) & 0x7fffffffu; }
+
+// Maximum of |w| over elements first, first + step, ... (groups of four where `vec`), as non-negative float bits: a NaN is
+// above every number there and reaches scale_of.
 __device__ inline unsigned absmax_bits(const float *__restrict__ w, size_t n, size_t first, size_t step, bool vec)
 {
-    float m = 0.0f;
+    unsigned m = 0;
     if (vec) {
         const size_t quads = n / 4;
         const v4f *w4 = reinterpret_cast<const v4f *>(w);
@@ -41,17 +44,17 @@ __device__ inline unsigned absmax_bits(const float *__restrict__ w, size_t n, si
             for (int k = 0; k < 4; k++) v[k] = w4[i + k * step];
 #pragma unroll
             for (int k = 0; k < 4; k++)
-                m = fmaxf(m, fmaxf(fmaxf(fabsf(v[k][0]), fabsf(v[k][1])), fmaxf(fabsf(v[k][2]), fabsf(v[k][3]))));
+                m = max(m, max(max(abs_bits(v[k][0]), abs_bits(v[k][1])), max(abs_bits(v[k][2]), abs_bits(v[k][3]))));
         }
         for (; i < quads; i += step) {
             const v4f v = w4[i];
-            m = fmaxf(m, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
+            m = max(m, max(max(abs_bits(v[0]), abs_bits(v[1])), max(abs_bits(v[2]), abs_bits(v[3]))));
         }
-        if (first < n - 4 * quads) m = fmaxf(m, fabsf(w[4 * quads + first]));
+        if (first < n - 4 * quads) m = max(m, abs_bits(w[4 * quads + first]));
     } else {
-        for (size_t i = first; i < n; i += step) m = fmaxf(m, fabsf(w[i]));
+        for (size_t i = first; i < n; i += step) m = max(m, abs_bits(w[i]));
     }
-    return __float_as_uint(m);
+    return m;
 }
 
 // Maximum over the workgroup, in every thread.

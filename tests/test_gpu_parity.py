@@ -470,6 +470,22 @@ def test_weight_quantizer_edges(H, hq, n, offset):
     assert np.array_equal(Wq[:n].cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("n", [4099, 160 * 1024 + 1])
+@pytest.mark.parametrize("value", [np.nan, -np.inf])
+def test_weight_quantizer_not_finite(H, hq, n, value):
+    """One launch and two: a NaN leaves the scale at 1, an infinity makes it infinite; either's own code is the lowest."""
+    w = np.random.default_rng(n).uniform(-50, 50, n).astype(np.float32)
+    w[n // 2] = value
+    want = np.rint(w) if np.isnan(value) else np.zeros(n, np.float32)
+    want[n // 2] = -127
+    Wq, wq = torch.empty(n, dtype=torch.int8, device="cuda"), hq.new_qparams(123.0, 7)
+    hq.hq_weight_quantize(H.dev(w), n, Wq, wq)
+    torch.cuda.synchronize()
+    q = H.read_qparams(wq)
+    assert np.float32(q["scale"]) == (1 if np.isnan(value) else np.inf) and int(q["zero_point"]) == 0
+    assert np.array_equal(Wq.cpu().numpy(), want)
+
+
 def test_asymmetric_gradients_and_symmetric_inputs(H, hq):
     """Zero points on the gradient side (the paper quantizes gradients asymmetrically in its
     ablations, Sec. 5.1) and none on the input side."""
