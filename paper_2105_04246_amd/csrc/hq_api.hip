@@ -5,7 +5,6 @@
 #include "hq_internal.h"
 
 #include <mutex>
-#include <cstdlib>
 
 // Scratch memory of hq_gemm_wgrad_static: one array per GPU, held from the moment the library is
 // loaded on that GPU until the process ends.  In host code the array's name is only a handle for

@@ -223,8 +223,8 @@ __device__ inline HqEpilogue hq_make_epilogue(float acc_scale, const hq_range *r
     // each) of that quotient, of float(c) and of the product: 1e-6 of it and one unit cover them
     const float hi = __fmul_rn(__fdiv_rn(e.fhi + 0.5f, e.mult), 0.999999f) - 1.0f;
     const float lo = __fmul_rn(__fdiv_rn(e.flo - 0.5f, e.mult), 0.999999f) + 1.0f;
-    e.c_hi = hi < 2147483000.0f ? (int)hi : INT_MAX;
-    e.c_lo = lo > -2147483000.0f ? (int)lo : INT_MIN;
+    e.c_hi = hi < 2147483648.0f ? (int)hi : INT_MAX;
+    e.c_lo = lo > -2147483648.0f ? (int)lo : INT_MIN;
     return e;
 }
 
@@ -327,14 +327,36 @@ __device__ inline void hq_requant_group(const int *c, const HqEpilogue &ep, int 
 // ---------------------------------------------------------------------------------------
 struct HqSr { unsigned k0, k1; };          // low and high half of the seed
 
-__device__ inline unsigned hq_sr_bits(unsigned idx_lo, unsigned hi_term, unsigned k0)
+__device__ inline unsigned hq_sr_first(unsigned idx_lo, unsigned k0) { return (idx_lo ^ (idx_lo >> 16)) * 0x85ebca6bu + k0; }
+
+__device__ inline unsigned hq_sr_rest(unsigned h, unsigned hi_term)      // hi_term = idx_hi * 0x85ebca77 + k1
 {
-    unsigned h = idx_lo;                   // hi_term = idx_hi * 0x85ebca77 + k1
-    h ^= h >> 16; h *= 0x85ebca6bu; h += k0;
     h ^= hi_term;
     h ^= h >> 13; h *= 0xc2b2ae35u; h ^= h >> 16;
     h *= 0x9e3779b1u; h ^= h >> 15;
     return h;
+}
+
+__device__ inline unsigned hq_sr_bits(unsigned idx_lo, unsigned hi_term, unsigned k0)
+{
+    return hq_sr_rest(hq_sr_first(idx_lo, k0), hi_term);
+}
+
+// hq_sr_first of the indices idx_lo .. idx_lo + N - 1, idx_lo a multiple of N = 4, 8 or 16.  The generator's integer
+// multiplications run at a quarter of the rate and are what stochastic rounding costs; here one serves N elements.  All
+// N share the bits above the lowest log2 N, so element e multiplies b ^ e, b that of element 0, and flipping bit k of b
+// adds or takes 2^k: the products differ by sums of +-(constant << k).
+template <int N> __device__ inline void hq_sr_first_n(unsigned idx_lo, unsigned k0, unsigned *h)
+{
+    static_assert(N == 4 || N == 8 || N == 16, "aligned groups");
+    const unsigned b = idx_lo ^ (idx_lo >> 16);
+    h[0] = b * 0x85ebca6bu + k0;
+#pragma unroll
+    for (int k = 1; k < N; k *= 2) {
+        const unsigned up = 0x85ebca6bu * (unsigned)k, d = (b & (unsigned)k) ? 0u - up : up;
+#pragma unroll
+        for (int e = 0; e < k; e++) h[k + e] = h[e] + d;
+    }
 }
 
 // One value (the depthwise stencil's epilogue): as hq_requant, with stochastic rounding.
@@ -351,8 +373,9 @@ __device__ inline int hq_requant_sr(int c, const HqRequant &q, const HqSr &sr, s
 }
 
 // As hq_requant_group, with stochastic rounding; idx0 is the tensor index of c[0], the N values
-// are consecutive elements.
-template <int N, bool FULL_GRID>
+// are consecutive elements.  ALIGN (4, or N) divides idx0: channel counts are multiples of 4, and of 16 where a
+// kernel takes 16 only.
+template <int N, bool FULL_GRID, int ALIGN = 4>
 __device__ inline void hq_requant_group_sr(const int *c, const HqEpilogue &ep, const HqSr &sr, size_t idx0, int &mn,
                                            int &mx, unsigned &w_lo, unsigned &w_hi, int *words)
 {
@@ -361,13 +384,17 @@ __device__ inline void hq_requant_group_sr(const int *c, const HqEpilogue &ep, c
     for (int e = 1; e + 1 < N; e += 2) { gmn = hq_min3(gmn, c[e], c[e + 1]); gmx = hq_max3(gmx, c[e], c[e + 1]); }
     gmn = min(gmn, c[N - 1]); gmx = max(gmx, c[N - 1]);
     mn = min(mn, gmn); mx = max(mx, gmx);
-    const unsigned lo0 = (unsigned)idx0, hi0 = (unsigned)(idx0 >> 32);
-    const unsigned term0 = hi0 * 0x85ebca77u + sr.k1, term1 = (hi0 + 1u) * 0x85ebca77u + sr.k1;
     float f[N];
+    unsigned h[N], term[N / ALIGN];
+#pragma unroll
+    for (int g = 0; g < N / ALIGN; g++) {                                // (no carry into the high word inside such a group)
+        const size_t idx = idx0 + (size_t)(g * ALIGN);
+        term[g] = (unsigned)(idx >> 32) * 0x85ebca77u + sr.k1;
+        hq_sr_first_n<ALIGN>((unsigned)idx, sr.k0, h + g * ALIGN);
+    }
 #pragma unroll
     for (int e = 0; e < N; e++) {
-        const unsigned lo = lo0 + (unsigned)e;
-        const unsigned bits = hq_sr_bits(lo, lo < lo0 ? term1 : term0, sr.k0);       // carry into the high word
+        const unsigned bits = hq_sr_rest(h[e], term[e / ALIGN]);
         const float x = __fmul_rn((float)c[e], ep.mult), fl = floorf(x);
         const float u = __fmul_rn((float)(bits >> 8), 1.0f / 16777216.0f);
         f[e] = __fsub_rn(x, fl) > u ? __fadd_rn(fl, 1.0f) : fl;
