@@ -365,7 +365,7 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void hq_band_kernel(cons
                             for (int r = 0; r < 16; r++) c[r] = acc[i][j][r];
                             if (FUSED) {
                                 int w[4];
-                                if (SR) hq_requant_group_sr<16, FULL>(c, ep, a.sr, m * a.N + nb, mn, mx, nlo, nhi, w);
+                                if (SR) hq_requant_group_sr<16, FULL, 16>(c, ep, a.sr, m * a.N + nb, mn, mx, nlo, nhi, w);
                                 else hq_requant_group<16, FULL>(c, ep, mn, mx, nlo, nhi, w);
                                 const v4i packed = {w[0], w[1], w[2], w[3]};
                                 *reinterpret_cast<v4i *>(a.out8 + m * a.N + nb) = packed;

@@ -290,7 +290,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_bandw_kernel(const BandwArgs
                     const size_t o = m * a.N + nb;
                     if (FUSED) {
                         int w[4];
-                        if (SR) hq_requant_group_sr<16, FULL>(c, ep, a.sr, o, mn, mx, nlo, nhi, w);
+                        if (SR) hq_requant_group_sr<16, FULL, 16>(c, ep, a.sr, o, mn, mx, nlo, nhi, w);
                         else hq_requant_group<16, FULL>(c, ep, mn, mx, nlo, nhi, w);
                         const v4i v = {w[0], w[1], w[2], w[3]};
                         *reinterpret_cast<v4i *>(a.out8 + o) = v;

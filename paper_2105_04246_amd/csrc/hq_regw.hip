@@ -227,7 +227,7 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
                 for (int e = 0; e < 16; e++) c[e] = acc[nb][e];
                 const size_t o = (size_t)P * a.N + n0 + 32 * nb + 16 * half;
                 int w[4];
-                if constexpr (MODE == 2) hq_requant_group_sr<16, FULL>(c, ep, a.sr, o, mn, mx, nlo, nhi, w);
+                if constexpr (MODE == 2) hq_requant_group_sr<16, FULL, 16>(c, ep, a.sr, o, mn, mx, nlo, nhi, w);
                 else                     hq_requant_group<16, FULL>(c, ep, mn, mx, nlo, nhi, w);
                 *reinterpret_cast<v4i *>(a.out8 + o) = v4i{w[0], w[1], w[2], w[3]};
             }

@@ -26,12 +26,11 @@ __global__ __launch_bounds__(HQ_THREADS) void tensor_pass_kernel(const float *__
     if (QUANT) rq = hq_make_requant(1.0f, *qp, r->qlo, r->qhi);       // a real value is an accumulator of unit 1
     int mn = INT_MAX, mx = INT_MIN;
     unsigned nlo = 0, nhi = 0;
-    auto one = [&](float v, size_t idx) __attribute__((always_inline)) -> int {
+    auto one = [&](float v, unsigned bits) __attribute__((always_inline)) -> int {
         if (MINMAX) { const int k = hq_float_key(v); mn = min(mn, k); mx = max(mx, k); }
         if (!QUANT) return 0;
         float q;
         if (SR) {
-            const unsigned bits = hq_sr_bits((unsigned)idx, (unsigned)(idx >> 32) * 0x85ebca77u + sr.k1, sr.k0);
             const float y = __fmul_rn(v, rq.mult), fl = floorf(y);
             const float u = __fmul_rn((float)(bits >> 8), 1.0f / 16777216.0f);
             q = __fsub_rn(y, fl) > u ? __fadd_rn(fl, 1.0f) : fl;
@@ -50,17 +49,25 @@ __global__ __launch_bounds__(HQ_THREADS) void tensor_pass_kernel(const float *__
 #pragma unroll
         for (int k = 0; k < 4; k++) v[k] = src[k];
         v4i packed;
+        unsigned bits[TQ_GROUP] = {};
+        if (SR) {
+            const size_t i0 = g * TQ_GROUP;
+            const unsigned term = (unsigned)(i0 >> 32) * 0x85ebca77u + sr.k1;
+            hq_sr_first_n<TQ_GROUP>((unsigned)i0, sr.k0, bits);
+#pragma unroll
+            for (int e = 0; e < TQ_GROUP; e++) bits[e] = hq_sr_rest(bits[e], term);
+        }
 #pragma unroll
         for (int k = 0; k < 4; k++) {
-            const size_t i0 = g * TQ_GROUP + 4 * k;
-            const int c0 = one(v[k][0], i0), c1 = one(v[k][1], i0 + 1), c2 = one(v[k][2], i0 + 2), c3 = one(v[k][3], i0 + 3);
+            const int c0 = one(v[k][0], bits[4 * k]), c1 = one(v[k][1], bits[4 * k + 1]), c2 = one(v[k][2], bits[4 * k + 2]),
+                      c3 = one(v[k][3], bits[4 * k + 3]);
             packed[k] = (int)hq_pack4(c0, c1, c2, c3);
         }
         if (QUANT) reinterpret_cast<v4i *>(out)[g] = packed;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         for (size_t i = groups * TQ_GROUP; i < n; i++) {               // fewer than 16 elements
-            const int c = one(x[i], i);
+            const int c = one(x[i], SR ? hq_sr_bits((unsigned)i, (unsigned)(i >> 32) * 0x85ebca77u + sr.k1, sr.k0) : 0u);
             if (QUANT) out[i] = (int8_t)c;
         }
         if (MINMAX) {
