@@ -19,6 +19,7 @@
 #include "hq_device.h"
 #include "hq_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -380,10 +381,34 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
     const size_t k = a.wrow / (a.classed ? (size_t)p->stride * p->stride : 1);      // reduction of an average tile
     auto tiles = [&](int tm, int tn) { return (M + tm - 1) / tm * (unsigned long long)((a.N + tn - 1) / tn); };
     if (!aligned) {
-        // two or more workgroups per compute unit here; always in the class form, whose exact-division test
-        // per word the tile kernel repeats for every tap
-        if (tiles(32, 32) <= 512) return launch2<2, 2, 8, 1, false>(a, mode, stream);
-        if (tiles(64, 64) > 512 && !(a.classed && p->stride > 1)) return HQ_E_BADSHAPE;
+        // Two or more workgroups per compute unit here.  A tile pays for the masks of its taps, for the partial sums through
+        // LDS and for adding them however short its reduction is, the tile kernel mainly for its 64-byte stages (4-byte
+        // loads, in strided input gradients a division test each), and with few channels for its 256-pixel tiles.  The two
+        // sides below are in proportion to what is left of a launch without its start-up, fitted to 3500 launches of 1 .. 49
+        // taps, 4 .. 600 reduced and 16 .. 600 output channels in the three rounding modes; one in 40 is on the wrong side by
+        // more than 5 %.  Forward, this / tile kernel: one tap, 20384 pixels -> 64, 56 reduced 8.7 / 7.7 us, 100: 9.7 / 10.0,
+        // 200: 11.0 / 14.7; nine taps, 4704 pixels -> 256, 108 reduced 12.9 / 8.5, 900: 26.2 / 29.3; 49 taps, 5096 -> 128, 588
+        // reduced 27.9 / 20.8.  Input gradients of stride 2: 1x1, 401408 pixels of 32, 36 reduced 28.2 / 26.9, 100: 30.0 / 42.5;
+        // 3x3, 119168 pixels of 128, 20 channels 56 / 31, 36: 56 / 57, 100: 69 / 114.
+        const bool strided = a.classed && p->stride > 1;
+        const double t32 = (double)tiles(32, 32), t = (double)tiles(64, a.N <= 32 ? 32 : 64);
+        const double stages = (double)((a.wrow + 63) / 64);
+        if (t32 <= (strided ? 512 : 256)) return launch2<2, 2, 8, 1, false>(a, mode, stream);
+        double tile, split;
+        if (strided) {
+            const double g = (double)(a.N <= 64 ? tiles(256, 64) : tiles(128, 128));
+            const double per_class = (double)taps / (p->stride * p->stride);
+            tile = std::max(1.0, g / 400) * ((mode == 1 ? 0 : 0.95) + (a.N <= 64 ? 9.8 : 6.2) * stages);
+            split = std::max(1.0, t / (a.N <= 32 ? 100 : 80)) *
+                    ((a.N <= 32 ? 0.55 : 1.0) + 0.43 * std::min(1.0, per_class) + 0.11 * per_class);
+        } else {
+            if (tiles(64, 64) > 512) return HQ_E_BADSHAPE;
+            tile = a.N <= 64 ? (mode == 2 ? 1.0 : -0.5) + 2.9 * stages : (mode == 2 ? 1.2 : 0.4) + 1.6 * stages;
+            split = t32 <= 512 ? std::max(1.0, t32 / 206) * 0.19 * taps
+                               : std::max(1.0, t / 207) * ((a.N <= 32 ? 1.3 : 1.9) + 0.42 * taps);
+        }
+        if (split > tile) return HQ_E_BADSHAPE;
+        if (!strided && t32 <= 512) return launch2<2, 2, 8, 1, false>(a, mode, stream);
         if (a.N <= 32) return launch2<4, 2, 4, 1, false>(a, mode, stream);
         return launch2<4, 4, 4, 1, false>(a, mode, stream);
     }

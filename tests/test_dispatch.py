@@ -1,0 +1,44 @@
+"""The lines of the dispatch rules: which kernel takes a call on either side of each (no GPU: see launches.py).  The
+figures behind the lines stand beside the rules."""
+import launches
+
+LINEAR, CONV, DEPTHWISE = 0, 1, 2
+
+
+def conv(B, hw, C, k, stride, Cout, pad=None):
+    return (CONV, B, hw, hw, C, k, k, stride, k // 2 if pad is None else pad, Cout)
+
+
+def check(cases):
+    """cases: (operation, problem, start of the first kernel's name) each."""
+    got = launches.calls([(op, p) for op, p, _ in cases])
+    for (op, p, want), g in zip(cases, got):
+        assert g[0].kernel.startswith(want), (op, p, g[0].kernel, "expected " + want)
+
+
+def test_short_reductions_off_16_stay_with_the_tile_kernel():
+    """The split-reduction kernel's 4-byte form pays off only where its wavefronts have a reduction to share."""
+    ks, tile = "hq_ksplit_kernel", "hq_gemm_kernel"
+    check([("fwd", conv(6, 28, 24, 1, 1, 96), ks),              # one round of 32 x 32 tiles: whatever the reduction
+           ("fwd", conv(26, 28, 56, 1, 1, 64), tile),           # 20384 pixels, two rounds, 56 reduced
+           ("fwd", conv(26, 28, 100, 1, 1, 64), ks),
+           ("fwd", conv(13, 28, 56, 1, 1, 128), tile),
+           ("fwd", conv(13, 28, 200, 1, 1, 128), ks),
+           ("fwd", conv(20, 10, 12, 3, 1, 256), tile),          # nine taps of 12, under two rounds of 32 x 32 tiles
+           ("fwd", conv(20, 10, 20, 3, 1, 256), ks),
+           ("fwd", conv(6, 28, 12, 3, 1, 256), tile),           # more than a round of 64 x 64
+           ("fwd", conv(6, 28, 100, 3, 1, 256), ks),
+           ("fwd", conv(26, 14, 12, 7, 1, 128), tile),          # 49 taps of 12
+           ("fwd", conv(26, 14, 36, 7, 1, 128), ks),
+           ("dgrad", (LINEAR, 8000, 1, 1, 128, 1, 1, 1, 0, 12), tile),
+           ("dgrad", (LINEAR, 64, 1, 1, 128, 1, 1, 1, 0, 12), ks)])
+
+
+def test_strided_input_gradients_off_16_weigh_the_reduction_against_the_tiles():
+    ks, tile = "hq_ksplit_kernel", "hq_gemm_kernel"
+    check([("dgrad", conv(64, 112, 20, 1, 2, 20), tile), ("dgrad", conv(64, 112, 36, 1, 2, 36), tile),
+           ("dgrad", conv(64, 112, 100, 1, 2, 100), tile), ("dgrad", conv(64, 112, 20, 3, 2, 20), ks),
+           ("dgrad", conv(64, 112, 36, 3, 2, 36), ks), ("dgrad", conv(64, 112, 100, 3, 2, 100), ks),
+           ("dgrad", conv(34, 25, 608, 1, 2, 24), tile), ("dgrad", conv(128, 56, 64, 1, 2, 200), ks),
+           ("dgrad", conv(64, 28, 24, 1, 2, 24), ks), ("dgrad", conv(9, 50, 100, 3, 3, 12), tile),
+           ("dgrad_sr", conv(64, 112, 36, 1, 2, 36), tile), ("dgrad", conv(8, 28, 100, 1, 2, 100), ks)])

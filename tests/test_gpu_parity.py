@@ -335,7 +335,9 @@ SMALL_LAUNCHES = [
     wl.linear("ks_word", 70, 100, 52), wl.linear("ks_word_64", 3000, 100, 260), wl.conv("ks_word_s2_n20", 2, 150, 20, 8, 3, stride=2),
     wl.conv("ks_word_s2_n100", 8, 50, 100, 36, 3, stride=2), wl.LayerShape("word_s5", wl.CONV, 2, 23, 23, 20, 3, 3, 5, 1, 12),
     wl.conv("past_band", 12, 24, 64, 64, 3), wl.conv("past_bandw", 9, 28, 128, 192, 3), wl.linear("past_gather", 4200, 272, 520),
-    wl.LayerShape("past_mask", wl.CONV, 1, 14, 14, 16, 9, 9, 1, 4, 32)]
+    wl.LayerShape("past_mask", wl.CONV, 1, 14, 14, 16, 9, 9, 1, 4, 32),
+    wl.conv("ks_word_s2_many", 24, 56, 36, 36, 3, stride=2), wl.conv("past_word_s2_1x1", 40, 56, 36, 36, 1, stride=2, pad=0),
+    wl.conv("past_word_1x1", 26, 28, 56, 64, 1, pad=0)]
 
 
 @pytest.mark.parametrize("L", SMALL_LAUNCHES, ids=[l.name for l in SMALL_LAUNCHES])
