@@ -222,10 +222,22 @@ static int gemm_common(const hq_problem *p, int dgrad, const int8_t *A, const hq
         if (dgrad || sr_seed) return HQ_E_BADSHAPE;
         return hq_try_launch_direct(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream));
     }
-    rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
+    // 3x3 layers with 64 reduced channels have kernels of their own, which beat split reductions once those need tiles of
+    // 32 x 64 (8192 pixels -> 64: 8.5 us against 7.8 with the weights in registers, 7.9 with the weights in LDS), except with
+    // stochastic rounding, where little work per workgroup counts more (8.5 against 9.3 and 8.8).
+    const bool own64 = !sr_seed && p->kind == HQ_CONV2D && p->R == 3 && p->S == 3 && (dgrad ? p->Cout : p->C) == 64;
+    rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed, own64);
     if (rc != HQ_E_BADSHAPE) return rc;
     rc = hq_try_launch_regw(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
     if (rc != HQ_E_BADSHAPE) return rc;
+    if (own64) {
+        if ((dgrad ? p->C : p->Cout) <= 64) {
+            rc = hq_try_launch_band(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream));
+            if (rc != HQ_E_BADSHAPE) return rc;
+        }
+        rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream));
+        if (rc != HQ_E_BADSHAPE) return rc;
+    }
     if (sr_seed) {
         // stochastic rounding: the two 3x3 / 1x1 fast paths, else the two general kernels
         if (p->kind == HQ_DEPTHWISE)

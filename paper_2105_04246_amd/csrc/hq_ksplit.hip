@@ -322,7 +322,8 @@ int launch2(KsArgs &a, int mode, hipStream_t s)
 
 int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
                          const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
-                         int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed)
+                         int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed,
+                         bool small_tiles)
 {
     if (p->kind == HQ_DEPTHWISE || (!dgrad && p->C < 8)) return HQ_E_BADSHAPE;      // (first layers have their own kernels)
     const int OH = (p->H + 2 * p->pad - p->R) / p->stride + 1, OW = (p->W + 2 * p->pad - p->S) / p->stride + 1;
@@ -375,11 +376,15 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
     a.m_fast = (size_t)a.N * a.wrow > (size_t)a.B * a.Hs * a.Ws * a.Cs;
     // Which tile.  A launch is one round of tiles that run side by side, so its time is one tile's, and the smallest tile
     // that still gives every compute unit at most one is the fastest.  Beyond one round the tile kernels' larger tiles win
-    // (fewer bytes fetched per multiply-add), earlier where the weights-resident kernel takes the layer and where the
-    // reduction is too short for a 64 x 64 tile to pay for adding its partial sums.  (Strided input gradients of at most 64
-    // channels would be 256-pixel tiles over the whole reduction: 32 of them for 16x16x64 <- 8x8x128 at batch 32, 17 -> 7.6 us.)
+    // (fewer bytes fetched per multiply-add), earlier where the reduction is too short for a 64 x 64 tile to pay for adding
+    // its partial sums and for the masks of its taps.  (Strided input gradients of at most 64 channels would be 256-pixel
+    // tiles over the whole reduction: 32 of them for 16x16x64 <- 8x8x128 at batch 32, 17 -> 7.6 us.)
     const size_t k = a.wrow / (a.classed ? (size_t)p->stride * p->stride : 1);      // reduction of an average tile
-    auto tiles = [&](int tm, int tn) { return (M + tm - 1) / tm * (unsigned long long)((a.N + tn - 1) / tn); };
+    auto tiles = [&](int tm, int tn) {
+        unsigned long long m = 0;
+        for (int c = 0; c < a.ncls; c++) m += ((unsigned long long)a.B * a.cls[c].Hc * a.cls[c].Wc + tm - 1) / tm;
+        return m * (unsigned long long)((a.N + tn - 1) / tn);
+    };
     if (!aligned) {
         // Two or more workgroups per compute unit here.  A tile pays for the masks of its taps, for the partial sums through
         // LDS and for adding them however short its reduction is, the tile kernel mainly for its 64-byte stages (4-byte
@@ -415,8 +420,15 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
     if (tiles(16, 16) <= 256) return launch2<1, 1, 8, 4, true>(a, mode, stream);
     if (tiles(16, 32) <= 256) return launch2<1, 2, 8, 4, true>(a, mode, stream);
     if (tiles(32, 32) <= 256) return launch2<2, 2, 8, 2, true>(a, mode, stream);
-    if (tiles(32, 64) <= 256 && (k >= 512 || (a.classed && a.N <= 64)) && !(a.Cs == 64 && p->R == 3 && p->stride == 1))
+    if (small_tiles) return HQ_E_BADSHAPE;
+    // 2500 pixels -> 128, one tap, this / tile kernel: 512 reduced 6.5 / 6.2 us, 640 6.5 / 6.7, 1024 6.9 / 8.2
+    if (tiles(32, 64) <= 256 && (k >= (a.N <= 64 ? 512 : 576) || (a.classed && a.N <= 64)))
         return launch2<2, 4, 8, 2, true>(a, mode, stream);
-    if (tiles(64, 64) <= 256 && k >= 1152) return launch2<4, 4, 8, 2, true>(a, mode, stream);
+    // The tile kernels are the gather kernel with its own 64 x 64 tiles where N > 64 (5096 pixels -> 128: nine taps, 1152 reduced
+    // 12.4 / 10.3 us, 2304 13.6 / 14.7; 25 taps, 1200: 19.7 / 14.7; 49 taps, 1568: 30.5 / 21.0, 6272: 0.93 of it), with 256-pixel tiles
+    // where N <= 64 (twice the time of these already at 1152), and the streamed-weights kernel (1152: 1.25 times).
+    const bool streamed = taps == 9 && p->S == 3 && p->stride == 1 && p->pad == 1 && a.Cs % 64 == 0 && a.N % 16 == 0 && a.N >= 128;
+    if (tiles(64, 64) <= 256 && k >= (a.N <= 64 || a.classed || streamed ? (size_t)1152 : (size_t)(1350 + 70 * taps)))
+        return launch2<4, 4, 8, 2, true>(a, mode, stream);
     return HQ_E_BADSHAPE;
 }

@@ -42,3 +42,28 @@ def test_strided_input_gradients_off_16_weigh_the_reduction_against_the_tiles():
            ("dgrad", conv(34, 25, 608, 1, 2, 24), tile), ("dgrad", conv(128, 56, 64, 1, 2, 200), ks),
            ("dgrad", conv(64, 28, 24, 1, 2, 24), ks), ("dgrad", conv(9, 50, 100, 3, 3, 12), tile),
            ("dgrad_sr", conv(64, 112, 36, 1, 2, 36), tile), ("dgrad", conv(8, 28, 100, 1, 2, 100), ks)])
+
+
+def test_split_reductions_of_whole_chunks_end_where_the_tile_kernels_are_faster():
+    small, large = "hq_ksplit_kernel<2, 4, 8, 2, true", "hq_ksplit_kernel<4, 4, 8, 2, true"
+    tile = "hq_gemm_kernel"
+    check([("fwd", (LINEAR, 2500, 1, 1, 512, 1, 1, 1, 0, 128), tile), ("fwd", (LINEAR, 2500, 1, 1, 640, 1, 1, 1, 0, 128), small),
+           ("fwd", (LINEAR, 5000, 1, 1, 512, 1, 1, 1, 0, 64), small),
+           ("fwd", (LINEAR, 5000, 1, 1, 1280, 1, 1, 1, 0, 128), tile), ("fwd", (LINEAR, 5000, 1, 1, 1536, 1, 1, 1, 0, 128), large),
+           ("fwd", conv(26, 28, 128, 3, 2, 128), tile), ("fwd", conv(26, 28, 256, 3, 2, 128), large),
+           ("fwd", conv(26, 14, 128, 3, 1, 128), large),                   # against the streamed-weights kernel
+           ("fwd", conv(60, 28, 128, 3, 2, 64), large),
+           ("fwd", conv(16, 28, 64, 5, 2, 200), tile), ("fwd", conv(16, 28, 96, 5, 2, 200), tile),
+           ("fwd", conv(16, 28, 192, 5, 2, 200), large), ("fwd", conv(11, 14, 32, 7, 1, 200), tile)])
+    # a strided input gradient's tiles are counted class by class: 242 pixels in four classes of 61, 61, 60 and 60
+    # make 16 tiles of 16 pixels a column, not 16.0
+    assert launches.calls([("dgrad", conv(2, 11, 504, 2, 2, 32, 0))])[0][0].blocks <= 256
+
+
+def test_64_channel_layers_go_to_their_own_kernels_where_those_take_them():
+    ks, regw, band = "hq_ksplit_kernel", "hq_regw_kernel", "hq_band_kernel"
+    check([("fwd", conv(10, 28, 64, 3, 1, 64), regw), ("fwd", conv(2, 28, 64, 3, 1, 64), ks),
+           ("fwd", conv(10, 30, 64, 3, 1, 64, 0), band),                                  # no padding
+           ("fwd", (CONV, 2, 20, 130, 64, 3, 3, 1, 1, 64), ks),                           # too wide for either
+           ("fwd", conv(26, 28, 64, 3, 2, 64), band), ("fwd", conv(20, 28, 64, 3, 2, 80), ks),
+           ("dgrad_sr", conv(10, 28, 64, 3, 1, 64), ks), ("dgrad_sr", conv(16, 28, 64, 3, 1, 64), regw)])

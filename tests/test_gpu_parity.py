@@ -337,7 +337,8 @@ SMALL_LAUNCHES = [
     wl.conv("past_band", 12, 24, 64, 64, 3), wl.conv("past_bandw", 9, 28, 128, 192, 3), wl.linear("past_gather", 4200, 272, 520),
     wl.LayerShape("past_mask", wl.CONV, 1, 14, 14, 16, 9, 9, 1, 4, 32),
     wl.conv("ks_word_s2_many", 24, 56, 36, 36, 3, stride=2), wl.conv("past_word_s2_1x1", 40, 56, 36, 36, 1, stride=2, pad=0),
-    wl.conv("past_word_1x1", 26, 28, 56, 64, 1, pad=0)]
+    wl.conv("past_word_1x1", 26, 28, 56, 64, 1, pad=0),
+    wl.linear("ks_32x64_long", 2600, 592, 132), wl.linear("ks_64x64_long", 2000, 1424, 400), wl.conv("ks_64x64_s2", 13, 21, 256, 272, 3, stride=2)]
 
 
 @pytest.mark.parametrize("L", SMALL_LAUNCHES, ids=[l.name for l in SMALL_LAUNCHES])
