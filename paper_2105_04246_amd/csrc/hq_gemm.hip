@@ -33,6 +33,7 @@
 // launch (Sec. 4, step 1).  With `out32` set, the kernel is pass 1 of the dynamic baseline:
 // it stores the corrected 32-bit outputs (the accumulator-save term of eq. (5)) and gathers min / max.
 #include "hq_device.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -632,7 +633,21 @@ int hq_launch_gemm(const hq_problem *p, int dgrad, const int8_t *A, const hq_qpa
         // fully connected layers): 64 x 64 tiles, four times as many workgroups
         if (aligned && !strided && a.nchunks >= 16 && tiles < 256)
             return launch2m<64, 64, 2, 2, 128, false, true>(a, mode, stream);
-        if (a.nchunks >= 16 && !(aligned && tiles >= 3 * 256)) return launch2<128, 128, 2, 2, 128>(a, strided, aligned, mode, stream);
+        // Stochastic rounding makes a tile's end several times as long, so resident workgroups to hide it count for more:
+        // 128-byte stages only while two workgroups per compute unit hold all tiles that have a tap, and where few stages are
+        // cut short (by the end of the reduction; in a filter's taps and a strided layer's classes by many channels).  Input
+        // gradients, 128- / 64-byte stages: 3255 x 2048 -> 3624 54.9 / 48.1 us, 50176 x 288 -> 128 18.0 / 15.7, 5x5 50176 x 64 -> 128
+        // 35.8 / 32.0, 3x3 stride 2 39984 x 128 -> 256 22.7 / 19.6; 4096 x 4096 -> 4096 49.9 / 58.9, 5x5 29792 x 176 -> 132 60.6 / 64.7,
+        // 3x3 stride 2 19992 x 512 -> 128 25.1 / 26.4.
+        auto long_stages = [&] {
+            if (!aligned) return a.taps > 1;
+            const long classes = strided ? (long)p->stride * p->stride : 1;
+            if (tiles * std::min((long)a.taps, classes) > 2 * 256 * classes) return false;
+            if (a.taps == 1 && !strided) return a.nchunks >= 64 || a.nchunks % 8 == 0;
+            return a.cpt >= 10 && (!strided || a.nchunks >= (a.cpt >= 28 ? 48 : 200));
+        };
+        const bool wide = mode != 2 || long_stages();
+        if (a.nchunks >= 16 && wide && !(aligned && tiles >= 3 * 256)) return launch2<128, 128, 2, 2, 128>(a, strided, aligned, mode, stream);
         return launch2<128, 128, 2, 2, 64>(a, strided, aligned, mode, stream);
     }
     if (a.N > 32) return launch2<256, 64, 4, 1, 64>(a, strided, aligned, mode, stream);

@@ -67,3 +67,13 @@ def test_64_channel_layers_go_to_their_own_kernels_where_those_take_them():
            ("fwd", (CONV, 2, 20, 130, 64, 3, 3, 1, 1, 64), ks),                           # too wide for either
            ("fwd", conv(26, 28, 64, 3, 2, 64), band), ("fwd", conv(20, 28, 64, 3, 2, 80), ks),
            ("dgrad_sr", conv(10, 28, 64, 3, 1, 64), ks), ("dgrad_sr", conv(16, 28, 64, 3, 1, 64), regw)])
+
+
+def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
+    long_, short = "hq_gemm_kernel<128, 128, 2, 2, 128", "hq_gemm_kernel<128, 128, 2, 2, 64"
+    check([("dgrad_sr", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2048), short), ("dgrad", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2048), long_),
+           ("dgrad_sr", (LINEAR, 4096, 1, 1, 2048, 1, 1, 1, 0, 2048), long_), ("dgrad_sr", (LINEAR, 4096, 1, 1, 4096, 1, 1, 1, 0, 1024), short),
+           ("dgrad_sr", conv(51, 28, 128, 1, 1, 288), short), ("dgrad_sr", conv(51, 28, 128, 1, 1, 256), long_),
+           ("dgrad_sr", conv(60, 28, 96, 5, 2, 64), short), ("dgrad_sr", conv(41, 28, 256, 3, 2, 448), long_),
+           ("dgrad_sr", conv(41, 28, 256, 3, 2, 256), short), ("dgrad_sr", conv(64, 28, 128, 5, 1, 64), short),
+           ("dgrad_sr", conv(38, 28, 320, 1, 2, 1024), long_), ("dgrad_sr", (LINEAR, 5000, 1, 1, 1000, 1, 1, 1, 0, 500), short)])

@@ -346,6 +346,18 @@ def test_small_launches_and_the_lines_to_the_tile_kernels(H, hq, L):
     test_random_shapes_all_ops(H, hq, L)
 
 
+# Stochastic rounding in the tile kernels, on both sides of the line between long and short stages.
+@pytest.mark.parametrize("L", [wl.conv("sr_long_classes", 11, 28, 68, 448, 3, stride=2), wl.conv("sr_short_classes", 11, 28, 68, 112, 3, stride=2),
+                               wl.conv("sr_short_last_stage", 40, 28, 132, 288, 1, pad=0), wl.conv("sr_long", 40, 28, 132, 256, 1, pad=0)], ids=lambda l: l.name)
+def test_stochastic_tile_kernels(H, hq, L):
+    track, Wdev = H.TensorTrack(0.9, True), None
+    for t in range(2):                                       # dynamic, stochastic
+        _, W, dY = rand_layer_inputs(L, 30 + t)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=11 if t else None)
+
+
 # Weights in registers: units of 256 pixels that span rows and images in every way, the last one short; widest image, two
 # channel blocks, the smallest launch that takes the kernel; an image too wide for it.
 REGW_SHAPES = [wl.LayerShape("regw", wl.CONV, B, Hh, Ww, 64, 3, 3, 1, 1, n)
