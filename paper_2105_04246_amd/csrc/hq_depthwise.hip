@@ -744,8 +744,9 @@ int hq_launch_depthwise(const hq_problem *p, int dgrad, const int8_t *A, const h
         const int cols = s2_dgrad ? OW : (OW + 1) / 2;
         const long xb = ((long)p->B * cols * (p->C / 4) + HQ_THREADS - 1) / HQ_THREADS;
         // strips of output rows: about 16 workgroups per compute unit, at least four rows each (a strip reads two input
-        // rows beyond its own)
-        int strips = (int)std::min((4096 + xb - 1) / xb, (long)(OH + 3) / 4);
+        // rows beyond its own); shorter ones as long as that makes no more than two workgroups per compute unit, since a
+        // strip is a serial chain (1 x 14 x 14 x 960, stride 2, stochastic input gradient: four rows 8.6 us, one 4.7)
+        int strips = (int)std::max(std::min((4096 + xb - 1) / xb, (long)(OH + 3) / 4), std::min((long)OH, 512 / xb));
         d.rows_per_strip = (OH + strips - 1) / strips;
         strips = (OH + d.rows_per_strip - 1) / d.rows_per_strip;
         const dim3 grid((unsigned)xb, (unsigned)strips);
@@ -795,10 +796,11 @@ int hq_launch_depthwise_wgrad(const hq_problem *p, const int8_t *X, const hq_qpa
         d.B = p->B; d.H = p->H; d.W = p->W; d.OH = OH; d.OW = OW; d.C = p->C;
         // One workgroup of DW_WG_THREADS per compute unit: every workgroup ends with up to 10 * C atomics on the same
         // addresses, so more of them cost more than the latency they hide.  Strips of at least four rows where the
-        // images alone are too few, then images in turn.
+        // images alone are too few, then images in turn; shorter ones up to 64 workgroups and 28 strips (32 x 7 x 7 x 32: four rows
+        // 10.3 us, one 9.4).
         const long per = (long)((OW + 3) / 4) * (p->C / 4);          // threads of one image
         const long most = 256L * DW_WG_THREADS;
-        int strips = (int)std::max(1L, std::min(most / (per * p->B), (long)(OH + 3) / 4));
+        int strips = (int)std::max({1L, std::min(most / (per * p->B), (long)(OH + 3) / 4), std::min({(long)OH, 28L, 64L * DW_WG_THREADS / (per * p->B)})});
         d.rows_per_strip = (OH + strips - 1) / strips;
         strips = (OH + d.rows_per_strip - 1) / d.rows_per_strip;
         d.images = (int)std::max(1L, std::min((long)p->B, most / (per * strips)));

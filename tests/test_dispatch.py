@@ -77,3 +77,14 @@ def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
            ("dgrad_sr", conv(60, 28, 96, 5, 2, 64), short), ("dgrad_sr", conv(41, 28, 256, 3, 2, 448), long_),
            ("dgrad_sr", conv(41, 28, 256, 3, 2, 256), short), ("dgrad_sr", conv(64, 28, 128, 5, 1, 64), short),
            ("dgrad_sr", conv(38, 28, 320, 1, 2, 1024), long_), ("dgrad_sr", (LINEAR, 5000, 1, 1, 1000, 1, 1, 1, 0, 500), short)])
+
+
+def test_small_depthwise_launches_are_cut_into_short_strips():
+    """Workgroups of the launch: a strip is a serial chain, so few threads get as many strips as there are rows."""
+    def blocks(op, *layer):
+        B, hw, C, stride = layer
+        return max(l.blocks for l in launches.calls([(op, (DEPTHWISE, B, hw, hw, C, 3, 3, stride, 1, C))])[0] if l.kernel.startswith("hq_dw3x3"))
+    for op, layer, want in (("dgrad_sr", (1, 14, 960, 2), 7 * 7), ("fwd", (2, 28, 32, 1), 28), ("dgrad", (1, 7, 32, 1), 7),
+                            ("fwd", (8, 56, 192, 1), 42 * 14),      # at the line: strips of four rows
+                            ("wgrad", (32, 7, 32, 1), 7), ("wgrad", (1, 7, 960, 2), 4), ("wgrad", (8, 28, 192, 1), 6 * 10), ("wgrad", (1, 112, 16, 1), 28)):
+        assert blocks(op, *layer) == want, (op, layer, blocks(op, *layer))
