@@ -215,12 +215,25 @@ int hq_try_launch_wgrad_small(const hq_problem *p, const int8_t *X, const hq_qpa
     // 64 x 64 tiles, half the reads).  More steps: as long as the tiles run side by side and each reads less than about 10 us
     // worth; beyond, the split-K kernels (a 7 x 7 x 512 layer at batch 32 23 -> 9 us, 8192 pixels under 36 tiles 16 -> 12,
     // 12544 pixels under 128 tiles 22 -> 31).  Rows off 16 bytes are read by words and reach that point earlier.
+    // The time here grows with the pixels alone (8.2 us for 4700, 9.2 for 6000, 11.2 for 8000), that of the split-K kernels with
+    // the work: small gradients turn over earlier (3x3 16 -> 16 at 8000 pixels 11.1 us against 9.4, 64 -> 64 11.3 against 11.9).
+    // And every XCD reads all pixels it has a tile of, of whole 128-byte lines (with 256 channels half of them: eight tiles of
+    // 32 channels, one per XCD): once they do not fit its L2 the time jumps (3x3 stride 2, 128 -> 64: 4.0 MB 10.1 us, 4.2 MB 15.9
+    // against 13.1; but 96 -> 128, where the split-K kernel needs two tiles, 17.1 against 22.5).
     if (a.M <= 512) {
         if (tiles(32, 32) <= 2304) return launch<1, 1, 4, 4>(a, stream);
         return a.M <= 256 ? launch<2, 2, 4, 2>(a, stream) : HQ_E_BADSHAPE;
     }
     if (a.M <= 2048 && tiles(32, 32) <= 256) return launch<1, 1, 8, 4>(a, stream);
     if (a.M <= 2048 && tiles(32, 64) <= 256) return launch<1, 2, 8, 2>(a, stream);
-    if (a.M <= 8192 && tiles(32, 32) <= 256 && a.g16 && a.x16) return launch<1, 1, 16, 2>(a, stream);
+    auto worth_it = [&] {
+        if (a.M <= 5120) return true;
+        const unsigned long long image = (unsigned long long)p->B * p->H * p->W, x = (image < M * a.taps ? image : M * a.taps) * a.C;
+        const unsigned long long per_xcd = ((a.C + 31) / 32 % 8 == 0 ? x / 2 : x) + M * a.N, weights = (unsigned long long)a.N * a.taps * a.C;
+        const unsigned least = a.taps == 1 ? (a.M <= 6400 ? 0 : 8192) : (a.M <= 6400 ? 6400 : a.M <= 7168 ? 12800 : 20480);
+        return weights >= least && (per_xcd <= (4u << 20) || (a.N >= 128 && a.C >= 96));
+    };
+    if (a.M <= 8192 && tiles(32, 32) <= 256 && a.g16 && a.x16 && worth_it())
+        return launch<1, 1, 16, 2>(a, stream);
     return HQ_E_BADSHAPE;
 }

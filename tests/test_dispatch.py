@@ -88,3 +88,13 @@ def test_small_depthwise_launches_are_cut_into_short_strips():
                             ("fwd", (8, 56, 192, 1), 42 * 14),      # at the line: strips of four rows
                             ("wgrad", (32, 7, 32, 1), 7), ("wgrad", (1, 7, 960, 2), 4), ("wgrad", (8, 28, 192, 1), 6 * 10), ("wgrad", (1, 112, 16, 1), 28)):
         assert blocks(op, *layer) == want, (op, layer, blocks(op, *layer))
+
+
+def test_one_launch_weight_gradients_end_where_split_k_is_faster():
+    one, split, band = "hq_wgrad_small_kernel", "zero_kernel", "hq_wgrad_band_kernel"
+    check([("wgrad", conv(41, 28, 128, 3, 2, 64), split), ("wgrad", conv(33, 28, 128, 3, 2, 64), one),       # 8036, 6468 pixels: past and in the L2
+           ("wgrad", conv(41, 28, 128, 3, 2, 128), one), ("wgrad", conv(41, 28, 256, 3, 2, 32), split),
+           ("wgrad", conv(33, 28, 256, 3, 2, 32), one),
+           ("wgrad", conv(41, 14, 16, 3, 1, 16), split), ("wgrad", conv(26, 14, 16, 3, 1, 16), one),
+           ("wgrad", conv(41, 14, 64, 1, 1, 64), split), ("wgrad", conv(41, 14, 64, 1, 1, 128), one),
+           ("wgrad", conv(41, 14, 64, 3, 1, 64), one), ("wgrad", conv(42, 14, 64, 3, 1, 64), band)])

@@ -381,7 +381,8 @@ def test_weights_in_registers(H, hq, L, g_asym):
 WGRAD_LINES = [wl.linear("ws_1px", 1, 16, 4), wl.linear("ws_4w", 100, 52, 68), wl.linear("ws_64", 70, 2064, 1040), wl.conv("ws_8w", 3, 25, 48, 36, 3),
                wl.linear("ws_32x64", 1030, 304, 848), wl.conv("ws_16w_s2", 9, 50, 32, 80, 3, stride=2), wl.LayerShape("ws_5x3", wl.CONV, 2, 19, 14, 20, 5, 3, 3, 2, 48),
                wl.linear("past_ws_512", 520, 1040, 1040), wl.linear("past_ws_64", 300, 2064, 1040), wl.conv("past_ws_band", 12, 27, 64, 64, 3),
-               wl.conv("past_ws_s2", 9, 62, 32, 80, 3, stride=2), wl.conv("past_ws_c36", 4, 47, 36, 100, 3, stride=2), wl.conv("past_ws_big", 20, 29, 80, 96, 1, stride=1, pad=0)]
+               wl.conv("past_ws_s2", 9, 62, 32, 80, 3, stride=2), wl.conv("past_ws_c36", 4, 47, 36, 100, 3, stride=2), wl.conv("past_ws_big", 20, 29, 80, 96, 1, stride=1, pad=0),
+               wl.conv("past_ws_l2", 41, 28, 128, 64, 3, stride=2), wl.conv("past_ws_little", 41, 14, 16, 16, 3), wl.conv("ws_l2_two_tiles", 41, 28, 96, 128, 3, stride=2)]
 
 
 @pytest.mark.parametrize("L", WGRAD_LINES, ids=[l.name for l in WGRAD_LINES])
