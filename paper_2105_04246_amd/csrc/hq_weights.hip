@@ -3,12 +3,13 @@
 //
 // A network's update calls both for every layer, and most layers hold so few weights (10^4 .. 10^6) that
 // a launch costs more than its memory traffic: what bounds these entry points is the number of launches
-// and the longest serial chain in each.  Hence one launch for hq_weight_prepare, one for hq_weight_quantize
-// up to QW_ONE elements, two beyond.  All weights of ResNet-18 (21 layers, 11.7 M): 167 launches before, 52 now.
+// and the longest serial chain in each.  Hence one launch for hq_weight_prepare (two beyond COL_ONE lines), one for
+// hq_weight_quantize up to QW_ONE elements, two beyond.  All weights of ResNet-18 (21 layers, 11.7 M): 167 launches before, 51 now.
 #include "hq_device.h"
 #include "hq_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -75,7 +76,7 @@ __device__ inline float scale_of(unsigned bits)
 
 // code of w: rne(w / s) with the division rounded once.  w * (1 / s) differs from that quotient by less than 4e-5
 // (|quotient| <= 127, two roundings of 2^-24 each), so its rounding is the quotient's unless it lies that
-// close to a half; only then is the division carried out (about one value in 10^4).
+// close to a half; only then is the division carried out (about two values in 10^4).
 __device__ inline int code_of(float w, float s, float inv)
 {
     const float q = __fmul_rn(w, inv);
@@ -150,12 +151,21 @@ __global__ __launch_bounds__(QW_THREADS) void weight_quantize_kernel(const float
 // ---------------------------------------------------------------------------------------
 // Re-laying and sums
 // ---------------------------------------------------------------------------------------
+// Lines that one workgroup takes (as 16-byte loads / with 256 channels or more, where the rest of the launch takes longer / by
+// words), and at least when they are split.  One / two launches: 512 channels, 4608 lines 8.7 / 8.9 us, 9216 20.7 / 13.4; 1024
+// channels, 6400 lines 19.9 / 22.7; 64 channels, 36864 lines 23.5 / 9.3; 100 channels, 3136 lines 9.3 / 9.8, 4608 10.8 / 8.9.
+constexpr long COL_ONE = 5120, COL_ONE_WIDE = 8192, COL_ONE_WORDS = 4096, COL_PART = 1024;
+
 struct PrepArgs {
     const int8_t *W;
     int8_t *Wd;
     int32_t *rowsum, *colsum, *colsum2;
     int rows, taps, C;              // W[rows][taps][C]
     int row_blocks, col_blocks;     // workgroups of the first two roles; the rest re-lay tiles
+    int col_parts;                  // workgroups that share the lines of one column block, which meet by atomics if more than one
+    int32_t *clear;                 // C words to clear for such a launch that follows
+    int fold;                       // lines of fewer than 16 channels that are read as one
+    int lines, share;               // (folded) lines; of a workgroup's part
     int tiles_n, tiles_c;           // 64 x 64 tiles per tap
     int in_align, out_align;        // 16, 4 or 1: what divides the address of W / of every line of Wd
 };
@@ -181,15 +191,19 @@ __device__ inline v4i load_codes16(const int8_t *p, int n, int align)
 // Three roles, by workgroup index, all reading W (from L2 after the first touch):
 //   row sums      one wavefront per row of taps * C codes
 //   column sums   a workgroup owns 16 channels and runs over all rows * taps lines, so that nothing has to be
-//                 cleared beforehand and no atomics meet
+//                 cleared beforehand and no atomics meet; four lines of a thread are in flight, since the lines lie in
+//                 as many cache lines and the chain of loads is the longest of the launch
 //   re-laying     64 x 64 tiles of one tap, transposed through LDS: W[n][tap][c] -> Wd[c][tap][n]
+// Beyond COL_ONE lines the chain is longer than another launch: that one splits the lines over workgroups.
 __global__ __launch_bounds__(HQ_THREADS) void weight_prepare_kernel(const PrepArgs a)
 {
     __shared__ __attribute__((aligned(16))) int8_t tile[64 * 68];
-    __shared__ int part[HQ_THREADS / 64][16];
+    __shared__ int sums[HQ_THREADS / 64][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const size_t len = (size_t)a.taps * a.C;
     int block = blockIdx.x;
+    if (a.clear)
+        for (int c = block * HQ_THREADS + tid; c < a.C; c += gridDim.x * HQ_THREADS) a.clear[c] = 0;
     if (block < a.row_blocks) {
         const int row = block * (HQ_THREADS / 64) + wave;
         if (row >= a.rows) return;
@@ -207,29 +221,53 @@ __global__ __launch_bounds__(HQ_THREADS) void weight_prepare_kernel(const PrepAr
     }
     block -= a.row_blocks;
     const int align = min(a.in_align, a.C % 16 == 0 ? 16 : a.C % 4 == 0 ? 4 : 1);
-    if (block < a.col_blocks) {
-        const int c0 = 16 * block, nc = min(16, a.C - c0);
-        const size_t lines = (size_t)a.rows * a.taps;
+    if (block < a.col_blocks * a.col_parts) {
+        const int width = a.C * a.fold, walign = min(a.in_align, width % 16 == 0 ? 16 : width % 4 == 0 ? 4 : 1);
+        const int column = a.col_parts == 1 ? block : block / a.col_parts, part = block - column * a.col_parts;
+        const int c0 = 16 * column, nc = min(16, width - c0);
+        const int lo = a.share * part, lines = min(a.lines, lo + a.share);
         int s[16] = {};
-        for (size_t l = tid; l < lines; l += HQ_THREADS) {
-            const v4i v = load_codes16(a.W + l * a.C + c0, nc, align);
+        auto run = [&](auto al) {
+            auto load = [&](int l) { return load_codes16(a.W + (size_t)l * width + c0, nc, decltype(al)::value); };
+            auto add = [&](const v4i &v) {
 #pragma unroll
-            for (int e = 0; e < 16; e++) s[e] = __builtin_amdgcn_sdot4(v[e >> 2], 1 << (8 * (e & 3)), s[e], false);
-        }
+                for (int e = 0; e < 16; e++) s[e] = __builtin_amdgcn_sdot4(v[e >> 2], 1 << (8 * (e & 3)), s[e], false);
+            };
+            int l = lo + tid;
+            if (decltype(al)::value > 1)                 // (off 4 bytes: 16 loads a line are in flight anyway)
+                for (int full = (lines - lo) / (4 * HQ_THREADS); full > 0; full--, l += 4 * HQ_THREADS) {
+                    v4i v[4];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) v[k] = load(l + k * HQ_THREADS);
+#pragma unroll
+                    for (int k = 0; k < 4; k++) add(v[k]);
+                }
+#pragma unroll 1
+            for (; l < lines; l += HQ_THREADS) add(load(l));
+        };
+        if (walign == 16) run(std::integral_constant<int, 16>());
+        else if (walign == 4) run(std::integral_constant<int, 4>());
+        else run(std::integral_constant<int, 1>());
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             const int t = hq_wave_reduce(s[e], HqAdd());
-            if (lane == 0) part[wave][e] = t;
+            if (lane == 0) sums[wave][e] = t;
         }
         __syncthreads();
-        if (tid < nc) {
-            const int t = part[0][tid] + part[1][tid] + part[2][tid] + part[3][tid];
-            if (a.colsum) a.colsum[c0 + tid] = t;
-            if (a.colsum2) a.colsum2[c0 + tid] = t;
+        if (tid < (a.fold > 1 ? a.C : nc)) {
+            int t = 0;
+            for (int j = tid; j < (a.fold > 1 ? nc : tid + 1); j += a.C) t += sums[0][j] + sums[1][j] + sums[2][j] + sums[3][j];
+            if (a.col_parts > 1) {
+                atomicAdd(a.colsum + c0 + tid, t);
+            } else {
+                if (a.colsum) a.colsum[c0 + tid] = t;
+                if (a.colsum2) a.colsum2[c0 + tid] = t;
+            }
         }
         return;
     }
-    block -= a.col_blocks;
+    block -= a.col_blocks * a.col_parts;
+    if (!a.Wd) return;
     const int tc = block % a.tiles_c, tn = block / a.tiles_c % a.tiles_n, tap = block / (a.tiles_c * a.tiles_n);
     const int c0 = 64 * tc, n0 = 64 * tn, r = tid >> 2, q = 16 * (tid & 3);
     {
@@ -280,9 +318,26 @@ int hq_launch_weight_prepare(const hq_problem *p, const int8_t *W, int8_t *Wd, i
         a.out_align = std::min(align_of(Wd), p->Cout % 16 == 0 ? 16 : 4);        // Cout % 4 == 0
     }
     a.tiles_n = (a.rows + 63) / 64; a.tiles_c = (a.C + 63) / 64;
-    const unsigned blocks = (unsigned)(a.row_blocks + a.col_blocks) + (a.Wd ? (unsigned)a.tiles_n * a.tiles_c * a.taps : 0u);
+    a.col_parts = 1;
+    a.fold = a.C == 3 ? 4 : (long)a.rows * a.taps < 1024 ? 1 : a.C == 4 ? 4 : a.C == 8 ? 2 : 1;
+    if ((long)a.rows * a.taps % a.fold != 0) a.fold = 1;
+    const long lines = (long)a.rows * a.taps / a.fold;
+    const int col_blocks = a.col_blocks;
+    a.lines = a.share = (int)lines;
+    const bool apart = a.colsum && !a.colsum2 &&
+                       lines > (a.in_align != 16 || a.C * a.fold % 16 != 0 ? COL_ONE_WORDS : a.C >= 256 ? COL_ONE_WIDE : COL_ONE);
+    if (apart) { a.col_blocks = 0; a.clear = a.colsum; }
+    unsigned blocks = (unsigned)(a.row_blocks + a.col_blocks) + (a.Wd ? (unsigned)a.tiles_n * a.tiles_c * a.taps : 0u);
+    if (apart && blocks == 0) blocks = (unsigned)((a.C + HQ_THREADS - 1) / HQ_THREADS);
     if (blocks == 0) return HQ_OK;
     hipLaunchKernelGGL(weight_prepare_kernel, dim3(blocks), dim3(HQ_THREADS), 0, s, a);
+    if (apart) {
+        a.clear = nullptr; a.Wd = nullptr; a.row_blocks = 0;
+        a.col_blocks = col_blocks;
+        a.col_parts = (int)std::min((lines + COL_PART - 1) / COL_PART, std::max(1L, 1024L / col_blocks));
+        a.share = (int)((lines + a.col_parts - 1) / a.col_parts);
+        hipLaunchKernelGGL(weight_prepare_kernel, dim3((unsigned)(a.col_blocks * a.col_parts)), dim3(HQ_THREADS), 0, s, a);
+    }
     return launch_status();
 }
 

@@ -98,3 +98,13 @@ def test_one_launch_weight_gradients_end_where_split_k_is_faster():
            ("wgrad", conv(41, 14, 16, 3, 1, 16), split), ("wgrad", conv(26, 14, 16, 3, 1, 16), one),
            ("wgrad", conv(41, 14, 64, 1, 1, 64), split), ("wgrad", conv(41, 14, 64, 1, 1, 128), one),
            ("wgrad", conv(41, 14, 64, 3, 1, 64), one), ("wgrad", conv(42, 14, 64, 3, 1, 64), band)])
+
+
+def test_column_sums_over_many_lines_are_shared():
+    """hq_weight_prepare: a workgroup walks at most 8192 lines (rows of the weight tensor per tap) alone."""
+    few, many = launches.calls([("weight_prepare", conv(1, 7, 512, 3, 1, 512)), ("weight_prepare", conv(1, 7, 64, 3, 1, 4096))])
+    assert len(few) == 1 and len(many) == 2
+    assert many[1].kernel == "weight_prepare_kernel" and many[1].blocks == 4 * 36
+    one, words, stem = launches.calls([("weight_prepare", conv(1, 7, 4, 7, 1, 256)), ("weight_prepare", conv(1, 7, 36, 3, 1, 512)),
+                                       ("weight_prepare", conv(1, 7, 3, 7, 2, 64))])
+    assert (len(one), len(words), len(stem)) == (1, 2, 1)      # lines of 4 channels are read four at a time

@@ -428,7 +428,8 @@ def test_weight_prepare_layouts_and_sums(H, hq):
     assert np.array_equal(Wd.Wd.cpu().numpy().reshape(L.C, L.R, L.S, L.Cout), W.codes.transpose(3, 1, 2, 0))
 
 
-@pytest.mark.parametrize("shape", [(3, 1, 4, 4), (1, 7, 3, 64), (3, 3, 36, 100), (1, 1, 1024, 1000), (3, 3, 68, 8), (5, 2, 80, 132)],
+@pytest.mark.parametrize("shape", [(3, 1, 4, 4), (1, 7, 3, 64), (3, 3, 36, 100), (1, 1, 1024, 1000), (3, 3, 68, 8), (5, 2, 80, 132),
+                                   (7, 7, 3, 256), (7, 7, 4, 420), (5, 3, 8, 700), (3, 3, 16, 1024), (5, 5, 36, 260), (3, 3, 272, 600)],
                          ids=lambda s: "%dx%d_c%d_n%d" % s)
 @pytest.mark.parametrize("offset", [0, 4, 1])
 def test_weight_prepare_edges(H, hq, shape, offset):
