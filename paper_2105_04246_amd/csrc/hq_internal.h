@@ -22,6 +22,9 @@ int hq_try_launch_regw(const hq_problem *p, int dgrad, const int8_t *A, const hq
                        int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream,
                        const uint64_t *sr_seed = nullptr);
 
+// Workgroups (bands of one image's rows) of the kernel below for a 3x3 layer with B images of Ho output rows.
+long hq_band_workgroups(int B, int Ho);
+
 // Fast path for layers whose weights fit in LDS; HQ_E_BADSHAPE means "not covered, use hq_launch_gemm".
 // sr_seed as for hq_launch_gemm.
 int hq_try_launch_band(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,

@@ -108,3 +108,12 @@ def test_column_sums_over_many_lines_are_shared():
     one, words, stem = launches.calls([("weight_prepare", conv(1, 7, 4, 7, 1, 256)), ("weight_prepare", conv(1, 7, 36, 3, 1, 512)),
                                        ("weight_prepare", conv(1, 7, 3, 7, 2, 64))])
     assert (len(one), len(words), len(stem)) == (1, 2, 1)      # lines of 4 channels are read four at a time
+
+
+def test_32_bit_pass_of_64_channel_layers_over_few_pixels():
+    ks, regw, band = "hq_ksplit_kernel", "hq_regw_kernel", "hq_band_kernel"
+    check([("dynamic_fwd", conv(7, 16, 64, 3, 1, 64), ks), ("dynamic_fwd", conv(12, 16, 64, 3, 1, 64), band),
+           ("dynamic_dgrad", conv(64, 16, 64, 3, 1, 64), band), ("dynamic_fwd", conv(128, 16, 64, 3, 1, 64), regw),
+           ("dynamic_fwd", conv(64, 16, 64, 3, 1, 128), regw), ("dynamic_fwd", conv(300, 7, 64, 3, 1, 64), regw),
+           ("dynamic_fwd", conv(47, 16, 64, 3, 1, 64), regw),
+           ("fwd", conv(64, 16, 64, 3, 1, 64), regw)])
