@@ -37,7 +37,6 @@
 #include <type_traits>
 #include "hq_internal.h"
 
-
 namespace {
 
 struct BandArgs {

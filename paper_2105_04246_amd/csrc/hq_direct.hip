@@ -224,11 +224,11 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_direct_kernel(const DirectAr
 
 
 // ---------------------------------------------------------------------------------------------------------
-// The same layer with the input rows staged in LDS (even stride, W * C a multiple of 4): a workgroup walks
+// The same layer with the input rows staged in LDS (W a multiple of 4): a workgroup walks
 // bands of whole output rows; the input rows a band needs are copied once into LDS with every pixel widened
 // to 4 bytes (3-channel pixels: three funnel shifts per four pixels; the fourth byte meets a zero weight)
-// inside a frame of zero-point pixels, so a lane's 16 bytes of an input fragment are two aligned 8-byte
-// LDS reads at (input row) * pitch + 4 * stride * ox, with no bounds logic and no byte masks.  The k-step of
+// inside a frame of zero-point pixels, so a lane's 16 bytes of an input fragment are two 8-byte LDS reads
+// (odd strides: four words) at (input row) * pitch + 4 * stride * ox, with no bounds logic and no byte masks.  The k-step of
 // filter row r is then tap s at bytes 4 s .. 4 s + 3 (weights of the fourth byte and of taps past S are 0).
 // The next band's rows are on their way (global -> registers) while this band is multiplied.
 struct StemArgs {
@@ -243,9 +243,11 @@ struct StemArgs {
 
 constexpr int ST_TASKS = 5;        // staged 4-pixel groups per thread and band (host checks the fit)
 
-template <int NT, bool FUSED, int CH, bool EVEN>
+// OUT: 0 32-bit outputs of 16 channels, 1 codes, 2 32-bit outputs of more channels (whole lines, see the epilogue).
+template <int NT, int OUT, int CH, bool EVEN>
 __global__ __launch_bounds__(HQ_THREADS, 2) void hq_stem_kernel(const StemArgs sa)
 {
+    constexpr bool FUSED = OUT == 1, LINES = OUT == 2;
     const DirectArgs &a = sa.d;
     extern __shared__ __attribute__((aligned(16))) int8_t stem_lds[];
     __shared__ int red[4 * (HQ_THREADS / 64)];
@@ -269,7 +271,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_stem_kernel(const StemArgs s
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < NT; j++) {
-            const int n = j * 32 + dr_sigma32(lane & 31);
+            const int n = j * 32 + (LINES ? lane & 31 : dr_sigma32(lane & 31));
 #pragma unroll
             for (int r = 0; r < DR_MAXR; r++) {
                 v4i v = {0, 0, 0, 0};
@@ -375,19 +377,51 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_stem_kernel(const StemArgs s
         v16i acc[NT];
 #pragma unroll
         for (int j = 0; j < NT; j++)
+            if constexpr (!LINES) {
 #pragma unroll
-            for (int g = 0; g < 4; g++) {
-                const v4i bz = *reinterpret_cast<const v4i *>(bzs + j * 32 + 16 * half + 4 * g);
+                for (int g = 0; g < 4; g++) {
+                    const v4i bz = *reinterpret_cast<const v4i *>(bzs + j * 32 + 16 * half + 4 * g);
 #pragma unroll
-                for (int e = 0; e < 4; e++) acc[j][4 * g + e] = bz[e];
+                    for (int e = 0; e < 4; e++) acc[j][4 * g + e] = bz[e];
+                }
+            } else {
+                const int bz = bzs[j * 32 + (lane & 31)];
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[j][e] = bz;
             }
 #pragma unroll
         for (int r = 0; r < DR_MAXR; r++) {
             if (r < a.R) {
 #pragma unroll
                 for (int j = 0; j < NT; j++)
-                    acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[r][j], af[r][0], acc[j], 0, 0, 0);
+                    acc[j] = LINES ? __builtin_amdgcn_mfma_i32_32x32x32_i8(af[r][0], wf[r][j], acc[j], 0, 0, 0)
+                                   : __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[r][j], af[r][0], acc[j], 0, 0, 0);
             }
+        }
+        // Whole lines: the products are formed transposed, so a lane holds one channel of 16 pixels and a store of the wavefront
+        // writes 128-byte lines.  With 16 channels of one pixel a lane it touches 64 lines, a quarter of each, and workgroups in
+        // step keep meeting on the same memory channels (whole dynamic call, 3x3, 248 x 56 x 56 x 3 -> 64: 157 us, now 93; stride 2
+        // 50 -> 36).  16 channels are one run of memory that way and half-empty stores this way (200 x 112 x 112: 105 / 118 us).
+        if constexpr (LINES) {
+            const int left = npix - blk * 32;
+            const size_t p0 = m0 + blk * 32;
+#pragma unroll
+            for (int j = 0; j < NT; j++) {
+                if (j * 32 + (lane & 31) >= a.N) continue;
+                const unsigned lo = (unsigned)(4 * half * a.N + j * 32 + (lane & 31));
+                int c[16];
+#pragma unroll
+                for (int e = 0; e < 16; e++) c[e] = acc[j][e];
+                if (left >= 32) hq_minmax_group<16>(c, mn, mx);
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    const int row = 8 * (e >> 2) + (e & 3);
+                    int32_t *dst = a.out32 + (p0 + row) * a.N;
+                    if (left >= 32) dst[lo] = c[e];
+                    else if (row + 4 * half < left) { dst[lo] = c[e]; mn = min(mn, c[e]); mx = max(mx, c[e]); }
+                }
+            }
+            return;
         }
         auto epilogue = [&](auto full) {
             constexpr bool FULL = decltype(full)::value;
@@ -402,7 +436,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_stem_kernel(const StemArgs s
 #pragma unroll
                 for (int e = 0; e < 16; e++) c[e] = acc[j][e];
                 const size_t o = m * a.N + nb;
-                if (FUSED) {
+                if constexpr (FUSED) {
                     int w[4];
                     hq_requant_group<16, FULL>(c, ep, mn, mx, nlo, nhi, w);
                     const v4i v = {w[0], w[1], w[2], w[3]};
@@ -516,16 +550,16 @@ int hq_try_launch_direct(const hq_problem *p, int dgrad, const int8_t *A, const 
             auto slaunch = [&](auto kern) {
                 hipLaunchKernelGGL(kern, dim3(sblocks), dim3(HQ_THREADS), lds, stream, sa);
             };
-            auto even = [&](auto nt, auto fu, auto ch) {
-                if (p->stride % 2 == 0) slaunch(hq_stem_kernel<nt.value, fu.value, ch.value, true>);
-                else                    slaunch(hq_stem_kernel<nt.value, fu.value, ch.value, false>);
+            auto even = [&](auto nt, auto out, auto ch) {
+                if (p->stride % 2 == 0) slaunch(hq_stem_kernel<nt.value, out.value, ch.value, true>);
+                else                    slaunch(hq_stem_kernel<nt.value, out.value, ch.value, false>);
             };
-            using one = std::integral_constant<int, 1>; using two = std::integral_constant<int, 2>;
-            auto channels = [&](auto nt, auto fu) {
-                if (p->C == 4) even(nt, fu, std::integral_constant<int, 4>()); else even(nt, fu, std::integral_constant<int, 3>());
+            auto channels = [&](auto nt, auto out) {
+                if (p->C == 4) even(nt, out, std::integral_constant<int, 4>()); else even(nt, out, std::integral_constant<int, 3>());
             };
-            if (a.N > 32) { if (fused) channels(two(), std::true_type()); else channels(two(), std::false_type()); }
-            else          { if (fused) channels(one(), std::true_type()); else channels(one(), std::false_type()); }
+            using zero = std::integral_constant<int, 0>; using one = std::integral_constant<int, 1>; using two = std::integral_constant<int, 2>;
+            if (a.N > 32) { if (fused) channels(two(), one()); else channels(two(), two()); }
+            else          { if (fused) channels(one(), one()); else if (a.N > 16) channels(one(), two()); else channels(one(), zero()); }
             return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
         }
     }

@@ -117,3 +117,9 @@ def test_32_bit_pass_of_64_channel_layers_over_few_pixels():
            ("dynamic_fwd", conv(64, 16, 64, 3, 1, 128), regw), ("dynamic_fwd", conv(300, 7, 64, 3, 1, 64), regw),
            ("dynamic_fwd", conv(47, 16, 64, 3, 1, 64), regw),
            ("fwd", conv(64, 16, 64, 3, 1, 64), regw)])
+
+
+def test_32_bit_pass_of_first_layers_stores_whole_lines():
+    got = launches.calls([("dynamic_fwd", conv(8, 56, 3, 3, 1, n)) for n in (16, 32, 48)] + [("fwd", conv(8, 56, 3, 3, 1, 48))])
+    assert [g[0].kernel for g in got] == ["hq_stem_kernel<1, 0, 3, false>", "hq_stem_kernel<1, 2, 3, false>",
+                                          "hq_stem_kernel<2, 2, 3, false>", "hq_stem_kernel<2, 1, 3, false>"]
