@@ -243,7 +243,7 @@ struct StemArgs {
 
 constexpr int ST_TASKS = 5;        // staged 4-pixel groups per thread and band (host checks the fit)
 
-// OUT: 0 32-bit outputs of 16 channels, 1 codes, 2 32-bit outputs of more channels (whole lines, see the epilogue).
+// OUT: 0 32-bit outputs, 1 codes, 2 32-bit outputs in whole lines (see the epilogue).
 template <int NT, int OUT, int CH, bool EVEN>
 __global__ __launch_bounds__(HQ_THREADS, 2) void hq_stem_kernel(const StemArgs sa)
 {
@@ -533,13 +533,18 @@ int hq_try_launch_direct(const hq_problem *p, int dgrad, const int8_t *A, const 
             rows = r;
         }
         if (rows >= 1) {
-            // few images: bands short enough for one to every compute unit, down to a 32-pixel block per wavefront
-            // (7x7 stem of one 224 x 224 image: 23 -> 8 us)
-            while (rows > 1 && (long)p->B * ((OH + rows - 1) / rows) < 256 && rows * OW > 128) rows--;
+            // Few images: bands of equal height, as many as are resident at once, two to every compute unit, down to a 32-pixel
+            // block per wavefront (7x7 stem of one 224 x 224 image: 23 -> 8 us).  3x3 stride 1, 56 x 56 x 3 -> 48, batch 130: bands
+            // of 55 rows and of one 35 us, of 28 rows 30, of 19 rows 18.6; batch 256: one band to an image 31, two 24.  (32-bit outputs
+            // of 16 channels: one to every compute unit, 100 x 32 x 32 13.5 us against 15.7.)
+            int nb = (OH + rows - 1) / rows;
+            auto height = [&](int n) { return (OH + n - 1) / n; };
+            while ((fused || a.N > 16 ? (long)p->B * (nb + 1) <= 512 : (long)p->B * nb < 256) && height(nb) * OW > 128) nb++;
+            rows = height(nb);
             // prefer a band height that divides the image and fills whole 128-pixel rounds of the four wavefronts
             int best = rows;
             for (int r = rows; r >= 1 && r * 2 > rows; r--)
-                if (OH % r == 0 && (r * OW) % 128 == 0) { best = r; break; }
+                if (OH % r == 0 && (r * OW) % 128 == 0 && ((long)p->B * (OH / r) <= 512 || OH / r == nb)) { best = r; break; }
             sa.rows_out = best;
             sa.in_rows = (best - 1) * p->stride + p->R;
             sa.bands_per_image = (OH + best - 1) / best;
@@ -558,8 +563,10 @@ int hq_try_launch_direct(const hq_problem *p, int dgrad, const int8_t *A, const 
                 if (p->C == 4) even(nt, out, std::integral_constant<int, 4>()); else even(nt, out, std::integral_constant<int, 3>());
             };
             using zero = std::integral_constant<int, 0>; using one = std::integral_constant<int, 1>; using two = std::integral_constant<int, 2>;
-            if (a.N > 32) { if (fused) channels(two(), one()); else channels(two(), two()); }
-            else          { if (fused) channels(one(), one()); else if (a.N > 16) channels(one(), two()); else channels(one(), zero()); }
+            // whole lines pay from about 30 K pixels on: their longer code starts later (1 x 56 x 56 -> 64, whole call 11.6 / 12.7 us)
+            const bool lines = a.N > 16 && a.M >= 30000;
+            if (a.N > 32) { if (fused) channels(two(), one()); else if (lines) channels(two(), two()); else channels(two(), zero()); }
+            else          { if (fused) channels(one(), one()); else if (lines) channels(one(), two()); else channels(one(), zero()); }
             return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
         }
     }

@@ -120,6 +120,16 @@ def test_32_bit_pass_of_64_channel_layers_over_few_pixels():
 
 
 def test_32_bit_pass_of_first_layers_stores_whole_lines():
-    got = launches.calls([("dynamic_fwd", conv(8, 56, 3, 3, 1, n)) for n in (16, 32, 48)] + [("fwd", conv(8, 56, 3, 3, 1, 48))])
+    got = launches.calls([("dynamic_fwd", conv(B, 56, 3, 3, 1, n)) for B, n in ((16, 16), (16, 32), (16, 48), (8, 48))] + [("fwd", conv(16, 56, 3, 3, 1, 48))])
     assert [g[0].kernel for g in got] == ["hq_stem_kernel<1, 0, 3, false>", "hq_stem_kernel<1, 2, 3, false>",
-                                          "hq_stem_kernel<2, 2, 3, false>", "hq_stem_kernel<2, 1, 3, false>"]
+                                          "hq_stem_kernel<2, 2, 3, false>", "hq_stem_kernel<2, 0, 3, false>", "hq_stem_kernel<2, 1, 3, false>"]
+
+
+def test_bands_of_first_layers_are_even_and_resident():
+    """Workgroups of the launch: one per band up to 512."""
+    def blocks(op, *c):
+        return launches.calls([(op, conv(*c))])[0][0].blocks
+    assert blocks("fwd", 130, 56, 3, 3, 1, 48) == 390 and blocks("fwd", 256, 56, 3, 3, 1, 48) == 512
+    assert blocks("fwd", 100, 32, 3, 3, 1, 48) == 500              # not 800 bands of four rows in two uneven rounds
+    assert blocks("fwd", 1, 224, 3, 7, 2, 64) == 112 and blocks("fwd", 300, 56, 3, 3, 1, 48) == 300
+    assert blocks("dynamic_fwd", 100, 32, 3, 3, 1, 16) < 500

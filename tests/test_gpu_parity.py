@@ -182,7 +182,8 @@ def test_rgb_first_layer(H, hq, L, g_asym):
 # weight tensor, many short images.
 STEM_EDGES = [wl.LayerShape("stem", wl.CONV, *v) for v in
               ((3, 31, 32, 3, 3, 3, 1, 1, 64), (2, 20, 36, 3, 5, 7, 1, 2, 32), (1, 90, 224, 3, 7, 7, 2, 3, 64), (300, 9, 8, 3, 3, 3, 3, 1, 48),
-               (1, 5, 4, 3, 1, 1, 1, 0, 16), (2, 33, 64, 4, 3, 3, 1, 1, 64), (1, 9, 12, 4, 7, 8, 3, 3, 16), (5, 40, 260, 4, 2, 3, 1, 1, 32))]
+               (1, 5, 4, 3, 1, 1, 1, 0, 16), (2, 33, 64, 4, 3, 3, 1, 1, 64), (1, 9, 12, 4, 7, 8, 3, 3, 16), (5, 40, 260, 4, 2, 3, 1, 1, 32),
+               (30, 29, 36, 3, 3, 3, 1, 1, 48), (30, 29, 36, 4, 3, 3, 1, 1, 64), (30, 29, 36, 3, 5, 5, 1, 2, 32), (12, 110, 112, 3, 7, 7, 2, 3, 64))]
 
 
 @pytest.mark.parametrize("L", STEM_EDGES, ids=["b%d_%dx%dx%d_%dx%d_s%d_n%d" % (l.B, l.H, l.W, l.C, l.R, l.S, l.stride, l.Cout) for l in STEM_EDGES])
