@@ -638,9 +638,9 @@ int hq_launch_gemm(const hq_problem *p, int dgrad, const int8_t *A, const hq_qpa
         // cut short (by the end of the reduction; in a filter's taps and a strided layer's classes by many channels).  Input
         // gradients, 128- / 64-byte stages: 3255 x 2048 -> 3624 54.9 / 48.1 us, 50176 x 288 -> 128 18.0 / 15.7, 5x5 50176 x 64 -> 128
         // 35.8 / 32.0, 3x3 stride 2 39984 x 128 -> 256 22.7 / 19.6; 4096 x 4096 -> 4096 49.9 / 58.9, 5x5 29792 x 176 -> 132 60.6 / 64.7,
-        // 3x3 stride 2 19992 x 512 -> 128 25.1 / 26.4.
+        // 3x3 stride 2 19992 x 512 -> 128 25.1 / 26.4, 3873 x 3532 -> 1668 by words 128 / 166.
         auto long_stages = [&] {
-            if (!aligned) return a.taps > 1;
+            if (!aligned) return tiles <= 2 * 256 && (a.taps > 1 || a.nchunks >= 28);
             const long classes = strided ? (long)p->stride * p->stride : 1;
             if (tiles * std::min((long)a.taps, classes) > 2 * 256 * classes) return false;
             if (a.taps == 1 && !strided) return a.nchunks >= 64 || a.nchunks % 8 == 0;
