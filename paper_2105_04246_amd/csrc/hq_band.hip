@@ -401,14 +401,10 @@ constexpr size_t BAND_LDS_MAX = 160 * 1024;
 template <int C, int KSZ, int NT, int PR, int PJ, int NG, int MODE>
 int launch_band_mode(const BandArgs &a, int blocks, size_t lds, hipStream_t s)
 {
-    static bool configured = false;
-    if (!configured) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(hq_band_kernel<C, KSZ, NT, PR, PJ, NG, MODE>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)BAND_LDS_MAX) != hipSuccess)
-            return HQ_E_HIP;
-        configured = true;
-    }
-    hipLaunchKernelGGL((hq_band_kernel<C, KSZ, NT, PR, PJ, NG, MODE>), dim3(blocks), dim3(256 * NG), lds, s, a);
+    static std::atomic<unsigned long long> allowed{0};
+    auto kern = hq_band_kernel<C, KSZ, NT, PR, PJ, NG, MODE>;
+    if (!hq_allow_lds(kern, BAND_LDS_MAX, allowed)) return HQ_E_HIP;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256 * NG), lds, s, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }
 

@@ -356,24 +356,15 @@ int hq_try_launch_bandw(const hq_problem *p, int dgrad, const int8_t *A, const h
     const size_t patch_bytes = ((size_t)a.patch_px * BW_CK + 1023) & ~(size_t)1023;
     const size_t lds = 4 * BW_BN * BW_CK + 2 * patch_bytes + 4 * BW_BN + 64;
     if (lds > 158 * 1024) return HQ_E_BADSHAPE;            // (two workgroups per compute unit up to 78 KiB)
-    static bool configured = false;
-    if (!configured) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(hq_bandw_kernel<0>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(hq_bandw_kernel<1>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void *>(hq_bandw_kernel<2>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-            return HQ_E_HIP;
-        configured = true;
-    }
     long items = (long)a.ntiles * a.nchunks;
     // Too few tiles for the chip under a reduction long enough to matter (4 x 4 images with 512 channels):
     // the gather kernel's 64 x 64 tiles spread the same work over four times as many workgroups.
     if (items < 192 && (unsigned long long)a.count * 9ull * (unsigned)C >= (1ull << 32)) return HQ_E_BADSHAPE;
     const int blocks = (int)(items < 512 ? items : 512);
-    if (out32 != nullptr) hipLaunchKernelGGL(hq_bandw_kernel<0>, dim3(blocks), dim3(HQ_THREADS), lds, stream, a);
-    else if (sr_seed)     hipLaunchKernelGGL(hq_bandw_kernel<2>, dim3(blocks), dim3(HQ_THREADS), lds, stream, a);
-    else                  hipLaunchKernelGGL(hq_bandw_kernel<1>, dim3(blocks), dim3(HQ_THREADS), lds, stream, a);
+    const int mode = out32 != nullptr ? 0 : sr_seed ? 2 : 1;
+    auto kern = mode == 0 ? hq_bandw_kernel<0> : mode == 2 ? hq_bandw_kernel<2> : hq_bandw_kernel<1>;
+    static std::atomic<unsigned long long> allowed[3];
+    if (!hq_allow_lds(kern, 160 * 1024, allowed[mode])) return HQ_E_HIP;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(HQ_THREADS), lds, stream, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }

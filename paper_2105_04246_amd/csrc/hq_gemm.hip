@@ -33,6 +33,7 @@
 // launch (Sec. 4, step 1).  With `out32` set, the kernel is pass 1 of the dynamic baseline:
 // it stores the corrected 32-bit outputs (the accumulator-save term of eq. (5)) and gathers min / max.
 #include "hq_device.h"
+#include "hq_internal.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -555,14 +556,8 @@ int launch3(GemmArgs &a, hipStream_t s)
     }
     const size_t lds = 2 * (size_t)(BM + BN) * (ALIGNED ? BKB : BKB + 16) + 4 * BN + 64;
     auto kern = hq_gemm_kernel<BM, BN, WGM, WGN, BKB, STRIDED, ALIGNED, MODE>;
-    static bool configured = false;
-    if (!configured) {
-        if (lds > 48 * 1024 &&
-            hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return HQ_E_HIP;
-        configured = true;
-    }
+    static std::atomic<unsigned long long> allowed{0};
+    if (!hq_allow_lds(kern, lds, allowed)) return HQ_E_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.m_tiles * a.n_tiles)), dim3(HQ_THREADS), lds, s, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }

@@ -3,6 +3,23 @@
 #include <hip/hip_runtime.h>
 #include "../../include/hq.h"
 
+#include <atomic>
+
+// Lets `kernel` have `bytes` of dynamic LDS on the current GPU.  The attribute belongs to a kernel on one GPU; `devices` (a
+// static of the caller, one for each kernel) has a bit for every GPU on which it has been set.
+template <typename K> inline bool hq_allow_lds(K *kernel, size_t bytes, std::atomic<unsigned long long> &devices)
+{
+    if (bytes <= 48 * 1024) return true;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0) return false;
+    const unsigned long long bit = dev < 64 ? 1ull << dev : 0;
+    if (devices.load(std::memory_order_relaxed) & bit) return true;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+        return false;
+    devices.fetch_or(bit, std::memory_order_relaxed);
+    return true;
+}
+
 // sr_seed: NULL = round to nearest even; otherwise (host pointer) the seed of stochastic rounding.
 int hq_launch_gemm(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
                    const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,

@@ -299,13 +299,8 @@ int launch3(KsArgs &a, hipStream_t s)
     a.n_tiles = (a.N + 16 * TNB - 1) / (16 * TNB);
     const size_t lds = (size_t)NW * 1024 * (TMB * TNB > D * (TMB + TNB) ? TMB * TNB : D * (TMB + TNB)) + 4 * 16 * TNB + 16 * NW;
     auto kern = hq_ksplit_kernel<TMB, TNB, NW, D, ALIGNED, MODE>;
-    static bool configured = false;
-    if (lds > 48 * 1024 && !configured) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return HQ_E_HIP;
-        configured = true;
-    }
+    static std::atomic<unsigned long long> allowed{0};
+    if (!hq_allow_lds(kern, lds, allowed)) return HQ_E_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.m_tiles * a.n_tiles)), dim3(NW * 64), lds, s, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }

@@ -290,14 +290,10 @@ int hq_try_launch_regw(const hq_problem *p, int dgrad, const int8_t *A, const hq
     a.inv_W = 1.0f / (float)W; a.inv_H = 1.0f / (float)H;
     if (sr_seed && out32) return HQ_E_BADARG;
     a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
-    auto kern = out32 ? hq_regw_kernel<0> : sr_seed ? hq_regw_kernel<2> : hq_regw_kernel<1>;
-    static bool configured = false;
-    if (!configured) {
-        for (auto k : {hq_regw_kernel<0>, hq_regw_kernel<1>, hq_regw_kernel<2>})
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024) != hipSuccess)
-                return HQ_E_HIP;
-        configured = true;
-    }
+    const int mode = out32 ? 0 : sr_seed ? 2 : 1;
+    auto kern = mode == 0 ? hq_regw_kernel<0> : mode == 2 ? hq_regw_kernel<2> : hq_regw_kernel<1>;
+    static std::atomic<unsigned long long> allowed[3];
+    if (!hq_allow_lds(kern, 156 * 1024, allowed[mode])) return HQ_E_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.runs * a.nparts)), dim3(RW_THREADS), lds, stream, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }

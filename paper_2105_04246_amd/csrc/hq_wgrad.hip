@@ -961,12 +961,8 @@ bool launch_wgrad_band(const hq_problem *p, const WbandPlan &pl, const WgradArgs
     a.prows = pl.prows; a.PW = p->W + 2;
     a.xchunks = a.prows * a.PW * 4; a.gchunks = a.npix * 4;
     a.buf_bytes = (unsigned)pl.buf_bytes;
-    static bool configured = false;
-    if (!configured) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(hq_wgrad_band_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return false;
-        configured = true;
-    }
+    static std::atomic<unsigned long long> allowed{0};
+    if (!hq_allow_lds(hq_wgrad_band_kernel, 160 * 1024, allowed)) return false;
     hipLaunchKernelGGL(hq_wgrad_band_kernel, dim3((unsigned)(pl.parts * pl.splits)), dim3(WB_THREADS), pl.lds, stream, a);
     return true;
 }
@@ -1058,15 +1054,9 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
             sa.bands_per_image = (OH + rows - 1) / rows;
             sa.nbands = p->B * sa.bands_per_image;
             const size_t lds = 2 * ((size_t)sa.xrows * sa.LP + (size_t)sa.kpad * sa.gpitch) + 64;
-            static bool configured = false;
-            if (!configured) {
-                if (hipFuncSetAttribute(reinterpret_cast<const void *>(hq_wgrad_stem_kernel<3>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024) != hipSuccess ||
-                    hipFuncSetAttribute(reinterpret_cast<const void *>(hq_wgrad_stem_kernel<4>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024) != hipSuccess)
-                    return HQ_E_HIP;
-                configured = true;
-            }
+            static std::atomic<unsigned long long> allowed[2];
+            if (!hq_allow_lds(hq_wgrad_stem_kernel<3>, 80 * 1024, allowed[0]) || !hq_allow_lds(hq_wgrad_stem_kernel<4>, 80 * 1024, allowed[1]))
+                return HQ_E_HIP;
             const size_t zwords = sums_bytes / 4;
             hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((zwords + 255) / 256 > 1024 ? 1024 : (zwords + 255) / 256)),
                                dim3(256), 0, stream, a.acc, zwords);

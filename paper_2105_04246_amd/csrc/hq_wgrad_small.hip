@@ -182,12 +182,8 @@ int launch(WsmallArgs &a, hipStream_t s)
     const int blocks = a.xt * ((a.N + 32 * NB - 1) / (32 * NB));
     a.ride.first = blocks;
     auto kern = hq_wgrad_small_kernel<NB, KB, NW, D>;
-    static bool configured = false;
-    if (lds > 48 * 1024 && !configured) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return HQ_E_HIP;
-        configured = true;
-    }
+    static std::atomic<unsigned long long> allowed{0};
+    if (!hq_allow_lds(kern, lds, allowed)) return HQ_E_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(blocks + a.ride.n)), dim3(NW * 64), lds, s, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }

@@ -134,3 +134,18 @@ def test_bands_of_first_layers_are_even_and_resident():
     assert blocks("fwd", 100, 32, 3, 3, 1, 48) == 500              # not 800 bands of four rows in two uneven rounds
     assert blocks("fwd", 1, 224, 3, 7, 2, 64) == 112 and blocks("fwd", 300, 56, 3, 3, 1, 48) == 300
     assert blocks("dynamic_fwd", 100, 32, 3, 3, 1, 16) < 500
+
+
+def test_every_gpu_of_a_process_is_told_of_large_lds():
+    """The attribute that allows a kernel more dynamic LDS belongs to one GPU: a second GPU of the process needs it, too."""
+    work = [("fwd", conv(128, 56, 64, 3, 1, 64)), ("dynamic_fwd", conv(128, 56, 64, 3, 1, 64)), ("dgrad_sr", conv(128, 56, 64, 3, 1, 64)),
+            ("fwd", conv(128, 28, 128, 3, 1, 128)), ("dynamic_fwd", conv(128, 28, 128, 3, 1, 128)), ("dgrad_sr", conv(128, 28, 128, 3, 1, 128)),
+            ("fwd", conv(128, 57, 64, 3, 2, 64)), ("fwd", conv(1, 7, 512, 3, 1, 512)), ("fwd", conv(26, 14, 128, 3, 1, 128)),
+            ("fwd", (LINEAR, 256, 1, 1, 512, 1, 1, 1, 0, 512)), ("fwd", conv(64, 28, 256, 3, 2, 512)),
+            ("wgrad", conv(128, 56, 64, 3, 1, 64)), ("wgrad", conv(64, 224, 3, 7, 2, 64)), ("wgrad", conv(64, 224, 4, 7, 2, 64)), ("wgrad", conv(3, 14, 256, 3, 1, 256)),
+            ("wgrad", conv(20, 14, 256, 3, 1, 64))]
+    got = launches.calls([(op, p, dev) for dev in (0, 1) for op, p in work])
+    large = [l for calls in got[len(work):] for l in calls if l.lds > 48 * 1024]
+    assert len({l.kernel for l in large}) >= 8
+    for l in large:
+        assert l.lds_allowed >= l.lds, l
