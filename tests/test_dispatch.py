@@ -149,3 +149,22 @@ def test_every_gpu_of_a_process_is_told_of_large_lds():
     assert len({l.kernel for l in large}) >= 8
     for l in large:
         assert l.lds_allowed >= l.lds, l
+
+
+def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_for():
+    import test_gpu_parity as T
+    def regw(op, s):
+        B, H, W, C, n = s
+        return launches.calls([(op, (CONV, B, H, W, C, 3, 3, 1, 1, n))])[0][0].kernel.startswith("hq_regw_kernel")
+    assert all(regw(op, s) for s in T.REGW_ALL_MODES for op in ("dynamic_fwd", "dynamic_dgrad", "fwd", "dgrad", "dgrad_sr"))
+    assert all(regw("fwd", s) for s in T.REGW_FORWARD)
+    assert all(regw(op, s) for s in T.REGW_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
+    assert not any(regw(op, s) for s in T.REGW_PAST for op in ("dynamic_fwd", "fwd", "dgrad", "dgrad_sr"))
+    one, four = "hq_wgrad_small_kernel<1, 1, 4, 4>", "hq_wgrad_small_kernel<2, 2, 4, 2>"
+    want = {"ws_1px": one, "ws_32_2145": one, "ws_32_300px": one, "ws_32_2304": one, "ws_64": four, "ws_64_256px": four, "past_ws_64": "zero_kernel",
+            "past_ws_512": "zero_kernel", "ws_32x64": "hq_wgrad_small_kernel<1, 2, 8, 2>", "ws_8w": "hq_wgrad_small_kernel<1, 1, 8, 4>",
+            "ws_16w_s2": "hq_wgrad_small_kernel<1, 1, 16, 2>"}
+    lines = [L for L in T.WGRAD_LINES if L.name in want]
+    assert len(lines) == len(want)
+    for L, got in zip(lines, launches.calls([("wgrad", tuple(L)[1:]) for L in lines])):
+        assert got[0].kernel == want[L.name], (L.name, got[0].kernel)

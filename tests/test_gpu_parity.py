@@ -359,13 +359,18 @@ def test_stochastic_tile_kernels(H, hq, L):
         track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=11 if t else None)
 
 
-# Weights in registers: units of 256 pixels that span rows and images in every way, the last one short; widest image, two
-# channel blocks, the smallest launch that takes the kernel; an image too wide for it.
-REGW_SHAPES = [wl.LayerShape("regw", wl.CONV, B, Hh, Ww, 64, 3, 3, 1, 1, n)
-               for B, Hh, Ww, n in ((7, 31, 29, 64), (131, 7, 7, 64), (4200, 1, 1, 64), (1500, 3, 1, 64), (20, 2, 125, 128), (1, 40, 126, 64), (1, 40, 128, 64))]
+# Weights in registers: units of 256 pixels that span rows and images in every way, the last one short.  The lists say what the
+# kernel takes of each shape (test_dispatch.py holds them to it): both directions in every mode, the forward pass, the input
+# gradient, or nothing.
+REGW_ALL_MODES = [(4, 40, 121, 64, 64), (700, 13, 1, 64, 64), (300, 16, 2, 64, 64)]       # widest image; narrowest ones; units over several images
+REGW_FORWARD = [(7, 31, 29, 64, 64), (131, 7, 7, 64, 64), (1, 65, 64, 64, 64), (33, 17, 19, 64, 128)]    # smallest launch; two channel blocks
+REGW_BACKWARD = [(33, 17, 19, 128, 64)]                                                    # two channel blocks, stochastic too
+REGW_PAST = [(2, 40, 122, 64, 64), (4200, 1, 1, 64, 64), (1500, 3, 1, 64, 64), (20, 2, 125, 64, 128), (1, 40, 126, 64, 64), (1, 40, 128, 64, 64)]
+REGW_SHAPES = [wl.LayerShape("regw", wl.CONV, B, Hh, Ww, c, 3, 3, 1, 1, n)
+               for B, Hh, Ww, c, n in REGW_FORWARD + REGW_ALL_MODES + REGW_BACKWARD + REGW_PAST]
 
 
-@pytest.mark.parametrize("L", REGW_SHAPES, ids=["b%d_%dx%d_n%d" % (l.B, l.H, l.W, l.Cout) for l in REGW_SHAPES])
+@pytest.mark.parametrize("L", REGW_SHAPES, ids=["b%d_%dx%d_c%d_n%d" % (l.B, l.H, l.W, l.C, l.Cout) for l in REGW_SHAPES])
 @pytest.mark.parametrize("g_asym", [False, True])
 def test_weights_in_registers(H, hq, L, g_asym):
     y_track, g_track = H.TensorTrack(0.9, g_asym), H.TensorTrack(0.9, not g_asym)
@@ -379,11 +384,13 @@ def test_weights_in_registers(H, hq, L, g_asym):
 
 
 # Weight gradients in one launch: tiles of every size, channel counts off 16 and 32, pixels off 32, and past each line.
-WGRAD_LINES = [wl.linear("ws_1px", 1, 16, 4), wl.linear("ws_4w", 100, 52, 68), wl.linear("ws_64", 70, 2064, 1040), wl.conv("ws_8w", 3, 25, 48, 36, 3),
+WGRAD_LINES = [wl.linear("ws_1px", 1, 16, 4), wl.linear("ws_4w", 100, 52, 68), wl.linear("ws_32_2145", 70, 2064, 1040), wl.conv("ws_8w", 3, 25, 48, 36, 3),
                wl.linear("ws_32x64", 1030, 304, 848), wl.conv("ws_16w_s2", 9, 50, 32, 80, 3, stride=2), wl.LayerShape("ws_5x3", wl.CONV, 2, 19, 14, 20, 5, 3, 3, 2, 48),
-               wl.linear("past_ws_512", 520, 1040, 1040), wl.linear("past_ws_64", 300, 2064, 1040), wl.conv("past_ws_band", 12, 27, 64, 64, 3),
+               wl.linear("past_ws_512", 520, 1040, 1040), wl.linear("ws_32_300px", 300, 2064, 1040), wl.conv("past_ws_band", 12, 27, 64, 64, 3),
                wl.conv("past_ws_s2", 9, 62, 32, 80, 3, stride=2), wl.conv("past_ws_c36", 4, 47, 36, 100, 3, stride=2), wl.conv("past_ws_big", 20, 29, 80, 96, 1, stride=1, pad=0),
-               wl.conv("past_ws_l2", 41, 28, 128, 64, 3, stride=2), wl.conv("past_ws_little", 41, 14, 16, 16, 3), wl.conv("ws_l2_two_tiles", 41, 28, 96, 128, 3, stride=2)]
+               wl.conv("past_ws_l2", 41, 28, 128, 64, 3, stride=2), wl.conv("past_ws_little", 41, 14, 16, 16, 3), wl.conv("ws_l2_two_tiles", 41, 28, 96, 128, 3, stride=2),
+               wl.linear("ws_32_2304", 256, 2048, 1136), wl.linear("ws_64", 70, 2068, 1140), wl.linear("ws_64_256px", 256, 2068, 1140),
+               wl.linear("past_ws_64", 257, 2068, 1140)]
 
 
 @pytest.mark.parametrize("L", WGRAD_LINES, ids=[l.name for l in WGRAD_LINES])
