@@ -158,8 +158,8 @@ int hq_gemm_dgrad(const hq_problem *p /* host */,
  * (linear index of the element in dX, seed).  The result therefore depends on the seed and the
  * tensor only, not on the kernel's tiling; callers derive `seed` (host value) from their base
  * seed, the tensor and the iteration.  Clamping, clip counts, statistics and all other arguments
- * as hq_gemm_dgrad.  Same kernel selection as hq_gemm_dgrad, except that HQ_DEPTHWISE layers
- * always take the general stencil.                                                           */
+ * as hq_gemm_dgrad.  The kernels are those of hq_gemm_dgrad; which of them takes a
+ * layer may differ, since rounding costs more here.                                          */
 int hq_gemm_dgrad_sr(const hq_problem *p /* host */,
                      const int8_t *dY, const hq_qparams *gq,
                      const int8_t *Wd, const hq_qparams *wq, const int32_t *wdsum,

@@ -248,7 +248,7 @@ static int gemm_common(const hq_problem *p, int dgrad, const int8_t *A, const hq
         if (rc != HQ_E_BADSHAPE) return rc;
     }
     if (sr_seed) {
-        // stochastic rounding: the two 3x3 / 1x1 fast paths, else the two general kernels
+        // stochastic rounding: never a first layer (no input gradient)
         if (p->kind == HQ_DEPTHWISE)
             return hq_launch_depthwise(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
         rc = hq_try_launch_bandw(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);

@@ -98,10 +98,10 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_depthwise_kernel(const DwArgs a
 // ---------------------------------------------------------------------------------------
 // 3x3 with padding 1 and stride 1 or 2: the depthwise layers of MobileNetV2-style blocks (Table 5, DW rows).
 //
-// What bounds these kernels is the vector ALU (the earlier stride-1 kernel, one column per thread: 27.8 instructions per
-// output, 84 % busy, 71 us for 128 x 56 x 56 x 192 against 30 us of memory traffic; now 43 us, stride 2 18 instead of 67 and
-// its input gradient 25 instead of 239), so they are written for few instructions per output.  A thread owns four channels (one word) of two neighbouring output columns and slides down a
-// strip of rows.  Pixels come as packed words of four channels; the words of four adjacent columns are byte-transposed (8
+// What bounds these kernels is the vector ALU: 19.5 instructions per output, whose issue takes 86 % of the 44 us of 128 x 56 x 56 x
+// 192 (30 us of memory traffic; the earlier stride-1 kernel, one column per thread, had 26 and took 71 us), 65 % of the time with
+// stride 2 (18 us instead of 67) and 91 % in its input gradient (25 instead of 239).  Hence few instructions per output.  A
+// thread owns four channels (one word) of two neighbouring output columns and slides down a strip of rows.  Pixels come as packed words of four channels; the words of four adjacent columns are byte-transposed (8
 // v_perm_b32) into one word per channel, and a filter row on it is one 4-way byte dot product per output: the second column's
 // weights are the first's shifted by one byte.  Rows are addressed by a uniform pointer plus a fixed lane offset, so loads cost
 // no address arithmetic, and the fill of columns outside the image is one select per word.  Lanes run along (column,
@@ -516,9 +516,10 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_depthwise_wgrad_kernel(const Dw
 // channels of four neighbouring output columns and walks down a strip of rows and over several images.  The reduction
 // runs over pixels, so the four columns' gradients and the inputs of one tap column are byte-transposed words, and a tap's
 // share of the four pixels is one 4-way dot product; the words of the neighbouring tap columns are the same pixels moved
-// by one (one v_perm each).  5.5 vector instructions per pixel and channel (22.5 in the earlier kernel, which packed rows and
-// fetched every input three times): 38 us instead of 68 for 128 x 56 x 56 x 192, stride 2 21 instead of 86.  Threads that share channels meet in LDS, and the workgroup leaves with one
-// atomic per value.  Where the gradient's zero point is not 0 a second walk, with ones in place of the gradients, gathers the
+// by one (one v_perm each).  7.0 vector instructions per pixel and channel (22.5 in the earlier kernel, which packed rows and
+// fetched every input three times): 38 us instead of 68 for 128 x 56 x 56 x 192, stride 2 21 instead of 86.  Their issue is a third of
+// that now; one workgroup per compute unit waits for its loads.  Threads that share channels meet in LDS, and the workgroup
+// leaves with one atomic per value.  Where the gradient's zero point is not 0 a second walk, with ones in place of the gradients, gathers the
 // column sums of the input that remove it.
 struct Dw3WgradArgs {
     const int8_t *X, *G;

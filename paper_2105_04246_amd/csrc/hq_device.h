@@ -8,7 +8,7 @@
 typedef int v4i  __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-#define HQ_THREADS 256                     // every compute kernel runs 4 wavefronts of 64 lanes
+#define HQ_THREADS 256                     // 4 wavefronts of 64 lanes; kernels with other sizes name their own
 
 // x / d by multiplication, for d >= 1 and x * d < 2^32: magic = (unsigned)ceil(2^32 / d), which for
 // d == 1 wraps to 0 and is then taken as "no division".  The host computes the constant.

@@ -4,13 +4,13 @@
 //
 // What bounds such a launch is the latency of one tile's serial chain: load, wait, barrier, multiply, once per stage
 // (about 1 us each; 46 us for 7x7x512 -> 512 at batch 1).  Here the wavefronts of a workgroup share a small
-// output tile and split its reduction: wavefront w takes the 64-byte steps w, w + NW, ..., loads both
-// operands' MFMA fragments straight from global memory into registers D steps ahead, and meets the others only once, when
-// the partial sums are added through LDS.  No barrier, no LDS traffic and no shared stage inside the reduction; every
-// wavefront keeps D x (TMB + TNB) KB in flight.  The price is that an operand byte is fetched once per tile
-// instead of once per larger tile, so the rate is bound by the 64 bytes a clock a compute unit loads:
-// (TM + TN) x K / 64 clocks per tile.  Measured (forward, before -> now): 7x7x512 -> 512 at batch 1 45 -> 8.4 us, 14x14x256
-// 25 -> 7.3, 28x28x128 16 -> 6.9; 256 x 512 -> 1000 with 1000 reduced 30 -> 10; 4x4x512 at batch 128 24 -> 17 us.
+// output tile and split its reduction: wavefront w takes the 64-byte steps w, w + NW, ... and meets the others only once, when
+// the partial sums are added through LDS.  There is no barrier inside the reduction.  Aligned form: each wavefront brings its
+// steps into LDS of its own (direct-to-LDS loads of whole lines, D steps ahead), D x (TMB + TNB) KB in flight, and reads the MFMA
+// fragments from there.  4-byte form (channel counts off 16): fragments straight from global memory into registers.  The price is
+// that an operand byte is fetched once per tile instead of once per larger tile, so the rate is bound by the 64 bytes a clock a
+// compute unit loads: (TM + TN) x K / 64 clocks per tile.  Measured (forward, before -> now): 7x7x512 -> 512 at batch 1 45 -> 8.4 us,
+// 14x14x256 25 -> 7.3, 28x28x128 16 -> 6.9; 256 x 512 -> 1000 with 1000 reduced 30 -> 10; 4x4x512 at batch 128 24 -> 17 us.
 //
 // Both operations are  out[m][n] = sum_{tap,c} A[pix(m,tap)][c] * Bw[n][tap][c]  as in the gather kernel, with the
 // same class form for strided input gradients (an output pixel's class fixes its taps; everything else is one class).

@@ -8,10 +8,10 @@
 // A unit is 256 consecutive output pixels, 32 per wavefront, of the tensor's [image][row][column] order, whatever rows and
 // images it spans.  The input rows it needs are copied to LDS in padded-image order (a row of padding above and below
 // every image), one patch row per wavefront and turn, while the unit before is multiplied; pixels have a pitch of
-// 80 bytes, which keeps the fragment reads (32 pixels at one 16-byte chunk) free of bank conflicts and lets a tap be a
-// constant offset from the pixel's address.
-// Measured: 24 us at that size (about 9 of them start-up and the end, 2.1 per unit of 1.2 us of matrix work), 61 x 37 x 23
-// x 64, whose rows fit no band of the other kernel, 16 -> 8.5 us.
+// 80 bytes, which spreads the fragment reads (32 pixels at one 16-byte chunk) over the banks (conflicts: 18 % of LDS's busy cycles)
+// and lets a tap be a constant offset from the pixel's address.
+// Measured: 24 us at that size, 6 or 7 units to a workgroup: 8 for a launch of one unit each, 2.6 for each further one (1.2 of them
+// matrix work); 61 x 37 x 23 x 64, whose rows fit no band of the other kernel, 16 -> 8.5 us.
 #include "hq_device.h"
 #include "hq_internal.h"
 
