@@ -635,7 +635,10 @@ int hq_launch_gemm(const hq_problem *p, int dgrad, const int8_t *A, const hq_qpa
         // 35.8 / 32.0, 3x3 stride 2 39984 x 128 -> 256 22.7 / 19.6; 4096 x 4096 -> 4096 49.9 / 58.9, 5x5 29792 x 176 -> 132 60.6 / 64.7,
         // 3x3 stride 2 19992 x 512 -> 128 25.1 / 26.4, 3873 x 3532 -> 1668 by words 128 / 166.
         auto long_stages = [&] {
-            if (!aligned) return tiles <= 2 * 256 && (a.taps > 1 || a.nchunks >= 28);
+            // (by words, one tap: from 28 chunks where a compute unit holds one tile, 900 x 360 -> 4000 17.7 / 18.1, 424: 20.6 / 20.0;
+            // from 21 where some hold two, the short stages' barriers then add up: 3187 -> 1544, 260 reduced 19.6 / 19.3, 328
+            // 20.6 / 21.9, 360 20.8 / 22.6, 424 23.9 / 25.2)
+            if (!aligned) return tiles <= 2 * 256 && (a.taps > 1 || a.nchunks >= (tiles > 256 ? 21 : 28));
             const long classes = strided ? (long)p->stride * p->stride : 1;
             if (tiles * std::min((long)a.taps, classes) > 2 * 256 * classes) return false;
             if (a.taps == 1 && !strided) return a.nchunks >= 64 || a.nchunks % 8 == 0;

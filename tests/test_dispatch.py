@@ -77,7 +77,9 @@ def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
            ("dgrad_sr", conv(60, 28, 96, 5, 2, 64), short), ("dgrad_sr", conv(41, 28, 256, 3, 2, 448), long_),
            ("dgrad_sr", conv(41, 28, 256, 3, 2, 256), short), ("dgrad_sr", conv(64, 28, 128, 5, 1, 64), short),
            ("dgrad_sr", conv(38, 28, 320, 1, 2, 1024), long_), ("dgrad_sr", (LINEAR, 5000, 1, 1, 1000, 1, 1, 1, 0, 300), short),
-           ("dgrad_sr", (LINEAR, 3873, 1, 1, 1668, 1, 1, 1, 0, 3532), long_), ("dgrad_sr", (LINEAR, 5000, 1, 1, 2000, 1, 1, 1, 0, 1004), short)])
+           ("dgrad_sr", (LINEAR, 3873, 1, 1, 1668, 1, 1, 1, 0, 3532), long_), ("dgrad_sr", (LINEAR, 5000, 1, 1, 2000, 1, 1, 1, 0, 1004), short),
+           ("dgrad_sr", (LINEAR, 3187, 1, 1, 1544, 1, 1, 1, 0, 324), long_), ("dgrad_sr", (LINEAR, 3187, 1, 1, 1544, 1, 1, 1, 0, 316), short),
+           ("dgrad_sr", (LINEAR, 900, 1, 1, 4000, 1, 1, 1, 0, 360), short), ("dgrad_sr", (LINEAR, 900, 1, 1, 4000, 1, 1, 1, 0, 436), long_)])
 
 
 def test_small_depthwise_launches_are_cut_into_short_strips():

@@ -349,7 +349,8 @@ def test_small_launches_and_the_lines_to_the_tile_kernels(H, hq, L):
 
 # Stochastic rounding in the tile kernels, on both sides of the line between long and short stages.
 @pytest.mark.parametrize("L", [wl.conv("sr_long_classes", 11, 28, 68, 448, 3, stride=2), wl.conv("sr_short_classes", 11, 28, 68, 112, 3, stride=2),
-                               wl.conv("sr_short_last_stage", 40, 28, 132, 288, 1, pad=0), wl.conv("sr_long", 40, 28, 132, 256, 1, pad=0)], ids=lambda l: l.name)
+                               wl.conv("sr_short_last_stage", 40, 28, 132, 288, 1, pad=0), wl.conv("sr_long", 40, 28, 132, 256, 1, pad=0),
+                               wl.linear("sr_long_by_words", 2900, 1412, 324)], ids=lambda l: l.name)
 def test_stochastic_tile_kernels(H, hq, L):
     track, Wdev = H.TensorTrack(0.9, True), None
     for t in range(2):                                       # dynamic, stochastic
