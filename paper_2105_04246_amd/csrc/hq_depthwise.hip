@@ -87,7 +87,7 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_depthwise_kernel(const DwArgs a
             *reinterpret_cast<v4i *>(a.out32 + (size_t)m * a.C + c) = v;
         }
     }
-    hq_block_stats_commit(mn, mx, nlo, nhi, a.st, red);
+    hq_block_stats_commit(mn, mx, nlo, nhi, a.st, red, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         a.st->acc_scale = acc_scale;
         atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)a.M * (unsigned long long)a.C);
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_dw3x3_kernel(const Dw3Args a)
     if (live) {
         if (MODE == 0 || ep.full_grid) run(std::true_type()); else run(std::false_type());
     }
-    hq_block_stats_commit(mn, mx, nlo, nhi, a.st, red);
+    hq_block_stats_commit(mn, mx, nlo, nhi, a.st, red, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         a.st->acc_scale = acc_scale;
         atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)a.B * a.OH * a.OW * (unsigned long long)a.C);
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_dw3x3_s2_dgrad_kernel(const Dw3
     if (live) {
         if (MODE == 0 || ep.full_grid) run(std::true_type()); else run(std::false_type());
     }
-    hq_block_stats_commit(mn, mx, nlo, nhi, a.st, red);
+    hq_block_stats_commit(mn, mx, nlo, nhi, a.st, red, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
         a.st->acc_scale = acc_scale;
         atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)a.B * a.H * a.W * (unsigned long long)a.C);

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <limits.h>
+#include <stddef.h>
 #include "../../include/hq.h"
 
 typedef int v4i  __attribute__((ext_vector_type(4)));
@@ -439,23 +440,28 @@ __device__ inline unsigned hq_pack4(int a, int b, int c, int d)
 // Wavefront and workgroup reductions for the online statistics.
 // ---------------------------------------------------------------------------------------
 
-// Exchange with the lane whose index differs in bit `k` (k < 32: ds_swizzle inside each
-// half of the wavefront; k == 32: across the halves).
-template <int K> __device__ inline int hq_lane_xor(int v)
+// The value of the lane's partner inside its row of 16 lanes, without LDS: lane ^ 1, lane ^ 2, the mirror image in the 8 lanes,
+// the mirror image in the 16 lanes (K = 1, 2, 4, 8).  Applied one after the other they combine every lane with every other.
+template <int K> __device__ inline int hq_lane_partner(int v)
 {
-    if (K < 32) return __builtin_amdgcn_ds_swizzle(v, (K << 10) | 0x1f);
-    return __shfl_xor(v, 32);
+    constexpr int ctrl = K == 1 ? 0xB1 : K == 2 ? 0x4E : K == 4 ? 0x141 : 0x140;
+    return __builtin_amdgcn_update_dpp(0, v, ctrl, 0xf, 0xf, false);
+}
+template <int N, typename Op> __device__ inline int hq_row_reduce(int v, Op op)     // groups of N = 4, 8 or 16 lanes
+{
+    v = op(v, hq_lane_partner<1>(v));
+    v = op(v, hq_lane_partner<2>(v));
+    if (N > 4) v = op(v, hq_lane_partner<4>(v));
+    if (N > 8) v = op(v, hq_lane_partner<8>(v));
+    return v;
 }
 
+// All 64 lanes take part; the result is uniform.
 template <typename Op> __device__ inline int hq_wave_reduce(int v, Op op)
 {
-    v = op(v, hq_lane_xor<1>(v));
-    v = op(v, hq_lane_xor<2>(v));
-    v = op(v, hq_lane_xor<4>(v));
-    v = op(v, hq_lane_xor<8>(v));
-    v = op(v, hq_lane_xor<16>(v));
-    v = op(v, hq_lane_xor<32>(v));
-    return v;
+    v = hq_row_reduce<16>(v, op);
+    return op(op(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+              op(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 
 struct HqMin { __device__ int operator()(int a, int b) const { return a < b ? a : b; } };
@@ -466,36 +472,47 @@ struct HqAdd { __device__ int operator()(int a, int b) const { return a + b; } }
 // second level through LDS, then one atomic per field from one lane, into the partial record
 // chosen by the workgroup's index: consecutive workgroups land on different 128-byte lines, so
 // a launch's atomics do not queue on one address.  `red` is LDS space for 4 * (NTHREADS / 64)
-// ints.  Must be called by all NTHREADS threads of the workgroup.
+// ints.  Must be called by all NTHREADS threads of the workgroup; `block` is its index in the launch.
+// It is the end of every launch's serial chain, so it is written for latency: exchanges inside rows of 16 lanes and scalar
+// reads instead of LDS permutes, sums only where something was clipped, and the second level in one LDS read whose lanes
+// hold one field each (2000 -> 1300 cycles of a small launch's 16 K).
 template <int NTHREADS>
 __device__ inline void hq_block_stats_commit_n(int mn, int mx, unsigned nlo, unsigned nhi,
-                                               hq_stats *st, int *red)
+                                               hq_stats *st, int *red, unsigned block = blockIdx.x)
 {
+    constexpr int NW = NTHREADS / 64;
+    static_assert(NW == 4 || NW == 8 || NW == 16, "a field is a group of NW lanes");
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     mn = hq_wave_reduce(mn, HqMin());
     mx = hq_wave_reduce(mx, HqMax());
-    nlo = (unsigned)hq_wave_reduce((int)nlo, HqAdd());
-    nhi = (unsigned)hq_wave_reduce((int)nhi, HqAdd());
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    constexpr int NW = NTHREADS / 64;
-    if (lane == 0) { red[wave] = mn; red[NW + wave] = mx; red[2 * NW + wave] = (int)nlo; red[3 * NW + wave] = (int)nhi; }
+    if (__any((nlo | nhi) != 0)) {
+        nlo = (unsigned)hq_wave_reduce((int)nlo, HqAdd());
+        nhi = (unsigned)hq_wave_reduce((int)nhi, HqAdd());
+    }
+    if (lane == 0) { red[wave] = mn; red[NW + wave] = ~mx; red[2 * NW + wave] = (int)nlo; red[3 * NW + wave] = (int)nhi; }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long lo = 0, hi = 0;
-        for (int w = 0; w < NW; w++) {
-            mn = min(mn, red[w]); mx = max(mx, red[NW + w]);
-            lo += (unsigned)red[2 * NW + w]; hi += (unsigned)red[3 * NW + w];
+    if (wave == 0) {
+        const int f = lane / NW, v = f < 4 ? red[lane] : 0;
+        // ~ reverses the order: the smallest ~mx is that of the largest mx
+        const int least = hq_row_reduce<NW>(v, HqMin()), sum = hq_row_reduce<NW>(v, HqAdd());
+        int8_t *part = reinterpret_cast<int8_t *>(&st->part[block % HQ_STATS_PARTS]);
+        // (a lane's own address: with a common one the compiler puts a loop over the lanes around an atomic that one lane does)
+        static_assert(offsetof(hq_stats_part, acc_max) == 4 && offsetof(hq_stats_part, clip_lo) == 8 && offsetof(hq_stats_part, clip_hi) == 16, "");
+        unsigned word = f < 2 ? 4u * f : 8u * (f - 1);
+        asm volatile("" : "+v"(word));
+        part += word;
+        if (lane % NW == 0) {                              // (a workgroup without values leaves the record as it is)
+            if (f == 0) atomicMin(reinterpret_cast<int *>(part), least);
+            if (f == 1) atomicMax(reinterpret_cast<int *>(part), ~least);
+            if ((f == 2 || f == 3) && sum) atomicAdd(reinterpret_cast<unsigned long long *>(part), (unsigned long long)(unsigned)sum);
         }
-        const unsigned block = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-        hq_stats_part *part = &st->part[block % HQ_STATS_PARTS];
-        if (mn <= mx) { atomicMin(&part->acc_min, mn); atomicMax(&part->acc_max, mx); }
-        if (lo) atomicAdd((unsigned long long *)&part->clip_lo, lo);
-        if (hi) atomicAdd((unsigned long long *)&part->clip_hi, hi);
     }
 }
 
-__device__ inline void hq_block_stats_commit(int mn, int mx, unsigned nlo, unsigned nhi, hq_stats *st, int *red)
+__device__ inline void hq_block_stats_commit(int mn, int mx, unsigned nlo, unsigned nhi, hq_stats *st, int *red,
+                                             unsigned block = blockIdx.x)
 {
-    hq_block_stats_commit_n<HQ_THREADS>(mn, mx, nlo, nhi, st, red);
+    hq_block_stats_commit_n<HQ_THREADS>(mn, mx, nlo, nhi, st, red, block);
 }
 
 // Moves what the partial records hold into the record's leading fields and empties them.

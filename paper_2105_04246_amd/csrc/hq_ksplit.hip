@@ -11,6 +11,10 @@
 // that an operand byte is fetched once per tile instead of once per larger tile, so the rate is bound by the 64 bytes a clock a
 // compute unit loads: (TM + TN) x K / 64 clocks per tile.  Measured (forward, before -> now): 7x7x512 -> 512 at batch 1 45 -> 8.4 us,
 // 14x14x256 25 -> 7.3, 28x28x128 16 -> 6.9; 256 x 512 -> 1000 with 1000 reduced 30 -> 10; 4x4x512 at batch 128 24 -> 17 us.
+// What is left is fixed: of the 16 K cycles a 56x56x64 launch then took (clock stamps), 1.1 K were its loads and matrix work, the
+// rest arguments and operands fetched one miss after the other (2 + 1.2 K), a mask of every pixel's taps (5 K), loads of steps
+// past the end, divisions and statistics (2 K).  Those are gone, requested together, or moved under the first loads: 10 K
+// cycles, ResNet-18's forward pass at batch 1 155 -> 119 us, its step on 32 images of 64x64 525 -> 425 us.
 //
 // Both operations are  out[m][n] = sum_{tap,c} A[pix(m,tap)][c] * Bw[n][tap][c]  as in the gather kernel, with the
 // same class form for strided input gradients (an output pixel's class fixes its taps; everything else is one class).
@@ -41,7 +45,6 @@ struct KsClass {
     int ns, taps;                  // taps per row of the class's tap grid, taps in all
     int dh, dw;                    // source pixel of tap (0, 0) for y = x = 0
     int w0;                        // weight tap of tap (0, 0)
-    int tile0;                     // first row tile
     unsigned magic_Wc, magic_Hc, magic_ns;
 };
 
@@ -64,6 +67,7 @@ struct KsArgs {
     int m_tiles, n_tiles, m_fast;  // m_fast: consecutive workgroups share their weights, not their pixels
     int classed, ncls;             // classed: the zero-point term is summed from the class's own weights
     HqSr sr;
+    int tile0[16];                 // first row tile of each class
     KsClass cls[16];
 };
 
@@ -90,13 +94,21 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
     const int lchunk = ALIGNED ? (lane & 3) ^ ((lrow >> 1) & 3) : g;     // and its 16-byte chunk of the step
     const int frag = r16 * 64 + 16 * (g ^ ((r16 >> 1) & 3));
 
+    // The arguments span several cache lines; asked for where they are used they arrive one after the other, a miss each.
+    const KsClass &c0 = a.cls[0];
+    int m_tiles = a.m_tiles;
+    asm("" : "+s"(m_tiles) : "s"(a.A), "s"(a.aq), "s"(a.st), "s"(a.M), "s"(a.wrow), "s"(a.istep), "s"(a.sr.k1), "s"(a.tile0[0]),
+        "s"(a.tile0[15]), "s"(c0.ph), "s"(c0.magic_ns));
     int tile_m, tile_n;
-    if (a.m_fast) { tile_n = blockIdx.x / a.m_tiles; tile_m = blockIdx.x - tile_n * a.m_tiles; }
+    if (a.m_fast) { tile_n = blockIdx.x / m_tiles; tile_m = blockIdx.x - tile_n * m_tiles; }
     else          { tile_m = blockIdx.x / a.n_tiles; tile_n = blockIdx.x - tile_m * a.n_tiles; }
     int ci = 0;
-    while (ci + 1 < a.ncls && tile_m >= a.cls[ci + 1].tile0) ci++;
+    while (ci + 1 < a.ncls && tile_m >= a.tile0[ci + 1]) ci++;
     const KsClass &cl = a.cls[ci];
-    const int m0 = (tile_m - cl.tile0) * TM, n0 = tile_n * TN;
+    const int m0 = (tile_m - a.tile0[ci]) * TM, n0 = tile_n * TN;
+    int w0 = cl.w0;
+    unsigned magic_ns = cl.magic_ns, magic_div = a.magic_div;
+    asm("" : "+s"(w0), "+s"(magic_ns), "+s"(magic_div));                 // (kept, not read again for every load)
     const int Wc = cl.Wc, Hc = cl.Hc, ns = cl.ns, taps = cl.taps, Mrows = a.B * Hc * Wc;
     const int units = ALIGNED ? taps * a.cpt : taps * a.Cs / 4;          // 16-byte chunks / 4-byte words of the reduction
     auto decode = [&](int m, int &x, int &y, int &b) {
@@ -109,23 +121,16 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
     const int8_t *zero = reinterpret_cast<const int8_t *>(ks_fill_rows.w[0]);
     if (a.classed && tid < TN) bzs[tid] = 0;
 
-    // per pixel of the lane: address of tap (0, 0), a bit per tap that says whether it has a source
+    // per pixel of the lane: its source pixel and address of tap (0, 0)
     const int8_t *arow[TMB];
-    unsigned long long amask[TMB];
+    int ay[TMB], ax[TMB];
 #pragma unroll
     for (int i = 0; i < TMB; i++) {
         const int m = m0 + 16 * i + lrow;
         int x, y, b;
         decode(m < Mrows ? m : 0, x, y, b);              // rows past the end repeat row 0; nothing of them is stored
-        const int iy = y * a.istep + cl.dh, ix = x * a.istep + cl.dw;
-        arow[i] = a.A + ((ptrdiff_t)((ptrdiff_t)b * a.Hs + iy) * a.Ws + ix) * a.Cs;
-        unsigned long long mk = 0;
-        for (int t = 0, r = 0, c = 0; t < taps; t++) {
-            const int sy = iy + a.sgn * r, sx = ix + a.sgn * c;
-            if (sy >= 0 && sy < a.Hs && sx >= 0 && sx < a.Ws) mk |= 1ull << t;
-            if (++c == ns) { c = 0; r++; }
-        }
-        amask[i] = mk;
+        ay[i] = y * a.istep + cl.dh; ax[i] = x * a.istep + cl.dw;
+        arow[i] = a.A + ((ptrdiff_t)((ptrdiff_t)b * a.Hs + ay[i]) * a.Ws + ax[i]) * a.Cs;
     }
     const int8_t *brow[TNB];
 #pragma unroll
@@ -134,28 +139,43 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
         brow[j] = a.Bw + (size_t)(n < a.N ? n : 0) * a.wrow;
     }
 
-    // offsets of unit u (chunk or word): from a pixel's tap (0, 0), from a weight row, and its tap
-    auto locate = [&](int u, int &aoff, int &woff, int &tap) {
+    // What the epilogue reads is requested before the reduction: fetched after it, a launch's last memory round trip (1.2 K of
+    // 16 K cycles) would be its own.
+    constexpr int UPT = TMB * TNB > NW ? TMB * TNB / NW : 1;             // groups of 4 channels of one pixel per thread
+    float scale_a = a.aq->scale, scale_b = a.bq->scale;
+    hq_range range = {};
+    if (MODE != 0) range = *a.range;
+    v4i bz[UPT];
+#pragma unroll
+    for (int k = 0; k < UPT; k++) {
+        const int u = tid + k * NW * 64, n = n0 + 16 * ((u >> 6) / TMB) + 4 * ((u & 63) >> 4);
+        bz[k] = v4i{0, 0, 0, 0};
+        if (!a.classed && u < TMB * TNB * 64 && n < a.N) bz[k] = *reinterpret_cast<const v4i *>(a.bsum + n);
+    }
+
+    // unit u (chunk or word): its tap's source pixel relative to tap (0, 0), its offsets from a pixel's tap (0, 0) and from a
+    // weight row.  A tap has a source where that pixel lies in the image: two compares a load, where a mask of the taps worked
+    // out beforehand costs a launch of nine taps 1.7 K cycles for every pixel of a lane before its first load.
+    auto locate = [&](int u, int &dy, int &dx, int &aoff, int &woff) {
         const int per = ALIGNED ? a.cpt : a.Cs;
         const int k = ALIGNED ? u : 4 * u;
-        tap = (int)hq_magic_div((unsigned)k, a.magic_div);
-        const int tr = (int)hq_magic_div((unsigned)tap, cl.magic_ns), ts = tap - tr * ns;
+        const int tap = (int)hq_magic_div((unsigned)k, magic_div);
+        const int tr = (int)hq_magic_div((unsigned)tap, magic_ns), ts = tap - tr * ns;
         const int c = (k - tap * per) * (ALIGNED ? 16 : 1);
-        aoff = a.sgn * (tr * a.Ws + ts) * a.Cs + c;
-        woff = (cl.w0 + tr * a.wr + ts * a.wc) * a.Cs + c;
+        dy = a.sgn * tr; dx = a.sgn * ts;
+        aoff = (dy * a.Ws + dx) * a.Cs + c;
+        woff = (w0 + tr * a.wr + ts * a.wc) * a.Cs + c;
     };
+    auto inside = [&](int i, int dy, int dx) { return (unsigned)(ay[i] + dy) < (unsigned)a.Hs && (unsigned)(ax[i] + dx) < (unsigned)a.Ws; };
     int8_t *const stage0 = smem + wave * D * (TMB + TNB) * 1024;         // [D][TMB + TNB][1024], this wavefront's own
     auto load_lds = [&](int step, int d) {
         const int u = 4 * step + lchunk;
         const bool ok = u < units;
-        int aoff, woff, tap;
-        locate(u, aoff, woff, tap);
+        int dy, dx, aoff, woff;
+        locate(u, dy, dx, aoff, woff);
         int8_t *dst = stage0 + d * (TMB + TNB) * 1024;
 #pragma unroll
-        for (int i = 0; i < TMB; i++) {
-            const bool in = ok && ((amask[i] >> (tap & 63)) & 1ull) != 0;
-            hq_global_to_lds16(in ? arow[i] + aoff : fill, dst + 1024 * i);
-        }
+        for (int i = 0; i < TMB; i++) hq_global_to_lds16(ok && inside(i, dy, dx) ? arow[i] + aoff : fill, dst + 1024 * i);
 #pragma unroll
         for (int j = 0; j < TNB; j++) hq_global_to_lds16(ok ? brow[j] + woff : zero, dst + 1024 * (TMB + j));
     };
@@ -164,13 +184,10 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
         for (int d = 0; d < 4; d++) {
             const int u = 16 * step + 4 * lchunk + d;
             const bool ok = u < units;
-            int aoff, woff, tap;
-            locate(u, aoff, woff, tap);
+            int dy, dx, aoff, woff;
+            locate(u, dy, dx, aoff, woff);
 #pragma unroll
-            for (int i = 0; i < TMB; i++) {
-                const bool in = ok && ((amask[i] >> (tap & 63)) & 1ull) != 0;
-                af[i][d] = *reinterpret_cast<const int *>(in ? arow[i] + aoff : fill);
-            }
+            for (int i = 0; i < TMB; i++) af[i][d] = *reinterpret_cast<const int *>(ok && inside(i, dy, dx) ? arow[i] + aoff : fill);
 #pragma unroll
             for (int j = 0; j < TNB; j++) bf[j][d] = *reinterpret_cast<const int *>(ok ? brow[j] + woff : zero);
         }
@@ -184,7 +201,7 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
     int wsum[TNB] = {};
     const bool own_sums = a.classed && za != 0;
 
-    // Steps past the end read the fill rows and add nothing, so the loads need no branch.
+    // (4-byte form: steps past the end read the fill rows and add nothing, so the loads need no branch)
     const int nsteps = (units + (ALIGNED ? 3 : 15)) / (ALIGNED ? 4 : 16);
     auto multiply = [&](const v4i (&af)[TMB], const v4i (&bf)[TNB]) {
         if (own_sums)
@@ -198,36 +215,54 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
             for (int i = 0; i < TMB; i++)
                 acc[j][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bf[j], af[i], acc[j][i], 0, 0, 0);
     };
-    if (wave < nsteps) {
-        if constexpr (ALIGNED) {
+    float acc_scale;
+    HqEpilogue ep = {1.0f, 0.0f, 0.0f, 0.0f, true};
+    auto requant_constants = [&]() {                     // (the empty statements keep their divisions behind the first loads,
+        auto behind = [](auto x) {                       // and before the reduction)
+            int v = __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x));
+            asm volatile("" : "+s"(v));
+            return __builtin_bit_cast(decltype(x), v);
+        };
+        acc_scale = __fmul_rn(behind(scale_a), behind(scale_b));
+        if (MODE != 0) {
+            range.qp.scale = behind(range.qp.scale); range.qp.zero_point = behind(range.qp.zero_point);
+            range.qlo = behind(range.qlo); range.qhi = behind(range.qhi);
+            ep = hq_make_epilogue(acc_scale, &range);
+            asm volatile("" : "+v"(ep.mult), "+v"(ep.flo), "+v"(ep.fhi), "+v"(ep.zoff), "+v"(ep.c_lo), "+v"(ep.c_hi));
+        }
+    };
+    if constexpr (ALIGNED) {
 #pragma unroll
-            for (int d = 0; d < D; d++) load_lds(wave + NW * d, d);
-            int d = 0;
-            for (int s = wave; s < nsteps; s += NW) {
-                // this wavefront's own loads only: no barrier
-                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 1) * (TMB + TNB)) : "memory");
-                const int8_t *src = stage0 + d * (TMB + TNB) * 1024 + frag;
-                v4i af[TMB], bf[TNB];
+        for (int d = 0; d < D; d++)
+            if (wave + NW * d < nsteps) load_lds(wave + NW * d, d);
+        requant_constants();
+        int d = 0;
+        for (int s = wave; s < nsteps; s += NW) {
+            // this wavefront's own loads only: no barrier.  D - 1 later steps are in flight; at the end fewer, and all are
+            // waited for.
+            if (s + NW * (D - 1) < nsteps) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((D - 1) * (TMB + TNB)) : "memory");
+            else                           asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const int8_t *src = stage0 + d * (TMB + TNB) * 1024 + frag;
+            v4i af[TMB], bf[TNB];
 #pragma unroll
-                for (int i = 0; i < TMB; i++) af[i] = *reinterpret_cast<const v4i *>(src + 1024 * i);
+            for (int i = 0; i < TMB; i++) af[i] = *reinterpret_cast<const v4i *>(src + 1024 * i);
 #pragma unroll
-                for (int j = 0; j < TNB; j++) bf[j] = *reinterpret_cast<const v4i *>(src + 1024 * (TMB + j));
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the stage has been read: it can be filled again
-                load_lds(s + NW * D, d);
-                multiply(af, bf);
-                d = d + 1 == D ? 0 : d + 1;
-            }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        } else {
-            v4i af[D][TMB], bf[D][TNB];
+            for (int j = 0; j < TNB; j++) bf[j] = *reinterpret_cast<const v4i *>(src + 1024 * (TMB + j));
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // the stage has been read: it can be filled again
+            if (s + NW * D < nsteps) load_lds(s + NW * D, d);
+            multiply(af, bf);
+            d = d + 1 == D ? 0 : d + 1;
+        }
+    } else {
+        v4i af[D][TMB], bf[D][TNB];
 #pragma unroll
-            for (int d = 0; d < D; d++) load_regs(wave + NW * d, af[d], bf[d]);
-            for (int s = wave; s < nsteps; s += NW * D) {
+        for (int d = 0; d < D; d++) load_regs(wave + NW * d, af[d], bf[d]);
+        requant_constants();
+        for (int s = wave; s < nsteps; s += NW * D) {
 #pragma unroll
-                for (int d = 0; d < D; d++) {
-                    multiply(af[d], bf[d]);
-                    load_regs(s + NW * (d + D), af[d], bf[d]);
-                }
+            for (int d = 0; d < D; d++) {
+                multiply(af[d], bf[d]);
+                load_regs(s + NW * (d + D), af[d], bf[d]);
             }
         }
     }
@@ -242,14 +277,17 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
     __syncthreads();
 
     // ---- epilogue: a thread = 4 consecutive channels of one pixel
-    const float acc_scale = __fmul_rn(a.aq->scale, a.bq->scale);
-    HqEpilogue ep = {1.0f, 0.0f, 0.0f, 0.0f, true};
-    if (MODE != 0) ep = hq_make_epilogue(acc_scale, a.range);
+    // (waited for here: left to the epilogue, threads without a group would wait for the others' stores with them)
+#pragma unroll
+    for (int k = 0; k < UPT; k++) asm volatile("" : "+v"(bz[k]));
     int mn = INT_MAX, mx = INT_MIN;
     unsigned nlo = 0, nhi = 0;
     auto epilogue = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
-        for (int u = tid; u < TMB * TNB * 64; u += NW * 64) {
+#pragma unroll
+        for (int k = 0; k < UPT; k++) {
+            const int u = tid + k * NW * 64;
+            if (u >= TMB * TNB * 64) break;
             const int l = u & 63, i = (u >> 6) % TMB, j = (u >> 6) / TMB;
             int m = m0 + 16 * i + (l & 15);
             const int nc = 16 * j + 4 * (l >> 4), n = n0 + nc;
@@ -263,7 +301,7 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
                 decode(m, x, y, b);
                 m = (b * a.Ho + cl.ph + a.ostep * y) * a.Wo + cl.pw + a.ostep * x;
             } else {
-                c -= za * *reinterpret_cast<const v4i *>(a.bsum + n);
+                c -= za * bz[k];
             }
             const int cc[4] = {c[0], c[1], c[2], c[3]};
             const size_t o = (size_t)m * a.N + n;
@@ -283,7 +321,7 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
     if (blockIdx.x == 0 && tid == 0) {
         a.st->acc_scale = acc_scale;
         atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)a.M * (unsigned long long)a.N);
-        if (MODE != 0) *a.outq = a.range->qp;
+        if (MODE != 0) *a.outq = range.qp;
     }
 }
 
@@ -292,7 +330,7 @@ int launch3(KsArgs &a, hipStream_t s)
 {
     int t = 0;
     for (int c = 0; c < a.ncls; c++) {
-        a.cls[c].tile0 = t;
+        a.tile0[c] = t;
         t += (a.B * a.cls[c].Hc * a.cls[c].Wc + 16 * TMB - 1) / (16 * TMB);
     }
     a.m_tiles = t;
