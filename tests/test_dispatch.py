@@ -82,6 +82,22 @@ def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
            ("dgrad_sr", (LINEAR, 900, 1, 1, 4000, 1, 1, 1, 0, 360), short), ("dgrad_sr", (LINEAR, 900, 1, 1, 4000, 1, 1, 1, 0, 436), long_)])
 
 
+def test_whole_lines_per_stage_between_split_reductions_and_row_tiles():
+    ring, ks, bandw, tile = "hq_ring_kernel", "hq_ksplit_kernel", "hq_bandw_kernel", "hq_gemm_kernel"
+    check([("fwd", conv(26, 14, 256, 3, 1, 256), ring), ("dgrad", conv(26, 14, 256, 3, 1, 256), ring), ("dgrad_sr", conv(26, 14, 256, 3, 1, 256), ring),
+           ("dynamic_fwd", conv(26, 14, 256, 3, 1, 256), ring), ("fwd", conv(128, 4, 512, 3, 1, 512), ks),
+           ("fwd", conv(256, 16, 128, 3, 1, 128), ring), ("fwd", conv(257, 16, 128, 3, 1, 128), bandw),         # 512 and 514 tiles
+           ("dgrad", conv(257, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(257, 16, 128, 3, 1, 128), ring),
+           ("fwd", conv(257, 16, 128, 5, 1, 128), ring), ("fwd", conv(257, 32, 128, 3, 2, 128), ring),           # not the row tiles' layers
+           ("dgrad", conv(257, 32, 256, 3, 2, 256), tile),                                                      # strided
+           ("fwd", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), ring), ("fwd", (LINEAR, 8192, 1, 1, 896, 1, 1, 1, 0, 1024), tile),
+           ("dgrad", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), tile),
+           ("fwd", conv(26, 14, 192, 3, 1, 256), bandw), ("fwd", conv(34, 13, 128, 3, 1, 144), ring), ("fwd", conv(128, 14, 256, 3, 1, 120), tile),
+           ("fwd", conv(20, 30, 128, 3, 1, 144), ring), ("fwd", (LINEAR, 4200, 1, 1, 1024, 1, 1, 1, 0, 272), ring),
+           ("fwd", (LINEAR, 1300, 1, 1, 1024, 1, 1, 1, 0, 1168), ring), ("fwd", conv(40, 29, 128, 3, 2, 272), ring),
+           ("dgrad", conv(40, 16, 128, 3, 1, 128, 2), ring), ("fwd", (CONV, 20, 17, 19, 128, 5, 3, 1, 1, 160), ring)])
+
+
 def test_small_depthwise_launches_are_cut_into_short_strips():
     """Workgroups of the launch: a strip is a serial chain, so few threads get as many strips as there are rows."""
     def blocks(op, *layer):

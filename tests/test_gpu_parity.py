@@ -384,6 +384,27 @@ def test_weights_in_registers(H, hq, L, g_asym):
         g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
+# Whole 128-byte lines per stage: pixels and channels off the 128 x 128 tile, mirrored taps under every padding, strides, filters that
+# are not square, the shortest reduction, bands of eight pixel tiles with a short last one.
+RING_SHAPES = [wl.conv("ring_n144", 34, 13, 128, 144, 3), wl.conv("ring_both_ways", 26, 14, 256, 256, 3), wl.conv("ring_s2", 40, 29, 128, 272, 3, stride=2),
+               wl.LayerShape("ring_5x3", wl.CONV, 20, 17, 19, 128, 5, 3, 1, 1, 160), wl.conv("ring_pad2", 40, 16, 128, 128, 3, pad=2),
+               wl.conv("ring_pad0", 40, 18, 128, 128, 3, pad=0), wl.linear("ring_8_stages", 4200, 1024, 272), wl.linear("ring_bands", 1300, 1024, 1168)]
+
+
+@pytest.mark.parametrize("L", RING_SHAPES, ids=[l.name for l in RING_SHAPES])
+def test_whole_lines_per_stage(H, hq, L):
+    y_track, g_track = H.TensorTrack(0.9, False), H.TensorTrack(0.9, True)
+    Wdev = None
+    for t in range(3):                                       # dynamic, nearest, stochastic
+        X, W, dY = rand_layer_inputs(L, 120 + t, g_asym=True)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        if t < 2:
+            y_track.step(L, "fwd", X, W0, H.DevTensor(X), Wdev)
+        if L.Cout % 128 == 0 and L.kind == wl.CONV:
+            g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
+
+
 # Weight gradients in one launch: tiles of every size, channel counts off 16 and 32, pixels off 32, and past each line.
 WGRAD_LINES = [wl.linear("ws_1px", 1, 16, 4), wl.linear("ws_4w", 100, 52, 68), wl.linear("ws_32_2145", 70, 2064, 1040), wl.conv("ws_8w", 3, 25, 48, 36, 3),
                wl.linear("ws_32x64", 1030, 304, 848), wl.conv("ws_16w_s2", 9, 50, 32, 80, 3, stride=2), wl.LayerShape("ws_5x3", wl.CONV, 2, 19, 14, 20, 5, 3, 3, 2, 48),
