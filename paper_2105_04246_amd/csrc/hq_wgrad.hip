@@ -17,6 +17,8 @@
 #include "hq_device.h"
 #include "hq_internal.h"
 
+#include <algorithm>
+
 namespace {
 
 constexpr int MB = 64;             // pixels staged per step (two MFMA k-steps of 32)
@@ -315,7 +317,7 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
 // wavefront owns one 32-channel block of C and taps 0..4 or 5..8 for both 32-blocks of Cout:
 // 7 fragments feed 10 MFMAs.
 // ---------------------------------------------------------------------------------------
-// Weight gradient of a network's first layer (3 or 4 input channels, even stride, W a multiple of 4, at most
+// Weight gradient of a network's first layer (3 or 4 input channels, W a multiple of 4, at most 8 filter rows and
 // 8 taps per filter row, at most 64 output channels in multiples of 16) with the input rows staged in LDS.
 // A workgroup walks bands of whole output rows.  The input rows of a band are copied into LDS once, every
 // pixel widened to 4 bytes, inside a frame of zero-point pixels; filter row r of output pixel (oy, ox) is then
@@ -323,12 +325,20 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
 // with a pitch of 4 * stride bytes, which the transposing LDS read takes as they lie (column 4 s + c of
 // filter row r; the columns of the fourth byte and of taps past S are dropped at the end).  The gradient rows
 // of the band are copied beside them.  Wavefront (wn, wk) owns output channels 32 wn .. 32 wn + 31 and filter
-// rows 4 wk .. 4 wk + 3; sums stay in registers over all bands of the workgroup and leave with one atomic
-// add per value.
+// rows 4 wk .. 4 wk + 3 (at most 4 filter rows: all of them, for every second k-step); sums stay in registers over all bands
+// of the workgroup.
+// The transposing read wants 8-byte addresses.  Under an odd stride the odd pixels of a row lie 4 bytes off, and read a second
+// copy of the rows that is shifted by as much.
+// Measured, whole call with its clearing and finalizing launches (9 us), before -> now: 3x3 stride 1, 128 x 64 x 64 x 3 -> 64 (then one
+// tile column per 32 packed columns, loads of unaligned runs) 73.5 -> 36.4 us, 64 x 32 x 32 x 3 -> 32 40.5 -> 14.3, 5x5 on
+// 64 x 96 x 96 x 4 -> 48 63 -> 36; 3x3 stride 2, 128 x 112 x 112 x 3 -> 32 38.7 -> 27.1; 7x7 stride 2, 256 x 224 x 224 x 3 -> 64 135 -> 125.
+// What bounds it now: small ones the 512 workgroups' atomics on the same lines (256 workgroups: 34 us for the first, but 199 for the
+// last), the 7x7 one its 76 vector instructions per k-step and wavefront (44 % of the time) and the wait for a band's loads.
 struct WstemArgs {
     WgradArgs w;
     int rows_out, in_rows, LP;     // output rows per band, input rows it needs, LDS pitch of an input row
-    int xrows;                     // input rows a buffer has room for: (rows_out - 1) * stride + 8
+    int xrows;                     // input rows a buffer has room for: (rows_out - 1) * stride + 8 (4 with at most 4 filter rows)
+    int second;                    // odd strides: offset of the second copy of the input rows, 4 bytes further right; else 0
     int bands_per_image, nbands;
     int groups;                    // 16-byte groups of four pixels per input row: W / 4
     unsigned magic_groups, magic_OW;
@@ -347,9 +357,11 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wn = wave >> 1, wk = wave & 1;
     const int zx = a.xq->zero_point;
     const int fill = (int)((unsigned)(zx & 0xff) * 0x01010101u);   // unsigned: the product may set bit 31
-    const int xbytes = sa.xrows * sa.LP, gbytes = sa.kpad * sa.gpitch, buf_bytes = xbytes + gbytes;
+    const bool halves = a.R <= 4;                                   // the filter rows fit one wavefront: two share the k-steps
+    const int row0 = halves ? 0 : wk * 4;
+    const int xbytes = sa.xrows * sa.LP * (sa.second ? 2 : 1), gbytes = sa.kpad * sa.gpitch, buf_bytes = xbytes + gbytes;
     int8_t *zero_row = ws_lds + 2 * (size_t)buf_bytes;              // 64 bytes of 0: the source of pixels past a band
-    const bool do_gsum = wk == 0 && zx != 0;                        // column sums of G (times z_x later)
+    const bool do_gsum = (wk == 0 || halves) && zx != 0;            // column sums of G (times z_x later)
     const bool do_xsum = wn == 0 && a.gq->zero_point != 0;          // column sums of the gathered input
 
     // the frame: the input part of both buffers starts as zero-point pixels; staging only writes the W image
@@ -397,22 +409,22 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
             const bool ok = x_row[k] >= 0 && iy >= 0 && iy < a.H;
             const int8_t *src = ok ? xrow0 + x_src[k] : a.X;
 #pragma unroll
-            for (int c = 0; c < CH; c++) {
-                const int x = reinterpret_cast<const int *>(src)[c];
-                stx[k][c] = ok ? x : fill;
-            }
+            for (int c = 0; c < CH; c++) stx[k][c] = reinterpret_cast<const int *>(src)[c];
         }
         const int npix = nrows * a.OW;
         const int8_t *g0 = a.G + ((size_t)b * a.OH + oy0) * a.OW * a.N;
 #pragma unroll
         for (int k = 0; k < WS_GT; k++) {
             const bool ok = g_px[k] < npix;
-            const v4i x = *reinterpret_cast<const v4i *>(ok ? g0 + g_src[k] : a.G);
-            stg[k] = ok ? x : v4i{0, 0, 0, 0};
+            stg[k] = *reinterpret_cast<const v4i *>(ok ? g0 + g_src[k] : a.G);
         }
     };
-    auto stage_store = [&](int buf) {
+    // (what lies outside the image or past the band is replaced here: next to the loads it would wait for them)
+    auto stage_store = [&](int buf, int band) {
         int8_t *xb = ws_lds + (size_t)buf * buf_bytes, *gb = xb + xbytes;
+        int b, oy0, nrows;
+        band_rows(band, b, oy0, nrows);
+        const int iy0 = oy0 * a.stride - a.pad, npix = nrows * a.OW;
 #pragma unroll
         for (int k = 0; k < WS_XT; k++) {
             if (x_row[k] < 0) continue;
@@ -426,11 +438,14 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
                 v[2] = (int)__builtin_amdgcn_alignbyte(w2, w1, 2);
                 v[3] = (int)(w2 >> 8);
             }
+            const int iy = iy0 + x_row[k];
+            if (iy < 0 || iy >= a.H) v = v4i{fill, fill, fill, fill};
             *reinterpret_cast<v4i *>(xb + x_dst[k]) = v;
+            if (sa.second) *reinterpret_cast<v4i *>(xb + x_dst[k] + sa.second) = v;
         }
 #pragma unroll
         for (int k = 0; k < WS_GT; k++)
-            if (g_dst[k] >= 0) *reinterpret_cast<v4i *>(gb + g_dst[k]) = stg[k];
+            if (g_dst[k] >= 0) *reinterpret_cast<v4i *>(gb + g_dst[k]) = g_px[k] < npix ? stg[k] : v4i{0, 0, 0, 0};
     };
 
     v16i acc[4];
@@ -445,7 +460,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
     __syncthreads();
     if (band_begin < band_end) {
         stage_load(band_begin);
-        stage_store(0);
+        stage_store(0, band_begin);
     }
     __syncthreads();
     // transposing read: lane l hands in the address of 8 bytes (columns 16 * grp + 8 * (j & 1) ..) of pixel row
@@ -476,7 +491,9 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
                 const bool ok = px < npix;
                 const unsigned q = ok ? (unsigned)px : 0u;
                 const unsigned orow = hq_magic_div(q, sa.magic_OW), ox = q - orow * (unsigned)a.OW;
-                pa[h] = ok ? xoff + (orow * (unsigned)a.stride + (unsigned)(wk * 4)) * (unsigned)sa.LP + 4u * (unsigned)a.stride * ox + (unsigned)tcol
+                // (a transposing read wants 8-byte addresses: under an odd stride the odd pixels have theirs in the second copy)
+                pa[h] = ok ? xoff + (orow * (unsigned)a.stride + (unsigned)row0) * (unsigned)sa.LP + 4u * (unsigned)a.stride * ox +
+                                 (ox & 1u) * (unsigned)sa.second + (unsigned)tcol
                            : zero_off;
                 pstep[h] = ok ? (unsigned)sa.LP : 0u;
             }
@@ -503,32 +520,39 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
         };
         // two fragment sets: the next k-step's reads are on their way while this one is multiplied
         v4i gfA, gfB, xfA[4], xfB[4];
-        if (nks > 0) load_frags(0, gfA, xfA);
-        for (int ks = 0; ks < nks; ks += 2) {
-            if (ks + 1 < nks) load_frags(ks + 1, gfB, xfB);
+        const int first = halves ? wk : 0, step = halves ? 2 : 1;
+        if (first < nks) load_frags(first, gfA, xfA);
+        for (int ks = first; ks < nks; ks += 2 * step) {
+            if (ks + step < nks) load_frags(ks + step, gfB, xfB);
             multiply(gfA, xfA);
-            if (ks + 1 >= nks) break;
-            if (ks + 2 < nks) load_frags(ks + 2, gfA, xfA);
+            if (ks + step >= nks) break;
+            if (ks + 2 * step < nks) load_frags(ks + 2 * step, gfA, xfA);
             multiply(gfB, xfB);
         }
-        if (band + 1 < band_end) stage_store(buf ^ 1);
+        if (band + 1 < band_end) stage_store(buf ^ 1, band + 1);
         __syncthreads();
     }
 
     // ---- flush.  G fragments were the first MFMA operand: lane l holds column l % 32 of the filter row and
-    // output channels 8 * (e / 4) + 4 * (l / 32) + e % 4 of the wavefront's block
-    const size_t krow = (size_t)a.R * a.S * CH;
+    // output channels 8 * (e / 4) + 4 * (l / 32) + e % 4 of the wavefront's block.  All workgroups add to the same few lines, where
+    // every request of a line queues (about 13 clocks), however few of its words it adds to: straight from the fragments, 9 or 21
+    // words of a line at a time, that queue took most of a small launch.  The wavefronts' sums are put together in LDS (free
+    // after the last band's barrier) and go out as whole lines, each workgroup starting elsewhere.
+    const int krow = a.R * a.S * CH, words = a.N * krow;
+    int *sum = reinterpret_cast<int *>(ws_lds);
+    for (int q = tid; q < words; q += HQ_THREADS) sum[q] = 0;
+    __syncthreads();
     const int col = lane & 31, tap = col >> 2, ch = col & 3;
     const bool col_ok = tap < a.S && ch < CH;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-        const int r = wk * 4 + j;
+        const int r = row0 + j;
         if (r >= a.R || !col_ok) continue;
-        const size_t wc = ((size_t)r * a.S + tap) * CH + ch;
+        const int wc = (r * a.S + tap) * CH + ch;
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             const int n = wn * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-            if (n < a.N && acc[j][e] != 0) atomicAdd(a.acc + (size_t)n * krow + wc, acc[j][e]);
+            if (n < a.N) atomicAdd(sum + n * krow + wc, acc[j][e]);
         }
         if (do_xsum) {
             const int s = xs[j] + __shfl_xor(xs[j], 32);
@@ -539,6 +563,15 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
         const int s = gs + __shfl_xor(gs, 32);
         const int n = wn * 32 + (lane & 31);
         if (lane < 32 && n < a.N && s != 0) atomicAdd(a.gsum + n, s);
+    }
+    __syncthreads();
+    const int chunks = (words + HQ_THREADS - 1) / HQ_THREADS;
+    int q = (int)(blockIdx.x % (unsigned)chunks) * HQ_THREADS + tid;
+    for (int k = 0; k < chunks; k++) {
+        const int v = q < words ? sum[q] : 0;
+        if (v != 0) atomicAdd(a.acc + q, v);
+        q += HQ_THREADS;
+        if (q >= chunks * HQ_THREADS) q -= chunks * HQ_THREADS;
     }
 }
 
@@ -1024,13 +1057,14 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
         return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
     }
 
-    // first layers on even strides: input rows staged in LDS (hq_wgrad_stem_kernel)
-    if ((a.C == 3 || a.C == 4) && p->stride % 2 == 0 && p->W % 4 == 0 && p->S <= 8 && p->R <= 8 && a.N <= 64 &&
+    // first layers: input rows staged in LDS (hq_wgrad_stem_kernel)
+    if ((a.C == 3 || a.C == 4) && p->W % 4 == 0 && p->S <= 8 && p->R <= 8 && a.N <= 64 &&
         a.N % 16 == 0 && (reinterpret_cast<uintptr_t>(X) & 3) == 0 && (reinterpret_cast<uintptr_t>(dY) & 15) == 0) {
         WstemArgs sa;
         sa.w = a;
         sa.w.direct = 0;
-        const int lp_reads = 4 * (OW - 1) * p->stride + 32, lp_image = 4 * (p->W + p->pad);
+        const int copies = p->stride % 2 ? 2 : 1, frows = p->R <= 4 ? 4 : 8;
+        const int lp_reads = 4 * (OW - 1) * p->stride + 32 + 4 * (copies - 1), lp_image = 4 * (p->W + p->pad) + 4 * (copies - 1);
         sa.LP = ((lp_reads > lp_image ? lp_reads : lp_image) + 15) & ~15;
         sa.groups = p->W / 4;
         sa.magic_groups = hq_magic32((unsigned)sa.groups);
@@ -1041,7 +1075,7 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
         int rows = 0;
         for (int r = 1; r <= OH; r++) {
             const int in_rows = (r - 1) * p->stride + p->R, kpad = (r * OW + 31) / 32 * 32;
-            if ((size_t)((r - 1) * p->stride + 8) * sa.LP + (size_t)kpad * sa.gpitch > 39 * 1024 || in_rows * sa.groups > WS_XT * HQ_THREADS ||
+            if ((size_t)copies * ((r - 1) * p->stride + frows) * sa.LP + (size_t)kpad * sa.gpitch > 39 * 1024 || in_rows * sa.groups > WS_XT * HQ_THREADS ||
                 kpad * sa.gchunks > WS_GT * HQ_THREADS)
                 break;
             rows = r;
@@ -1049,11 +1083,12 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
         if (rows >= 1 && (unsigned long long)p->B * OH * OW < (1ull << 31)) {
             sa.rows_out = rows;
             sa.in_rows = (rows - 1) * p->stride + p->R;
-            sa.xrows = (rows - 1) * p->stride + 8;
+            sa.xrows = (rows - 1) * p->stride + frows;
+            sa.second = copies == 2 ? sa.xrows * sa.LP + 4 : 0;
             sa.kpad = (rows * OW + 31) / 32 * 32;
             sa.bands_per_image = (OH + rows - 1) / rows;
             sa.nbands = p->B * sa.bands_per_image;
-            const size_t lds = 2 * ((size_t)sa.xrows * sa.LP + (size_t)sa.kpad * sa.gpitch) + 64;
+            const size_t lds = std::max(2 * ((size_t)copies * sa.xrows * sa.LP + (size_t)sa.kpad * sa.gpitch) + 64, 4 * (size_t)a.N * K);
             static std::atomic<unsigned long long> allowed[2];
             if (!hq_allow_lds(hq_wgrad_stem_kernel<3>, 80 * 1024, allowed[0]) || !hq_allow_lds(hq_wgrad_stem_kernel<4>, 80 * 1024, allowed[1]))
                 return HQ_E_HIP;

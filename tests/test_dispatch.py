@@ -119,6 +119,15 @@ def test_one_launch_weight_gradients_end_where_split_k_is_faster():
            ("wgrad", conv(41, 14, 64, 3, 1, 64), one), ("wgrad", conv(42, 14, 64, 3, 1, 64), band)])
 
 
+def test_first_layer_weight_gradients_stage_their_rows_under_every_stride():
+    def kernels(*layer):
+        return [l.kernel for l in launches.calls([("wgrad", layer)])[0]]
+    for layer, want in (((CONV, 40, 33, 64, 3, 3, 3, 1, 1, 64), "hq_wgrad_stem_kernel<3>"), ((CONV, 9, 61, 64, 3, 7, 7, 3, 3, 64), "hq_wgrad_stem_kernel<3>"),
+                        ((CONV, 4, 60, 60, 4, 4, 8, 1, 0, 64), "hq_wgrad_stem_kernel<4>"), ((CONV, 40, 33, 64, 3, 9, 3, 1, 1, 64), "hq_wgrad_kernel"),
+                        ((CONV, 40, 33, 66, 3, 3, 3, 1, 1, 64), "hq_wgrad_kernel"), ((CONV, 40, 33, 64, 3, 3, 3, 1, 1, 80), "hq_wgrad_kernel")):
+        assert any(k.startswith(want) for k in kernels(*layer)), (layer, kernels(*layer))
+
+
 def test_column_sums_over_many_lines_are_shared():
     """hq_weight_prepare: a workgroup walks at most 8192 lines (rows of the weight tensor per tap) alone."""
     few, many = launches.calls([("weight_prepare", conv(1, 7, 512, 3, 1, 512)), ("weight_prepare", conv(1, 7, 64, 3, 1, 4096))])

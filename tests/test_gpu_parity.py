@@ -405,6 +405,25 @@ def test_whole_lines_per_stage(H, hq, L):
             g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
+# First layers with staged input rows: odd strides read odd pixels from a second copy, at most four filter rows share the k-steps of
+# a band between two wavefronts; bands of one k-step, images of one band, last bands with fewer rows, every filter row in use.
+STEM_WGRAD = [wl.LayerShape("stem_wgrad", wl.CONV, B, Hh, Ww, C, R, S, st, pad, N)
+              for B, Hh, Ww, C, R, S, st, pad, N in ((40, 33, 64, 3, 3, 3, 1, 1, 64), (3, 120, 132, 3, 3, 3, 1, 1, 48), (2, 90, 68, 4, 5, 5, 1, 2, 32),
+                                                     (5, 70, 72, 3, 3, 3, 2, 1, 16), (9, 61, 64, 3, 7, 7, 3, 3, 64), (4, 60, 60, 4, 4, 8, 1, 0, 64),
+                                                     (3, 65, 64, 3, 8, 8, 1, 4, 64), (2, 224, 224, 3, 3, 3, 1, 1, 64))]
+
+
+@pytest.mark.parametrize("L", STEM_WGRAD, ids=["b%d_%dx%dx%d_%dx%d_s%d_n%d" % (l.B, l.H, l.W, l.C, l.R, l.S, l.stride, l.Cout) for l in STEM_WGRAD])
+def test_staged_first_layer_weight_gradients(H, hq, L):
+    g = np.random.default_rng([79, L.R, L.W])
+    X = wl.normal_image(g, wl.in_shape(L))
+    for dY in (wl.to_asymmetric_codes(g.laplace(0, 1e-3, wl.out_shape(L)).astype(np.float32) + np.float32(4e-4)), wl.laplace_gradient(g, wl.out_shape(L), 1e-3)):
+        dW, dWa = H.gpu_wgrad(L, H.DevTensor(X), H.DevTensor(dY))
+        ref = oracle.wgrad(H.oracle_problem(L), X.codes, X.zero_point, dY.codes, dY.zero_point)
+        assert np.array_equal(dWa, ref)
+        assert np.array_equal(dW, oracle.wgrad_scale(ref, X.scale, dY.scale))
+
+
 # Weight gradients in one launch: tiles of every size, channel counts off 16 and 32, pixels off 32, and past each line.
 WGRAD_LINES = [wl.linear("ws_1px", 1, 16, 4), wl.linear("ws_4w", 100, 52, 68), wl.linear("ws_32_2145", 70, 2064, 1040), wl.conv("ws_8w", 3, 25, 48, 36, 3),
                wl.linear("ws_32x64", 1030, 304, 848), wl.conv("ws_16w_s2", 9, 50, 32, 80, 3, stride=2), wl.LayerShape("ws_5x3", wl.CONV, 2, 19, 14, 20, 5, 3, 3, 2, 48),
