@@ -60,7 +60,11 @@ __device__ inline v4i load16(const int8_t *p, int nbytes, bool aligned16)
 // past S * 3 stay zero), so a thread's 16-byte chunk is 16 consecutive bytes of memory at any byte
 // address: aligned loads plus a byte-wise funnel shift, then byte masks that replace the taps outside the
 // image with the zero-point code.
-template <int TN, int TK, bool PACKED, bool PACKED3 = false>
+// ALIGNED: rows of both operands are whole 16-byte chunks (and the pixel decode fits hq_magic_div): loads without a branch, lanes without
+// a source read the tensor's first bytes, and what they hold is replaced when it is stored to LDS.  With a branch per load
+// and per alignment a stage of 8 MFMAs was some 400 instructions: 3x3 stride 2, 256 x 28 x 28 x 128 -> 256 58.0 us, now 53.5; 1x1,
+// 128 x 56 x 56 x 32 -> 192 30.2, now 28.8; linear 8192 x 1024 -> 1024 47.4, now 43.6.
+template <int TN, int TK, bool PACKED, bool PACKED3 = false, bool ALIGNED = false>
 __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
 {
     static_assert(!PACKED3 || PACKED, "the 3-channel form is a packed form");
@@ -131,7 +135,31 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
         }
     }
     v4i greg[GLD], xreg[XLD];
+    unsigned gok = 0, xin = 0, xrow = 0;                        // ALIGNED, a bit per load: gradient, input pixel, pixel at all
     auto load_stage = [&](int mb) {
+        if constexpr (ALIGNED) {
+            const int n = n0 + (tid % GCH) * 16, c = c0 + (tid % XCH) * 16;          // (HQ_THREADS is a multiple of both)
+            gok = xin = xrow = 0;
+#pragma unroll
+            for (int i = 0; i < GLD; i++) {
+                const int m = mb + (tid + i * HQ_THREADS) / GCH;
+                const bool ok = m < m_end && n < a.N;
+                greg[i] = *reinterpret_cast<const v4i *>(ok ? a.G + (size_t)m * a.N + n : a.G);
+                gok |= ok ? 1u << i : 0u;
+            }
+#pragma unroll
+            for (int i = 0; i < XLD; i++) {
+                const int m = mb + (tid + i * HQ_THREADS) / XCH;
+                const unsigned t = hq_magic_div((unsigned)m, a.magic_OW), b = hq_magic_div(t, a.magic_OH);
+                const int iy = (int)(t - b * (unsigned)a.OH) * a.stride - a.pad + tr;
+                const int ix = (int)((unsigned)m - t * (unsigned)a.OW) * a.stride - a.pad + ts;
+                const bool row = m < m_end && c < a.C, in = row && (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+                xreg[i] = *reinterpret_cast<const v4i *>(in ? a.X + (((size_t)b * a.H + iy) * a.W + ix) * a.C + c : a.X);
+                xin |= in ? 1u << i : 0u;
+                xrow |= row ? 1u << i : 0u;
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < GLD; i++) {
             const int idx = tid + i * HQ_THREADS, row = idx / GCH, col = (idx % GCH) * 16;
@@ -200,12 +228,13 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
 #pragma unroll
         for (int i = 0; i < GLD; i++) {
             const int idx = tid + i * HQ_THREADS, row = idx / GCH, col = (idx % GCH) * 16;
-            *reinterpret_cast<v4i *>(&Gs[buf][row * PG + col]) = greg[i];
+            *reinterpret_cast<v4i *>(&Gs[buf][row * PG + col]) = !ALIGNED || (gok >> i & 1) ? greg[i] : v4i{0, 0, 0, 0};
         }
 #pragma unroll
         for (int i = 0; i < XLD; i++) {
             const int idx = tid + i * HQ_THREADS, row = idx / XCH, col = (idx % XCH) * 16;
-            *reinterpret_cast<v4i *>(&Xs[buf][row * PX + col]) = xreg[i];
+            const int z = xrow >> i & 1 ? fill : 0;             // a tap outside the image: real zero; past the end: nothing
+            *reinterpret_cast<v4i *>(&Xs[buf][row * PX + col]) = !ALIGNED || (xin >> i & 1) ? xreg[i] : v4i{z, z, z, z};
         }
     };
 
@@ -1142,6 +1171,10 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
     dim3 grid((unsigned)(xt * yt * splits));
     if (a.C == 3) hipLaunchKernelGGL((hq_wgrad_kernel<64, 256, true, true>), grid, dim3(HQ_THREADS), 0, stream, a);
     else if (packed) hipLaunchKernelGGL((hq_wgrad_kernel<64, 256, true>), grid, dim3(HQ_THREADS), 0, stream, a);
+    else if (a.g16 && a.x16 && a.magic_ok) {
+        if (big) hipLaunchKernelGGL((hq_wgrad_kernel<128, 128, false, false, true>), grid, dim3(HQ_THREADS), 0, stream, a);
+        else     hipLaunchKernelGGL((hq_wgrad_kernel<64, 64, false, false, true>), grid, dim3(HQ_THREADS), 0, stream, a);
+    }
     else if (big) hipLaunchKernelGGL((hq_wgrad_kernel<128, 128, false>), grid, dim3(HQ_THREADS), 0, stream, a);
     else          hipLaunchKernelGGL((hq_wgrad_kernel<64, 64, false>), grid, dim3(HQ_THREADS), 0, stream, a);
 

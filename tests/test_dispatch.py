@@ -119,6 +119,14 @@ def test_one_launch_weight_gradients_end_where_split_k_is_faster():
            ("wgrad", conv(41, 14, 64, 3, 1, 64), one), ("wgrad", conv(42, 14, 64, 3, 1, 64), band)])
 
 
+def test_tile_weight_gradients_load_without_branches_where_rows_are_whole_chunks():
+    def kernel(*layer):
+        return [l.kernel for l in launches.calls([("wgrad", layer)])[0] if l.kernel.startswith("hq_wgrad_kernel")][0]
+    for layer, want in ((conv(46, 28, 80, 3, 2, 144), "<128, 128, false, false, true>"), (conv(13, 29, 48, 5, 1, 80), "<64, 64, false, false, true>"),
+                        (conv(47, 14, 208, 1, 1, 96), "<128, 128, false, false, true>"), (conv(46, 28, 84, 3, 2, 144), "<128, 128, false, false, false>")):
+        assert kernel(*layer).startswith("hq_wgrad_kernel" + want), (layer, kernel(*layer))
+
+
 def test_first_layer_weight_gradients_stage_their_rows_under_every_stride():
     def kernels(*layer):
         return [l.kernel for l in launches.calls([("wgrad", layer)])[0]]

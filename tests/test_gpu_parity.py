@@ -405,6 +405,18 @@ def test_whole_lines_per_stage(H, hq, L):
             g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
+# Weight gradients by tiles: rows of whole 16-byte chunks (loads without a branch) and off them, tiles of 64 and 128 with columns and
+# rows left over, taps outside the image on every side, the last run of pixels short.
+TILE_WGRAD = [wl.conv("tw_128_s2", 46, 28, 80, 144, 3, stride=2), wl.conv("tw_64_5x5", 13, 29, 48, 80, 5), wl.conv("tw_128_1x1", 47, 14, 208, 96, 1, pad=0),
+              wl.conv("tw_off16", 46, 28, 84, 144, 3, stride=2), wl.LayerShape("tw_3x2_s3", wl.CONV, 60, 37, 35, 32, 3, 2, 3, 1, 112)]
+
+
+@pytest.mark.parametrize("L", TILE_WGRAD, ids=[l.name for l in TILE_WGRAD])
+@pytest.mark.parametrize("g_asym", [False, True])
+def test_tile_weight_gradients(H, hq, L, g_asym):
+    test_weight_gradient_lines(H, hq, L, g_asym)
+
+
 # First layers with staged input rows: odd strides read odd pixels from a second copy, at most four filter rows share the k-steps of
 # a band between two wavefronts; bands of one k-step, images of one band, last bands with fewer rows, every filter row in use.
 STEM_WGRAD = [wl.LayerShape("stem_wgrad", wl.CONV, B, Hh, Ww, C, R, S, st, pad, N)
