@@ -137,7 +137,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_bandw_kernel(const BandwArgs
             wsrc[k] = a.Bw + (size_t)(wrow_ok[k] ? n : 0) * wrow + ck * 16;
         }
         // The weights go through registers (two steps = four 16-byte loads per thread, requested at the start of a
-        // stage, written to LDS at its end): the direct-to-LDS path moves about 20 bytes per clock and compute
+        // stage, written to LDS at its end): in a loop with a barrier per step direct-to-LDS loads bring about 20 bytes per clock and compute
         // unit, register loads 30 to 35, and a stage of two workgroups needs 32 KB of weights per 2048 clocks.
         v4i wreg[2][2];
         auto load_weights = [&](int stage) {
