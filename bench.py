@@ -167,17 +167,22 @@ def kernel_family(wl, L, op):
     if op == "wgrad":
         if k3 and L.C % 64 == 0 and L.Cout % 64 == 0:
             return "hq_wgrad_band_kernel + wband_finalize_kernel"
-        if staged and L.R <= 8 and L.Cout <= 64 and L.Cout % 16 == 0:
+        if first and L.W % 4 == 0 and L.S <= 8 and L.R <= 8 and L.Cout <= 64 and L.Cout % 16 == 0:
             return "hq_wgrad_stem_kernel + wgrad_finalize_kernel"
         return "hq_wgrad_kernel + wgrad_finalize_kernel"
     cin = L.Cout if op == "dgrad" else L.C
     cout = L.C if op == "dgrad" else L.Cout
     if op == "fwd" and first:
         return "hq_stem_kernel" if staged else "hq_direct_kernel"
+    oh, ow = (L.H + 2 * L.pad - L.R) // L.stride + 1, (L.W + 2 * L.pad - L.S) // L.stride + 1
+    tiles = -(-L.B * (oh * ow if op == "fwd" else L.H * L.W) // 128) * -(-cout // 128)
+    if (cin % 128 == 0 and cout % 16 == 0 and cout >= 128 and L.R * L.S * cin >= 1024 and 64 < tiles and (tiles <= 512 or not k3) and
+            (op == "fwd" or (L.stride == 1 and L.R == L.S > 1))):
+        return "hq_ring_kernel"
     if k3 and cin % 64 == 0 and cin >= 128 and cout >= 128:
         return "hq_bandw_kernel"
     if k3 and cin == 64:
-        return "hq_band_kernel"
+        return "hq_regw_kernel"
     return "hq_gemm_kernel"
 
 
@@ -449,7 +454,7 @@ def main():
     value = step_ops / (wall_ms * 1e-3) / 1e12
 
     # ---- roofline of the dominant kernel: the slowest of the three GEMM launches ------------
-    names = {"fwd": "hq_band_kernel<64,3,2,8,1,fused> (forward)", "dgrad": "hq_band_kernel<64,3,2,8,1,fused> (dgrad)",
+    names = {"fwd": "hq_regw_kernel (forward)", "dgrad": "hq_regw_kernel (dgrad)",
              "wgrad": "hq_wgrad_band_kernel + wband_finalize_kernel (one hq_gemm_wgrad_update call)"}
     achieved = ops_gemm / (dom_ms * 1e-3) / 1e12
     # the int8 MFMA rate this device sustains in a register-only loop, next to the published peak
