@@ -61,8 +61,8 @@ int hq_try_launch_bandw(const hq_problem *p, int dgrad, const int8_t *A, const h
                         int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream,
                         const uint64_t *sr_seed = nullptr);
 
-// Layers whose reduced channels are a multiple of 128, from 8 lines of reduction and 65 tiles of 128 x 128 on; HQ_E_BADSHAPE: not
-// covered.  sr_seed as for hq_launch_gemm.
+// Layers whose reduced channels are a multiple of 128, from 8 lines of reduction and 65 tiles of 128 x 128 on (one tap: more);
+// HQ_E_BADSHAPE: not covered.  sr_seed as for hq_launch_gemm.
 int hq_try_launch_ring(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
                        const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
                        int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream,

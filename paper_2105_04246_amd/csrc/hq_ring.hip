@@ -307,11 +307,19 @@ int hq_try_launch_ring(const hq_problem *p, int dgrad, const int8_t *A, const hq
     // stages 31.5 / 28.3 us; linear 8192 x 1024 -> 1024, 8 stages 14.9 / 17.9).
     if (a.nst < 8) return HQ_E_BADSHAPE;
     // At most 64 tiles: the smaller tiles of the other kernels fill more compute units (3x3 on 128 x 4 x 4 x 512 -> 512: 20.2 us, split
-    // reduction 12.9).
+    // reduction 12.9).  From 65 on filters of several taps are faster here although most compute units have no tile (3x3 stride 2,
+    // 58 x 16 x 16 x 128 -> 320, 87 tiles 9.0 / 10.8 us; input gradient 3 x 28 x 28 x 1024 -> 512, 76 tiles 46.3 / 51.0, with stochastic
+    // rounding 26 x 14 x 14 x 640 -> 256, 80 tiles 26.0 / 31.3), also where most of the last column of tiles is empty (stride 2,
+    // 11 x 56 x 56 x 128 -> 160, 136 tiles 9.2 / 11.1).
     const long tiles = (long)a.m_tiles * a.n_tiles;
     if (tiles <= 64) return HQ_E_BADSHAPE;
-    // One-tap input gradients stay with the tile kernel, whose stage lengths are chosen for them.
-    if (dgrad && taps == 1) return HQ_E_BADSHAPE;
+    // One tap: while the tile kernel holds all its 64 x 64 tiles at once, two to a compute unit, it is ahead of this kernel's longer
+    // start and end, unless those weigh little: round-to-nearest-even from 10 lines on.  This / tile kernel, linear: input gradients
+    // 5120 x 1024 -> 192 8.6 / 7.9 us, 4319 x 1280 -> 272 9.8 / 9.8, 640 x 3072 -> 2048 16.1 / 20.6, 12281 x 1024 -> 192 9.2 / 10.1,
+    // 22528 x 1536 -> 320 26.8 / 36.6; with stochastic rounding 5120 x 1024 -> 192 10.5 / 8.4, 6016 x 1152 -> 320 11.3 / 10.3,
+    // 8794 x 1280 -> 384 12.0 / 14.3; dynamic, forward, 4678 x 1024 -> 160 15.8 / 14.2, 10987 x 2560 -> 320 35.0 / 39.3.
+    const long small_tiles = (long)((M + 63) / 64) * ((a.N + 63) / 64);
+    if (taps == 1 && small_tiles <= 512 && (out32 || sr_seed || a.nst < 10)) return HQ_E_BADSHAPE;
     // Past two tiles to a compute unit the kernel that stages a row tile's input once for all nine taps is level or up to 3 % ahead
     // (3x3, 256 x 14 x 14 x 256 -> 256: 41.3 / 39.9 us, 128 x 32 x 32 x 128 27.9 / 26.7), but not with stochastic rounding, whose long
     // epilogues its larger tiles overlap less (46.2 / 46.7, 32.6 / 33.7; 256 x 28 x 28 x 128 55.0 / 58.9).

@@ -71,8 +71,8 @@ def test_64_channel_layers_go_to_their_own_kernels_where_those_take_them():
 
 def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
     long_, short = "hq_gemm_kernel<128, 128, 2, 2, 128", "hq_gemm_kernel<128, 128, 2, 2, 64"
-    check([("dgrad_sr", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2048), short), ("dgrad", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2048), long_),
-           ("dgrad_sr", (LINEAR, 4096, 1, 1, 2048, 1, 1, 1, 0, 2048), long_), ("dgrad_sr", (LINEAR, 4096, 1, 1, 4096, 1, 1, 1, 0, 1024), short),
+    check([("dgrad_sr", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2064), short), ("dgrad", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2064), long_),
+           ("dgrad_sr", (LINEAR, 4096, 1, 1, 2048, 1, 1, 1, 0, 2064), long_), ("dgrad_sr", (LINEAR, 4096, 1, 1, 4096, 1, 1, 1, 0, 1040), short),
            ("dgrad_sr", conv(51, 28, 128, 1, 1, 288), short), ("dgrad_sr", conv(51, 28, 128, 1, 1, 256), long_),
            ("dgrad_sr", conv(60, 28, 96, 5, 2, 64), short), ("dgrad_sr", conv(41, 28, 256, 3, 2, 448), long_),
            ("dgrad_sr", conv(41, 28, 256, 3, 2, 256), short), ("dgrad_sr", conv(64, 28, 128, 5, 1, 64), short),
@@ -91,11 +91,23 @@ def test_whole_lines_per_stage_between_split_reductions_and_row_tiles():
            ("fwd", conv(257, 16, 128, 5, 1, 128), ring), ("fwd", conv(257, 32, 128, 3, 2, 128), ring),           # not the row tiles' layers
            ("dgrad", conv(257, 32, 256, 3, 2, 256), tile),                                                      # strided
            ("fwd", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), ring), ("fwd", (LINEAR, 8192, 1, 1, 896, 1, 1, 1, 0, 1024), tile),
-           ("dgrad", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), tile),
+           ("dgrad", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), ring), ("dgrad_sr", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), ring),
+           ("dgrad", conv(42, 28, 128, 1, 1, 1024), ring),
            ("fwd", conv(26, 14, 192, 3, 1, 256), bandw), ("fwd", conv(34, 13, 128, 3, 1, 144), ring), ("fwd", conv(128, 14, 256, 3, 1, 120), tile),
-           ("fwd", conv(20, 30, 128, 3, 1, 144), ring), ("fwd", (LINEAR, 4200, 1, 1, 1024, 1, 1, 1, 0, 272), ring),
-           ("fwd", (LINEAR, 1300, 1, 1, 1024, 1, 1, 1, 0, 1168), ring), ("fwd", conv(40, 29, 128, 3, 2, 272), ring),
+           ("fwd", conv(20, 30, 128, 3, 1, 144), ring), ("fwd", (LINEAR, 6700, 1, 1, 1024, 1, 1, 1, 0, 272), ring),
+           ("fwd", (LINEAR, 1700, 1, 1, 1280, 1, 1, 1, 0, 1168), ring), ("fwd", conv(40, 29, 128, 3, 2, 272), ring),
            ("dgrad", conv(40, 16, 128, 3, 1, 128, 2), ring), ("fwd", (CONV, 20, 17, 19, 128, 5, 3, 1, 1, 160), ring)])
+
+
+def test_whole_lines_of_one_tap_start_past_two_small_tiles_to_a_compute_unit():
+    """64 x 64 tiles of the tile kernel: 512 or fewer keep it, with round-to-nearest-even below 10 lines."""
+    ring, tile = "hq_ring_kernel", "hq_gemm_kernel"
+    def lin(M, k, n, dgrad=True):
+        return (LINEAR, M, 1, 1, n, 1, 1, 1, 0, k) if dgrad else (LINEAR, M, 1, 1, k, 1, 1, 1, 0, n)
+    check([("dgrad", lin(8192, 1024, 256), tile), ("dgrad", lin(8193, 1024, 256), ring), ("dgrad", lin(8192, 1152, 256), tile), ("dgrad", lin(8192, 1280, 256), ring),
+           ("fwd", lin(8192, 1152, 256, False), tile), ("fwd", lin(8192, 1280, 256, False), ring), ("fwd", lin(8193, 1024, 256, False), ring),
+           ("dgrad_sr", lin(8192, 2048, 256), tile), ("dgrad_sr", lin(8193, 1024, 256), ring),
+           ("dynamic_fwd", lin(8192, 2048, 256, False), tile), ("dynamic_fwd", lin(8193, 1024, 256, False), ring), ("dynamic_dgrad", lin(8193, 1024, 256), ring)])
 
 
 def test_small_depthwise_launches_are_cut_into_short_strips():

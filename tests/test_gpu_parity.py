@@ -388,7 +388,8 @@ def test_weights_in_registers(H, hq, L, g_asym):
 # are not square, the shortest reduction, bands of eight pixel tiles with a short last one.
 RING_SHAPES = [wl.conv("ring_n144", 34, 13, 128, 144, 3), wl.conv("ring_both_ways", 26, 14, 256, 256, 3), wl.conv("ring_s2", 40, 29, 128, 272, 3, stride=2),
                wl.LayerShape("ring_5x3", wl.CONV, 20, 17, 19, 128, 5, 3, 1, 1, 160), wl.conv("ring_pad2", 40, 16, 128, 128, 3, pad=2),
-               wl.conv("ring_pad0", 40, 18, 128, 128, 3, pad=0), wl.linear("ring_8_stages", 4200, 1024, 272), wl.linear("ring_bands", 1300, 1024, 1168)]
+               wl.conv("ring_pad0", 40, 18, 128, 128, 3, pad=0), wl.linear("past_ring", 4200, 1024, 272), wl.linear("past_ring_bands", 1300, 1024, 1168),
+               wl.linear("ring_8_stages", 6700, 1024, 272), wl.linear("ring_bands", 1700, 1280, 1168)]
 
 
 @pytest.mark.parametrize("L", RING_SHAPES, ids=[l.name for l in RING_SHAPES])
@@ -403,6 +404,20 @@ def test_whole_lines_per_stage(H, hq, L):
             y_track.step(L, "fwd", X, W0, H.DevTensor(X), Wdev)
         if L.Cout % 128 == 0 and L.kind == wl.CONV:
             g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
+
+
+# Input gradients of one tap: channels and pixels off the tile, the shortest reduction, images; in the last column and band of tiles.
+RING_ONE_TAP = [wl.linear("ring_dgrad_8_lines", 6700, 272, 1024), wl.linear("ring_dgrad_bands", 1700, 1168, 1280), wl.conv("ring_dgrad_1x1", 34, 14, 144, 1280, 1, pad=0)]
+
+
+@pytest.mark.parametrize("L", RING_ONE_TAP, ids=[l.name for l in RING_ONE_TAP])
+def test_whole_lines_of_one_tap(H, hq, L):
+    track, Wdev = H.TensorTrack(0.9, True), None
+    for t in range(3):                                       # dynamic, nearest, stochastic
+        _, W, dY = rand_layer_inputs(L, 130 + t, g_asym=True)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
 # Weight gradients by tiles: rows of whole 16-byte chunks (loads without a branch) and off them, tiles of 64 and 128 with columns and
