@@ -18,6 +18,8 @@
 // output channels; four wavefronts, each 64 pixels x 128 channels (128 accumulators per lane).
 #include "hq_device.h"
 #include "hq_internal.h"
+
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -316,7 +318,42 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_bandw_kernel(const BandwArgs
     }
 }
 
+// The tiles of a launch over H x W images; false: not covered.
+struct BandwTiles {
+    int rows, nimg, per_image;     // as in BandwArgs
+    int ntiles, patch_px;
+    size_t lds;
+};
+
+bool bandw_tiles(const hq_problem *p, int dgrad, BandwTiles *t)
+{
+    if (p->kind != HQ_CONV2D || p->R != 3 || p->S != 3 || p->stride != 1 || p->pad != 1) return false;
+    const int C = dgrad ? p->Cout : p->C, N = dgrad ? p->C : p->Cout;
+    if (C % 64 != 0 || C < 128 || N % 16 != 0 || N < 128) return false;
+    if (p->H * p->W > 128) {
+        t->nimg = 1;
+        t->rows = std::min(256 / p->W, p->H);
+        if (t->rows < 1) return false;
+    } else {
+        t->nimg = 256 / (p->H * p->W);
+        t->rows = p->H;
+    }
+    t->per_image = (p->H + t->rows - 1) / t->rows;
+    t->ntiles = t->nimg == 1 ? p->B * t->per_image : (p->B + t->nimg - 1) / t->nimg;
+    t->patch_px = t->nimg * (t->rows + 2) * (p->W + 2);
+    const size_t patch_bytes = ((size_t)t->patch_px * BW_CK + 1023) & ~(size_t)1023;
+    t->lds = 4 * BW_BN * BW_CK + 2 * patch_bytes + 4 * BW_BN + 64;
+    return t->lds <= 158 * 1024;                           // (two workgroups per compute unit up to 80 KiB)
+}
+
 } // namespace
+
+long hq_bandw_items(const hq_problem *p, int dgrad)
+{
+    BandwTiles t;
+    if (!bandw_tiles(p, dgrad, &t) || t.lds > 80 * 1024) return 0;
+    return (long)t.ntiles * (((dgrad ? p->C : p->Cout) + BW_BN - 1) / BW_BN);
+}
 
 // 3x3, stride 1, pad 1, C % 64 == 0 and C >= 128, Cout % 16 == 0 and Cout >= 128 (forward); the
 // input gradient of such a layer with the roles of C and Cout swapped.  HQ_E_BADSHAPE: not covered.
@@ -325,37 +362,26 @@ int hq_try_launch_bandw(const hq_problem *p, int dgrad, const int8_t *A, const h
                         int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed)
 {
     if (sr_seed && out32) return HQ_E_BADARG;
-    if (p->kind != HQ_CONV2D || p->R != 3 || p->S != 3 || p->stride != 1 || p->pad != 1) return HQ_E_BADSHAPE;
+    BandwTiles t;
+    if (!bandw_tiles(p, dgrad, &t)) return HQ_E_BADSHAPE;
     const int C = dgrad ? p->Cout : p->C, N = dgrad ? p->C : p->Cout;
-    if (C % 64 != 0 || C < 128 || N % 16 != 0 || N < 128) return HQ_E_BADSHAPE;
     BandwArgs a;
     a.A = A; a.Bw = Bw; a.bsum = bsum; a.aq = aq; a.bq = bq; a.range = range;
     a.out8 = out8; a.out32 = out32; a.outq = outq; a.st = st;
     a.Bn = p->B; a.H = p->H; a.W = p->W; a.C = C; a.N = N;
     a.pad = 1; a.flip = dgrad ? 1 : 0;
-    if (p->H * p->W >= 256 || p->H * p->W * 2 > 256) {
-        a.nimg = 1;
-        a.rows = 256 / p->W < 1 ? 0 : 256 / p->W;
-        if (a.rows > p->H) a.rows = p->H;
-        if (a.rows < 1) return HQ_E_BADSHAPE;
-    } else {
-        a.nimg = 256 / (p->H * p->W);
-        a.rows = p->H;
-    }
-    a.tiles_per_image = (p->H + a.rows - 1) / a.rows;
-    a.ntiles = a.nimg == 1 ? p->B * a.tiles_per_image : (p->B + a.nimg - 1) / a.nimg;
+    a.nimg = t.nimg; a.rows = t.rows;
+    a.tiles_per_image = t.per_image;
+    a.ntiles = t.ntiles;
     a.nchunks = (N + BW_BN - 1) / BW_BN;
     a.PH = a.rows + 2; a.PW = p->W + 2;
-    a.patch_px = a.nimg * a.PH * a.PW;
+    a.patch_px = t.patch_px;
     a.magic_img = hq_magic32((unsigned)(a.PH * a.PW));
     a.magic_PW = hq_magic32((unsigned)a.PW);
     a.magic_HW = hq_magic32((unsigned)(p->H * p->W));
     a.magic_W = hq_magic32((unsigned)p->W);
     a.count = (unsigned long long)p->B * p->H * p->W * N;
     a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
-    const size_t patch_bytes = ((size_t)a.patch_px * BW_CK + 1023) & ~(size_t)1023;
-    const size_t lds = 4 * BW_BN * BW_CK + 2 * patch_bytes + 4 * BW_BN + 64;
-    if (lds > 158 * 1024) return HQ_E_BADSHAPE;            // (two workgroups per compute unit up to 78 KiB)
     long items = (long)a.ntiles * a.nchunks;
     // Too few tiles for the chip under a reduction long enough to matter (4 x 4 images with 512 channels):
     // the gather kernel's 64 x 64 tiles spread the same work over four times as many workgroups.
@@ -365,6 +391,6 @@ int hq_try_launch_bandw(const hq_problem *p, int dgrad, const int8_t *A, const h
     auto kern = mode == 0 ? hq_bandw_kernel<0> : mode == 2 ? hq_bandw_kernel<2> : hq_bandw_kernel<1>;
     static std::atomic<unsigned long long> allowed[3];
     if (!hq_allow_lds(kern, 160 * 1024, allowed[mode])) return HQ_E_HIP;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(HQ_THREADS), lds, stream, a);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(HQ_THREADS), t.lds, stream, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }

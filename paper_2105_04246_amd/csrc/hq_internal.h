@@ -60,6 +60,9 @@ int hq_try_launch_bandw(const hq_problem *p, int dgrad, const int8_t *A, const h
                         const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
                         int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream,
                         const uint64_t *sr_seed = nullptr);
+// Work items of such a launch, 256 pixels x 128 channels each (what a row or an image leaves of that is idle); 0: not covered, or
+// only one workgroup to a compute unit.
+long hq_bandw_items(const hq_problem *p, int dgrad);
 
 // Layers whose reduced channels are a multiple of 128, from 8 lines of reduction and 65 tiles of 128 x 128 on (one tap: more);
 // HQ_E_BADSHAPE: not covered.  sr_seed as for hq_launch_gemm.

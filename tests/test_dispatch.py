@@ -86,8 +86,7 @@ def test_whole_lines_per_stage_between_split_reductions_and_row_tiles():
     ring, ks, bandw, tile = "hq_ring_kernel", "hq_ksplit_kernel", "hq_bandw_kernel", "hq_gemm_kernel"
     check([("fwd", conv(26, 14, 256, 3, 1, 256), ring), ("dgrad", conv(26, 14, 256, 3, 1, 256), ring), ("dgrad_sr", conv(26, 14, 256, 3, 1, 256), ring),
            ("dynamic_fwd", conv(26, 14, 256, 3, 1, 256), ring), ("fwd", conv(128, 4, 512, 3, 1, 512), ks),
-           ("fwd", conv(256, 16, 128, 3, 1, 128), ring), ("fwd", conv(257, 16, 128, 3, 1, 128), bandw),         # 512 and 514 tiles
-           ("dgrad", conv(257, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(257, 16, 128, 3, 1, 128), ring),
+           ("fwd", conv(256, 16, 128, 3, 1, 128), ring), ("fwd", conv(257, 16, 128, 3, 1, 128), ring),
            ("fwd", conv(257, 16, 128, 5, 1, 128), ring), ("fwd", conv(257, 32, 128, 3, 2, 128), ring),           # not the row tiles' layers
            ("dgrad", conv(257, 32, 256, 3, 2, 256), tile),                                                      # strided
            ("fwd", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), ring), ("fwd", (LINEAR, 8192, 1, 1, 896, 1, 1, 1, 0, 1024), tile),
@@ -97,6 +96,18 @@ def test_whole_lines_per_stage_between_split_reductions_and_row_tiles():
            ("fwd", conv(20, 30, 128, 3, 1, 144), ring), ("fwd", (LINEAR, 6700, 1, 1, 1024, 1, 1, 1, 0, 272), ring),
            ("fwd", (LINEAR, 1700, 1, 1, 1280, 1, 1, 1, 0, 1168), ring), ("fwd", conv(40, 29, 128, 3, 2, 272), ring),
            ("dgrad", conv(40, 16, 128, 3, 1, 128, 2), ring), ("fwd", (CONV, 20, 17, 19, 128, 5, 3, 1, 1, 160), ring)])
+
+
+def test_row_tiles_stay_where_they_fill_their_half_rounds():
+    """Past 512 tiles of whole lines: halves of a round, 256 tiles each, against twice those of the row tiles' items."""
+    ring, bandw = "hq_ring_kernel", "hq_bandw_kernel"
+    check([("fwd", conv(384, 16, 128, 3, 1, 128), ring), ("fwd", conv(385, 16, 128, 3, 1, 128), bandw),        # 768 and 770 tiles, 384 and 385 items
+           ("dgrad", conv(384, 16, 128, 3, 1, 128), ring), ("dgrad", conv(385, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(385, 16, 128, 3, 1, 128), ring),
+           ("dynamic_fwd", conv(385, 16, 128, 3, 1, 128), bandw), ("dynamic_dgrad", conv(384, 16, 128, 3, 1, 128), ring),
+           ("fwd", conv(512, 16, 128, 3, 1, 128), bandw), ("fwd", conv(513, 16, 128, 3, 1, 128), ring),        # a third half round for one item
+           ("fwd", conv(256, 14, 256, 3, 1, 256), bandw), ("fwd", conv(257, 14, 256, 3, 1, 256), ring),
+           ("fwd", conv(512, 14, 128, 3, 1, 128), bandw), ("fwd", conv(480, 14, 128, 3, 1, 128), ring),        # 736 tiles
+           ("fwd", conv(32, 64, 128, 3, 1, 128), ring), ("fwd", conv(512, 8, 512, 3, 1, 512), ring)])          # one workgroup to a compute unit
 
 
 def test_whole_lines_of_one_tap_start_past_two_small_tiles_to_a_compute_unit():
