@@ -364,13 +364,12 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
     a.A = A; a.Bw = Bw; a.bsum = bsum; a.aq = aq; a.bq = bq; a.range = range;
     a.out8 = out8; a.out32 = out32; a.outq = outq; a.st = st; a.B = p->B;
     const int taps = p->R * p->S;
-    if (taps > 64) return HQ_E_BADSHAPE;                 // a pixel's tap mask has 64 bits
     if (!dgrad) { a.N = p->Cout; a.Cs = p->C; a.Hs = p->H; a.Ws = p->W; a.Ho = OH; a.Wo = OW; }
     else        { a.N = p->C; a.Cs = p->Cout; a.Hs = OH; a.Ws = OW; a.Ho = p->H; a.Wo = p->W; }
     const unsigned long long M = (unsigned long long)a.B * a.Ho * a.Wo, lim = 1ull << 32;
     a.wrow = (size_t)taps * a.Cs;
-    // operands of hq_magic_div
-    if (M * (unsigned)(a.Ho > a.Wo ? a.Ho : a.Wo) >= lim || (a.wrow + 64) * a.Cs >= lim) return HQ_E_BADSHAPE;
+    // operands of hq_magic_div: pixels, offsets in a weight row, taps
+    if (M * (unsigned)(a.Ho > a.Wo ? a.Ho : a.Wo) >= lim || (a.wrow + 64) * a.Cs >= lim || (a.wrow + 64) / a.Cs * p->S >= lim) return HQ_E_BADSHAPE;
     a.M = (int)M;
     const bool aligned = a.Cs % 16 == 0;
     a.cpt = a.Cs / 16;

@@ -44,6 +44,15 @@ def test_strided_input_gradients_off_16_weigh_the_reduction_against_the_tiles():
            ("dgrad_sr", conv(64, 112, 36, 1, 2, 36), tile), ("dgrad", conv(8, 28, 100, 1, 2, 100), ks)])
 
 
+def test_filters_of_more_than_64_taps_are_split():
+    ks = "hq_ksplit_kernel"
+    for layer in ((CONV, 4, 14, 14, 256, 9, 8, 1, 4, 64), (CONV, 4, 14, 14, 256, 8, 8, 1, 4, 64), (CONV, 2, 23, 21, 32, 11, 11, 2, 5, 48),
+                  (CONV, 3, 13, 17, 20, 9, 8, 1, 4, 36), (CONV, 2, 19, 22, 12, 11, 11, 3, 5, 20)):
+        check([(op, layer, ks) for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")])
+    # (taps times taps per row past 2^32 are outside the kernel's divisions)
+    check([("fwd", (CONV, 1, 1, 70000, 16, 1, 65600, 1, 0, 16), "hq_gemm_kernel"), ("fwd", (CONV, 1, 1, 66000, 16, 1, 65500, 1, 0, 16), ks)])
+
+
 def test_split_reductions_of_whole_chunks_end_where_the_tile_kernels_are_faster():
     small, large = "hq_ksplit_kernel<2, 4, 8, 2, true", "hq_ksplit_kernel<4, 4, 8, 2, true"
     tile = "hq_gemm_kernel"

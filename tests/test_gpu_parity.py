@@ -336,7 +336,9 @@ SMALL_LAUNCHES = [
     wl.linear("ks_word", 70, 100, 52), wl.linear("ks_word_64", 3000, 100, 260), wl.conv("ks_word_s2_n20", 2, 150, 20, 8, 3, stride=2),
     wl.conv("ks_word_s2_n100", 8, 50, 100, 36, 3, stride=2), wl.LayerShape("word_s5", wl.CONV, 2, 23, 23, 20, 3, 3, 5, 1, 12),
     wl.conv("past_band", 12, 24, 64, 64, 3), wl.conv("past_bandw", 9, 28, 128, 192, 3), wl.linear("past_gather", 4200, 272, 520),
-    wl.LayerShape("past_mask", wl.CONV, 1, 14, 14, 16, 9, 9, 1, 4, 32),
+    wl.LayerShape("ks_9x9", wl.CONV, 1, 14, 14, 16, 9, 9, 1, 4, 32), wl.LayerShape("ks_9x8", wl.CONV, 4, 14, 14, 64, 9, 8, 1, 4, 64),
+    wl.LayerShape("ks_11x11_s2", wl.CONV, 2, 23, 21, 32, 11, 11, 2, 5, 48), wl.LayerShape("ks_word_9x8", wl.CONV, 3, 13, 17, 20, 9, 8, 1, 4, 36),
+    wl.LayerShape("ks_word_11x11_s3", wl.CONV, 2, 19, 22, 12, 11, 11, 3, 5, 20), wl.LayerShape("past_9x9", wl.CONV, 20, 14, 14, 16, 9, 9, 1, 4, 260),
     wl.conv("ks_word_s2_many", 24, 56, 36, 36, 3, stride=2), wl.conv("past_word_s2_1x1", 40, 56, 36, 36, 1, stride=2, pad=0),
     wl.conv("past_word_1x1", 26, 28, 56, 64, 1, pad=0),
     wl.linear("ks_32x64_long", 2600, 592, 132), wl.linear("ks_64x64_long", 2000, 1424, 400), wl.conv("ks_64x64_s2", 13, 21, 256, 272, 3, stride=2)]
