@@ -222,33 +222,12 @@ static int gemm_common(const hq_problem *p, int dgrad, const int8_t *A, const hq
         if (dgrad || sr_seed) return HQ_E_BADSHAPE;
         return hq_try_launch_direct(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream));
     }
-    // 3x3 layers with 64 reduced channels have kernels of their own, which beat split reductions once those need tiles of
-    // 32 x 64 (8192 pixels -> 64: 8.5 us against 7.8 with the weights in registers, 7.9 with the weights in LDS), except with
-    // stochastic rounding, where little work per workgroup counts more (8.5 against 9.3 and 8.8).
-    const bool own64 = !sr_seed && p->kind == HQ_CONV2D && p->R == 3 && p->S == 3 && (dgrad ? p->Cout : p->C) == 64;
-    // Their 32-bit pass over 2048 .. 16384 pixels of 64 outputs: the kernel with the weights in LDS first, which starts sooner, as
-    // long as its bands are one round (16 x 16 pixels, whole dynamic call, weights in LDS / in registers / split reduction: batch
-    // 12 12.2 / 13.5 / 13.1 us, 64 13.1 / 15.2; 282 bands at batch 47 18.5 / 14.5; 128 19.4 / 17.7).
-    const long pixels = (long)p->B * p->H * p->W;
-    if (own64 && out32 && (dgrad ? p->C : p->Cout) == 64 && p->stride == 1 && p->pad == 1 && pixels > 2048 && pixels <= 16384 &&
-        hq_band_workgroups(p->B, p->H) <= 256) {
-        rc = hq_try_launch_band(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream));
-        if (rc != HQ_E_BADSHAPE) return rc;
-    }
-    rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed, own64);
+    rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
     if (rc != HQ_E_BADSHAPE) return rc;
     rc = hq_try_launch_ring(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
     if (rc != HQ_E_BADSHAPE) return rc;
     rc = hq_try_launch_regw(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
     if (rc != HQ_E_BADSHAPE) return rc;
-    if (own64) {
-        if ((dgrad ? p->C : p->Cout) <= 64) {
-            rc = hq_try_launch_band(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream));
-            if (rc != HQ_E_BADSHAPE) return rc;
-        }
-        rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream));
-        if (rc != HQ_E_BADSHAPE) return rc;
-    }
     if (sr_seed) {
         // stochastic rounding: never a first layer (no input gradient)
         if (p->kind == HQ_DEPTHWISE)

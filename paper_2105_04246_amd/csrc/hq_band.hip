@@ -428,12 +428,6 @@ int launch_band_ng(const BandArgs &a, int ng, int blocks, size_t lds, hipStream_
 
 // Returns HQ_OK after launching, HQ_E_BADSHAPE if this path does not cover the problem (the
 // caller then uses the general gather kernel), HQ_E_HIP on a launch error.
-long hq_band_workgroups(int B, int Ho)
-{
-    const int bpi = std::min(Ho, (256 + B - 1) / B), rows = (Ho + bpi - 1) / bpi;
-    return (long)B * ((Ho + rows - 1) / rows);
-}
-
 int hq_try_launch_band(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
                        const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
                        int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed)

@@ -26,11 +26,11 @@ int hq_launch_gemm(const hq_problem *p, int dgrad, const int8_t *A, const hq_qpa
                    int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed = nullptr);
 
 // Launches with few output tiles (the wavefronts of a workgroup split the reduction); HQ_E_BADSHAPE: not covered.
-// sr_seed as for hq_launch_gemm.  small_tiles: only where tiles of at most 32 x 32 make one round.
+// sr_seed as for hq_launch_gemm.
 int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
                          const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
                          int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream,
-                         const uint64_t *sr_seed = nullptr, bool small_tiles = false);
+                         const uint64_t *sr_seed = nullptr);
 
 // 3x3 stride-1 layers with 64 reduced channels (weights in registers); HQ_E_BADSHAPE: not covered.
 // sr_seed as for hq_launch_gemm.
@@ -38,9 +38,6 @@ int hq_try_launch_regw(const hq_problem *p, int dgrad, const int8_t *A, const hq
                        const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
                        int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream,
                        const uint64_t *sr_seed = nullptr);
-
-// Workgroups (bands of one image's rows) of the kernel below for a 3x3 layer with B images of Ho output rows.
-long hq_band_workgroups(int B, int Ho);
 
 // Fast path for layers whose weights fit in LDS; HQ_E_BADSHAPE means "not covered, use hq_launch_gemm".
 // sr_seed as for hq_launch_gemm.

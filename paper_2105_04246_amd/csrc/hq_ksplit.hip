@@ -355,8 +355,7 @@ int launch2(KsArgs &a, int mode, hipStream_t s)
 
 int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
                          const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
-                         int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed,
-                         bool small_tiles)
+                         int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed)
 {
     if (p->kind == HQ_DEPTHWISE || (!dgrad && p->C < 8)) return HQ_E_BADSHAPE;      // (first layers have their own kernels)
     const int OH = (p->H + 2 * p->pad - p->R) / p->stride + 1, OW = (p->W + 2 * p->pad - p->S) / p->stride + 1;
@@ -406,11 +405,10 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
     const int mode = out32 ? 0 : sr_seed ? 2 : 1;
     a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
     a.m_fast = (size_t)a.N * a.wrow > (size_t)a.B * a.Hs * a.Ws * a.Cs;
-    // Which tile.  A launch is one round of tiles that run side by side, so its time is one tile's, and the smallest tile
-    // that still gives every compute unit at most one is the fastest.  Beyond one round the tile kernels' larger tiles win
-    // (fewer bytes fetched per multiply-add), earlier where the reduction is too short for a 64 x 64 tile to pay for adding
-    // its partial sums and for the masks of its taps.  (Strided input gradients of at most 64 channels would be 256-pixel
-    // tiles over the whole reduction: 32 of them for 16x16x64 <- 8x8x128 at batch 32, 17 -> 7.6 us.)
+    // Which tile.  While a launch is one round of tiles that run side by side its time is one tile's: the smallest tile that gives
+    // every compute unit at most one is the fastest (over 1350 launches within 0.4 % of the best of the five).  Beyond one round the
+    // tile kernels' larger tiles fetch fewer bytes per multiply-add.  (Strided input gradients of at most 64 channels would be
+    // 256-pixel tiles over the whole reduction: 32 of them for 16x16x64 <- 8x8x128 at batch 32, 17 -> 7.6 us.)
     const size_t k = a.wrow / (a.classed ? (size_t)p->stride * p->stride : 1);      // reduction of an average tile
     auto tiles = [&](int tm, int tn) {
         unsigned long long m = 0;
@@ -418,49 +416,55 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
         return m * (unsigned long long)((a.N + tn - 1) / tn);
     };
     if (!aligned) {
-        // Two or more workgroups per compute unit here.  A tile pays for the masks of its taps, for the partial sums through
-        // LDS and for adding them however short its reduction is, the tile kernel mainly for its 64-byte stages (4-byte
-        // loads, in strided input gradients a division test each), and with few channels for its 256-pixel tiles.  The two
-        // sides below are in proportion to what is left of a launch without its start-up, fitted to 3500 launches of 1 .. 49
-        // taps, 4 .. 600 reduced and 16 .. 600 output channels in the three rounding modes; one in 40 is on the wrong side by
-        // more than 5 %.  Forward, this / tile kernel: one tap, 20384 pixels -> 64, 56 reduced 8.7 / 7.7 us, 100: 9.7 / 10.0,
-        // 200: 11.0 / 14.7; nine taps, 4704 pixels -> 256, 108 reduced 12.9 / 8.5, 900: 26.2 / 29.3; 49 taps, 5096 -> 128, 588
-        // reduced 27.9 / 20.8.  Input gradients of stride 2: 1x1, 401408 pixels of 32, 36 reduced 28.2 / 26.9, 100: 30.0 / 42.5;
-        // 3x3, 119168 pixels of 128, 20 channels 56 / 31, 36: 56 / 57, 100: 69 / 114.
+        // Microseconds of a launch by its rounds of 256 tiles and its reduction, for the tiles here and for the tile kernel (64-byte
+        // stages of 4-byte loads, with few channels 256-pixel tiles), fitted to 830 launches of 1 .. 121 taps, 8 .. 2044 reduced and 4 ..
+        // 2048 output channels in the three rounding modes: the choice costs 0.6 % over always the fastest, 2 launches in 100 are on
+        // the wrong side by more than 5 %.  Forward, this / tile kernel: one tap, 2058 pixels -> 760, 244 reduced 10.6 / 11.8 us, 12996
+        // -> 252, four taps of 120: 25.7 / 18.7; nine taps, 3136 -> 160, 5364 reduced 40.6 / 129, 11956 -> 252, 6840: 205 / 167; 49 taps,
+        // 1152 -> 320, 392 reduced 6.8 / 16.6.
         const bool strided = a.classed && p->stride > 1;
-        const double t32 = (double)tiles(32, 32), t = (double)tiles(64, a.N <= 32 ? 32 : 64);
-        const double stages = (double)((a.wrow + 63) / 64);
+        const double t32 = (double)tiles(32, 32);
         if (t32 <= (strided ? 512 : 256)) return launch2<2, 2, 8, 1, false>(a, mode, stream);
-        double tile, split;
-        if (strided) {
-            const double g = (double)(a.N <= 64 ? tiles(256, 64) : tiles(128, 128));
-            const double per_class = (double)taps / (p->stride * p->stride);
-            tile = std::max(1.0, g / 400) * ((mode == 1 ? 0 : 0.95) + (a.N <= 64 ? 9.8 : 6.2) * stages);
-            split = std::max(1.0, t / (a.N <= 32 ? 100 : 80)) *
-                    ((a.N <= 32 ? 0.55 : 1.0) + 0.43 * std::min(1.0, per_class) + 0.11 * per_class);
-        } else {
-            if (tiles(64, 64) > 512) return HQ_E_BADSHAPE;
-            tile = a.N <= 64 ? (mode == 2 ? 1.0 : -0.5) + 2.9 * stages : (mode == 2 ? 1.2 : 0.4) + 1.6 * stages;
-            split = t32 <= 512 ? std::max(1.0, t32 / 206) * 0.19 * taps
-                               : std::max(1.0, t / 207) * ((a.N <= 32 ? 1.3 : 1.9) + 0.42 * taps);
+        if (!strided) {
+            if (a.N > 64 && tiles(64, 64) > 512) return HQ_E_BADSHAPE;       // (98 launches: level in the mean)
+            auto us = [&](int tm, int tn, double start, double round, double byte) {
+                return start + (double)((tiles(tm, tn) + 255) / 256) * (round + byte * (double)k);
+            };
+            const double s32 = us(32, 32, 3.5, 1.25, 0.0054), s64x32 = us(64, 32, 4.5, 0.95, 0.0058), s64 = us(64, 64, 3.6, 2.0, 0.0076);
+            const double sr = mode == 2 ? 1.0 : 0.0;
+            const double tile = a.N <= 32 ? 6.9 + 0.036 * (double)k + 4.6 * sr : a.N <= 64 ? 5.5 + 0.034 * (double)k + 2.5 * sr :
+                                k > 240 ? 6.6 + 0.0225 * (double)k + 2.9 * sr : us(128, 128, 5.9, 1.2, 0.0193) + 2.4 * sr;
+            if (std::min({s32, s64x32, s64}) > tile) return HQ_E_BADSHAPE;
+            if (s32 <= s64x32 && s32 <= s64) return launch2<2, 2, 8, 1, false>(a, mode, stream);
+            if (s64x32 <= s64) return launch2<4, 2, 4, 1, false>(a, mode, stream);
+            return launch2<4, 4, 4, 1, false>(a, mode, stream);
         }
+        // Strided input gradients: the tile kernel walks every tap with a division test per word, so the line lies at short reductions.
+        // The two sides are in proportion to what is left of a launch without its start-up (8 of 390 launches are on the wrong
+        // side by more than 5 %).  1x1, 401408 pixels of 32, 36 reduced 28.2 / 26.9 us, 100: 30.0 / 42.5; 3x3, 119168 pixels of 128, 20
+        // channels 56 / 31, 36: 56 / 57, 100: 69 / 114.
+        const double t = (double)tiles(64, a.N <= 32 ? 32 : 64), stages = (double)((a.wrow + 63) / 64);
+        const double g = (double)(a.N <= 64 ? tiles(256, 64) : tiles(128, 128)), per_class = (double)taps / (p->stride * p->stride);
+        const double tile = std::max(1.0, g / 400) * ((mode == 1 ? 0 : 0.95) + (a.N <= 64 ? 9.8 : 6.2) * stages);
+        const double split = std::max(1.0, t / (a.N <= 32 ? 100 : 80)) *
+                             ((a.N <= 32 ? 0.55 : 1.0) + 0.43 * std::min(1.0, per_class) + 0.11 * per_class);
         if (split > tile) return HQ_E_BADSHAPE;
-        if (!strided && t32 <= 512) return launch2<2, 2, 8, 1, false>(a, mode, stream);
         if (a.N <= 32) return launch2<4, 2, 4, 1, false>(a, mode, stream);
         return launch2<4, 4, 4, 1, false>(a, mode, stream);
     }
     if (tiles(16, 16) <= 256) return launch2<1, 1, 8, 4, true>(a, mode, stream);
     if (tiles(16, 32) <= 256) return launch2<1, 2, 8, 4, true>(a, mode, stream);
     if (tiles(32, 32) <= 256) return launch2<2, 2, 8, 2, true>(a, mode, stream);
-    if (small_tiles) return HQ_E_BADSHAPE;
-    // 2500 pixels -> 128, one tap, this / tile kernel: 512 reduced 6.5 / 6.2 us, 640 6.5 / 6.7, 1024 6.9 / 8.2
-    if (tiles(32, 64) <= 256 && (k >= (a.N <= 64 ? 512 : 576) || (a.classed && a.N <= 64)))
-        return launch2<2, 4, 8, 2, true>(a, mode, stream);
-    // The tile kernels are the gather kernel with its own 64 x 64 tiles where N > 64 (5096 pixels -> 128: nine taps, 1152 reduced
-    // 12.4 / 10.3 us, 2304 13.6 / 14.7; 25 taps, 1200: 19.7 / 14.7; 49 taps, 1568: 30.5 / 21.0, 6272: 0.93 of it), with 256-pixel tiles
-    // where N <= 64 (twice the time of these already at 1152), and the streamed-weights kernel (1152: 1.25 times).
-    const bool streamed = taps == 9 && p->S == 3 && p->stride == 1 && p->pad == 1 && a.Cs % 64 == 0 && a.N % 16 == 0 && a.N >= 128;
-    if (tiles(64, 64) <= 256 && k >= (a.N <= 64 || a.classed || streamed ? (size_t)1152 : (size_t)(1350 + 70 * taps)))
+    if (tiles(32, 64) <= 256) return launch2<2, 4, 8, 2, true>(a, mode, stream);
+    // One round is faster than the tile kernels whatever the reduction (this / tile kernel: nine taps of 16, 12887 pixels -> 64 5.7 /
+    // 10.7 us, 25 taps of 96, 3840 -> 256 9.0 / 19.1, 49 taps of 16, 7584 -> 128 7.0 / 18.3; one tap of 64, 886 -> 1024 5.7 / 5.7, of 768, 1024
+    // -> 1000 6.7 / 7.1), except for one tap of two or three 128-byte stages of the gather kernel's own 64 x 64 tiles (3136 -> 256, 256
+    // reduced 5.8 / 5.0, 384: 6.1 / 5.5; 7056 -> 80, 560: 6.5 / 6.6).
+    if (tiles(64, 64) <= 256 && !(taps == 1 && !a.classed && a.N > 64 && a.Cs >= 256 && a.Cs < 512))
         return launch2<4, 4, 8, 2, true>(a, mode, stream);
+    // A second round where the tile kernels have 256-pixel tiles for it, as long as the reduction is long (19845 pixels -> 32, 1024 reduced
+    // 8.7 / 14.1 us, 25480 -> 32, 256: 8.0 / 7.0; 24354 -> 64, 1024: 12.2 / 17.1, 32000 -> 64, 256: 10.3 / 8.7).
+    if (a.N <= 64 && tiles(64, 64) <= 512 && k >= 1024)
+        return a.N <= 32 ? launch2<2, 2, 8, 2, true>(a, mode, stream) : launch2<4, 4, 8, 2, true>(a, mode, stream);
     return HQ_E_BADSHAPE;
 }

@@ -17,21 +17,20 @@ def check(cases):
 
 
 def test_short_reductions_off_16_stay_with_the_tile_kernel():
-    """The split-reduction kernel's 4-byte form pays off only where its wavefronts have a reduction to share."""
+    """The split-reduction kernel's 4-byte form: one round of the smallest tile that makes one, several while they take less time than
+    the tile kernel's stages."""
     ks, tile = "hq_ksplit_kernel", "hq_gemm_kernel"
-    check([("fwd", conv(6, 28, 24, 1, 1, 96), ks),              # one round of 32 x 32 tiles: whatever the reduction
-           ("fwd", conv(26, 28, 56, 1, 1, 64), tile),           # 20384 pixels, two rounds, 56 reduced
-           ("fwd", conv(26, 28, 100, 1, 1, 64), ks),
-           ("fwd", conv(13, 28, 56, 1, 1, 128), tile),
-           ("fwd", conv(13, 28, 200, 1, 1, 128), ks),
-           ("fwd", conv(20, 10, 12, 3, 1, 256), tile),          # nine taps of 12, under two rounds of 32 x 32 tiles
-           ("fwd", conv(20, 10, 20, 3, 1, 256), ks),
-           ("fwd", conv(6, 28, 12, 3, 1, 256), tile),           # more than a round of 64 x 64
-           ("fwd", conv(6, 28, 100, 3, 1, 256), ks),
-           ("fwd", conv(26, 14, 12, 7, 1, 128), tile),          # 49 taps of 12
-           ("fwd", conv(26, 14, 36, 7, 1, 128), ks),
-           ("dgrad", (LINEAR, 8000, 1, 1, 128, 1, 1, 1, 0, 12), tile),
-           ("dgrad", (LINEAR, 64, 1, 1, 128, 1, 1, 1, 0, 12), ks)])
+    small, rows, large = (ks + "<%s, false" % s for s in ("2, 2, 8, 1", "4, 2, 4, 1", "4, 4, 4, 1"))
+    check([("fwd", conv(2, 28, 24, 1, 1, 96), small), ("fwd", conv(6, 28, 24, 1, 1, 96), rows), ("fwd", conv(20, 28, 100, 1, 1, 64), large),
+           ("fwd", conv(26, 28, 56, 1, 1, 64), tile), ("fwd", conv(26, 28, 100, 1, 1, 64), tile),        # 20384 pixels, two rounds
+           ("fwd", conv(26, 28, 200, 1, 1, 64), large),
+           ("fwd", conv(13, 28, 56, 1, 1, 128), tile), ("fwd", conv(13, 28, 200, 1, 1, 128), large),
+           ("fwd", conv(20, 10, 12, 3, 1, 256), rows), ("fwd", conv(16, 14, 36, 3, 1, 100), rows),
+           ("fwd", conv(6, 28, 12, 3, 1, 256), tile), ("fwd", conv(6, 28, 100, 3, 1, 256), large),
+           ("fwd", conv(26, 14, 12, 7, 1, 128), large), ("fwd", (LINEAR, 2058, 1, 1, 244, 1, 1, 1, 0, 760), large),
+           ("fwd", conv(53, 28, 20, 3, 1, 16), rows), ("fwd", conv(61, 14, 760, 3, 1, 252), tile), ("fwd", conv(16, 14, 596, 3, 1, 160), rows),
+           ("dgrad", (LINEAR, 16000, 1, 1, 128, 1, 1, 1, 0, 12), tile), ("dgrad", (LINEAR, 8000, 1, 1, 128, 1, 1, 1, 0, 12), large),
+           ("dgrad", (LINEAR, 64, 1, 1, 128, 1, 1, 1, 0, 12), small)])
 
 
 def test_strided_input_gradients_off_16_weigh_the_reduction_against_the_tiles():
@@ -54,28 +53,33 @@ def test_filters_of_more_than_64_taps_are_split():
 
 
 def test_split_reductions_of_whole_chunks_end_where_the_tile_kernels_are_faster():
-    small, large = "hq_ksplit_kernel<2, 4, 8, 2, true", "hq_ksplit_kernel<4, 4, 8, 2, true"
-    tile = "hq_gemm_kernel"
-    check([("fwd", (LINEAR, 2500, 1, 1, 512, 1, 1, 1, 0, 128), tile), ("fwd", (LINEAR, 2500, 1, 1, 640, 1, 1, 1, 0, 128), small),
-           ("fwd", (LINEAR, 5000, 1, 1, 512, 1, 1, 1, 0, 64), small),
-           ("fwd", (LINEAR, 5000, 1, 1, 1280, 1, 1, 1, 0, 128), tile), ("fwd", (LINEAR, 5000, 1, 1, 1536, 1, 1, 1, 0, 128), large),
-           ("fwd", conv(26, 28, 128, 3, 2, 128), tile), ("fwd", conv(26, 28, 256, 3, 2, 128), large),
-           ("fwd", conv(26, 14, 128, 3, 1, 128), large),                   # against the streamed-weights kernel
-           ("fwd", conv(60, 28, 128, 3, 2, 64), large),
-           ("fwd", conv(16, 28, 64, 5, 2, 200), tile), ("fwd", conv(16, 28, 96, 5, 2, 200), tile),
-           ("fwd", conv(16, 28, 192, 5, 2, 200), large), ("fwd", conv(11, 14, 32, 7, 1, 200), tile)])
+    def lin(M, k, n):
+        return (LINEAR, M, 1, 1, k, 1, 1, 1, 0, n)
+    ks, tile = "hq_ksplit_kernel", "hq_gemm_kernel"
+    s32, small, large = (ks + "<%s, true" % s for s in ("2, 2, 8, 2", "2, 4, 8, 2", "4, 4, 8, 2"))
+    check([("fwd", lin(2500, 512, 128), small), ("fwd", lin(2500, 256, 128), small), ("fwd", lin(5000, 512, 64), small),
+           ("fwd", lin(5000, 240, 128), large), ("fwd", lin(5000, 256, 128), tile), ("fwd", lin(5000, 496, 128), tile), ("fwd", lin(5000, 512, 128), large),
+           ("fwd", lin(12000, 256, 64), large), ("fwd", lin(8192, 1280, 128), large), ("fwd", lin(8193, 1040, 128), tile),
+           ("fwd", conv(26, 28, 128, 3, 2, 128), large), ("fwd", conv(43, 28, 128, 3, 2, 128), "hq_ring_kernel"),
+           ("fwd", conv(26, 14, 128, 3, 1, 128), large), ("fwd", conv(11, 14, 32, 7, 1, 200), large),
+           ("fwd", conv(16, 28, 64, 5, 2, 200), large), ("fwd", conv(25, 28, 192, 5, 2, 200), tile),
+           ("dgrad", conv(5, 28, 256, 1, 2, 256), large),                                          # strided: whatever the reduction
+           # a second round under at most 64 channels and a long reduction
+           ("fwd", lin(20000, 1024, 32), s32), ("fwd", lin(20000, 1008, 32), tile), ("fwd", lin(40000, 1024, 32), tile),
+           ("fwd", lin(20000, 1024, 64), large), ("fwd", lin(33000, 1024, 64), tile), ("fwd", lin(16000, 1024, 80), tile),
+           ("fwd", conv(60, 28, 128, 3, 2, 64), large), ("fwd", conv(102, 14, 128, 3, 1, 64), large)])
     # a strided input gradient's tiles are counted class by class: 242 pixels in four classes of 61, 61, 60 and 60
     # make 16 tiles of 16 pixels a column, not 16.0
     assert launches.calls([("dgrad", conv(2, 11, 504, 2, 2, 32, 0))])[0][0].blocks <= 256
 
 
-def test_64_channel_layers_go_to_their_own_kernels_where_those_take_them():
-    ks, regw, band = "hq_ksplit_kernel", "hq_regw_kernel", "hq_band_kernel"
-    check([("fwd", conv(10, 28, 64, 3, 1, 64), regw), ("fwd", conv(2, 28, 64, 3, 1, 64), ks),
-           ("fwd", conv(10, 30, 64, 3, 1, 64, 0), band),                                  # no padding
-           ("fwd", (CONV, 2, 20, 130, 64, 3, 3, 1, 1, 64), ks),                           # too wide for either
-           ("fwd", conv(26, 28, 64, 3, 2, 64), band), ("fwd", conv(20, 28, 64, 3, 2, 80), ks),
-           ("dgrad_sr", conv(10, 28, 64, 3, 1, 64), ks), ("dgrad_sr", conv(16, 28, 64, 3, 1, 64), regw)])
+def test_64_channel_layers_go_to_their_own_kernels_past_one_round():
+    ks, regw, band, tile = "hq_ksplit_kernel", "hq_regw_kernel", "hq_band_kernel", "hq_gemm_kernel"
+    check([(op, conv(20, 28, 64, 3, 1, 64), ks) for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")] +
+          [(op, conv(21, 28, 64, 3, 1, 64), regw) for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")] +
+          [("fwd", conv(10, 30, 64, 3, 1, 64, 0), ks), ("fwd", conv(21, 30, 64, 3, 1, 64, 0), band),                # no padding
+           ("fwd", (CONV, 2, 20, 130, 64, 3, 3, 1, 1, 64), ks), ("fwd", (CONV, 7, 20, 130, 64, 3, 3, 1, 1, 64), tile),      # too wide for either
+           ("fwd", conv(26, 28, 64, 3, 2, 64), ks), ("fwd", conv(90, 28, 64, 3, 2, 64), band), ("fwd", conv(20, 28, 64, 3, 2, 80), ks)])
 
 
 def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
@@ -178,13 +182,11 @@ def test_column_sums_over_many_lines_are_shared():
     assert (len(one), len(words), len(stem)) == (1, 2, 1)      # lines of 4 channels are read four at a time
 
 
-def test_32_bit_pass_of_64_channel_layers_over_few_pixels():
-    ks, regw, band = "hq_ksplit_kernel", "hq_regw_kernel", "hq_band_kernel"
-    check([("dynamic_fwd", conv(7, 16, 64, 3, 1, 64), ks), ("dynamic_fwd", conv(12, 16, 64, 3, 1, 64), band),
-           ("dynamic_dgrad", conv(64, 16, 64, 3, 1, 64), band), ("dynamic_fwd", conv(128, 16, 64, 3, 1, 64), regw),
-           ("dynamic_fwd", conv(64, 16, 64, 3, 1, 128), regw), ("dynamic_fwd", conv(300, 7, 64, 3, 1, 64), regw),
-           ("dynamic_fwd", conv(47, 16, 64, 3, 1, 64), regw),
-           ("fwd", conv(64, 16, 64, 3, 1, 64), regw)])
+def test_32_bit_pass_of_64_channel_layers():
+    ks, regw = "hq_ksplit_kernel", "hq_regw_kernel"
+    check([("dynamic_fwd", conv(7, 16, 64, 3, 1, 64), ks), ("dynamic_dgrad", conv(64, 16, 64, 3, 1, 64), ks),
+           ("dynamic_fwd", conv(65, 16, 64, 3, 1, 64), regw), ("dynamic_fwd", conv(64, 16, 64, 3, 1, 128), regw),
+           ("dynamic_fwd", conv(340, 7, 64, 3, 1, 64), regw)])
 
 
 def test_32_bit_pass_of_first_layers_stores_whole_lines():
@@ -226,7 +228,7 @@ def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_for():
     assert all(regw(op, s) for s in T.REGW_ALL_MODES for op in ("dynamic_fwd", "dynamic_dgrad", "fwd", "dgrad", "dgrad_sr"))
     assert all(regw("fwd", s) for s in T.REGW_FORWARD)
     assert all(regw(op, s) for s in T.REGW_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
-    assert not any(regw(op, s) for s in T.REGW_PAST for op in ("dynamic_fwd", "fwd", "dgrad", "dgrad_sr"))
+    assert not any(regw(op, s) for s in T.REGW_PAST + T.REGW_ONE_ROUND for op in ("dynamic_fwd", "fwd", "dgrad", "dgrad_sr"))
     one, four = "hq_wgrad_small_kernel<1, 1, 4, 4>", "hq_wgrad_small_kernel<2, 2, 4, 2>"
     want = {"ws_1px": one, "ws_32_2145": one, "ws_32_300px": one, "ws_32_2304": one, "ws_64": four, "ws_64_256px": four, "past_ws_64": "zero_kernel",
             "past_ws_512": "zero_kernel", "ws_32x64": "hq_wgrad_small_kernel<1, 2, 8, 2>", "ws_8w": "hq_wgrad_small_kernel<1, 1, 8, 4>",

@@ -341,7 +341,13 @@ SMALL_LAUNCHES = [
     wl.LayerShape("ks_word_11x11_s3", wl.CONV, 2, 19, 22, 12, 11, 11, 3, 5, 20), wl.LayerShape("past_9x9", wl.CONV, 20, 14, 14, 16, 9, 9, 1, 4, 260),
     wl.conv("ks_word_s2_many", 24, 56, 36, 36, 3, stride=2), wl.conv("past_word_s2_1x1", 40, 56, 36, 36, 1, stride=2, pad=0),
     wl.conv("past_word_1x1", 26, 28, 56, 64, 1, pad=0),
-    wl.linear("ks_32x64_long", 2600, 592, 132), wl.linear("ks_64x64_long", 2000, 1424, 400), wl.conv("ks_64x64_s2", 13, 21, 256, 272, 3, stride=2)]
+    wl.linear("ks_32x64_long", 2600, 592, 132), wl.linear("ks_64x64_long", 2000, 1424, 400), wl.conv("ks_64x64_s2", 13, 21, 256, 272, 3, stride=2),
+    # past one round of 64 x 64 tiles, a second round, and the kernels behind it
+    wl.linear("ks_two_rounds_n32", 17000, 1040, 32), wl.linear("ks_two_rounds_n64", 17000, 1040, 52), wl.linear("past_two_rounds", 33000, 1040, 20),
+    wl.linear("past_256x32", 17000, 256, 32), wl.conv("past_256x32_3x3", 24, 28, 48, 32, 3), wl.conv("past_256x32_s2", 26, 56, 32, 48, 3, stride=2),
+    wl.conv("past_256x64_s2", 11, 56, 64, 48, 3, stride=2), wl.linear("past_stages", 2000, 256, 400), wl.linear("past_word", 2058, 76, 760),
+    wl.conv("past_band_pad0", 21, 30, 64, 64, 3, pad=0), wl.conv("past_band_s2", 86, 28, 64, 64, 3, stride=2), wl.conv("past_band_wide", 4, 70, 64, 64, 3, pad=0),
+    wl.conv("ks_word_64x32", 16, 14, 36, 100, 3), wl.conv("ks_word_64x32_rounds", 53, 28, 20, 16, 3)]
 
 
 @pytest.mark.parametrize("L", SMALL_LAUNCHES, ids=[l.name for l in SMALL_LAUNCHES])
@@ -365,12 +371,13 @@ def test_stochastic_tile_kernels(H, hq, L):
 # Weights in registers: units of 256 pixels that span rows and images in every way, the last one short.  The lists say what the
 # kernel takes of each shape (test_dispatch.py holds them to it): both directions in every mode, the forward pass, the input
 # gradient, or nothing.
-REGW_ALL_MODES = [(4, 40, 121, 64, 64), (700, 13, 1, 64, 64), (300, 16, 2, 64, 64)]       # widest image; narrowest ones; units over several images
-REGW_FORWARD = [(7, 31, 29, 64, 64), (131, 7, 7, 64, 64), (1, 65, 64, 64, 64), (33, 17, 19, 64, 128)]    # smallest launch; two channel blocks
+REGW_ALL_MODES = [(4, 40, 121, 64, 64), (1300, 13, 1, 64, 64), (530, 16, 2, 64, 64)]      # widest image; narrowest ones; units over several images
+REGW_FORWARD = [(19, 31, 29, 64, 64), (335, 7, 7, 64, 64), (1, 253, 65, 64, 64), (33, 17, 19, 64, 128)]  # smallest launches; two channel blocks
 REGW_BACKWARD = [(33, 17, 19, 128, 64)]                                                    # two channel blocks, stochastic too
 REGW_PAST = [(2, 40, 122, 64, 64), (4200, 1, 1, 64, 64), (1500, 3, 1, 64, 64), (20, 2, 125, 64, 128), (1, 40, 126, 64, 64), (1, 40, 128, 64, 64)]
+REGW_ONE_ROUND = [(700, 13, 1, 64, 64), (300, 16, 2, 64, 64), (7, 31, 29, 64, 64), (131, 7, 7, 64, 64), (1, 65, 64, 64, 64)]     # split reductions
 REGW_SHAPES = [wl.LayerShape("regw", wl.CONV, B, Hh, Ww, c, 3, 3, 1, 1, n)
-               for B, Hh, Ww, c, n in REGW_FORWARD + REGW_ALL_MODES + REGW_BACKWARD + REGW_PAST]
+               for B, Hh, Ww, c, n in REGW_FORWARD + REGW_ALL_MODES + REGW_BACKWARD + REGW_PAST + REGW_ONE_ROUND]
 
 
 @pytest.mark.parametrize("L", REGW_SHAPES, ids=["b%d_%dx%d_c%d_n%d" % (l.B, l.H, l.W, l.C, l.Cout) for l in REGW_SHAPES])
