@@ -298,7 +298,8 @@ __global__ __launch_bounds__(HQ_THREADS, (BKB == 64 && BM == 128 && ALIGNED ? 4 
         const int coff = c16 * 16;
         const int8_t *fill_src = reinterpret_cast<const int8_t *>(gemm_fill_rows.w[za & 0xff]);
         const int8_t *zero_src = reinterpret_cast<const int8_t *>(gemm_fill_rows.w[0]);
-        const int tapoff = (CLASSED ? -(tr * a.Ws + ts) : tr * a.Ws + ts) * a.Cs + coff;   // from the row's tap (0, 0)
+        // from the row's tap (0, 0); image rows may be long enough for it to pass 2 GB
+        const ptrdiff_t tapoff = (ptrdiff_t)(CLASSED ? -(tr * a.Ws + ts) : tr * a.Ws + ts) * a.Cs + coff;
 #pragma unroll
         for (int i = 0; i < AROWS; i++) {
             bool ok;

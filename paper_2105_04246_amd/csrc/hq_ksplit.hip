@@ -369,6 +369,8 @@ int hq_try_launch_ksplit(const hq_problem *p, int dgrad, const int8_t *A, const 
     a.wrow = (size_t)taps * a.Cs;
     // operands of hq_magic_div: pixels, offsets in a weight row, taps
     if (M * (unsigned)(a.Ho > a.Wo ? a.Ho : a.Wo) >= lim || (a.wrow + 64) * a.Cs >= lim || (a.wrow + 64) / a.Cs * p->S >= lim) return HQ_E_BADSHAPE;
+    // 32-bit offsets from a pixel's tap (0, 0)
+    if (((unsigned long long)p->R * a.Ws + p->S) * a.Cs >= lim / 2) return HQ_E_BADSHAPE;
     a.M = (int)M;
     const bool aligned = a.Cs % 16 == 0;
     a.cpt = a.Cs / 16;

@@ -355,6 +355,24 @@ def test_small_launches_and_the_lines_to_the_tile_kernels(H, hq, L):
     test_random_shapes_all_ops(H, hq, L)
 
 
+def test_filter_rows_more_than_2_gb_apart(H, hq):
+    """A filter's last row lies 2 GB behind its first: only every 512th column of the wide image is used, so a small image of these
+    columns has the same outputs."""
+    wide = wl.LayerShape("rows_2gb_apart", wl.CONV, 1, 3, 32768, 32768, 3, 1, 512, 0, 16)
+    L = wl.LayerShape("its_columns", wl.CONV, 1, 3, 64, 32768, 3, 1, 1, 0, 16)
+    X, W, _ = rand_layer_inputs(L, 17)
+    Xd, Wdev, track = H.DevTensor(X), H.DevWeights(L, W), H.TensorTrack(0.9, False)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    Xw = H.DevTensor(X)
+    Xw.codes = torch.randint(-128, 128, wl.in_shape(wide), dtype=torch.int8, device="cuda", generator=gen)
+    Xw.codes[:, :, ::512] = Xd.codes
+    for t in range(2):                                       # dynamic, fused
+        r, st = track.r.clone(), track.st.clone()
+        want, _ = track.step(L, "fwd", X, W, Xd, Wdev)
+        got, _ = H.gpu_quantized_op(wide, "fwd", Xw, Wdev, r, st, "fused" if t else "dynamic")
+        assert np.array_equal(got, want)
+
+
 # Stochastic rounding in the tile kernels, on both sides of the line between long and short stages.
 @pytest.mark.parametrize("L", [wl.conv("sr_long_classes", 11, 28, 68, 448, 3, stride=2), wl.conv("sr_short_classes", 11, 28, 68, 112, 3, stride=2),
                                wl.conv("sr_short_last_stage", 40, 28, 132, 288, 1, pad=0), wl.conv("sr_long", 40, 28, 132, 256, 1, pad=0),
