@@ -501,9 +501,9 @@ __device__ inline void hq_block_stats_commit_n(int mn, int mx, unsigned nlo, uns
         unsigned word = f < 2 ? 4u * f : 8u * (f - 1);
         asm volatile("" : "+v"(word));
         part += word;
-        if (lane % NW == 0) {                              // (a workgroup without values leaves the record as it is)
-            if (f == 0) atomicMin(reinterpret_cast<int *>(part), least);
-            if (f == 1) atomicMax(reinterpret_cast<int *>(part), ~least);
+        if (lane % NW == 0) {                              // (a workgroup without values adds none)
+            if (f == 0 && least != INT_MAX) atomicMin(reinterpret_cast<int *>(part), least);
+            if (f == 1 && least != INT_MAX) atomicMax(reinterpret_cast<int *>(part), ~least);
             if ((f == 2 || f == 3) && sum) atomicAdd(reinterpret_cast<unsigned long long *>(part), (unsigned long long)(unsigned)sum);
         }
     }
