@@ -1109,6 +1109,14 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
                 break;
             rows = r;
         }
+        // Small launches: bands short enough for 64 workgroups, since one's bands are a serial chain; more of them only add their sums to the
+        // same lines (7x7, whole call, bands of as many rows as fit / for 64 / for 512 workgroups: 32 x 32 x 3 -> 32, one image 15.5 /
+        // 11.7 / 11.6 us, two of 64 x 64 15.1 / 12.5 / 12.6, five of 28 x 28 -> 64 15.8 / 14.4 / 16.3, 16 of 64 x 64 23.1 / 23.0 / 33.1).
+        rows = std::min(rows, (int)(((long)p->B * OH + 63) / 64));
+        // Sums of 48 KB and more over few pixels: the kernel with packed columns has less to clear and to add up (this / that, 8x8 on
+        // 32 x 32: x 4 -> 64, one image 17.2 / 14.2 us, four 17.7 / 14.9, six 18.2 / 16.6; x 3 -> 64, four 15.9 / 15.5, six 16.2 / 17.5; x 3 -> 48,
+        // 36 KB, four 14.5 / 14.8).
+        if (p->stride % 2 && (size_t)a.N * K >= 12288 && a.M < 6000) rows = 0;
         if (rows >= 1 && (unsigned long long)p->B * OH * OW < (1ull << 31)) {
             sa.rows_out = rows;
             sa.in_rows = (rows - 1) * p->stride + p->R;
