@@ -82,6 +82,7 @@ template <int MODE>
 __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a)
 {
     constexpr int NT = RG_THREADS, NW = NT / 64, L = 16 / NW;            // loads per operand and stage
+    static_assert(L == 2, "a stage has four places for its loads");
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
     __shared__ int red[4 * NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -133,15 +134,17 @@ __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a
         lts = row_done ? 0 : tap_done ? lts + 1 : lts;
         ltr += row_done ? 1 : 0;
     };
-    for (int d = 0; d < 2; d++)
-        if (d < a.nst) {
-            locate(0); locate(1); advance();
+    // (two stages ahead, and never fewer than two: the launcher takes 8 stages or more)
+    for (int d = 0; d < 2; d++) {
 #pragma unroll
-            for (int k = 0; k < 2; k++) {
-                load_own(aptr[k], lds0 + d * RG_STAGE + 8192 * k);
-                load_base(wb, boff[k], lds0 + d * RG_STAGE + RG_BM * RG_BK + 8192 * k);
-            }
+        for (int k = 0; k < L; k++) locate(k);
+        advance();
+#pragma unroll
+        for (int k = 0; k < L; k++) {
+            load_own(aptr[k], lds0 + d * RG_STAGE + 8192 * k);
+            load_base(wb, boff[k], lds0 + d * RG_STAGE + RG_BM * RG_BK + 8192 * k);
         }
+    }
 
     const float acc_scale = __fmul_rn(a.aq->scale, a.bq->scale);
     HqEpilogue ep = {1.0f, 0.0f, 0.0f, 0.0f, true};
@@ -172,8 +175,7 @@ __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a
         acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[ks][j], af[ks][i], acc[i][j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
-    if (a.nst >= 2) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    else            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * L) : "memory");
     __syncthreads();
     fragments(0, 0);
     int cur = 0;
@@ -206,7 +208,7 @@ __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a
         if (MORE) load_base(wb, boff[1], dst + 24576);
     };
     for (int s = 2; s < a.nst; s++) stage(std::true_type(), std::true_type());
-    if (a.nst >= 2) stage(std::false_type(), std::true_type());
+    stage(std::false_type(), std::true_type());
     stage(std::false_type(), std::false_type());
 
     int mn = INT_MAX, mx = INT_MIN;

@@ -241,6 +241,9 @@ def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_for():
     assert all(regw("fwd", s) for s in T.REGW_FORWARD)
     assert all(regw(op, s) for s in T.REGW_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
     assert not any(regw(op, s) for s in T.REGW_PAST + T.REGW_ONE_ROUND for op in ("dynamic_fwd", "fwd", "dgrad", "dgrad_sr"))
+    for L in T.RING_BACKWARD:
+        check([(op, tuple(L)[1:], "hq_ring_kernel") for op in ("dgrad", "dgrad_sr", "dynamic_dgrad")])
+    check([("dgrad", tuple(L)[1:], "hq_ring_kernel") for L in T.RING_ONE_TAP])
     one, four = "hq_wgrad_small_kernel<1, 1, 4, 4>", "hq_wgrad_small_kernel<2, 2, 4, 2>"
     want = {"ws_1px": one, "ws_32_2145": one, "ws_32_300px": one, "ws_32_2304": one, "ws_64": four, "ws_64_256px": four, "past_ws_64": "zero_kernel",
             "past_ws_512": "zero_kernel", "ws_32x64": "hq_wgrad_small_kernel<1, 2, 8, 2>", "ws_8w": "hq_wgrad_small_kernel<1, 1, 8, 4>",

@@ -433,12 +433,15 @@ def test_whole_lines_per_stage(H, hq, L):
             g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
-# Input gradients of one tap: channels and pixels off the tile, the shortest reduction, images; in the last column and band of tiles.
+# Input gradients: mirrored taps and channels off the tile, more tiles than are resident; one tap: channels and pixels off the tile, the
+# shortest reduction, images, bands of tiles.
+RING_BACKWARD = [wl.conv("ring_dgrad_n144", 34, 13, 144, 128, 3), wl.conv("ring_dgrad_n272", 20, 18, 272, 128, 3, pad=0),
+                 wl.conv("ring_dgrad_5x5", 17, 23, 208, 256, 5), wl.conv("ring_two_rounds", 257, 16, 128, 128, 3)]
 RING_ONE_TAP = [wl.linear("ring_dgrad_8_lines", 6700, 272, 1024), wl.linear("ring_dgrad_bands", 1700, 1168, 1280), wl.conv("ring_dgrad_1x1", 34, 14, 144, 1280, 1, pad=0)]
 
 
-@pytest.mark.parametrize("L", RING_ONE_TAP, ids=[l.name for l in RING_ONE_TAP])
-def test_whole_lines_of_one_tap(H, hq, L):
+@pytest.mark.parametrize("L", RING_BACKWARD + RING_ONE_TAP, ids=[l.name for l in RING_BACKWARD + RING_ONE_TAP])
+def test_whole_lines_backward(H, hq, L):
     track, Wdev = H.TensorTrack(0.9, True), None
     for t in range(3):                                       # dynamic, nearest, stochastic
         _, W, dY = rand_layer_inputs(L, 130 + t, g_asym=True)
