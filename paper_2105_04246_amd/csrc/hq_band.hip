@@ -62,8 +62,6 @@ struct BandArgs {
 
 constexpr int BM = 256;            // output pixels per tile: 4 wavefronts x 2 MFMA row blocks
 
-__device__ inline int sigma32(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
-
 template <int C> __device__ inline int wswz(int i)
 {
     return (C % 128 == 0) ? (i & 7) : (C % 64 == 0) ? ((i >> 2) & 3) : ((i >> 3) & 1);
@@ -110,7 +108,7 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void hq_band_kernel(cons
         for (int k = 0; k < WB; k++) {
             const int lin = base + tid + BAND_THREADS * k, idx = rotated(lin);
             const int cq = idx % NCH, t = (idx / NCH) % TAPS, row = idx / (NCH * TAPS);
-            const int n = (row & ~31) + sigma32(row & 31);
+            const int n = (row & ~31) + hq_sigma32(row & 31);
             const int tsrc = a.flip ? TAPS - 1 - t : t;
             wv[k] = v4i{0, 0, 0, 0};
             if (lin < wchunks && n < a.N)

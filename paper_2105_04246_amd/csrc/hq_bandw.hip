@@ -50,20 +50,6 @@ struct BandwArgs {
     HqSr sr;                       // seed of stochastic rounding (epilogue mode 2)
 };
 
-// 16-byte rows of one repeated byte value, indexed by that value: the source of the lanes of a direct-to-LDS
-// load that lie outside the image (zero-point code) or beyond the weight tensor (0), so that every lane of
-// every load has an address and a wavefront's count of outstanding loads does not depend on its data.
-struct BwFillRows {
-    unsigned w[256][4];
-    constexpr BwFillRows() : w()
-    {
-        for (int v = 0; v < 256; v++)
-            for (int k = 0; k < 4; k++) w[v][k] = (unsigned)v * 0x01010101u;
-    }
-};
-__device__ const BwFillRows bw_fill_rows = BwFillRows();
-
-__device__ inline int bw_sigma32(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
 __device__ inline int bw_swz(int row) { return (row >> 2) & 3; }
 
 // MODE: 0 = 32-bit outputs, 1 = fused requantization with round-half-even, 2 = fused with
@@ -82,8 +68,8 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_bandw_kernel(const BandwArgs
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);         // scalar: branches on it are uniform
     const int za = a.aq->zero_point;
-    const int8_t *fill_src = reinterpret_cast<const int8_t *>(bw_fill_rows.w[za & 0xff]);
-    const int8_t *zero_src = reinterpret_cast<const int8_t *>(bw_fill_rows.w[0]);
+    const int8_t *fill_src = reinterpret_cast<const int8_t *>(hq_fill_rows.w[za & 0xff]);
+    const int8_t *zero_src = reinterpret_cast<const int8_t *>(hq_fill_rows.w[0]);
     const float acc_scale = __fmul_rn(a.aq->scale, a.bq->scale);
     HqEpilogue ep = {1.0f, 0.0f, 0.0f, 0.0f, true};
     if (FUSED) ep = hq_make_epilogue(acc_scale, a.range);
@@ -134,7 +120,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_bandw_kernel(const BandwArgs
 #pragma unroll
         for (int k = 0; k < 2; k++) {
             const int q = tid + HQ_THREADS * k, row = q >> 2, ck = (q & 3) ^ bw_swz(row);
-            const int n = n0 + (row & ~31) + bw_sigma32(row & 31);
+            const int n = n0 + (row & ~31) + hq_sigma32(row & 31);
             wrow_ok[k] = n < a.N;
             wsrc[k] = a.Bw + (size_t)(wrow_ok[k] ? n : 0) * wrow + ck * 16;
         }

@@ -236,14 +236,42 @@ __device__ inline float hq_round_scaled(int c, float mult) { return rintf(__fmul
 // itself, waits for every outstanding LDS read before using any of them (it stops counting them), which
 // defeats fragment double buffering in the loops that follow.  The caller waits for the load with an explicit
 // "s_waitcnt vmcnt(..)" before a barrier; the compiler's own counts stay safe because loads retire in order.
-__device__ inline void hq_global_to_lds16(const void *src, void *wave_base)
+__device__ inline void hq_lds_load16(const void *src, unsigned dst)                        // (dst: LDS address, uniform)
 {
-    const unsigned m = __builtin_amdgcn_readfirstlane(
-        (unsigned)(size_t)(__attribute__((address_space(3))) void *)wave_base);
     unsigned keep;
     asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(keep) : "v"(src), "s"(m) : "memory");
+                 : "=&s"(keep) : "v"(src), "s"(dst) : "memory");
 }
+// ... from a uniform base plus a lane's offset.
+__device__ inline void hq_lds_load16(const int8_t *base, unsigned off, unsigned dst)
+{
+    unsigned keep;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
+                 : "=&s"(keep) : "v"(off), "s"(base), "s"(dst) : "memory");
+}
+// ... to a pointer that is the same in all lanes.
+__device__ inline unsigned hq_lds_address(void *wave_base)
+{
+    return __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) void *)wave_base);
+}
+__device__ inline void hq_global_to_lds16(const void *src, void *wave_base) { hq_lds_load16(src, hq_lds_address(wave_base)); }
+__device__ inline void hq_global_to_lds16(const int8_t *base, unsigned off, void *wave_base) { hq_lds_load16(base, off, hq_lds_address(wave_base)); }
+
+// 16-byte rows of one repeated byte value, indexed by that value: what lanes of such a load read that have no source (outside the
+// image: the zero-point code; past the reduction or the weights: 0), so that every lane has an address and a wavefront's count of
+// outstanding loads does not depend on its data.
+struct HqFillRows {
+    unsigned w[256][4];
+    constexpr HqFillRows() : w()
+    {
+        for (int v = 0; v < 256; v++)
+            for (int k = 0; k < 4; k++) w[v][k] = (unsigned)v * 0x01010101u;
+    }
+};
+static __device__ const HqFillRows hq_fill_rows = HqFillRows();
+
+// Row of a 32-row operand block that LDS row i holds, so that a lane of the 32 x 32 MFMA's result has 16 consecutive channels.
+__device__ inline int hq_sigma32(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
 
 typedef __attribute__((__vector_size__(2 * sizeof(int)))) int tr_v2i;
 #define LDS_PTR(T) __attribute__((address_space(3))) T *

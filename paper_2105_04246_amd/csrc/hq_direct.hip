@@ -38,8 +38,6 @@ struct DirectArgs {
     int tiles;                     // tiles of 32 * DR_MI pixels
 };
 
-__device__ inline int dr_sigma32(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
-
 // NT: 32-channel blocks of the output (N <= 32 * NT).  CH: input channels, 4 (a tap is one aligned word) or 3.
 template <int NT, bool FUSED, int CH>
 __global__ __launch_bounds__(HQ_THREADS, 2) void hq_direct_kernel(const DirectArgs a)
@@ -58,7 +56,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_direct_kernel(const DirectAr
     v4i wf[DR_MAXR][NT];
 #pragma unroll
     for (int j = 0; j < NT; j++) {
-        const int n = j * 32 + dr_sigma32(lane & 31);
+        const int n = j * 32 + hq_sigma32(lane & 31);
 #pragma unroll
         for (int r = 0; r < DR_MAXR; r++) {
             v4i v = {0, 0, 0, 0};
@@ -271,7 +269,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_stem_kernel(const StemArgs s
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < NT; j++) {
-            const int n = j * 32 + (LINES ? lane & 31 : dr_sigma32(lane & 31));
+            const int n = j * 32 + (LINES ? lane & 31 : hq_sigma32(lane & 31));
 #pragma unroll
             for (int r = 0; r < DR_MAXR; r++) {
                 v4i v = {0, 0, 0, 0};

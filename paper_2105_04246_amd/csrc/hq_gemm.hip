@@ -39,19 +39,6 @@
 
 namespace {
 
-// 16-byte rows of one repeated byte value, indexed by that value: the source of the lanes of a direct-to-LDS
-// load that have no source of their own (padding taps: zero-point code; rows and chunks past the end: 0), so
-// that a stage's loads need no branch per row.
-struct GemmFillRows {
-    unsigned w[256][4];
-    constexpr GemmFillRows() : w()
-    {
-        for (int v = 0; v < 256; v++)
-            for (int k = 0; k < 4; k++) w[v][k] = (unsigned)v * 0x01010101u;
-    }
-};
-__device__ const GemmFillRows gemm_fill_rows = GemmFillRows();
-
 // Class form of a strided input gradient: output pixels with (y mod stride, x mod stride) = (ph, pw) see the
 // same taps; such a class is an image of Hc x Wc pixels under a stride-1 stencil of nr x ns taps.
 struct GemmClass {
@@ -90,8 +77,6 @@ struct GemmArgs {
     int magic_ok;                  // the decode's operands are in hq_magic_div's range; 0: plain division
     HqSr sr;                       // MODE 2: seed of the stochastic rounding
 };
-
-__device__ inline int sigma32(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
 
 // BKB: bytes of reduction per stage.  STRIDED: input gradient of a strided layer (gather with
 // exact-division test); otherwise the stencil form.  ALIGNED: Cs % 16 == 0 (16-byte loads, one tap per chunk).
@@ -275,7 +260,7 @@ __global__ __launch_bounds__(HQ_THREADS, (BKB == 64 && BM == 128 && ALIGNED ? 4 
 #pragma unroll
     for (int i = 0; i < BROWS; i++) {
         const int row = lrow + RPP * i;                   // LDS row; holds channel sigma-permuted in its 32-block
-        const int n = n0 + (row & ~31) + sigma32(row & 31);
+        const int n = n0 + (row & ~31) + hq_sigma32(row & 31);
         brow_ok[i] = row < BN && n < a.N;
         bbase[i] = a.Bw + (size_t)(brow_ok[i] ? n : 0) * brow_len;
     }
@@ -296,8 +281,8 @@ __global__ __launch_bounds__(HQ_THREADS, (BKB == 64 && BM == 128 && ALIGNED ? 4 
     auto issue_stage = [&](int buf) {
         const bool chunk_ok = chunk < nchunks;
         const int coff = c16 * 16;
-        const int8_t *fill_src = reinterpret_cast<const int8_t *>(gemm_fill_rows.w[za & 0xff]);
-        const int8_t *zero_src = reinterpret_cast<const int8_t *>(gemm_fill_rows.w[0]);
+        const int8_t *fill_src = reinterpret_cast<const int8_t *>(hq_fill_rows.w[za & 0xff]);
+        const int8_t *zero_src = reinterpret_cast<const int8_t *>(hq_fill_rows.w[0]);
         // from the row's tap (0, 0); image rows may be long enough for it to pass 2 GB
         const ptrdiff_t tapoff = (ptrdiff_t)(CLASSED ? -(tr * a.Ws + ts) : tr * a.Ws + ts) * a.Cs + coff;
 #pragma unroll

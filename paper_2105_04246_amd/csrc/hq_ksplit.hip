@@ -28,18 +28,6 @@
 
 namespace {
 
-// 16-byte rows of one repeated byte: where a lane without a source reads (padding taps: zero-point code; chunks past
-// the reduction's end: 0).
-struct KsFillRows {
-    unsigned w[256][4];
-    constexpr KsFillRows() : w()
-    {
-        for (int v = 0; v < 256; v++)
-            for (int k = 0; k < 4; k++) w[v][k] = (unsigned)v * 0x01010101u;
-    }
-};
-__device__ const KsFillRows ks_fill_rows = KsFillRows();
-
 struct KsClass {
     int ph, pw, Hc, Wc;            // pixels (ph + ostep * y, pw + ostep * x) of the output image, y < Hc, x < Wc
     int ns, taps;                  // taps per row of the class's tap grid, taps in all
@@ -117,8 +105,8 @@ __global__ __launch_bounds__(NW * 64) void hq_ksplit_kernel(const KsArgs a)
     };
 
     const int za = a.aq->zero_point;
-    const int8_t *fill = reinterpret_cast<const int8_t *>(ks_fill_rows.w[za & 0xff]);
-    const int8_t *zero = reinterpret_cast<const int8_t *>(ks_fill_rows.w[0]);
+    const int8_t *fill = reinterpret_cast<const int8_t *>(hq_fill_rows.w[za & 0xff]);
+    const int8_t *zero = reinterpret_cast<const int8_t *>(hq_fill_rows.w[0]);
     if (a.classed && tid < TN) bzs[tid] = 0;
 
     // per pixel of the lane: its source pixel and address of tap (0, 0)

@@ -22,9 +22,6 @@ namespace {
 
 constexpr int RW_THREADS = 512, RW_UNIT = 256, RW_PITCH = 80, RW_LOADS = 10;   // loads: 64 slots of 16 bytes of a patch row each
 
-struct RegwFillRow { unsigned w[256][4]; constexpr RegwFillRow() : w() { for (int v = 0; v < 256; v++) for (int k = 0; k < 4; k++) w[v][k] = (unsigned)v * 0x01010101u; } };
-__device__ const RegwFillRow regw_fill_rows = RegwFillRow();
-
 struct RegwArgs {
     const int8_t *A, *Bw;
     const int32_t *bsum;
@@ -42,17 +39,6 @@ struct RegwArgs {
     float inv_W, inv_H;
     HqSr sr;
 };
-
-__device__ inline int sigma32(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
-
-// 16 bytes per lane from a uniform base plus a lane offset straight into LDS (see hq_global_to_lds16).
-__device__ inline void global_to_lds16(const int8_t *base, unsigned off, void *wave_base)
-{
-    const unsigned m = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) void *)wave_base);
-    unsigned keep;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
-                 : "=&s"(keep) : "v"(off), "s"(base), "s"(m) : "memory");
-}
 
 template <int MODE>
 __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a)
@@ -95,13 +81,13 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
             const int pad = g0 + 2 * b0 + pr;                        // row of the padded images
             const int img = (int)hq_magic_div((unsigned)pad, a.magic_H2), y = pad - img * (a.H + 2) - 1;
             const bool in = y >= 0 && y < a.H;
-            const int8_t *src = in ? a.A + ((size_t)img * a.H + y) * a.W * CB : reinterpret_cast<const int8_t *>(regw_fill_rows.w[za & 0xff]);
+            const int8_t *src = in ? a.A + ((size_t)img * a.H + y) * a.W * CB : reinterpret_cast<const int8_t *>(hq_fill_rows.w[za & 0xff]);
             int8_t *dst = smem + buf * bufbytes + pr * rowpitch;
 #pragma unroll
             for (int k = 0; k < RW_LOADS; k++)
             {
                 if (k >= nload) break;
-                if ((lmask >> k) & 1) global_to_lds16(src, in ? loff[k] : 0u, dst + 1024 * k);
+                if ((lmask >> k) & 1) hq_global_to_lds16(src, in ? loff[k] : 0u, dst + 1024 * k);
             }
         }
     };
@@ -124,12 +110,12 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
     if (tid < 64) bias[tid] = -za * bz;
     // Weights of this workgroup's 64 channels.  A fragment's 32 rows lie far apart, so loading them costs 64 cache lines a
     // KB: every wavefront fetches an eighth of the 36 fragments into LDS, where all read them from.  Row i of a fragment is
-    // channel sigma32(i), so that a lane ends up with 16 consecutive output channels; channel i for 32-bit outputs, whose
+    // channel hq_sigma32(i), so that a lane ends up with 16 consecutive output channels; channel i for 32-bit outputs, whose
     // products are formed transposed (see finish).
     v4i wf[9][KC][2];
     {
         int8_t *frags = smem + bufbytes;                             // the second buffer is not needed yet
-        const int8_t *wrow = a.Bw + (size_t)(n0 + (MODE == 0 ? lane & 31 : sigma32(lane & 31))) * 9 * CB + 16 * half;
+        const int8_t *wrow = a.Bw + (size_t)(n0 + (MODE == 0 ? lane & 31 : hq_sigma32(lane & 31))) * 9 * CB + 16 * half;
         for (int f = wave; f < 9 * KC * 2; f += RW_THREADS / 64) {
             const int nb = f & 1, kc = (f >> 1) % KC, t = (f >> 1) / KC;
             hq_global_to_lds16(wrow + (size_t)32 * nb * 9 * CB + (a.flip ? 8 - t : t) * CB + 32 * kc, frags + 1024 * f);

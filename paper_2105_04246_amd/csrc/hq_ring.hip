@@ -29,17 +29,6 @@ namespace {
 constexpr int RG_THREADS = 512, RG_BM = 128, RG_BN = 128, RG_BK = 128;   // tile, bytes of the reduction per stage
 constexpr int RG_STAGE = (RG_BM + RG_BN) * RG_BK;
 
-// 16-byte rows of one repeated byte: where lanes of padding taps read (zero-point code).
-struct RgFillRows {
-    unsigned w[256][4];
-    constexpr RgFillRows() : w()
-    {
-        for (int v = 0; v < 256; v++)
-            for (int k = 0; k < 4; k++) w[v][k] = (unsigned)v * 0x01010101u;
-    }
-};
-__device__ const RgFillRows rg_fill_rows = RgFillRows();
-
 struct RingArgs {
     const int8_t *A, *Bw;
     const int32_t *bsum;
@@ -60,23 +49,6 @@ struct RingArgs {
     int m_tiles, n_tiles;
     HqSr sr;
 };
-
-__device__ inline int sigma32(int i) { return ((i >> 2) & 1) * 16 + (i >> 3) * 4 + (i & 3); }
-
-// Direct-to-LDS loads, 16 bytes per lane to the LDS address `dst` (see hq_global_to_lds16): from addresses of the lanes' own, and from
-// a uniform base plus a lane offset.
-__device__ inline void load_own(const int8_t *p, unsigned dst)
-{
-    unsigned keep;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(keep) : "v"(p), "s"(dst) : "memory");
-}
-__device__ inline void load_base(const int8_t *base, unsigned off, unsigned dst)
-{
-    unsigned keep;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
-                 : "=&s"(keep) : "v"(off), "s"(base), "s"(dst) : "memory");
-}
 
 template <int MODE>
 __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a)
@@ -102,7 +74,7 @@ __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a
     const int m0 = tile_m * RG_BM, n0 = tile_n * RG_BN;
 
     const int za = a.aq->zero_point;
-    const int8_t *fill = reinterpret_cast<const int8_t *>(rg_fill_rows.w[za & 0xff]);
+    const int8_t *fill = reinterpret_cast<const int8_t *>(hq_fill_rows.w[za & 0xff]);
 
     // ---- loads: blocks of 8 rows, whole 128-byte lines; lane l lands at 16 * l, the chunks of a row are XOR-swizzled by the row
     const int8_t *arow[L], *aptr[L];
@@ -116,7 +88,7 @@ __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a
         ay[k] = (int)(t - b * (unsigned)a.Ho) * a.istep - a.pad;
         ax[k] = (int)(m - t * (unsigned)a.Wo) * a.istep - a.pad;
         arow[k] = a.A + ((ptrdiff_t)((ptrdiff_t)b * a.Hs + ay[k]) * a.Ws + ax[k]) * a.Cs + 16 * chunk;
-        const int n = n0 + (row & ~31) + sigma32(row & 31);
+        const int n = n0 + (row & ~31) + hq_sigma32(row & 31);
         boff[k] = (unsigned)(n < a.N ? n : 0) * a.wrow + 16u * (unsigned)chunk;
     }
     int lc = 0, ltr = 0, lts = 0;                                        // channel and tap of the next stage to load
@@ -141,8 +113,8 @@ __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a
         advance();
 #pragma unroll
         for (int k = 0; k < L; k++) {
-            load_own(aptr[k], lds0 + d * RG_STAGE + 8192 * k);
-            load_base(wb, boff[k], lds0 + d * RG_STAGE + RG_BM * RG_BK + 8192 * k);
+            hq_lds_load16(aptr[k], lds0 + d * RG_STAGE + 8192 * k);
+            hq_lds_load16(wb, boff[k], lds0 + d * RG_STAGE + RG_BM * RG_BK + 8192 * k);
         }
     }
 
@@ -199,13 +171,13 @@ __global__ __launch_bounds__(RG_THREADS, 4) void hq_ring_kernel(const RingArgs a
             fragments(cur, 0);
         }
         multiply(1, 0, 0);
-        if (MORE) load_own(aptr[0], dst);
+        if (MORE) hq_lds_load16(aptr[0], dst);
         multiply(1, 0, 1);
-        if (MORE) load_own(aptr[1], dst + 8192);
+        if (MORE) hq_lds_load16(aptr[1], dst + 8192);
         multiply(1, 1, 0);
-        if (MORE) load_base(wb, boff[0], dst + 16384);
+        if (MORE) hq_lds_load16(wb, boff[0], dst + 16384);
         multiply(1, 1, 1);
-        if (MORE) load_base(wb, boff[1], dst + 24576);
+        if (MORE) hq_lds_load16(wb, boff[1], dst + 24576);
     };
     for (int s = 2; s < a.nst; s++) stage(std::true_type(), std::true_type());
     stage(std::false_type(), std::true_type());
