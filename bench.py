@@ -163,22 +163,31 @@ def kernel_family(wl, L, op):
     """Name of the kernel the library's dispatch picks for one launch (mirrors the rules of hq_api.hip / the launchers)."""
     k3 = L.kind == wl.CONV and L.R == 3 and L.S == 3 and L.stride == 1 and L.pad == 1
     first = L.kind == wl.CONV and L.C in (3, 4)
-    staged = first and L.stride % 2 == 0 and L.W % 4 == 0 and L.S <= 8        # input rows staged in LDS
+    staged = first and L.W % 4 == 0 and L.S <= 8                              # input rows staged in LDS
+    oh, ow = (L.H + 2 * L.pad - L.R) // L.stride + 1, (L.W + 2 * L.pad - L.S) // L.stride + 1
+    up = lambda x, n: -(-x // n)
     if op == "wgrad":
+        if up(L.Cout, 64) * up(L.R * L.S * L.C, 64) >= 64 and L.B * oh * ow <= 1024 and not first:
+            return "hq_wgrad_small_kernel"
         if k3 and L.C % 64 == 0 and L.Cout % 64 == 0:
             return "hq_wgrad_band_kernel + wband_finalize_kernel"
-        if first and L.W % 4 == 0 and L.S <= 8 and L.R <= 8 and L.Cout <= 64 and L.Cout % 16 == 0:
+        if staged and L.R <= 8 and L.Cout <= 64 and L.Cout % 16 == 0:
             return "hq_wgrad_stem_kernel + wgrad_finalize_kernel"
         return "hq_wgrad_kernel + wgrad_finalize_kernel"
-    cin = L.Cout if op == "dgrad" else L.C
-    cout = L.C if op == "dgrad" else L.Cout
     if op == "fwd" and first:
         return "hq_stem_kernel" if staged else "hq_direct_kernel"
-    oh, ow = (L.H + 2 * L.pad - L.R) // L.stride + 1, (L.W + 2 * L.pad - L.S) // L.stride + 1
-    tiles = -(-L.B * (oh * ow if op == "fwd" else L.H * L.W) // 128) * -(-cout // 128)
-    if (cin % 128 == 0 and cout % 16 == 0 and cout >= 128 and L.R * L.S * cin >= 1024 and 64 < tiles and (tiles <= 512 or not k3) and
-            (op == "fwd" or (L.stride == 1 and L.R == L.S > 1))):
-        return "hq_ring_kernel"
+    cin, cout = (L.Cout, L.C) if op == "dgrad" else (L.C, L.Cout)
+    taps, strided = L.R * L.S, op == "dgrad" and (L.stride > 1 or L.R != L.S)
+    pixels = L.B * (oh * ow if op == "fwd" else L.H * L.W)
+    small, tiles = up(pixels, 64) * up(cout, 64), up(pixels, 128) * up(cout, 128)
+    if small <= 256 and not (taps == 1 and not strided and cout > 64 and 256 <= cin < 512):
+        return "hq_ksplit_kernel"
+    if cin % 128 == 0 and cout % 16 == 0 and cout >= 128 and taps * cin >= 1024 and tiles > 64 and not strided and (taps > 1 or small > 512 or taps * cin >= 1280):
+        rows, images = (max(1, min(256 // L.W, L.H)), 1) if L.H * L.W > 128 else (L.H, 256 // (L.H * L.W))
+        items = (up(L.B, images) if images > 1 else L.B * up(L.H, rows)) * up(cout, 128)
+        two = images * (rows + 2) * (L.W + 2) <= 376                          # row tiles: two workgroups to a compute unit
+        if not (k3 and two and tiles > 512 and up(tiles, 256) >= 2 * up(items, 256)):
+            return "hq_ring_kernel"
     if k3 and cin % 64 == 0 and cin >= 128 and cout >= 128:
         return "hq_bandw_kernel"
     if k3 and cin == 64:

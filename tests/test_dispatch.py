@@ -252,3 +252,12 @@ def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_for():
     assert len(lines) == len(want)
     for L, got in zip(lines, launches.calls([("wgrad", tuple(L)[1:]) for L in lines])):
         assert got[0].kernel == want[L.name], (L.name, got[0].kernel)
+
+
+def test_names_in_the_benchmark_follow_the_dispatch():
+    import bench
+    import workloads as wl
+    work = [(op, L) for net in (wl.resnet18_layers(B=256), wl.vgg16_layers(B=256)) for i, L in enumerate(net) for op in ("fwd", "dgrad", "wgrad") if i or op != "dgrad"]
+    for (op, L), got in zip(work, launches.calls([(op, tuple(L)[1:]) for op, L in work])):
+        names = [l.kernel.split("<")[0] for l in got if l.kernel != "zero_kernel"]
+        assert bench.kernel_family(wl, L, op) == " + ".join(names), (op, L, names)
