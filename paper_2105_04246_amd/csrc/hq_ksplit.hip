@@ -14,7 +14,7 @@
 // What is left is fixed: of the 16 K cycles a 56x56x64 launch then took (clock stamps), 1.1 K were its loads and matrix work, the
 // rest arguments and operands fetched one miss after the other (2 + 1.2 K), a mask of every pixel's taps (5 K), loads of steps
 // past the end, divisions and statistics (2 K).  Those are gone, requested together, or moved under the first loads: 10 K
-// cycles, ResNet-18's forward pass at batch 1 155 -> 119 us, its step on 32 images of 64x64 525 -> 425 us.
+// cycles, ResNet-18's forward pass at batch 1 155 -> 119 us, its step on 32 images of 64x64 525 -> 438 us.
 //
 // Both operations are  out[m][n] = sum_{tap,c} A[pix(m,tap)][c] * Bw[n][tap][c]  as in the gather kernel, with the
 // same class form for strided input gradients (an output pixel's class fixes its taps; everything else is one class).

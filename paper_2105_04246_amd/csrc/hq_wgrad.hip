@@ -361,6 +361,8 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
 // Measured, whole call with its clearing and finalizing launches (9 us), before -> now: 3x3 stride 1, 128 x 64 x 64 x 3 -> 64 (then one
 // tile column per 32 packed columns, loads of unaligned runs) 73.5 -> 36.4 us, 64 x 32 x 32 x 3 -> 32 40.5 -> 14.3, 5x5 on
 // 64 x 96 x 96 x 4 -> 48 63 -> 36; 3x3 stride 2, 128 x 112 x 112 x 3 -> 32 38.7 -> 27.1; 7x7 stride 2, 256 x 224 x 224 x 3 -> 64 135 -> 125.
+// Wide images, a band of one or two output rows whose input rows are staged again for the next: 3x3 stride 1, 224 x 224 x 3 -> 64 35.7 -> 18.1,
+// 5 x 224 x 224 x 3 -> 16 57.3 -> 21.4, 320 x 320 x 3 -> 32 46.2 -> 19.2; where no row fits (320 x 320 x 3 -> 64) the other kernel stays.
 // What bounds it now: small ones the 512 workgroups' atomics on the same lines (256 workgroups: 34 us for the first, but 199 for the
 // last), the 7x7 one its 76 vector instructions per k-step and wavefront (44 % of the time) and the wait for a band's loads.
 struct WstemArgs {
