@@ -283,8 +283,7 @@ __global__ __launch_bounds__(HQ_THREADS, (BKB == 64 && BM == 128 && ALIGNED ? 4 
         const int coff = c16 * 16;
         const int8_t *fill_src = reinterpret_cast<const int8_t *>(hq_fill_rows.w[za & 0xff]);
         const int8_t *zero_src = reinterpret_cast<const int8_t *>(hq_fill_rows.w[0]);
-        // from the row's tap (0, 0); image rows may be long enough for it to pass 2 GB
-        const ptrdiff_t tapoff = (ptrdiff_t)(CLASSED ? -(tr * a.Ws + ts) : tr * a.Ws + ts) * a.Cs + coff;
+        const int tapoff = (CLASSED ? -(tr * a.Ws + ts) : tr * a.Ws + ts) * a.Cs + coff;   // from the row's tap (0, 0)
 #pragma unroll
         for (int i = 0; i < AROWS; i++) {
             bool ok;
@@ -593,8 +592,11 @@ int hq_launch_gemm(const hq_problem *p, int dgrad, const int8_t *A, const hq_qpa
             strided = true; a.stride = p->stride; a.pad = p->pad; a.flip = 0;
         }
     }
-    // (the class form of the strided input gradient keeps at most 16 classes: larger strides take the 4-byte path)
-    const bool aligned = (a.Cs % 16) == 0 && !(strided && a.stride > 4);
+    // (the class form of the strided input gradient keeps at most 16 classes: larger strides take the 4-byte path; so do image rows
+    // so long that 32 bits do not hold a tap's offset from a pixel's first one, since that path's addresses have 64: in the loop
+    // of the 16-byte path they would cost stochastic input gradients 4 %)
+    const bool aligned = (a.Cs % 16) == 0 && !(strided && a.stride > 4) &&
+                         ((unsigned long long)p->R * a.Ws + p->S) * a.Cs < (1ull << 31);
     if (sr_seed && out32) return HQ_E_BADARG;
     const int mode = out32 ? 0 : sr_seed ? 2 : 1;
     if (sr_seed) { a.sr.k0 = (unsigned)*sr_seed; a.sr.k1 = (unsigned)(*sr_seed >> 32); } else { a.sr.k0 = a.sr.k1 = 0; }

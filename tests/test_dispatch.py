@@ -49,7 +49,7 @@ def test_filters_of_more_than_64_taps_are_split():
                   (CONV, 3, 13, 17, 20, 9, 8, 1, 4, 36), (CONV, 2, 19, 22, 12, 11, 11, 3, 5, 20)):
         check([(op, layer, ks) for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")])
     # (offsets from a pixel's first tap that pass 2 GB are outside its arithmetic)
-    check([("fwd", (CONV, 1, 3, 32768, 32768, 3, 1, 512, 0, 16), "hq_gemm_kernel"), ("fwd", (CONV, 1, 3, 21800, 32768, 3, 1, 512, 0, 16), ks)])
+    check([("fwd", (CONV, 1, 3, 32768, 32768, 3, 1, 512, 0, 16), "hq_gemm_kernel<256, 32, 4, 1, 64, false, false"), ("fwd", (CONV, 1, 3, 21800, 32768, 3, 1, 512, 0, 16), ks)])
     # (taps times taps per row past 2^32 are outside the kernel's divisions)
     check([("fwd", (CONV, 1, 1, 70000, 16, 1, 65600, 1, 0, 16), "hq_gemm_kernel"), ("fwd", (CONV, 1, 1, 66000, 16, 1, 65500, 1, 0, 16), ks)])
 
