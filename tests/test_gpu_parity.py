@@ -347,7 +347,7 @@ SMALL_LAUNCHES = [
     wl.linear("past_256x32", 17000, 256, 32), wl.conv("past_256x32_3x3", 24, 28, 48, 32, 3), wl.conv("past_256x32_s2", 26, 56, 32, 48, 3, stride=2),
     wl.conv("past_256x64_s2", 11, 56, 64, 48, 3, stride=2), wl.linear("past_stages", 2000, 256, 400), wl.linear("past_word", 2058, 76, 760),
     wl.conv("past_band_pad0", 21, 30, 64, 64, 3, pad=0), wl.conv("past_band_s2", 86, 28, 64, 64, 3, stride=2), wl.conv("past_band_wide", 4, 70, 64, 64, 3, pad=0),
-    wl.conv("ks_word_64x32", 16, 14, 36, 100, 3), wl.conv("ks_word_64x32_rounds", 53, 28, 20, 16, 3)]
+    wl.conv("ks_word_no_tap", 3, 21, 12, 20, 1, stride=2, pad=0), wl.conv("ks_word_64x32", 16, 14, 36, 100, 3), wl.conv("ks_word_64x32_rounds", 53, 28, 20, 16, 3)]
 
 
 @pytest.mark.parametrize("L", SMALL_LAUNCHES, ids=[l.name for l in SMALL_LAUNCHES])
