@@ -571,10 +571,10 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
     // after the last band's barrier) and go out as whole lines, each workgroup starting elsewhere.
     const int krow = a.R * a.S * CH, words = a.N * krow;
     int *sum = reinterpret_cast<int *>(ws_lds);
-    for (int q = tid; q < words; q += HQ_THREADS) sum[q] = 0;
-    __syncthreads();
     const int col = lane & 31, tap = col >> 2, ch = col & 3;
     const bool col_ok = tap < a.S && ch < CH;
+    // every word belongs to one lane and is stored, not added to a cleared one; two wavefronts that share the k-steps each have a copy
+    int *own = sum + (halves ? wk * words : 0);
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         const int r = row0 + j;
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
 #pragma unroll
         for (int e = 0; e < 16; e++) {
             const int n = wn * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-            if (n < a.N) atomicAdd(sum + n * krow + wc, acc[j][e]);
+            if (n < a.N) own[n * krow + wc] = acc[j][e];
         }
         if (do_xsum) {
             const int s = xs[j] + __shfl_xor(xs[j], 32);
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
     const int chunks = (words + HQ_THREADS - 1) / HQ_THREADS;
     int q = (int)(blockIdx.x % (unsigned)chunks) * HQ_THREADS + tid;
     for (int k = 0; k < chunks; k++) {
-        const int v = q < words ? sum[q] : 0;
+        const int v = q < words ? sum[q] + (halves ? sum[words + q] : 0) : 0;
         if (v != 0) atomicAdd(a.acc + q, v);
         q += HQ_THREADS;
         if (q >= chunks * HQ_THREADS) q -= chunks * HQ_THREADS;
@@ -1112,13 +1112,13 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
             rows = r;
         }
         // Small launches: bands short enough for 64 workgroups, since one's bands are a serial chain; more of them only add their sums to the
-        // same lines (7x7, whole call, bands of as many rows as fit / for 64 / for 512 workgroups: 32 x 32 x 3 -> 32, one image 15.5 /
-        // 11.7 / 11.6 us, two of 64 x 64 15.1 / 12.5 / 12.6, five of 28 x 28 -> 64 15.8 / 14.4 / 16.3, 16 of 64 x 64 23.1 / 23.0 / 33.1).
+        // same lines (7x7 stride 2 x 3, whole call, bands of as many rows as fit / for 64 workgroups: one image of 32 x 32 -> 32 12.9 /
+        // 11.2 us, six -> 64 14.9 / 12.9, 16 of 64 x 64 15.2 / 15.2; for 24 / 64 / 96 workgroups, two of 64 x 64 -> 32 11.7 / 11.2 / 11.2).
         rows = std::min(rows, (int)(((long)p->B * OH + 63) / 64));
-        // Sums of 48 KB and more over few pixels: the kernel with packed columns has less to clear and to add up (this / that, 8x8 on
-        // 32 x 32: x 4 -> 64, one image 17.2 / 14.2 us, four 17.7 / 14.9, six 18.2 / 16.6; x 3 -> 64, four 15.9 / 15.5, six 16.2 / 17.5; x 3 -> 48,
-        // 36 KB, four 14.5 / 14.8).
-        if (p->stride % 2 && (size_t)a.N * K >= 12288 && a.M < 6000) rows = 0;
+        // Sums of 56 KB and more over few pixels: the kernel with packed columns has less to add up (this / that, 8x8 x 4 -> 64: one image
+        // of 32 x 32 15.8 / 14.2 us, four 16.5 / 15.1, eight 16.9 / 18.5; stride 2, four of 64 x 64 16.5 / 15.1, 16 17.5 / 28.8; 7x7 x 4,
+        // 49 KB, one image 14.1 / 14.3; 8x8 x 3, 48 KB, 14.3 / 14.7).
+        if ((size_t)a.N * K >= 14336 && a.M < 6000) rows = 0;
         if (rows >= 1 && (unsigned long long)p->B * OH * OW < (1ull << 31)) {
             sa.rows_out = rows;
             sa.in_rows = (rows - 1) * p->stride + p->R;
@@ -1127,7 +1127,8 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
             sa.kpad = (rows * OW + 31) / 32 * 32;
             sa.bands_per_image = (OH + rows - 1) / rows;
             sa.nbands = p->B * sa.bands_per_image;
-            const size_t lds = std::max(2 * ((size_t)copies * sa.xrows * sa.LP + (size_t)sa.kpad * sa.gpitch) + 64, 4 * (size_t)a.N * K);
+            const size_t lds = std::max(2 * ((size_t)copies * sa.xrows * sa.LP + (size_t)sa.kpad * sa.gpitch) + 64,
+                                        (p->R <= 4 ? 8 : 4) * (size_t)a.N * K);
             static std::atomic<unsigned long long> allowed[2];
             if (!hq_allow_lds(hq_wgrad_stem_kernel<3>, 80 * 1024, allowed[0]) || !hq_allow_lds(hq_wgrad_stem_kernel<4>, 80 * 1024, allowed[1]))
                 return HQ_E_HIP;

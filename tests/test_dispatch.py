@@ -179,9 +179,10 @@ def test_small_first_layer_weight_gradients_are_cut_into_short_bands():
         return [(l.kernel.split("<")[0], l.blocks) for l in launches.calls([("wgrad", layer)])[0] if not l.kernel.startswith(("zero", "wgrad_finalize"))]
     assert blocks(CONV, 1, 32, 32, 3, 7, 7, 1, 3, 32) == [("hq_wgrad_stem_kernel", 32)] and blocks(CONV, 4, 32, 32, 3, 7, 7, 1, 3, 32) == [("hq_wgrad_stem_kernel", 64)]
     assert blocks(CONV, 5, 28, 28, 3, 7, 7, 1, 3, 64) == [("hq_wgrad_stem_kernel", 50)]          # 140 rows: bands of three
-    # large sums over few pixels under an odd stride
-    for B, c, n, stem in ((2, 4, 64, False), (23, 4, 64, False), (24, 4, 64, True), (2, 3, 64, False), (2, 3, 48, True), (2, 4, 32, True)):
-        assert (blocks(CONV, B, 12, 24, c, 8, 8, 1, 3, n)[0][0] == "hq_wgrad_stem_kernel") == stem, (B, c, n)
+    # large sums over few pixels, M = B * 11 * 23 under stride 1 and B * 7 * 13 under stride 2
+    for B, c, n, stride, stem in ((2, 4, 64, 1, False), (23, 4, 64, 1, False), (24, 4, 64, 1, True), (2, 3, 64, 1, True), (2, 4, 48, 1, True),
+                                  (65, 4, 64, 2, False), (66, 4, 64, 2, True)):
+        assert (blocks(CONV, B, 12, 24, c, 8, 8, stride, 4 if stride == 2 else 3, n)[0][0] == "hq_wgrad_stem_kernel") == stem, (B, c, n, stride)
 
 
 def test_column_sums_over_many_lines_are_shared():

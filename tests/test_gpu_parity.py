@@ -468,7 +468,8 @@ STEM_WGRAD = [wl.LayerShape("stem_wgrad", wl.CONV, B, Hh, Ww, C, R, S, st, pad, 
               for B, Hh, Ww, C, R, S, st, pad, N in ((40, 33, 64, 3, 3, 3, 1, 1, 64), (3, 120, 132, 3, 3, 3, 1, 1, 48), (2, 90, 68, 4, 5, 5, 1, 2, 32),
                                                      (5, 70, 72, 3, 3, 3, 2, 1, 16), (9, 61, 64, 3, 7, 7, 3, 3, 64), (4, 60, 60, 4, 4, 8, 1, 0, 64),
                                                      (3, 65, 64, 3, 8, 8, 1, 4, 64), (2, 224, 224, 3, 3, 3, 1, 1, 64),
-                                                     (1, 32, 32, 3, 7, 7, 1, 3, 32), (5, 28, 28, 3, 7, 7, 2, 3, 64), (2, 12, 24, 4, 8, 8, 1, 3, 64))]
+                                                     (1, 32, 32, 3, 7, 7, 1, 3, 32), (5, 28, 28, 3, 7, 7, 2, 3, 64), (2, 12, 24, 4, 8, 8, 1, 3, 64),
+                                                     (84, 12, 24, 4, 8, 8, 2, 4, 64), (2, 30, 32, 4, 4, 4, 2, 1, 64), (1, 9, 8, 4, 8, 7, 2, 3, 48))]
 
 
 @pytest.mark.parametrize("L", STEM_WGRAD, ids=["b%d_%dx%dx%d_%dx%d_s%d_n%d" % (l.B, l.H, l.W, l.C, l.R, l.S, l.stride, l.Cout) for l in STEM_WGRAD])
