@@ -301,9 +301,10 @@ int hq_try_launch_ring(const hq_problem *p, int dgrad, const int8_t *A, const hq
     // 10 % faster there (this / that, 16 x 16 x 256, images 192: 3 halves / 2 items 35.0 / 37.8 us, 256: 4 / 2 45.6 / 42.8, 320: 5 / 3
     // 56.3 / 62.1, 384: 6 / 3 67.2 / 64.8; 14 x 14 x 256, 240: 34.2 / 39.1, 256: 41.9 / 40.2, 280: 42.6 / 57.6; 28 x 28 x 128,
     // 128: 26.0 / 25.1, 256: 7 / 4 44.7 / 45.6), and where only one of its workgroups fits a compute unit it is never ahead (64 x 64
-    // x 128, 64 images 52.7 / 63.6).  Not with stochastic rounding, whose long epilogues its larger tiles overlap less (14 x 14 x
-    // 256, 256: 47.1 / 47.3; 16 x 16 x 256, 256: 50.8 / 50.0).
-    if (tiles > 512 && !sr_seed) {
+    // x 128, 64 images 52.7 / 63.6).  With stochastic rounding, whose long epilogues its larger tiles overlap less, from eight
+    // halves on (14 x 14 x 256, 256: 4 / 2 48.9 / 49.3; 16 x 16 x 256, 256: 4 / 2 55.6 / 55.8, 512: 8 / 4 99.5 / 95.5, 640: 10 / 5 124.9 /
+    // 120.4, 896: 14 / 7 167.9 / 158.4; 32 x 32 x 128, 256: 8 / 4 68.8 / 66.8, 320: 10 / 5 85.1 / 77.3, 384: 12 / 6 92.3 / 88.8).
+    if (tiles > (sr_seed ? 1792 : 512)) {
         const long items = hq_bandw_items(p, dgrad);
         if (items > 0 && (tiles + 255) / 256 >= 2 * ((items + 255) / 256)) return HQ_E_BADSHAPE;
     }

@@ -114,7 +114,7 @@ def test_whole_lines_per_stage_between_split_reductions_and_row_tiles():
 
 
 def test_row_tiles_stay_where_they_fill_their_half_rounds():
-    """Past 512 tiles of whole lines: halves of a round, 256 tiles each, against twice those of the row tiles' items."""
+    """Past 512 tiles of whole lines, 1792 with stochastic rounding: halves of a round, 256 tiles each, against twice those of the row tiles' items."""
     ring, bandw = "hq_ring_kernel", "hq_bandw_kernel"
     check([("fwd", conv(384, 16, 128, 3, 1, 128), ring), ("fwd", conv(385, 16, 128, 3, 1, 128), bandw),        # 768 and 770 tiles, 384 and 385 items
            ("dgrad", conv(384, 16, 128, 3, 1, 128), ring), ("dgrad", conv(385, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(385, 16, 128, 3, 1, 128), ring),
@@ -122,7 +122,10 @@ def test_row_tiles_stay_where_they_fill_their_half_rounds():
            ("fwd", conv(512, 16, 128, 3, 1, 128), bandw), ("fwd", conv(513, 16, 128, 3, 1, 128), ring),        # a third half round for one item
            ("fwd", conv(256, 14, 256, 3, 1, 256), bandw), ("fwd", conv(257, 14, 256, 3, 1, 256), ring),
            ("fwd", conv(512, 14, 128, 3, 1, 128), bandw), ("fwd", conv(480, 14, 128, 3, 1, 128), ring),        # 736 tiles
-           ("fwd", conv(32, 64, 128, 3, 1, 128), ring), ("fwd", conv(512, 8, 512, 3, 1, 512), ring)])          # one workgroup to a compute unit
+           ("fwd", conv(32, 64, 128, 3, 1, 128), ring), ("fwd", conv(512, 8, 512, 3, 1, 512), ring),           # one workgroup to a compute unit
+           ("dgrad_sr", conv(768, 16, 128, 3, 1, 128), ring), ("dgrad_sr", conv(1024, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(1152, 16, 128, 3, 1, 128), ring),
+           ("dgrad_sr", conv(1153, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(1025, 16, 128, 3, 1, 128), ring),
+           ("dgrad_sr", conv(128, 64, 128, 3, 1, 128), ring)])
 
 
 def test_whole_lines_of_one_tap_start_past_two_small_tiles_to_a_compute_unit():
