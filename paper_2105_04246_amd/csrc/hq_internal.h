@@ -85,6 +85,11 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
 int hq_try_launch_wgrad_small(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY,
                               const hq_qparams *gq, float *dW, int32_t *dW_acc, hipStream_t stream, const HqRideAlong *ride);
 
+// 3x3 stride-1 layers with channel counts that are multiples of 64; HQ_E_BADSHAPE: not covered.  ws: hq_wgrad_band_bytes (0: not covered).
+size_t hq_wgrad_band_bytes(const hq_problem *p);
+int hq_try_launch_wgrad_band(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY,
+                             const hq_qparams *gq, float *dW, int32_t *dW_acc, void *ws, hipStream_t stream, const HqRideAlong *ride);
+
 int hq_launch_depthwise_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY,
                               const hq_qparams *gq, float *dW, int32_t *dW_acc, void *ws, hipStream_t stream,
                               const HqRideAlong *ride = nullptr);

@@ -331,21 +331,6 @@ __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
 }
 
 // ---------------------------------------------------------------------------------------
-// 3x3, stride 1, pad 1, C % 64 == 0 and Cout % 64 == 0: the shape of most layers of the paper's
-// networks (Table 5; ResNet-18 basic blocks).  One workgroup owns a 64 (Cout) x 64 (C) block of
-// G_W for all nine taps (36 MFMA tiles, in registers for the whole launch) and walks a run of
-// pixel bands.  A band (a few output rows of one image, or a few whole small images) is
-// staged once: the dY rows as they lie in memory and the input rows with their one-pixel
-// border; the nine taps are nine shifted views of that input patch, so an input byte is
-// fetched once per band instead of once per tap.
-// The reduction index of an MFMA k-step is the output pixel; the transposing LDS read takes
-// a row address per lane, so each lane looks up the patch row of its pixels in a small
-// table (pixel -> row of tap (0,0)) and adds the tap's offset.
-// 512 threads: two groups of four wavefronts take alternate k-steps of a band (both groups
-// accumulate the same 36 tiles and are added through LDS at the end); inside a group a
-// wavefront owns one 32-channel block of C and taps 0..4 or 5..8 for both 32-blocks of Cout:
-// 7 fragments feed 10 MFMAs.
-// ---------------------------------------------------------------------------------------
 // Weight gradient of a network's first layer (3 or 4 input channels, W a multiple of 4, at most 8 filter rows and
 // 8 taps per filter row, at most 64 output channels in multiples of 16) with the input rows staged in LDS.
 // A workgroup walks bands of whole output rows.  The input rows of a band are copied into LDS once, every
@@ -607,271 +592,6 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
 }
 
 // ---------------------------------------------------------------------------------------
-constexpr int WB_THREADS = 512;
-constexpr int WB_P = 96;               // LDS pitch of a 64-channel pixel row (32 mod 64: transposing reads)
-constexpr int WB_XLD = 3, WB_GLD = 2;  // 16-byte chunks a thread stages per band (input patch / dY rows)
-constexpr int WB_SLOT_V4 = 2 * 5 * 4 * 256;   // 16-byte words of one workgroup's partial sums
-constexpr int WB_SUMS = 64 + 9 * 64;          // column sums a group of a workgroup leaves: dY [64], input [9][64]
-
-struct WbandArgs {
-    const int8_t *X, *G;
-    const hq_qparams *xq, *gq;
-    int32_t *partial;              // [slot][WB_SLOT_V4] 16-byte words: this workgroup's 64 x 9 x 64 sums
-    int32_t *sums;                 // [slot][2 groups][64 + 9 * 64]: column sums of dY and of the input taps
-    int B, H, W, C, N;
-    int rows, nimg;                // band: `rows` output rows of one image, or `nimg` whole images (rows == H)
-    int bands_per_img;
-    unsigned magic_bpi;            // ceil(2^32 / bands_per_img)
-    int nstages, stages_per_block, splits;
-    int cparts, nparts;            // C / 64, N / 64
-    int npix, npix_pad;            // output pixels of a band, rounded up to a k-step
-    int prows, PW;                 // patch rows (nimg * (rows + 2)) and patch row length (W + 2)
-    int xchunks, gchunks;          // 16-byte chunks of a patch / of a band of dY
-    unsigned buf_bytes;            // one LDS buffer: patch + dY band
-};
-
-__global__ __launch_bounds__(WB_THREADS) void hq_wgrad_band_kernel(const WbandArgs a)
-{
-    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
-    unsigned *tbl = reinterpret_cast<unsigned *>(smem);                 // [npix_pad] patch byte offset of pixel k
-    int8_t *bufs = smem + ((a.npix_pad * 4 + 15) & ~15);
-    const unsigned xbytes = (unsigned)a.prows * a.PW * WB_P;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: branches on it are uniform
-    const int grp = wave >> 2, cblk = wave & 1, th = (wave >> 1) & 1;
-    const int t0 = th ? 5 : 0, nt = th ? 4 : 5;
-
-    // workgroup -> (output block, run of bands); the blocks of one run sit on one XCD
-    int part, split;
-    {
-        const int per = a.cparts * a.nparts, total = per * a.splits;
-        const int full = (total / (8 * per)) * (8 * per);
-        if ((int)blockIdx.x < full) {
-            const int g8 = blockIdx.x / (8 * per), r = blockIdx.x % (8 * per);
-            split = g8 * 8 + (r & 7); part = r >> 3;
-        } else {
-            const int r = blockIdx.x - full;
-            split = full / per + r / per; part = r % per;
-        }
-    }
-    const int cp = part % a.cparts, np = part / a.cparts;
-    const int c0 = cp * 64, n0 = np * 64;
-    const int s_begin = split * a.stages_per_block, s_end = min(a.nstages, s_begin + a.stages_per_block);
-    const int zx = a.xq->zero_point;
-    const int fillw = (int)((unsigned)(zx & 0xff) * 0x01010101u);   // unsigned: the product may set bit 31
-    // a column sum is only ever multiplied by the other operand's zero point (the finalize kernel's
-    // correction terms): with that zero point at 0 it is not formed at all
-    const bool do_gsum = cp == 0 && cblk == 0 && th == 0 && zx != 0;
-    const bool do_xsum = np == 0 && a.gq->zero_point != 0;
-
-    // ---- per-thread staging plan (the same for every band)
-    int x_rel[WB_XLD], x_rowimg[WB_XLD];                 // source offset; patch row | image << 16
-    bool x_on[WB_XLD], x_col[WB_XLD];
-#pragma unroll
-    for (int i = 0; i < WB_XLD; i++) {
-        const int idx = tid + WB_THREADS * i, c16 = idx & 3, ppix = idx >> 2;
-        const int prow = ppix / a.PW, pcol = ppix - prow * a.PW;
-        x_on[i] = idx < a.xchunks;
-        const int il = prow / (a.rows + 2), pr = prow - il * (a.rows + 2);
-        x_rowimg[i] = pr | (il << 16);
-        x_col[i] = pcol >= 1 && pcol <= a.W;
-        x_rel[i] = ((il * a.H + pr - 1) * a.W + (pcol - 1)) * a.C + c16 * 16;
-    }
-    int g_rel[WB_GLD], g_il[WB_GLD];
-    bool g_on[WB_GLD];
-#pragma unroll
-    for (int i = 0; i < WB_GLD; i++) {
-        const int idx = tid + WB_THREADS * i, c16 = idx & 3, p = idx >> 2;
-        g_on[i] = idx < a.gchunks;
-        g_il[i] = p / (a.rows * a.W);
-        g_rel[i] = p * a.N + c16 * 16;
-    }
-    v4i xreg[WB_XLD], greg[WB_GLD];
-    auto load_stage = [&](int s) {
-        int b0, y0;
-        if (a.nimg == 1) { b0 = (int)hq_magic_div((unsigned)s, a.magic_bpi); y0 = (s - b0 * a.bands_per_img) * a.rows; }
-        else { b0 = s * a.nimg; y0 = 0; }
-        const size_t pix0 = ((size_t)b0 * a.H + y0) * a.W;
-        const int8_t *xs = a.X + pix0 * a.C + c0;
-        const int8_t *gs = a.G + pix0 * a.N + n0;
-#pragma unroll
-        for (int i = 0; i < WB_XLD; i++) {
-            const bool img = b0 + (x_rowimg[i] >> 16) < a.B;        // images past the end of the batch count as zeros
-            const bool inside = img && x_col[i] && (unsigned)(y0 + (x_rowimg[i] & 0xffff) - 1) < (unsigned)a.H;
-            const int f = img ? fillw : 0;                          // border of a real image: real zero
-            v4i v = {f, f, f, f};
-            if (x_on[i] && inside) v = *reinterpret_cast<const v4i *>(xs + x_rel[i]);
-            xreg[i] = v;
-        }
-#pragma unroll
-        for (int i = 0; i < WB_GLD; i++) {
-            v4i v = {0, 0, 0, 0};
-            if (g_on[i] && b0 + g_il[i] < a.B) v = *reinterpret_cast<const v4i *>(gs + g_rel[i]);
-            greg[i] = v;
-        }
-    };
-    auto store_stage = [&](int buf) {
-        int8_t *xb = bufs + buf * a.buf_bytes, *gb = xb + xbytes;
-#pragma unroll
-        for (int i = 0; i < WB_XLD; i++)
-            if (x_on[i]) {
-                const int idx = tid + WB_THREADS * i;
-                *reinterpret_cast<v4i *>(xb + (idx >> 2) * WB_P + (idx & 3) * 16) = xreg[i];
-            }
-#pragma unroll
-        for (int i = 0; i < WB_GLD; i++)
-            if (g_on[i]) {
-                const int idx = tid + WB_THREADS * i;
-                *reinterpret_cast<v4i *>(gb + (idx >> 2) * WB_P + (idx & 3) * 16) = greg[i];
-            }
-    };
-
-    // ---- start-up: first band on its way, pixel table, zero rows behind the last pixel of a band
-    if (s_begin < s_end) load_stage(s_begin);
-    for (int k = tid; k < a.npix_pad; k += WB_THREADS) {
-        unsigned off = 0;                                  // pixels past the band read patch row 0 (their dY is zero)
-        if (k < a.npix) {
-            const int il = k / (a.rows * a.W), rem = k - il * a.rows * a.W;
-            const int oy = rem / a.W, ox = rem - oy * a.W;
-            off = (unsigned)(((il * (a.rows + 2) + oy) * a.PW + ox) * WB_P);
-        }
-        tbl[k] = off;
-    }
-    for (int i = tid; i < (a.npix_pad - a.npix) * (WB_P / 4) * 2; i += WB_THREADS) {
-        const int buf = i / ((a.npix_pad - a.npix) * (WB_P / 4)), w = i % ((a.npix_pad - a.npix) * (WB_P / 4));
-        reinterpret_cast<int *>(bufs + buf * a.buf_bytes + xbytes + a.npix * WB_P)[w] = 0;
-    }
-    if (s_begin < s_end) store_stage(0);
-    __syncthreads();
-
-    v16i acc[2][5];
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-        for (int u = 0; u < 5; u++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) acc[i][u][r] = 0;
-    int gsv[2] = {0, 0}, xsv[5] = {0, 0, 0, 0, 0};
-
-    // lane's place in a fragment: rows klo and klo + 8 of the k-step, 8 bytes at column `fcol`
-    const int j16 = lane & 15;
-    const int klo = (lane >> 5) * 16 + (j16 >> 1);
-    const int fcol = 16 * ((lane >> 4) & 1) + 8 * (j16 & 1);
-    unsigned tapoff[5];
-#pragma unroll
-    for (int u = 0; u < 5; u++) {
-        const int t = min(t0 + u, 8);
-        tapoff[u] = (unsigned)(((t / 3) * a.PW + (t % 3)) * WB_P) + cblk * 32 + fcol;
-    }
-    const int nks = a.npix_pad / 32, ninv = a.npix_pad - a.npix;
-
-    for (int s = s_begin; s < s_end; s++) {
-        const int it = s - s_begin, buf = it & 1;
-        const bool more = s + 1 < s_end;
-        if (more) load_stage(s + 1);
-        const int8_t *xb = bufs + buf * a.buf_bytes, *gb = xb + xbytes;
-        for (int ks = (grp + it) & 1; ks < nks; ks += 2) {
-            const int kb = ks * 32;
-            const unsigned rlo = tbl[kb + klo], rhi = tbl[kb + klo + 8];
-            v4i gf[2], xf[5];
-#pragma unroll
-            for (int i = 0; i < 2; i++) {
-                const int8_t *p = gb + (kb + klo) * WB_P + i * 32 + fcol;
-                const tr_v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(tr_v2i))(p));
-                const tr_v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(tr_v2i))(p + 8 * WB_P));
-                gf[i] = v4i{lo[0], lo[1], hi[0], hi[1]};
-            }
-#pragma unroll
-            for (int u = 0; u < 5; u++) {
-                if (u < nt) {
-                    const tr_v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(tr_v2i))(xb + rlo + tapoff[u]));
-                    const tr_v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(tr_v2i))(xb + rhi + tapoff[u]));
-                    xf[u] = v4i{lo[0], lo[1], hi[0], hi[1]};
-                }
-            }
-            // the column sums ride behind the MFMAs of their own fragment (four dot products per tap, in the
-            // shadow of the matrix cores); issued after all ten MFMAs they would hold up the next k-step
-#pragma unroll
-            for (int u = 0; u < 5; u++) {
-                if (u < nt) {
-#pragma unroll
-                    for (int i = 0; i < 2; i++)
-                        acc[i][u] = __builtin_amdgcn_mfma_i32_32x32x32_i8(gf[i], xf[u], acc[i][u], 0, 0, 0);
-                    if (do_xsum) {
-#pragma unroll
-                        for (int d = 0; d < 4; d++) xsv[u] = __builtin_amdgcn_sdot4(xf[u][d], 0x01010101, xsv[u], false);
-                    }
-                    if (do_gsum && u < 2) {
-#pragma unroll
-                        for (int d = 0; d < 4; d++) gsv[u] = __builtin_amdgcn_sdot4(gf[u][d], 0x01010101, gsv[u], false);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        // the band's last k-step read patch row 0 for its `ninv` pixels past the band: take that back
-        // (in the group that took that k-step)
-        if (do_xsum && ninv > 0 && ((nks - 1 - grp - it) & 1) == 0 && lane < 32) {
-#pragma unroll
-            for (int u = 0; u < 5; u++)
-                if (u < nt) xsv[u] -= ninv * (int)xb[tapoff[u] - fcol + (lane & 31)];
-        }
-        if (more) store_stage(buf ^ 1);
-        __syncthreads();
-    }
-
-    // ---- add the two groups through LDS, one 32-block of Cout per round (the group that
-    // receives alternates), and store this workgroup's partial sums with plain 16-byte stores:
-    // partial[slot][i][u][r / 4][thread][r % 4].  The finalize kernel adds the slots; merging
-    // with atomics instead would queue every workgroup of the launch on the same lines.
-    int *xch = reinterpret_cast<int *>(smem);
-    const int t256 = tid & 255;
-    v4i *pout = reinterpret_cast<v4i *>(a.partial) + (size_t)(split * (a.cparts * a.nparts) + part) * WB_SLOT_V4;
-#pragma unroll
-    for (int i = 0; i < 2; i++) {
-        if (grp != i) {
-#pragma unroll
-            for (int u = 0; u < 5; u++)
-#pragma unroll
-                for (int r = 0; r < 16; r++) xch[(u * 16 + r) * 256 + t256] = acc[i][u][r];
-        }
-        __syncthreads();
-        if (grp == i) {
-#pragma unroll
-            for (int u = 0; u < 5; u++) {
-                if (u < nt) {
-#pragma unroll
-                    for (int rq = 0; rq < 4; rq++) {
-                        v4i v;
-#pragma unroll
-                        for (int e = 0; e < 4; e++) v[e] = acc[i][u][4 * rq + e] + xch[(u * 16 + 4 * rq + e) * 256 + t256];
-                        pout[((i * 5 + u) * 4 + rq) * 256 + t256] = v;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-    }
-    // column sums: plain stores as well, one record per workgroup and group
-    int *sp = a.sums + ((size_t)(split * (a.cparts * a.nparts) + part) * 2 + grp) * WB_SUMS;
-    if (do_gsum) {
-#pragma unroll
-        for (int i = 0; i < 2; i++) {
-            const int sm = gsv[i] + __shfl_xor(gsv[i], 32);
-            if (lane < 32) sp[i * 32 + lane] = sm;
-        }
-    }
-    if (do_xsum) {
-#pragma unroll
-        for (int u = 0; u < 5; u++) {
-            if (u < nt) {
-                const int sm = xsv[u] + __shfl_xor(xsv[u], 32);
-                if (lane < 32) sp[64 + (t0 + u) * 64 + cblk * 32 + lane] = sm;
-            }
-        }
-    }
-}
-
 __global__ void zero_kernel(int32_t *p, size_t n)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
@@ -898,138 +618,7 @@ __global__ void wgrad_finalize_kernel(const int32_t *acc, const int32_t *gsum, c
 }
 
 
-// Band kernel's finalize: adds the workgroups' partial sums (64 threads along C, TY taking every
-// TY-th slot), removes the zero points and scales.  One thread owns 4 consecutive output
-// channels of one (tap, c): the 16 bytes a lane of the band kernel stored.
-template <int TY>
-__global__ __launch_bounds__(64 * TY) void wband_finalize_kernel(const int32_t *partial, const int32_t *sums,
-                                                              const hq_qparams *xq, const hq_qparams *gq, unsigned M,
-                                                              int N, int C, int splits, float *dW, int32_t *dW_acc,
-                                                              const HqRideAlong ride)
-{
-    if (hq_ride_along(ride)) return;
-    __shared__ v4i sh[TY][64];
-    __shared__ int shx[TY][64], shg[TY][4];
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const int cparts = C / 64, parts = cparts * (N / 64);
-    const size_t o = (size_t)blockIdx.x * 64 + tx;                 // (n / 4, tap, c), c fastest
-    const int c = (int)(o % C), tap = (int)((o / C) % 9), n0 = (int)(o / ((size_t)9 * C)) * 4;
-    const int cp = c / 64, cblk = (c >> 5) & 1, np = n0 / 64, i = (n0 >> 5) & 1, rq = (n0 >> 3) & 3, lh = (n0 >> 2) & 1;
-    const int th = tap >= 5, u = tap - 5 * th;
-    const int t256 = (th * 2 + cblk) * 64 + lh * 32 + (c & 31);
-    const v4i *src = reinterpret_cast<const v4i *>(partial) + (size_t)(np * cparts + cp) * WB_SLOT_V4 +
-                     ((i * 5 + u) * 4 + rq) * 256 + t256;
-    const int *xsrc = sums + (size_t)cp * 2 * WB_SUMS + 64 + tap * 64 + (c & 63);            // workgroups with np == 0
-    const int *gsrc = sums + (size_t)(np * cparts) * 2 * WB_SUMS + (n0 & 63) + (tx & 3);    // workgroups with cp == 0
-    v4i sum = {0, 0, 0, 0};
-    int xs = 0, gs = 0;
-    // a column sum is only ever multiplied by the other operand's zero point: with that at 0 it is neither formed
-    // by the band kernel nor read here (uniform branches)
-    const bool need_xs = gq->zero_point != 0, need_gs = xq->zero_point != 0;
-    for (int s = ty; s < splits; s += TY) {
-        sum += src[(size_t)s * parts * WB_SLOT_V4];
-        const size_t so = (size_t)s * parts * 2 * WB_SUMS;
-        if (need_xs) xs += xsrc[so] + xsrc[so + WB_SUMS];
-        if (need_gs && tx < 4) gs += gsrc[so] + gsrc[so + WB_SUMS];
-    }
-    sh[ty][tx] = sum; shx[ty][tx] = xs;
-    if (tx < 4) shg[ty][tx] = gs;
-    __syncthreads();
-    if (ty != 0) return;
-    int g4[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int y = 1; y < TY; y++) { sum += sh[y][tx]; xs += shx[y][tx]; }
-#pragma unroll
-    for (int y = 0; y < TY; y++)
-#pragma unroll
-        for (int e = 0; e < 4; e++) g4[e] += shg[y][e];
-    const unsigned zx = (unsigned)xq->zero_point, zg = (unsigned)gq->zero_point;
-    const float sc = __fmul_rn(xq->scale, gq->scale);
-    const size_t K = (size_t)9 * C, k = (size_t)tap * C + c;
-    const unsigned xterm = zg * (unsigned)xs, both = M * zx * zg;
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-        const unsigned v = (unsigned)sum[e] - zx * (unsigned)g4[e] - xterm + both;
-        const size_t idx = (size_t)(n0 + e) * K + k;
-        if (dW_acc) dW_acc[idx] = (int)v;
-        dW[idx] = __fmul_rn(sc, (float)(int)v);
-    }
-}
-
 size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
-
-// Geometry of the band kernel for one layer (host, pure); covered == false: the tile kernel takes it.
-struct WbandPlan {
-    bool covered;
-    int rows, nimg, nstages, stages_per_block, splits, parts;
-    int npix, npix_pad, prows;
-    size_t lds, buf_bytes;
-};
-
-WbandPlan wband_plan(const hq_problem *p)
-{
-    WbandPlan pl = {};
-    if (p->kind != HQ_CONV2D || p->R != 3 || p->S != 3 || p->stride != 1 || p->pad != 1) return pl;
-    if (p->C % 64 != 0 || p->Cout % 64 != 0) return pl;
-    const int H = p->H, W = p->W;
-    // candidates: `rows` output rows of one image (rows | H), or `nimg` whole images; a band holds at
-    // most 256 pixels and what 512 threads stage in WB_XLD / WB_GLD chunks each.  Prefer the band
-    // that wastes the fewest k-steps (the two groups take ceil(nks / 2) k-steps per band).
-    int best_rows = 0, best_nimg = 0;
-    double best_eff = 0.0;
-    auto consider = [&](int rows, int nimg) {
-        const int npix = nimg * rows * W, prows = nimg * (rows + 2);
-        if (npix > 256 || npix * 4 > WB_GLD * WB_THREADS || prows * (W + 2) * 4 > WB_XLD * WB_THREADS) return;
-        const int nks = (npix + 31) / 32;
-        const double eff = (double)npix / (64.0 * ((nks + 1) / 2));
-        if (eff > best_eff + 1e-9 || (eff > best_eff - 1e-9 && npix > best_nimg * best_rows * W)) {
-            best_eff = eff; best_rows = rows; best_nimg = nimg;
-        }
-    };
-    for (int rows = 1; rows <= H; rows++) if (H % rows == 0) consider(rows, 1);
-    for (int nimg = 2; nimg * H * W <= 256; nimg++) consider(H, nimg);
-    if (best_rows == 0) return pl;
-    pl.rows = best_rows; pl.nimg = best_nimg;
-    pl.nstages = best_nimg == 1 ? p->B * (H / best_rows) : (p->B + best_nimg - 1) / best_nimg;
-    pl.parts = (p->C / 64) * (p->Cout / 64);
-    pl.npix = best_nimg * best_rows * W; pl.npix_pad = (pl.npix + 31) & ~31;
-    pl.prows = best_nimg * (best_rows + 2);
-    pl.buf_bytes = (size_t)pl.prows * (W + 2) * WB_P + (size_t)pl.npix_pad * WB_P;
-    pl.lds = (size_t)((pl.npix_pad * 4 + 15) & ~15) + 2 * pl.buf_bytes;
-    const size_t reduce_bytes = 5 * 16 * 256 * 4;           // the two groups meet in LDS at the end
-    if (pl.lds < reduce_bytes) pl.lds = reduce_bytes;
-    if (pl.lds > 160 * 1024) return pl;
-    int splits = pl.parts >= 256 ? 1 : (256 + pl.parts - 1) / pl.parts;     // one workgroup per compute unit
-    if (splits > pl.nstages) splits = pl.nstages;
-    pl.stages_per_block = (pl.nstages + splits - 1) / splits;
-    pl.splits = (pl.nstages + pl.stages_per_block - 1) / pl.stages_per_block;
-    pl.covered = true;
-    return pl;
-}
-
-size_t wband_partial_bytes(const WbandPlan &pl) { return pl.covered ? (size_t)pl.parts * pl.splits * WB_SLOT_V4 * 16 : 0; }
-size_t wband_sums_bytes(const WbandPlan &pl) { return pl.covered ? (size_t)pl.parts * pl.splits * 2 * WB_SUMS * 4 : 0; }
-
-bool launch_wgrad_band(const hq_problem *p, const WbandPlan &pl, const WgradArgs &w, int32_t *partial, int32_t *sums,
-                       hipStream_t stream)
-{
-    WbandArgs a;
-    a.X = w.X; a.G = w.G; a.xq = w.xq; a.gq = w.gq; a.partial = partial; a.sums = sums;
-    a.B = p->B; a.H = p->H; a.W = p->W; a.C = p->C; a.N = p->Cout;
-    a.rows = pl.rows; a.nimg = pl.nimg;
-    a.bands_per_img = p->H / pl.rows;
-    a.magic_bpi = hq_magic32((unsigned)a.bands_per_img);
-    a.nstages = pl.nstages; a.stages_per_block = pl.stages_per_block; a.splits = pl.splits;
-    a.cparts = p->C / 64; a.nparts = p->Cout / 64;
-    a.npix = pl.npix; a.npix_pad = pl.npix_pad;
-    a.prows = pl.prows; a.PW = p->W + 2;
-    a.xchunks = a.prows * a.PW * 4; a.gchunks = a.npix * 4;
-    a.buf_bytes = (unsigned)pl.buf_bytes;
-    static std::atomic<unsigned long long> allowed{0};
-    if (!hq_allow_lds(hq_wgrad_band_kernel, 160 * 1024, allowed)) return false;
-    hipLaunchKernelGGL(hq_wgrad_band_kernel, dim3((unsigned)(pl.parts * pl.splits)), dim3(WB_THREADS), pl.lds, stream, a);
-    return true;
-}
 
 } // namespace
 
@@ -1039,7 +628,7 @@ size_t hq_wgrad_workspace_bytes(const hq_problem *p)
     const size_t K = (size_t)p->R * p->S * p->C;
     if (p->kind == HQ_DEPTHWISE) return align16(4 * K) + align16(4 * (size_t)p->C) + align16(4 * K);
     return align16(4 * (size_t)p->Cout * K) + align16(4 * (size_t)p->Cout) + align16(4 * K) +
-           wband_partial_bytes(wband_plan(p)) + wband_sums_bytes(wband_plan(p));
+           hq_wgrad_band_bytes(p);
 }
 
 int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY,
@@ -1067,26 +656,8 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
 
     const int rc = hq_try_launch_wgrad_small(p, X, xq, dY, gq, dW, dW_acc, stream, ride);
     if (rc != HQ_E_BADSHAPE) return rc;
-    const WbandPlan pl = wband_plan(p);
-    if (pl.covered) {
-        // every workgroup stores its sums to a slot of its own: nothing to zero, no atomics
-        int32_t *partial = reinterpret_cast<int32_t *>(w + sums_bytes);
-        int32_t *sums = reinterpret_cast<int32_t *>(w + sums_bytes + wband_partial_bytes(pl));
-        if (!launch_wgrad_band(p, pl, a, partial, sums, stream)) return HQ_E_HIP;
-        const size_t quads = (size_t)a.N / 4 * K;              // multiple of 64 (C % 64 == 0)
-        ra.first = (int)(quads / 64);
-        const dim3 fgrid((unsigned)(quads / 64) + (unsigned)ra.n);
-        if (pl.splits >= 48)
-            hipLaunchKernelGGL(wband_finalize_kernel<16>, fgrid, dim3(1024), 0, stream, partial, sums, xq, gq,
-                               (unsigned)a.M, a.N, a.C, pl.splits, dW, dW_acc, ra);
-        else if (pl.splits >= 12)
-            hipLaunchKernelGGL(wband_finalize_kernel<4>, fgrid, dim3(256), 0, stream, partial, sums, xq, gq,
-                               (unsigned)a.M, a.N, a.C, pl.splits, dW, dW_acc, ra);
-        else
-            hipLaunchKernelGGL(wband_finalize_kernel<1>, fgrid, dim3(64), 0, stream, partial, sums, xq, gq,
-                               (unsigned)a.M, a.N, a.C, pl.splits, dW, dW_acc, ra);
-        return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
-    }
+    const int rc_band = hq_try_launch_wgrad_band(p, X, xq, dY, gq, dW, dW_acc, w + sums_bytes, stream, ride);
+    if (rc_band != HQ_E_BADSHAPE) return rc_band;
 
     // first layers: input rows staged in LDS (hq_wgrad_stem_kernel)
     if ((a.C == 3 || a.C == 4) && p->W % 4 == 0 && p->S <= 8 && p->R <= 8 && a.N <= 64 &&

@@ -160,6 +160,16 @@ def test_one_launch_weight_gradients_end_where_split_k_is_faster():
            ("wgrad", conv(41, 14, 64, 3, 1, 64), one), ("wgrad", conv(42, 14, 64, 3, 1, 64), band)])
 
 
+def test_framed_weight_gradients_weigh_runs_against_slots():
+    """Wide images as far as the ring fits LDS; one workgroup to a compute unit, and fewer where runs would be short."""
+    band, tile = "hq_wgrad_band_kernel", "zero_kernel"
+    check([("wgrad", (CONV, 1, 2, 570, 320, 3, 3, 1, 1, 256), band), ("wgrad", (CONV, 1, 2, 571, 320, 3, 3, 1, 1, 256), tile)])
+    def blocks(*layer):
+        return launches.calls([("wgrad", conv(*layer))])[0][0].blocks
+    assert blocks(256, 56, 64, 3, 1, 64) == 2 * 128 and blocks(256, 7, 512, 3, 1, 512) == 128 * 2 and blocks(64, 14, 384, 3, 1, 384) == 72 * 3
+    assert blocks(2000, 4, 64, 3, 1, 64) == 2 * 66                      # 391 units: runs of six
+
+
 def test_tile_weight_gradients_load_without_branches_where_rows_are_whole_chunks():
     def kernel(*layer):
         return [l.kernel for l in launches.calls([("wgrad", layer)])[0] if l.kernel.startswith("hq_wgrad_kernel")][0]
