@@ -182,14 +182,10 @@ def kernel_family(wl, L, op):
     small, tiles = up(pixels, 64) * up(cout, 64), up(pixels, 128) * up(cout, 128)
     if small <= 256 and not (taps == 1 and not strided and cout > 64 and 256 <= cin < 512):
         return "hq_ksplit_kernel"
+    if k3 and cin % 64 == 0 and cin >= 128 and cout % 16 == 0 and cout >= 128 and L.W <= 125:
+        return "hq_frame_kernel"
     if cin % 128 == 0 and cout % 16 == 0 and cout >= 128 and taps * cin >= 1024 and tiles > 64 and not strided and (taps > 1 or small > 512 or taps * cin >= 1280):
-        rows, images = (max(1, min(256 // L.W, L.H)), 1) if L.H * L.W > 128 else (L.H, 256 // (L.H * L.W))
-        items = (up(L.B, images) if images > 1 else L.B * up(L.H, rows)) * up(cout, 128)
-        two = images * (rows + 2) * (L.W + 2) <= 376                          # row tiles: two workgroups to a compute unit
-        if not (k3 and two and tiles > 512 and up(tiles, 256) >= 2 * up(items, 256)):
-            return "hq_ring_kernel"
-    if k3 and cin % 64 == 0 and cin >= 128 and cout >= 128:
-        return "hq_bandw_kernel"
+        return "hq_ring_kernel"
     if k3 and cin == 64:
         return "hq_regw_kernel"
     return "hq_gemm_kernel"

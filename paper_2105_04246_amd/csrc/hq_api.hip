@@ -224,6 +224,8 @@ static int gemm_common(const hq_problem *p, int dgrad, const int8_t *A, const hq
     }
     rc = hq_try_launch_ksplit(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
     if (rc != HQ_E_BADSHAPE) return rc;
+    rc = hq_try_launch_frame(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
+    if (rc != HQ_E_BADSHAPE) return rc;
     rc = hq_try_launch_ring(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
     if (rc != HQ_E_BADSHAPE) return rc;
     rc = hq_try_launch_regw(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);

@@ -334,13 +334,6 @@ bool bandw_tiles(const hq_problem *p, int dgrad, BandwTiles *t)
 
 } // namespace
 
-long hq_bandw_items(const hq_problem *p, int dgrad)
-{
-    BandwTiles t;
-    if (!bandw_tiles(p, dgrad, &t) || t.lds > 80 * 1024) return 0;
-    return (long)t.ntiles * (((dgrad ? p->C : p->Cout) + BW_BN - 1) / BW_BN);
-}
-
 // 3x3, stride 1, pad 1, C % 64 == 0 and C >= 128, Cout % 16 == 0 and Cout >= 128 (forward); the
 // input gradient of such a layer with the roles of C and Cout swapped.  HQ_E_BADSHAPE: not covered.
 int hq_try_launch_bandw(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,

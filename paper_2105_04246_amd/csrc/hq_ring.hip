@@ -296,18 +296,6 @@ int hq_try_launch_ring(const hq_problem *p, int dgrad, const int8_t *A, const hq
     // 8794 x 1280 -> 384 12.0 / 14.3; dynamic, forward, 4678 x 1024 -> 160 15.8 / 14.2, 10987 x 2560 -> 320 35.0 / 39.3.
     const long small_tiles = (long)((M + 63) / 64) * ((a.N + 63) / 64);
     if (taps == 1 && small_tiles <= 512 && (out32 || sr_seed || a.nst < 10)) return HQ_E_BADSHAPE;
-    // Past two tiles to a compute unit 3x3 layers of stride 1 compete with the kernel that stages a row tile's input once for all nine
-    // taps.  Both take their time in halves of a round, 256 tiles here, 256 items of twice the size there: equal amounts are up to
-    // 10 % faster there (this / that, 16 x 16 x 256, images 192: 3 halves / 2 items 35.0 / 37.8 us, 256: 4 / 2 45.6 / 42.8, 320: 5 / 3
-    // 56.3 / 62.1, 384: 6 / 3 67.2 / 64.8; 14 x 14 x 256, 240: 34.2 / 39.1, 256: 41.9 / 40.2, 280: 42.6 / 57.6; 28 x 28 x 128,
-    // 128: 26.0 / 25.1, 256: 7 / 4 44.7 / 45.6), and where only one of its workgroups fits a compute unit it is never ahead (64 x 64
-    // x 128, 64 images 52.7 / 63.6).  With stochastic rounding, whose long epilogues its larger tiles overlap less, from eight
-    // halves on (14 x 14 x 256, 256: 4 / 2 48.9 / 49.3; 16 x 16 x 256, 256: 4 / 2 55.6 / 55.8, 512: 8 / 4 99.5 / 95.5, 640: 10 / 5 124.9 /
-    // 120.4, 896: 14 / 7 167.9 / 158.4; 32 x 32 x 128, 256: 8 / 4 68.8 / 66.8, 320: 10 / 5 85.1 / 77.3, 384: 12 / 6 92.3 / 88.8).
-    if (tiles > (sr_seed ? 1792 : 512)) {
-        const long items = hq_bandw_items(p, dgrad);
-        if (items > 0 && (tiles + 255) / 256 >= 2 * ((items + 255) / 256)) return HQ_E_BADSHAPE;
-    }
     a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
     const int mode = out32 ? 0 : sr_seed ? 2 : 1;
     return mode == 0 ? launch<0>(a, stream) : mode == 1 ? launch<1>(a, stream) : launch<2>(a, stream);

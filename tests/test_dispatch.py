@@ -98,34 +98,34 @@ def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
 
 
 def test_whole_lines_per_stage_between_split_reductions_and_row_tiles():
-    ring, ks, bandw, tile = "hq_ring_kernel", "hq_ksplit_kernel", "hq_bandw_kernel", "hq_gemm_kernel"
-    check([("fwd", conv(26, 14, 256, 3, 1, 256), ring), ("dgrad", conv(26, 14, 256, 3, 1, 256), ring), ("dgrad_sr", conv(26, 14, 256, 3, 1, 256), ring),
-           ("dynamic_fwd", conv(26, 14, 256, 3, 1, 256), ring), ("fwd", conv(128, 4, 512, 3, 1, 512), ks),
-           ("fwd", conv(256, 16, 128, 3, 1, 128), ring), ("fwd", conv(257, 16, 128, 3, 1, 128), ring),
-           ("fwd", conv(257, 16, 128, 5, 1, 128), ring), ("fwd", conv(257, 32, 128, 3, 2, 128), ring),           # not the row tiles' layers
+    ring, ks, bandw, tile, frame = "hq_ring_kernel", "hq_ksplit_kernel", "hq_bandw_kernel", "hq_gemm_kernel", "hq_frame_kernel"
+    check([("fwd", conv(26, 14, 256, 3, 1, 256), frame), ("dgrad", conv(26, 14, 256, 3, 1, 256), frame), ("dgrad_sr", conv(26, 14, 256, 3, 1, 256), frame),
+           ("dynamic_fwd", conv(26, 14, 256, 3, 1, 256), frame), ("fwd", conv(128, 4, 512, 3, 1, 512), ks),
+           ("fwd", conv(257, 16, 128, 5, 1, 128), ring), ("fwd", conv(257, 32, 128, 3, 2, 128), ring),           # not the framed tiles' layers
+           ("fwd", conv(257, 18, 128, 3, 1, 128, 0), ring), ("dgrad_sr", conv(257, 18, 128, 3, 1, 128, 0), ring),
            ("dgrad", conv(257, 32, 256, 3, 2, 256), tile),                                                      # strided
            ("fwd", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), ring), ("fwd", (LINEAR, 8192, 1, 1, 896, 1, 1, 1, 0, 1024), tile),
            ("dgrad", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), ring), ("dgrad_sr", (LINEAR, 8192, 1, 1, 1024, 1, 1, 1, 0, 1024), ring),
            ("dgrad", conv(42, 28, 128, 1, 1, 1024), ring),
-           ("fwd", conv(26, 14, 192, 3, 1, 256), bandw), ("fwd", conv(34, 13, 128, 3, 1, 144), ring), ("fwd", conv(128, 14, 256, 3, 1, 120), tile),
-           ("fwd", conv(20, 30, 128, 3, 1, 144), ring), ("fwd", (LINEAR, 6700, 1, 1, 1024, 1, 1, 1, 0, 272), ring),
+           ("fwd", conv(26, 14, 192, 3, 1, 256), frame), ("fwd", conv(34, 13, 128, 3, 1, 144), frame), ("fwd", conv(128, 14, 256, 3, 1, 120), tile),
+           ("fwd", conv(20, 30, 128, 3, 1, 144), frame), ("fwd", (LINEAR, 6700, 1, 1, 1024, 1, 1, 1, 0, 272), ring),
            ("fwd", (LINEAR, 1700, 1, 1, 1280, 1, 1, 1, 0, 1168), ring), ("fwd", conv(40, 29, 128, 3, 2, 272), ring),
-           ("dgrad", conv(40, 16, 128, 3, 1, 128, 2), ring), ("fwd", (CONV, 20, 17, 19, 128, 5, 3, 1, 1, 160), ring)])
+           ("dgrad", conv(40, 16, 128, 3, 1, 128, 2), ring), ("fwd", (CONV, 20, 17, 19, 128, 5, 3, 1, 1, 160), ring),
+           # the patch of a tile on wide images does not fit
+           ("fwd", (CONV, 1, 70, 125, 128, 3, 3, 1, 1, 128), frame), ("fwd", (CONV, 1, 70, 126, 128, 3, 3, 1, 1, 128), ring),
+           ("fwd", (CONV, 1, 70, 125, 192, 3, 3, 1, 1, 128), frame), ("fwd", (CONV, 1, 70, 126, 192, 3, 3, 1, 1, 128), bandw)])
 
 
-def test_row_tiles_stay_where_they_fill_their_half_rounds():
-    """Past 512 tiles of whole lines, 1792 with stochastic rounding: halves of a round, 256 tiles each, against twice those of the row tiles' items."""
-    ring, bandw = "hq_ring_kernel", "hq_bandw_kernel"
-    check([("fwd", conv(384, 16, 128, 3, 1, 128), ring), ("fwd", conv(385, 16, 128, 3, 1, 128), bandw),        # 768 and 770 tiles, 384 and 385 items
-           ("dgrad", conv(384, 16, 128, 3, 1, 128), ring), ("dgrad", conv(385, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(385, 16, 128, 3, 1, 128), ring),
-           ("dynamic_fwd", conv(385, 16, 128, 3, 1, 128), bandw), ("dynamic_dgrad", conv(384, 16, 128, 3, 1, 128), ring),
-           ("fwd", conv(512, 16, 128, 3, 1, 128), bandw), ("fwd", conv(513, 16, 128, 3, 1, 128), ring),        # a third half round for one item
-           ("fwd", conv(256, 14, 256, 3, 1, 256), bandw), ("fwd", conv(257, 14, 256, 3, 1, 256), ring),
-           ("fwd", conv(512, 14, 128, 3, 1, 128), bandw), ("fwd", conv(480, 14, 128, 3, 1, 128), ring),        # 736 tiles
-           ("fwd", conv(32, 64, 128, 3, 1, 128), ring), ("fwd", conv(512, 8, 512, 3, 1, 512), ring),           # one workgroup to a compute unit
-           ("dgrad_sr", conv(768, 16, 128, 3, 1, 128), ring), ("dgrad_sr", conv(1024, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(1152, 16, 128, 3, 1, 128), ring),
-           ("dgrad_sr", conv(1153, 16, 128, 3, 1, 128), bandw), ("dgrad_sr", conv(1025, 16, 128, 3, 1, 128), ring),
-           ("dgrad_sr", conv(128, 64, 128, 3, 1, 128), ring)])
+def test_framed_tiles_are_the_largest_that_fill_their_rounds():
+    """Tiles of 128 to 512 pixels x 128 channels, one workgroup to a compute unit."""
+    def tile(op, *layer):
+        l = launches.calls([(op, conv(*layer))])[0][0]
+        return l.kernel.split("<")[1][3:7], l.blocks
+    assert tile("fwd", 128, 28, 128, 3, 1, 128) == ("4, 3", 224) and tile("fwd", 256, 28, 128, 3, 1, 128) == ("4, 3", 256)
+    assert tile("dgrad", 256, 14, 256, 3, 1, 256) == ("4, 3", 224) and tile("dgrad_sr", 256, 7, 512, 3, 1, 512) == ("2, 2", 196)
+    assert tile("fwd", 128, 32, 128, 3, 1, 128) == ("4, 4", 256) and tile("fwd", 128, 16, 256, 3, 1, 256) == ("2, 2", 256)
+    assert tile("fwd", 128, 8, 512, 3, 1, 512) == ("1, 1", 256) and tile("fwd", 64, 14, 384, 3, 1, 384) == ("2, 1", 198)
+    assert tile("dynamic_fwd", 60, 28, 128, 3, 1, 256) == ("3, 3", 246)
 
 
 def test_whole_lines_of_one_tap_start_past_two_small_tiles_to_a_compute_unit():
@@ -255,8 +255,12 @@ def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_for():
     assert all(regw("fwd", s) for s in T.REGW_FORWARD)
     assert all(regw(op, s) for s in T.REGW_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
     assert not any(regw(op, s) for s in T.REGW_PAST + T.REGW_ONE_ROUND for op in ("dynamic_fwd", "fwd", "dgrad", "dgrad_sr"))
-    for L in T.RING_BACKWARD:
-        check([(op, tuple(L)[1:], "hq_ring_kernel") for op in ("dgrad", "dgrad_sr", "dynamic_dgrad")])
+    for L in T.RING_BACKWARD + T.RING_OTHER:
+        check([(op, tuple(L)[1:], "hq_frame_kernel" if L.R == 3 and L.pad == 1 else "hq_ring_kernel") for op in ("dgrad", "dgrad_sr", "dynamic_dgrad")])
+    check([(op, tuple(L)[1:], "hq_frame_kernel") for L in T.FRAME_SHAPES for op in ("fwd", "dynamic_fwd")])
+    check([(op, tuple(L)[1:], "hq_frame_kernel") for L in T.FRAME_SHAPES if L.Cout % 64 == 0 for op in ("dgrad", "dgrad_sr", "dynamic_dgrad")])
+    assert {launches.calls([("fwd", tuple(L)[1:])])[0][0].kernel[16:23] for L in T.FRAME_SHAPES} == {"1, 1, 1", "1, 2, 1", "1, 2, 2", "1, 3, 3", "1, 4, 3", "1, 4, 4"}
+    check([(op, tuple(L)[1:], "hq_bandw_kernel") for L in T.WIDE_ROW_TILES for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")])
     check([("dgrad", tuple(L)[1:], "hq_ring_kernel") for L in T.RING_ONE_TAP])
     one, four = "hq_wgrad_small_kernel<1, 1, 4, 4>", "hq_wgrad_small_kernel<2, 2, 4, 2>"
     want = {"ws_1px": one, "ws_32_2145": one, "ws_32_300px": one, "ws_32_2304": one, "ws_64": four, "ws_64_256px": four, "past_ws_64": "zero_kernel",

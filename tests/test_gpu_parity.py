@@ -450,6 +450,46 @@ def test_whole_lines_backward(H, hq, L):
         track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
+# The same for filters that the framed tiles do not take.
+RING_OTHER = [wl.conv("ring_dgrad_n144_pad0", 34, 15, 144, 128, 3, pad=0), wl.conv("ring_two_rounds_pad0", 257, 18, 128, 128, 3, pad=0)]
+
+
+@pytest.mark.parametrize("L", RING_OTHER, ids=[l.name for l in RING_OTHER])
+def test_whole_lines_backward_without_padding(H, hq, L):
+    test_whole_lines_backward(H, hq, L)
+
+
+# Framed tiles of every size: pixels and channels off the tile, two chunks of channels and more, images of four pixels, one row, one column, the
+# widest whose patch fits, tiles that cover many images and tiles inside one, more tiles than compute units.
+FRAME_SHAPES = [wl.LayerShape("frame", wl.CONV, B, Hh, Ww, C, 3, 3, 1, 1, N)
+                for B, Hh, Ww, C, N in ((2080, 2, 2, 128, 128), (70, 120, 1, 128, 128), (140, 1, 60, 128, 128), (1, 70, 125, 128, 128), (43, 14, 14, 128, 128),
+                                        (107, 9, 13, 192, 192), (23, 38, 38, 128, 128), (330, 10, 10, 128, 144), (190, 7, 39, 128, 128), (51, 25, 26, 128, 144),
+                                        (128, 20, 20, 128, 144), (152, 20, 19, 128, 144), (256, 17, 15, 128, 144))]
+
+
+@pytest.mark.parametrize("L", FRAME_SHAPES, ids=["b%d_%dx%d_c%d_n%d" % (l.B, l.H, l.W, l.C, l.Cout) for l in FRAME_SHAPES])
+def test_framed_tiles(H, hq, L):
+    y_track, g_track = H.TensorTrack(0.9, False), H.TensorTrack(0.9, True)
+    Wdev = None
+    for t in range(3):                                       # dynamic, nearest, stochastic
+        X, W, dY = rand_layer_inputs(L, 140 + t, g_asym=True)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        if t < 2:
+            y_track.step(L, "fwd", X, W0, H.DevTensor(X), Wdev)
+        if L.Cout % 64 == 0:
+            g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
+
+
+# Images too wide for a framed tile's patch, channels off 128: row tiles.
+WIDE_ROW_TILES = [wl.LayerShape("wide_row_tiles", wl.CONV, 1, 66, 130, 192, 3, 3, 1, 1, 192)]
+
+
+@pytest.mark.parametrize("L", WIDE_ROW_TILES, ids=[l.name for l in WIDE_ROW_TILES])
+def test_wide_row_tiles(H, hq, L):
+    test_framed_tiles(H, hq, L)
+
+
 # Weight gradients by tiles: rows of whole 16-byte chunks (loads without a branch) and off them, tiles of 64 and 128 with columns and
 # rows left over, taps outside the image on every side, the last run of pixels short.
 TILE_WGRAD = [wl.conv("tw_128_s2", 46, 28, 80, 144, 3, stride=2), wl.conv("tw_64_5x5", 13, 29, 48, 80, 5), wl.conv("tw_128_1x1", 47, 14, 208, 96, 1, pad=0),
