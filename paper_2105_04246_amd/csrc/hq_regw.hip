@@ -5,13 +5,21 @@
 // else a phase does comes on top (the weights-in-LDS kernel: 28 us for 128 x 56 x 56 x 64 against 7 us of matrix work).
 // 64 channels x 576 reduced bytes are 144 registers per lane; then only the pixels come from LDS, 1 KB for two MFMAs.
 // A compute unit holds two wavefronts per SIMD: while one requantizes, the other multiplies.
+//
 // A unit is 256 consecutive output pixels, 32 per wavefront, of the tensor's [image][row][column] order, whatever rows and
-// images it spans.  The input rows it needs are copied to LDS in padded-image order (a row of padding above and below
-// every image), one patch row per wavefront and turn, while the unit before is multiplied; pixels have a pitch of
-// 80 bytes, which spreads the fragment reads (32 pixels at one 16-byte chunk) over the banks (conflicts: 18 % of LDS's busy cycles)
-// and lets a tap be a constant offset from the pixel's address.
-// Measured: 24 us at that size, 6 or 7 units to a workgroup: 8 for a launch of one unit each, 2.6 for each further one (1.2 of them
-// matrix work); 61 x 37 x 23 x 64, whose rows fit no band of the other kernel, 16 -> 8.5 us.
+// images it spans; a workgroup takes a run of units.  Their input is a stream of positions: image rows of W + 1 positions and images of
+// H + 1 rows, one column and one row of padding between neighbours, so that every tap is a constant distance in the stream.  The
+// positions go through a ring in LDS in blocks of 64, straight from global memory, as many as the next unit needs while this one is
+// multiplied (the run's first pixel starts the ring; a position outside the images loads a row of the zero point).  The ring is four
+// planes of 16 channels: a fragment's 32 positions are 512 consecutive bytes, without bank conflicts, and the taps of a filter row and the
+// halves of the channels are immediate offsets from one address per filter row.  What the framed stream costs in positions (a unit
+// of 3 x 3 images has 455) it costs only in loads: the matrix work is on pixels.  The ring holds two units of images up to 403 wide.
+//
+// Before, patches of padded rows were copied through registers into two buffers, 1,000 of 4,950 clocks of a unit, for images up
+// to 121 wide.  Measured, before -> now (us): 256 x 56 x 56 x 64 40.5 -> 38.3, 128 x 56 x 56 x 64 24.8 -> 23.2, 16 x 56 x 56 x 64 7.8 -> 7.2,
+// 61 x 37 x 23 x 64 7.8 -> 7.2, 400 x 7 x 7 x 64 7.8 -> 6.7; wider images, then the general kernel's: 16 x 224 x 224 x 64 79.9 -> 36.4,
+// 1 x 150 x 150 x 64 14.2 -> 6.8.  Bound by power where it fills the chip: with the requantization spread between the MFMAs a unit took
+// 3,600 clocks instead of 4,600, and the launch as long as before, at a lower clock rate.
 #include "hq_device.h"
 #include "hq_internal.h"
 
@@ -20,8 +28,13 @@
 
 namespace {
 
-constexpr int RW_THREADS = 512, RW_UNIT = 256, RW_PITCH = 80, RW_LOADS = 10;   // loads: 64 slots of 16 bytes of a patch row each
+constexpr int RW_THREADS = 512, RW_UNIT = 256, RW_BLOCK = 64;           // pixels of a unit, 32 per wavefront; positions that are loaded together
+constexpr int RW_RING = 1792;                                            // positions of the ring; its first block is repeated behind its end
+constexpr int RW_PLANE = (RW_RING + RW_BLOCK) * 16;                     // bytes of a plane: 16 channels of every position
+constexpr int RW_WEIGHTS = 64 * 9 * 64;
 
+struct RegwDivisor { unsigned m, s; };                                  // k / d = umulhi(k, m) >> s for k < 2^31; m = 0: d = 1
+struct RegwAdvance { int p, y, x; };                                    // a number of pixels as positions, rows and columns, or of positions as pixels ...
 struct RegwArgs {
     const int8_t *A, *Bw;
     const int32_t *bsum;
@@ -31,208 +44,257 @@ struct RegwArgs {
     int32_t *out32;
     hq_qparams *outq;
     hq_stats *st;
-    int M, N, H, W, PW;            // output pixels, channels; image; patch row W + 2 pixels
+    int M, N, H, W, PW;            // output pixels, channels; image; positions of a row: W + 1
     int flip;
-    int units, nparts, runs;       // units of 256 pixels; blocks of 64 channels; workgroups per channel block
-    int prows;                     // most patch rows of a unit
-    unsigned magic_W, magic_H, magic_H2;   // of W, H, H + 2
-    float inv_W, inv_H;
+    int units, nparts, runs;       // units; blocks of 64 channels; workgroups per channel block
+    RegwDivisor image, line, fimage, fline;          // H * W and W; (H + 1) * PW and PW
+    RegwAdvance unit, loads;       // a unit's pixels; 256 positions
     HqSr sr;
 };
 
 template <int MODE>
 __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a)
 {
-    constexpr int CB = 64, KC = CB / 32, STORES = MODE == 0 ? 32 : 2;
-    extern __shared__ __attribute__((aligned(16))) int8_t smem[];
+    // four planes of 16 channels, the weights of 64 channels (chunks of 16 bytes swizzled by bits 2 and 3 of the row)
+    extern __shared__ __attribute__((aligned(64))) int8_t smem[];
     __shared__ __attribute__((aligned(16))) int bias[64];
     __shared__ int red[4 * (RW_THREADS / 64)];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = lane >> 5;
+    const int half = lane >> 5, r32 = lane & 31;
 
-    const int run = blockIdx.x / a.nparts, n0 = (blockIdx.x - run * a.nparts) * 64;
+    const int run = __builtin_amdgcn_readfirstlane(blockIdx.x / a.nparts), n0 = (blockIdx.x - run * a.nparts) * 64;
     const int u_begin = (int)((long)a.units * run / a.runs), u_end = (int)((long)a.units * (run + 1) / a.runs);
-    const int za = a.aq->zero_point;
-    const int rowpitch = a.PW * RW_PITCH;
-    const int bufbytes = a.prows * rowpitch + 1024;                  // (a row's last load may end past it)
+    const unsigned lds0 = hq_lds_address(smem);
+    constexpr unsigned wlds = 4 * RW_PLANE;
 
-    // ---- staging plan: slot q of a patch row is 16-byte chunk q % 5 of pixel q / 5 (chunk 4: the padding of the pitch)
-    const int nload = (a.PW * 5 + 63) / 64;
-    unsigned loff[RW_LOADS];
-    unsigned lmask = 0;
+    // ---- weights of this workgroup's 64 channels: 36 KB in one piece
+    {
+        const int8_t *wsrc = a.Bw + (size_t)n0 * 576;
 #pragma unroll
-    for (int k = 0; k < RW_LOADS; k++) {
-        const int q = lane + 64 * k, px = q / 5, ch = q - 5 * px;
-        const bool ok = px >= 1 && px <= a.W && ch < 4;
-        loff[k] = ok ? (unsigned)((px - 1) * CB + ch * 16) : 0u;
-        lmask |= ok ? 1u << k : 0u;
+        for (int k = 0; k < 5; k++) {
+            const int f = wave + 8 * k;                                  // 36 loads of 64 chunks
+            const int q = 64 * f + lane, row = q / 36, ch = q - 36 * row;
+            if (f < 36) hq_lds_load16(wsrc + row * 576 + 16 * (ch ^ (row >> 2 & 3)), lds0 + wlds + 1024u * f);
+        }
     }
-    auto locate = [&](int p, int &g, int &b) {                       // row and image of an output pixel (uniform)
-        g = (int)hq_magic_div((unsigned)p, a.magic_W);
-        b = (int)hq_magic_div((unsigned)g, a.magic_H);
+
+    // ---- input: 16 channels of 64 positions per load; a wavefront loads two planes of every fourth block.
+    // The ring's place 0 is the first position under the run's first pixel, PW + 1 before the pixel's own.
+    auto over = [](unsigned k, RegwDivisor d) __attribute__((always_inline)) { return d.m ? __umulhi(k, d.m) >> d.s : k; };
+    auto position = [&](unsigned k, int &y, int &x) __attribute__((always_inline)) {   // of a pixel
+        const unsigned b = over(k, a.image), rem = k - b * (unsigned)(a.H * a.W);
+        y = (int)over(rem, a.line);
+        x = (int)(rem - (unsigned)y * (unsigned)a.W);
+        return ((int)b * (a.H + 1) + y) * a.PW + x;
     };
-    // patch rows wave, wave + 8, ... of unit u
-    auto stage = [&](int u, int buf) {
-        int g0, b0, g1, b1;
-        locate(u * RW_UNIT, g0, b0);
-        locate(min(a.M, (u + 1) * RW_UNIT) - 1, g1, b1);
-        const int rows = g1 - g0 + 2 * (b1 - b0) + 3;
-        for (int pr = wave; pr < rows; pr += RW_THREADS / 64) {
-            const int pad = g0 + 2 * b0 + pr;                        // row of the padded images
-            const int img = (int)hq_magic_div((unsigned)pad, a.magic_H2), y = pad - img * (a.H + 2) - 1;
-            const bool in = y >= 0 && y < a.H;
-            const int8_t *src = in ? a.A + ((size_t)img * a.H + y) * a.W * CB : reinterpret_cast<const int8_t *>(hq_fill_rows.w[za & 0xff]);
-            int8_t *dst = smem + buf * bufbytes + pr * rowpitch;
-#pragma unroll
-            for (int k = 0; k < RW_LOADS; k++)
-            {
-                if (k >= nload) break;
-                if ((lmask >> k) & 1) hq_global_to_lds16(src, in ? loff[k] : 0u, dst + 1024 * k);
+    int y0, x0, oy, ox;
+    const int origin = position((unsigned)(u_begin * RW_UNIT), y0, x0);
+    unsigned place = (unsigned)(position((unsigned)(u_begin * RW_UNIT + 32 * wave + r32), oy, ox) - origin);     // of the lane's pixel's first tap
+    auto needed = [&](int u) __attribute__((always_inline)) {           // blocks up to the unit's last position
+        int y, x;
+        return (unsigned)(position((unsigned)(min((u + 1) * RW_UNIT, a.M) - 1), y, x) + 2 * a.PW + 2 - origin) / RW_BLOCK + 1;
+    };
+    // pixel (as if the frame were not there, so that it is right where row and column lie inside the image), row and column of the lane's
+    // next position to load
+    int lp, ly, lx;
+    {
+        const unsigned k = (unsigned)(origin + RW_BLOCK * (wave & 3) + lane);
+        const unsigned b = over(k, a.fimage), rem = k - b * (unsigned)((a.H + 1) * a.PW);
+        ly = (int)over(rem, a.fline);
+        lx = (int)(rem - (unsigned)ly * (unsigned)a.PW);
+        lp = ((int)b * a.H + ly) * a.W + lx - (a.W + 1);
+        ly--; lx--;
+        if (lx < 0) { lx += a.PW; ly--; lp++; }
+        if (ly < 0) { ly += a.H + 1; lp += a.W; }
+    }
+    const int za = __builtin_amdgcn_readfirstlane(a.aq->zero_point);
+    const int8_t *input = a.A + 32 * (wave >> 2);
+    const int8_t *src;
+    bool pending = true;                                                 // `src` has been used
+    int second;                                                          // the other plane's distance: a position outside an image has one row of fill
+    auto prepare = [&]() __attribute__((always_inline)) {
+        const bool there = ((unsigned)lp < (unsigned)a.M) & (ly < a.H) & (lx < a.W);
+        unsigned long long p = (unsigned long long)(uintptr_t)input + (unsigned long long)(unsigned)lp * 64u;
+        asm("" : "+v"(p));                                              // (selected, not branched around)
+        src = reinterpret_cast<const int8_t *>((uintptr_t)(there ? p : (unsigned long long)(uintptr_t)hq_fill_rows.w[za & 0xff]));
+        second = there ? 16 : 0;
+        lx += a.loads.x; ly += a.loads.y; lp += a.loads.p;
+        const bool cx = lx >= a.PW;
+        lx -= cx ? a.PW : 0; ly += cx; lp -= cx;
+        const bool cy = ly > a.H;
+        ly -= cy ? a.H + 1 : 0; lp -= cy ? a.W : 0;
+        pending = false;
+    };
+    unsigned block = wave & 3;                                           // the wavefront's next
+    unsigned at = RW_BLOCK * (wave & 3);                                 // its place in the ring
+    auto load = [&](unsigned end) __attribute__((always_inline)) {      // the wavefront's blocks before `end`, the first of them prepared
+        while (block < end) {
+            const unsigned to = lds0 + 2 * RW_PLANE * (wave >> 2) + at * 16;
+            hq_lds_load16(src, to);
+            hq_lds_load16(src + second, to + RW_PLANE);
+            if (at == 0) {
+                hq_lds_load16(src, to + RW_RING * 16);
+                hq_lds_load16(src + second, to + RW_PLANE + RW_RING * 16);
             }
+            at = at + 4 * RW_BLOCK >= RW_RING ? at + 4 * RW_BLOCK - RW_RING : at + 4 * RW_BLOCK;
+            block += 4;
+            pending = true;
+            if (block < end) prepare();
         }
     };
-
     const int bz = tid < 64 ? a.bsum[n0 + tid] : 0;
     const float acc_scale = __fmul_rn(a.aq->scale, a.bq->scale);
     HqEpilogue ep = {};
-    if (MODE != 0) ep = hq_make_epilogue(acc_scale, a.range);
-    if (u_begin < u_end) stage(u_begin, 0);
-    // padding columns of a buffer's patch rows: never written again
-    auto pad_columns = [&](int buf) {
-        const unsigned f = (unsigned)(za & 0xff) * 0x01010101u;
-        const v4i fv = {(int)f, (int)f, (int)f, (int)f};
-        for (int i = tid; i < a.prows * 8; i += RW_THREADS) {
-            const int ch = i & 3, side = (i >> 2) & 1, pr = i >> 3;
-            *reinterpret_cast<v4i *>(smem + buf * bufbytes + pr * rowpitch + (side ? (a.W + 1) * RW_PITCH : 0) + 16 * ch) = fv;
-        }
-    };
-    pad_columns(0);
-    if (tid < 64) bias[tid] = -za * bz;
-    // Weights of this workgroup's 64 channels.  A fragment's 32 rows lie far apart, so loading them costs 64 cache lines a
-    // KB: every wavefront fetches an eighth of the 36 fragments into LDS, where all read them from.  Row i of a fragment is
-    // channel hq_sigma32(i), so that a lane ends up with 16 consecutive output channels; channel i for 32-bit outputs, whose
-    // products are formed transposed (see finish).
-    v4i wf[9][KC][2];
-    {
-        int8_t *frags = smem + bufbytes;                             // the second buffer is not needed yet
-        const int8_t *wrow = a.Bw + (size_t)(n0 + (MODE == 0 ? lane & 31 : hq_sigma32(lane & 31))) * 9 * CB + 16 * half;
-        for (int f = wave; f < 9 * KC * 2; f += RW_THREADS / 64) {
-            const int nb = f & 1, kc = (f >> 1) % KC, t = (f >> 1) / KC;
-            hq_global_to_lds16(wrow + (size_t)32 * nb * 9 * CB + (a.flip ? 8 - t : t) * CB + 32 * kc, frags + 1024 * f);
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < 9; t++)
-#pragma unroll
-            for (int kc = 0; kc < KC; kc++)
-#pragma unroll
-                for (int nb = 0; nb < 2; nb++) wf[t][kc][nb] = *reinterpret_cast<const v4i *>(frags + 1024 * ((t * KC + kc) * 2 + nb) + 16 * lane);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __syncthreads();
+    if (MODE != 0) {
+        ep = hq_make_epilogue(acc_scale, a.range);
+        auto uniform = [](auto &v) { v = __builtin_bit_cast(std::decay_t<decltype(v)>, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v))); };
+        uniform(ep.mult); uniform(ep.flo); uniform(ep.fhi); uniform(ep.zoff); uniform(ep.c_hi); uniform(ep.c_lo);
     }
-    pad_columns(1);
+    prepare();
+    load(needed(u_begin));
+    if (pending) prepare();
+    if (tid < 64) bias[tid] = -za * bz;
+
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const unsigned mine = lds0 + RW_PLANE * half;
     int mn = INT_MAX, mx = INT_MIN;
     unsigned nlo = 0, nhi = 0;
+    int first = u_begin * RW_UNIT + 32 * wave;                           // the wavefront's first pixel of the unit that is finished next
 
     auto body = [&](auto full) {
         constexpr bool FULL = decltype(full)::value;
-        v16i acc[2];
-        auto multiply = [&](int u, int buf) {
-            int g0, b0;
-            locate(u * RW_UNIT, g0, b0);
-            // row and image relative to the unit's first, from small numbers (exact: the error of the product is far
-            // below the distance to the next integer of (q + 1/2) / W)
-            const int q = min(u * RW_UNIT + wave * 32 + (lane & 31), a.M - 1) - g0 * a.W;
-            const int rr = (int)(((float)q + 0.5f) * a.inv_W), x = q - rr * a.W;
-            const int bb = (int)(((float)(g0 - b0 * a.H + rr) + 0.5f) * a.inv_H);
-            const int8_t *p0 = smem + buf * bufbytes + (rr + 2 * bb) * rowpitch + x * RW_PITCH + 16 * half;
+        // (different statements keep the compiler from loading the weights ahead of the choice, where their registers would be laid out
+        // for both forms of the loop at once, with spills in either)
+        if (FULL) asm volatile("; whole grid" ::: "memory"); else asm volatile("; part of the grid" ::: "memory");
+        constexpr int D = MODE == 2 ? 2 : 3;                             // fragment sets: taps ahead, and the one in use (3 would spill with the random bits)
+        // Row i of a weight fragment is channel hq_sigma32(i), so that a lane ends up with 16 consecutive output channels; channel i for
+        // 32-bit outputs, whose products are formed transposed (see finish32).
+        v4i wf[9][2][2];
 #pragma unroll
-            for (int nb = 0; nb < 2; nb++)
-                if constexpr (MODE == 0) {
-                    const int bz = bias[32 * nb + (lane & 31)];
+        for (int t = 0; t < 9; t++)
 #pragma unroll
-                    for (int e = 0; e < 16; e++) acc[nb][e] = bz;
-                } else
+            for (int kc = 0; kc < 2; kc++)
 #pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const v4i bz = *reinterpret_cast<const v4i *>(bias + 32 * nb + 16 * half + 4 * k);
-#pragma unroll
-                    for (int e = 0; e < 4; e++) acc[nb][4 * k + e] = bz[e];
+                for (int nb = 0; nb < 2; nb++) {
+                    const int row = 32 * nb + (MODE == 0 ? r32 : hq_sigma32(r32)), tap = a.flip ? 8 - t : t;
+                    wf[t][kc][nb] = *reinterpret_cast<const v4i *>(smem + wlds + row * 576 + 16 * ((4 * tap + 2 * kc + half) ^ (row >> 2 & 3)));
                 }
-            // the next tap's fragments are requested before this tap's MFMAs
-            v4i af[2][KC];
-            auto fetch = [&](int t, v4i (&f)[KC]) {
-                const int8_t *pr = p0 + t / 3 * rowpitch + t % 3 * RW_PITCH;
+        v16i acc[2];
+        v4i af[D][2];
+        // the lane's place in its plane under the three filter rows; the taps of a row and the other half of the channels are constant distances
+        unsigned row[3];
+        auto rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int kc = 0; kc < KC; kc++) f[kc] = *reinterpret_cast<const v4i *>(pr + 32 * kc);
-            };
-            fetch(0, af[0]);
+            for (int r = 0; r < 3; r++) {
+                const unsigned k = place + (unsigned)(r * a.PW);
+                row[r] = mine + 16 * min(k, k - RW_RING);               // (k < 2 * RW_RING)
+            }
+            ox += a.unit.x; oy += a.unit.y; place += (unsigned)a.unit.p;
+            const bool cx = ox >= a.W;
+            ox -= cx ? a.W : 0; oy += cx; place += cx;
+            const bool cy = oy >= a.H;
+            oy -= cy ? a.H : 0; place += cy ? (unsigned)a.PW : 0u;
+            place = min(place, place - RW_RING);
+        };
+        auto fetch = [&](int t) __attribute__((always_inline)) {
+            LDS_PTR(const int8_t) q = (LDS_PTR(const int8_t))(size_t)row[t / 3] + t % 3 * 16;
+            af[t % D][0] = *(LDS_PTR(const v4i))q;
+            af[t % D][1] = *(LDS_PTR(const v4i))(q + 2 * RW_PLANE);
+        };
+        auto begin = [&](int nb) __attribute__((always_inline)) {
+            if constexpr (MODE == 0) {
+                const int b = bias[32 * nb + r32];
+#pragma unroll
+                for (int e = 0; e < 16; e++) acc[nb][e] = b;
+            } else
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const v4i b = *reinterpret_cast<const v4i *>(bias + 32 * nb + 16 * half + 4 * k);
+#pragma unroll
+                for (int e = 0; e < 4; e++) acc[nb][4 * k + e] = b[e];
+            }
+        };
+        auto multiply = [&]() __attribute__((always_inline)) {
+            rows();
+            begin(0); begin(1);
+#pragma unroll
+            for (int t = 0; t < D - 1; t++) fetch(t);
 #pragma unroll
             for (int t = 0; t < 9; t++) {
-                if (t < 8) fetch(t + 1, af[(t + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
+                if (t + D - 1 < 9) fetch(t + D - 1);
 #pragma unroll
-                for (int kc = 0; kc < KC; kc++)
+                for (int kc = 0; kc < 2; kc++)
 #pragma unroll
-                    for (int nb = 0; nb < 2; nb++)
-                        acc[nb] = MODE == 0 ? __builtin_amdgcn_mfma_i32_32x32x32_i8(af[t & 1][kc], wf[t][kc][nb], acc[nb], 0, 0, 0)
-                                            : __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[t][kc][nb], af[t & 1][kc], acc[nb], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int nb = 0; nb < 2; nb++) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        acc[nb] = MODE == 0 ? __builtin_amdgcn_mfma_i32_32x32x32_i8(af[t % D][kc], wf[t][kc][nb], acc[nb], 0, 0, 0)
+                                            : __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[t][kc][nb], af[t % D][kc], acc[nb], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        // the next address is worked out while the matrix cores are busy
+                        if (t == 4 && kc == 0 && nb == 0 && pending) prepare();
+                    }
             }
         };
-        // 32-bit outputs: a lane holds one channel of 16 pixels, so a store of the wavefront writes two whole 128-byte lines
-        // (with 16 channels of one pixel a lane it would touch 64 lines, a quarter of each: 44 us against 30 for
-        // 128 x 56 x 56 x 64).
-        auto finish32 = [&](int u) {
-            const int P0 = u * RW_UNIT + wave * 32, left = a.M - P0;
-            const unsigned lo = (unsigned)(4 * half * a.N + (lane & 31));
+        // 32-bit outputs: a lane holds one channel of 16 pixels, so a store of the wavefront writes two whole 128-byte lines (with 16
+        // channels of one pixel a lane it would touch 64 lines, a quarter of each: 44 us against 30 for 128 x 56 x 56 x 64).
+        auto finish32 = [&]() __attribute__((always_inline)) {
+            const unsigned mine32 = (unsigned)(4 * half * a.N + r32);
+            const bool whole = first + 32 <= a.M;
 #pragma unroll
             for (int nb = 0; nb < 2; nb++) {
                 int c[16];
 #pragma unroll
                 for (int e = 0; e < 16; e++) c[e] = acc[nb][e];
-                if (left >= 32) hq_minmax_group<16>(c, mn, mx);
+                int32_t *out = a.out32 + (size_t)(unsigned)first * a.N + n0 + 32 * nb;
+                if (whole) hq_minmax_group<16>(c, mn, mx);
 #pragma unroll
                 for (int e = 0; e < 16; e++) {
-                    const int row = 8 * (e >> 2) + (e & 3);
-                    int32_t *dst = a.out32 + (size_t)(P0 + row) * a.N + n0 + 32 * nb;
-                    if (left >= 32) dst[lo] = c[e];
-                    else if (row + 4 * half < left) { dst[lo] = c[e]; mn = min(mn, c[e]); mx = max(mx, c[e]); }
+                    asm("" : "+s"(out));                                // (a uniform address and the lane's part, not 16 addresses)
+                    if (whole) out[mine32] = c[e];
+                    else if (first + 8 * (e >> 2) + (e & 3) + 4 * half < a.M) { out[mine32] = c[e]; mn = min(mn, c[e]); mx = max(mx, c[e]); }
+                    out += e % 4 == 3 ? 5 * a.N : a.N;
                 }
             }
         };
-        auto finish = [&](int u) {
-            if constexpr (MODE == 0) { finish32(u); return; }
-            const int P = u * RW_UNIT + wave * 32 + (lane & 31);
-            if (P >= a.M) return;
+        // Returns whether all the wavefront's stores were issued.
+        auto finish = [&]() __attribute__((always_inline)) {
+            const bool whole = first + 32 <= a.M;
+            const int pixel = first + r32;
+            if constexpr (MODE == 0) {
+                finish32();
+            } else if (pixel < a.M) {
 #pragma unroll
-            for (int nb = 0; nb < 2; nb++) {
-                int c[16];
+                for (int nb = 0; nb < 2; nb++) {
+                    int c[16];
 #pragma unroll
-                for (int e = 0; e < 16; e++) c[e] = acc[nb][e];
-                const size_t o = (size_t)P * a.N + n0 + 32 * nb + 16 * half;
-                int w[4];
-                if constexpr (MODE == 2) hq_requant_group_sr<16, FULL, 16>(c, ep, a.sr, o, mn, mx, nlo, nhi, w);
-                else                     hq_requant_group<16, FULL>(c, ep, mn, mx, nlo, nhi, w);
-                *reinterpret_cast<v4i *>(a.out8 + o) = v4i{w[0], w[1], w[2], w[3]};
+                    for (int e = 0; e < 16; e++) c[e] = acc[nb][e];
+                    const size_t o = (size_t)(unsigned)pixel * a.N + n0 + 32 * nb + 16 * half;
+                    int w[4];
+                    if constexpr (MODE == 2) hq_requant_group_sr<16, FULL, 16>(c, ep, a.sr, o, mn, mx, nlo, nhi, w);
+                    else                     hq_requant_group<16, FULL>(c, ep, mn, mx, nlo, nhi, w);
+                    *reinterpret_cast<v4i *>(a.out8 + o) = v4i{w[0], w[1], w[2], w[3]};
+                }
             }
+            first += RW_UNIT;
+            return whole;
         };
         // Between two barriers one of a SIMD's two wavefronts multiplies first and requantizes then, the other (`late`)
         // requantizes its unit before and then multiplies, so that the matrix cores and the vector ALU both have work.
         const bool late = wave >= RW_THREADS / 128;
+        bool stored = false;                                            // a unit's stores since the last loads
         for (int u = u_begin; u < u_end; u++) {
-            const int buf = (u - u_begin) & 1;
-            // this wavefront's rows of unit u are in LDS once only the stores issued after them are under way
-            if (u == u_begin || (late && u == u_begin + 1)) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-            else                                           asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STORES) : "memory");
+            // this wavefront's blocks of the unit are in LDS once only the stores issued after them are under way
+            if (stored) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(MODE == 0 ? 32 : 2) : "memory");
+            else        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            if (u + 1 < u_end) stage(u + 1, buf ^ 1);
-            if (late && u > u_begin) finish(u - 1);
-            multiply(u, buf);
-            if (!late) finish(u);
+            if (u + 1 < u_end) load(needed(u + 1));
+            stored = false;
+            if (late && u > u_begin) stored = finish();
+            multiply();
+            if (!late) stored = finish();
         }
-        if (late && u_end > u_begin) finish(u_end - 1);
+        if (late && u_end > u_begin) finish();
     };
     if (MODE == 0 || ep.full_grid) body(std::true_type()); else body(std::false_type());
     hq_block_stats_commit_n<RW_THREADS>(mn, mx, nlo, nhi, a.st, red);
@@ -254,16 +316,12 @@ int hq_try_launch_regw(const hq_problem *p, int dgrad, const int8_t *A, const hq
     if (Cs != 64 || N % 64 != 0) return HQ_E_BADSHAPE;
     const unsigned long long M = (unsigned long long)p->B * p->H * p->W;
     const int H = p->H, W = p->W;
-    // operands of hq_magic_div and the exactness of the float divisions
-    if ((M + RW_UNIT) * (unsigned)((H > W ? H : W) + 2) >= (1ull << 32) || H > 4096 || W > 4096) return HQ_E_BADSHAPE;
+    if ((unsigned long long)p->B * (H + 1) * (W + 1) >= (1ull << 31) - 4096) return HQ_E_BADSHAPE;      // (positions are ints)
+    // the ring holds a unit's positions and the next one's, blocks loaded as wholes
+    const int lines = (2 * RW_UNIT - 2) / W + 1, images = (2 * RW_UNIT - 2) / (H * W) + 1;
+    if (2 * RW_UNIT + lines + images * (W + 1) + 2 * (W + 1) + 2 + RW_BLOCK > RW_RING) return HQ_E_BADSHAPE;
     RegwArgs a = {};
-    a.PW = W + 2;
-    if ((a.PW * 5 + 63) / 64 > RW_LOADS) return HQ_E_BADSHAPE;
-    const int rows = (RW_UNIT + W - 2) / W + 1;                      // most output rows a unit touches
-    a.prows = rows + 2 + 2 * ((rows + H - 2) / H);
-    const size_t buf = (size_t)a.prows * a.PW * RW_PITCH + 1024;
-    const size_t lds = buf + std::max(buf, (size_t)36 * 1024);
-    if (lds > 156 * 1024) return HQ_E_BADSHAPE;
+    a.PW = W + 1;
     a.A = A; a.Bw = Bw; a.bsum = bsum; a.aq = aq; a.bq = bq; a.range = range;
     a.out8 = out8; a.out32 = out32; a.outq = outq; a.st = st;
     a.M = (int)M; a.N = N; a.H = H; a.W = W; a.flip = dgrad;
@@ -272,14 +330,25 @@ int hq_try_launch_regw(const hq_problem *p, int dgrad, const int8_t *A, const hq
     a.runs = 256 / a.nparts;
     if (a.runs < 1) a.runs = 1;
     if (a.runs > a.units) a.runs = a.units;
-    a.magic_W = hq_magic32((unsigned)W); a.magic_H = hq_magic32((unsigned)H); a.magic_H2 = hq_magic32((unsigned)(H + 2));
-    a.inv_W = 1.0f / (float)W; a.inv_H = 1.0f / (float)H;
+    auto divisor = [](unsigned d) {
+        unsigned l = 1;
+        while ((1ull << l) < d) l++;
+        return d < 2 ? RegwDivisor{0, 0} : RegwDivisor{(unsigned)(((1ull << (31 + l)) + d - 1) / d), l - 1};
+    };
+    const int image = H * W, fimage = (H + 1) * a.PW, step = 4 * RW_BLOCK;
+    a.image = divisor((unsigned)image); a.line = divisor((unsigned)W);
+    a.fimage = divisor((unsigned)fimage); a.fline = divisor((unsigned)a.PW);
+    a.unit.y = RW_UNIT % image / W; a.unit.x = RW_UNIT % image % W;
+    a.unit.p = RW_UNIT / image * fimage + a.unit.y * a.PW + a.unit.x;
+    a.loads.y = step % fimage / a.PW; a.loads.x = step % fimage % a.PW;
+    a.loads.p = (step / fimage * H + a.loads.y) * W + a.loads.x;
     if (sr_seed && out32) return HQ_E_BADARG;
     a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
     const int mode = out32 ? 0 : sr_seed ? 2 : 1;
     auto kern = mode == 0 ? hq_regw_kernel<0> : mode == 2 ? hq_regw_kernel<2> : hq_regw_kernel<1>;
+    constexpr size_t lds = 4 * RW_PLANE + RW_WEIGHTS;
     static std::atomic<unsigned long long> allowed[3];
-    if (!hq_allow_lds(kern, 156 * 1024, allowed[mode])) return HQ_E_HIP;
+    if (!hq_allow_lds(kern, lds, allowed[mode])) return HQ_E_HIP;
     hipLaunchKernelGGL(kern, dim3((unsigned)(a.runs * a.nparts)), dim3(RW_THREADS), lds, stream, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }

@@ -80,7 +80,8 @@ def test_64_channel_layers_go_to_their_own_kernels_past_one_round():
     check([(op, conv(20, 28, 64, 3, 1, 64), ks) for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")] +
           [(op, conv(21, 28, 64, 3, 1, 64), regw) for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")] +
           [("fwd", conv(10, 30, 64, 3, 1, 64, 0), ks), ("fwd", conv(21, 30, 64, 3, 1, 64, 0), band),                # no padding
-           ("fwd", (CONV, 2, 20, 130, 64, 3, 3, 1, 1, 64), ks), ("fwd", (CONV, 7, 20, 130, 64, 3, 3, 1, 1, 64), tile),      # too wide for either
+           ("fwd", (CONV, 2, 20, 130, 64, 3, 3, 1, 1, 64), ks), ("fwd", (CONV, 7, 20, 130, 64, 3, 3, 1, 1, 64), regw),
+           ("fwd", (CONV, 2, 30, 403, 64, 3, 3, 1, 1, 64), regw), ("fwd", (CONV, 2, 30, 404, 64, 3, 3, 1, 1, 64), tile),    # too wide for either
            ("fwd", conv(26, 28, 64, 3, 2, 64), ks), ("fwd", conv(90, 28, 64, 3, 2, 64), band), ("fwd", conv(20, 28, 64, 3, 2, 80), ks)])
 
 
@@ -254,6 +255,8 @@ def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_for():
     assert all(regw(op, s) for s in T.REGW_ALL_MODES for op in ("dynamic_fwd", "dynamic_dgrad", "fwd", "dgrad", "dgrad_sr"))
     assert all(regw("fwd", s) for s in T.REGW_FORWARD)
     assert all(regw(op, s) for s in T.REGW_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
+    assert all(regw("fwd", s) for s in T.REGW_RING_FORWARD)
+    assert all(regw(op, s) for s in T.REGW_RING_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
     assert not any(regw(op, s) for s in T.REGW_PAST + T.REGW_ONE_ROUND for op in ("dynamic_fwd", "fwd", "dgrad", "dgrad_sr"))
     for L in T.RING_BACKWARD + T.RING_OTHER:
         check([(op, tuple(L)[1:], "hq_frame_kernel" if L.R == 3 and L.pad == 1 else "hq_ring_kernel") for op in ("dgrad", "dgrad_sr", "dynamic_dgrad")])

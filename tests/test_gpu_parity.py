@@ -411,6 +411,28 @@ def test_weights_in_registers(H, hq, L, g_asym):
         g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
+# The same kernel's ring of input positions: runs of several units that wrap round it, under images that are mostly frame (whose positions come
+# many blocks to a unit); the widest images; lines that are images.
+REGW_RING_FORWARD = [(1880, 3, 3, 64, 1024), (4, 12, 403, 64, 64), (170, 1, 100, 64, 64)]
+REGW_RING_BACKWARD = [(4300, 2, 2, 1024, 64), (4, 12, 403, 64, 64), (170, 1, 100, 64, 64)]
+
+
+@pytest.mark.parametrize("s", REGW_RING_FORWARD + REGW_RING_BACKWARD[:1], ids=lambda s: "b%d_%dx%d_c%d_n%d" % s)
+def test_weights_in_registers_with_a_wrapping_ring(H, hq, s):
+    B, Hh, Ww, c, n = s
+    L = wl.LayerShape("regw_ring", wl.CONV, B, Hh, Ww, c, 3, 3, 1, 1, n)
+    y_track, g_track = H.TensorTrack(0.9, False), H.TensorTrack(0.9, True)
+    Wdev = None
+    for t in range(3):                                       # dynamic, nearest, stochastic
+        X, W, dY = rand_layer_inputs(L, 95 + t, x_asym=True, g_asym=True)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        if s in REGW_RING_FORWARD and t < 2:
+            y_track.step(L, "fwd", X, W0, H.DevTensor(X), Wdev)
+        if s in REGW_RING_BACKWARD:
+            g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
+
+
 # Whole 128-byte lines per stage: pixels and channels off the 128 x 128 tile, mirrored taps under every padding, strides, filters that
 # are not square, the shortest reduction, bands of eight pixel tiles with a short last one.
 RING_SHAPES = [wl.conv("ring_n144", 34, 13, 128, 144, 3), wl.conv("ring_both_ways", 26, 14, 256, 256, 3), wl.conv("ring_s2", 40, 29, 128, 272, 3, stride=2),
