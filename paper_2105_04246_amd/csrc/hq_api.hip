@@ -230,6 +230,8 @@ static int gemm_common(const hq_problem *p, int dgrad, const int8_t *A, const hq
     if (rc != HQ_E_BADSHAPE) return rc;
     rc = hq_try_launch_regw(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
     if (rc != HQ_E_BADSHAPE) return rc;
+    rc = hq_try_launch_point(p, dgrad, A, aq, Bw, bq, bsum, range, out, out32, outq, st, as_stream(stream), sr_seed);
+    if (rc != HQ_E_BADSHAPE) return rc;
     if (sr_seed) {
         // stochastic rounding: never a first layer (no input gradient)
         if (p->kind == HQ_DEPTHWISE)

@@ -19,7 +19,7 @@
 //     patch of a group is requested during its MFMA phase (into registers, a few rows between
 //     taps) and written to LDS at the start of its epilogue phase, when nobody reads that patch.
 //     A loader thread owns PJ 16-byte chunks of a patch row: one for rows of up to 64 pixels at 64
-//     channels, two for rows of up to 126 pixels, three for the 192-channel 1x1 layers.
+//     channels, two for rows of up to 126 pixels.
 //   * A band whose last tile is one wavefront's worth of pixels does not spend half steps on it:
 //     the second group, idle in half step 0, multiplies and requantizes it there from a third
 //     patch buffer.
@@ -60,6 +60,7 @@ struct BandArgs {
     int sr_on;
 };
 
+constexpr int BAND_THREADS = 512;  // two groups of four wavefronts, which alternate matrix-core phase and epilogue phase in lockstep, half a step apart
 constexpr int BM = 256;            // output pixels per tile: 4 wavefronts x 2 MFMA row blocks
 
 template <int C> __device__ inline int wswz(int i)
@@ -68,18 +69,12 @@ template <int C> __device__ inline int wswz(int i)
 }
 
 // PR: patch rows prefetched per tile (>= PRmax), PJ: 16-byte column chunks per thread and row.
-// NG: groups of four wavefronts in a workgroup.  NG == 2: the two groups alternate matrix-core
-// phase and epilogue phase in lockstep, half a step apart.  NG == 1 (when the LDS holds two
-// workgroups with their own copy of the weights): a workgroup runs its phases one after the other
-// and the two workgroups of a compute unit overlap freely, without a common barrier and without the
-// idle half steps at both ends.
 // MODE: 0 = 32-bit outputs (first pass of the dynamic baseline), 1 = fused requantization with
 // round-half-even, 2 = fused with stochastic rounding (input gradients).
-template <int C, int KSZ, int NT, int PR, int PJ, int NG, int MODE>
-__global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void hq_band_kernel(const BandArgs a)
+template <int C, int KSZ, int NT, int PR, int PJ, int MODE>
+__global__ __launch_bounds__(BAND_THREADS, 1) void hq_band_kernel(const BandArgs a)
 {
     constexpr bool FUSED = MODE != 0, SR = MODE == 2;
-    constexpr int BAND_THREADS = 256 * NG;
     constexpr int NCH = C / 16, KS = C / 32, PP = C + 16, BN = 32 * NT, TAPS = KSZ * KSZ;
     constexpr int WROW = TAPS * C;                        // bytes per weight row in LDS
     extern __shared__ __attribute__((aligned(16))) int8_t smem[];
@@ -87,11 +82,11 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void hq_band_kernel(cons
     int8_t *Wl = smem;                                     // [npad][TAPS][C], chunks swizzled
     int *bz = reinterpret_cast<int *>(smem + (size_t)a.npad * WROW);     // [npad]  z_a * bsum[n]
     int8_t *Pl = reinterpret_cast<int8_t *>(bz + a.npad);  // one patch per group [PRmax * PW][PP]
-    int8_t *Pt = Pl + NG * (size_t)patch_bytes;            // patch of an early last tile (if a.tail_patch)
-    int *red = reinterpret_cast<int *>(Pl + (NG + a.tail_patch) * (size_t)patch_bytes);
+    int8_t *Pt = Pl + 2 * (size_t)patch_bytes;            // patch of an early last tile (if a.tail_patch)
+    int *red = reinterpret_cast<int *>(Pl + (2 + a.tail_patch) * (size_t)patch_bytes);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: branches on it are uniform
-    const int grp = NG == 2 ? wave >> 2 : 0, gwave = wave & 3, gtid = tid & 255;
+    const int grp = wave >> 2, gwave = wave & 3, gtid = tid & 255;
     int8_t *Pg = Pl + grp * patch_bytes;                   // this group's patch
 
     // ---- start-up, part 1: everything that does not depend on other loads is requested before anything
@@ -194,7 +189,7 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void hq_band_kernel(cons
     // A last tile that one wavefront covers does not get half steps of its own: the second group,
     // which would idle through half step 0, multiplies and requantizes it there, from a patch
     // buffer of its own (so that the group's first regular patch can be written meanwhile).
-    const bool early_tail = NG == 2 && a.tail_patch && nchunk == 1 && nitem >= 2 && (p1 - p0) - (ntile - 1) * BM <= 64;
+    const bool early_tail = a.tail_patch && nchunk == 1 && nitem >= 2 && (p1 - p0) - (ntile - 1) * BM <= 64;
     const int nmain = early_tail ? nitem - 1 : nitem;      // items that take turns in the half steps
     const bool tail_grp = early_tail && grp == 1;
     if (tail_grp) {
@@ -234,21 +229,21 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void hq_band_kernel(cons
 
     // Half step h: item h is multiplied (by group h & 1) while item h-1 goes through the
     // epilogue (in the other group, which multiplied it during half step h-1).
-    const int nhalf = NG == 2 ? nmain + 1 : 2 * nitem;
+    const int nhalf = nmain + 1;
     for (int h = 0; h < nhalf; h++) {
       const bool tail_now = tail_grp && h == 0;
       const int8_t *Psrc = tail_now ? Pt : Pg;
       for (int sub = 0; sub < (tail_now ? 2 : 1); sub++) {
-        const bool mfma_phase = tail_now ? sub == 0 : NG == 2 ? (h & 1) == grp : (h & 1) == 0;
+        const bool mfma_phase = tail_now ? sub == 0 : (h & 1) == grp;
         // this group's item in this half step
-        const int item = tail_now ? nitem - 1 : NG == 2 ? (mfma_phase ? h : h - 1) : h >> 1;
+        const int item = tail_now ? nitem - 1 : mfma_phase ? h : h - 1;
         if (item >= 0 && (item < nmain || tail_now)) {
             const int tile = nchunk == 1 ? item : item / nchunk, nc = item - tile * nchunk;
             const int ps = p0 + tile * BM;
             if (mfma_phase) {
                 // -------------------------------------------------- matrix-core phase
                 if (tail_now && grp < nmain) stash(Pg);    // nobody reads this group's patch in this half step
-                const int nxt = item + NG;
+                const int nxt = item + 2;
                 have_pf = !tail_now && nxt < nmain && (nchunk == 1 || nxt / nchunk != tile);
                 const bool active = ps + gwave * 64 < p1;
                 // the next tile's patch rows are requested between the taps (a few per tap), where the
@@ -396,30 +391,22 @@ __global__ __launch_bounds__(256 * NG, NG == 1 ? 2 : 1) void hq_band_kernel(cons
 
 constexpr size_t BAND_LDS_MAX = 160 * 1024;
 
-template <int C, int KSZ, int NT, int PR, int PJ, int NG, int MODE>
+template <int C, int KSZ, int NT, int PR, int PJ, int MODE>
 int launch_band_mode(const BandArgs &a, int blocks, size_t lds, hipStream_t s)
 {
     static std::atomic<unsigned long long> allowed{0};
-    auto kern = hq_band_kernel<C, KSZ, NT, PR, PJ, NG, MODE>;
+    auto kern = hq_band_kernel<C, KSZ, NT, PR, PJ, MODE>;
     if (!hq_allow_lds(kern, BAND_LDS_MAX, allowed)) return HQ_E_HIP;
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256 * NG), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(BAND_THREADS), lds, s, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }
 
-template <int C, int KSZ, int NT, int PR, int PJ, int NG>
-int launch_band(const BandArgs &a, int mode, int blocks, size_t lds, hipStream_t s)
-{
-    if (mode == 0) return launch_band_mode<C, KSZ, NT, PR, PJ, NG, 0>(a, blocks, lds, s);
-    if (mode == 1) return launch_band_mode<C, KSZ, NT, PR, PJ, NG, 1>(a, blocks, lds, s);
-    return launch_band_mode<C, KSZ, NT, PR, PJ, NG, 2>(a, blocks, lds, s);
-}
-
 template <int C, int KSZ, int NT, int PR, int PJ>
-int launch_band_ng(const BandArgs &a, int ng, int blocks, size_t lds, hipStream_t s)
+int launch_band(const BandArgs &a, int blocks, size_t lds, hipStream_t s)
 {
-    const int mode = a.out32 ? 0 : a.sr_on ? 2 : 1;
-    return ng == 1 ? launch_band<C, KSZ, NT, PR, PJ, 1>(a, mode, blocks, lds, s)
-                   : launch_band<C, KSZ, NT, PR, PJ, 2>(a, mode, blocks, lds, s);
+    if (a.out32) return launch_band_mode<C, KSZ, NT, PR, PJ, 0>(a, blocks, lds, s);
+    if (!a.sr_on) return launch_band_mode<C, KSZ, NT, PR, PJ, 1>(a, blocks, lds, s);
+    return launch_band_mode<C, KSZ, NT, PR, PJ, 2>(a, blocks, lds, s);
 }
 
 } // namespace
@@ -448,44 +435,33 @@ int hq_try_launch_band(const hq_problem *p, int dgrad, const int8_t *A, const hq
         a.stride = 1; a.pad = p->R - 1 - p->pad; a.flip = 1;
     }
     const int KSZ = p->R;
-    int NT, PJ;
-    if (C == 64 && KSZ == 3) { NT = 2; PJ = ((a.Wo - 1) * a.stride + KSZ) * 4 > 256 ? 2 : 1; }   // patch rows of up to 64 / 128 pixels
-    else if (C == 32 && KSZ == 1) { NT = 2; PJ = 1; }
-    else if (C == 192 && KSZ == 1) { NT = 1; PJ = 3; }
-    else return HQ_E_BADSHAPE;
+    if (C != 64 || KSZ != 3) return HQ_E_BADSHAPE;
+    const int NT = 2, PJ = ((a.Wo - 1) * a.stride + KSZ) * 4 > 256 ? 2 : 1;                 // patch rows of up to 64 / 128 pixels
     if ((a.N % 16) != 0 || a.Ho * a.Wo >= 65536) return HQ_E_BADSHAPE;
     const int BN = 32 * NT;
     a.npad = (a.N + BN - 1) / BN * BN;
     a.PW = (a.Wo - 1) * a.stride + KSZ;
     if (a.PW * (C / 16) > 256 * PJ) return HQ_E_BADSHAPE;
 
-    // bands: one two-group workgroup per CU, or (1x1 layers, where it measured faster: short tiles,
-    // small weights) two independent one-group workgroups when the LDS holds both
-    size_t lds = 0;
-    int ng = 1, prmax = 0;
-    for (ng = KSZ == 1 ? 1 : 2; ng <= 2; ng++) {
-        int bpi = ((ng == 1 ? 512 : 256) + p->B - 1) / p->B;
-        if (bpi > a.Ho) bpi = a.Ho;
-        if (bpi < 1) bpi = 1;
-        a.rows_per_band = (a.Ho + bpi - 1) / bpi;
-        a.bands_per_image = (a.Ho + a.rows_per_band - 1) / a.rows_per_band;
-        // most patch rows any tile needs
-        prmax = 0;
-        for (int band = 0; band < a.bands_per_image; band++) {
-            const int r0 = band * a.rows_per_band, r1 = (r0 + a.rows_per_band < a.Ho) ? r0 + a.rows_per_band : a.Ho;
-            for (int ps = r0 * a.Wo; ps < r1 * a.Wo; ps += BM) {
-                const int last = (ps + BM < r1 * a.Wo ? ps + BM : r1 * a.Wo) - 1;
-                const int rows = (last / a.Wo - ps / a.Wo) * a.stride + KSZ;
-                if (rows > prmax) prmax = rows;
-            }
+    // bands: one workgroup per CU
+    int bpi = (256 + p->B - 1) / p->B;
+    if (bpi > a.Ho) bpi = a.Ho;
+    a.rows_per_band = (a.Ho + bpi - 1) / bpi;
+    a.bands_per_image = (a.Ho + a.rows_per_band - 1) / a.rows_per_band;
+    // most patch rows any tile needs
+    int prmax = 0;
+    for (int band = 0; band < a.bands_per_image; band++) {
+        const int r0 = band * a.rows_per_band, r1 = (r0 + a.rows_per_band < a.Ho) ? r0 + a.rows_per_band : a.Ho;
+        for (int ps = r0 * a.Wo; ps < r1 * a.Wo; ps += BM) {
+            const int last = (ps + BM < r1 * a.Wo ? ps + BM : r1 * a.Wo) - 1;
+            const int rows = (last / a.Wo - ps / a.Wo) * a.stride + KSZ;
+            if (rows > prmax) prmax = rows;
         }
-        lds = (size_t)a.npad * KSZ * KSZ * C + (size_t)a.npad * 4 + ng * (size_t)prmax * a.PW * (C + 16) + 128;
-        if (ng == 1 && 2 * (lds + 1024) <= BAND_LDS_MAX) break;      // two workgroups fit (1 KiB each of slack)
-        if (ng == 2) break;
     }
+    size_t lds = (size_t)a.npad * KSZ * KSZ * C + (size_t)a.npad * 4 + 2 * (size_t)prmax * a.PW * (C + 16) + 128;
     a.PRmax = prmax;
     a.tail_patch = 0;
-    if (ng == 2 && lds + (size_t)prmax * a.PW * (C + 16) <= BAND_LDS_MAX) {
+    if (lds + (size_t)prmax * a.PW * (C + 16) <= BAND_LDS_MAX) {
         a.tail_patch = 1;
         lds += (size_t)prmax * a.PW * (C + 16);
     }
@@ -493,20 +469,8 @@ int hq_try_launch_band(const hq_problem *p, int dgrad, const int8_t *A, const hq
     a.magic_Wo = hq_magic32((unsigned)a.Wo);
     a.count = (unsigned long long)p->B * a.Ho * a.Wo * a.N;
     const int blocks = p->B * a.bands_per_image;
-    if (C == 64 && PJ == 2) {
-        if (prmax <= 6) return launch_band_ng<64, 3, 2, 6, 2>(a, ng, blocks, lds, stream);
-        return HQ_E_BADSHAPE;
-    }
-    if (C == 64) {
-        if (prmax <= 8) return launch_band_ng<64, 3, 2, 8, 1>(a, ng, blocks, lds, stream);
-        if (prmax <= 12) return launch_band_ng<64, 3, 2, 12, 1>(a, ng, blocks, lds, stream);
-        return HQ_E_BADSHAPE;
-    }
-    if (C == 32) {
-        if (prmax <= 6) return launch_band_ng<32, 1, 2, 6, 1>(a, ng, blocks, lds, stream);
-        if (prmax <= 14) return launch_band_ng<32, 1, 2, 14, 1>(a, ng, blocks, lds, stream);
-        return HQ_E_BADSHAPE;
-    }
-    if (prmax <= 6) return launch_band_ng<192, 1, 1, 6, 3>(a, ng, blocks, lds, stream);
+    if (PJ == 2) return prmax <= 6 ? launch_band<64, 3, 2, 6, 2>(a, blocks, lds, stream) : HQ_E_BADSHAPE;
+    if (prmax <= 8) return launch_band<64, 3, 2, 8, 1>(a, blocks, lds, stream);
+    if (prmax <= 12) return launch_band<64, 3, 2, 12, 1>(a, blocks, lds, stream);
     return HQ_E_BADSHAPE;
 }

@@ -39,7 +39,14 @@ int hq_try_launch_regw(const hq_problem *p, int dgrad, const int8_t *A, const hq
                        int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream,
                        const uint64_t *sr_seed = nullptr);
 
-// Fast path for layers whose weights fit in LDS; HQ_E_BADSHAPE means "not covered, use hq_launch_gemm".
+// At most 192 reduced channels under one tap (pixels straight into registers, weights in LDS); HQ_E_BADSHAPE: not covered.
+// sr_seed as for hq_launch_gemm.
+int hq_try_launch_point(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
+                       const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
+                       int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream,
+                       const uint64_t *sr_seed = nullptr);
+
+// Fast path for 3x3 layers with 64 reduced channels whose weights fit in LDS; HQ_E_BADSHAPE means "not covered, use hq_launch_gemm".
 // sr_seed as for hq_launch_gemm.
 int hq_try_launch_band(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
                        const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,

@@ -85,6 +85,19 @@ def test_64_channel_layers_go_to_their_own_kernels_past_one_round():
            ("fwd", conv(26, 28, 64, 3, 2, 64), ks), ("fwd", conv(90, 28, 64, 3, 2, 64), band), ("fwd", conv(20, 28, 64, 3, 2, 80), ks)])
 
 
+def test_short_reductions_split_channels_for_want_of_pixels():
+    point, tile = "hq_point_kernel", "hq_gemm_kernel"
+    check([("fwd", (LINEAR, 40000, 1, 1, 192, 1, 1, 1, 0, 256), point), ("fwd", (LINEAR, 40000, 1, 1, 208, 1, 1, 1, 0, 256), tile),
+           ("fwd", (LINEAR, 40000, 1, 1, 184, 1, 1, 1, 0, 256), tile), ("fwd", (LINEAR, 40000, 1, 1, 192, 1, 1, 1, 0, 248), tile),      # off 16
+           ("fwd", (LINEAR, 40000, 1, 1, 128, 1, 1, 1, 0, 256), tile), ("dynamic_fwd", (LINEAR, 40000, 1, 1, 128, 1, 1, 1, 0, 256), point),
+           ("fwd", (LINEAR, 65504, 1, 1, 128, 1, 1, 1, 0, 256), tile), ("fwd", (LINEAR, 65505, 1, 1, 128, 1, 1, 1, 0, 256), point),
+           ("fwd", (LINEAR, 40000, 1, 1, 128, 1, 1, 1, 0, 240), point), ("fwd", (LINEAR, 40000, 1, 1, 96, 1, 1, 1, 0, 256), point),
+           ("fwd", conv(64, 57, 64, 1, 2, 64), point)])
+    def blocks(*c):
+        return launches.calls([("fwd", (LINEAR, c[0], 1, 1, c[1], 1, 1, 1, 0, c[2]))])[0][0].blocks
+    assert blocks(401408, 32, 192) == 512 and blocks(8192, 192, 4096) == 512 and blocks(8192, 64, 512) == 256 and blocks(70000, 128, 512) == 512
+
+
 def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
     long_, short = "hq_gemm_kernel<128, 128, 2, 2, 128", "hq_gemm_kernel<128, 128, 2, 2, 64"
     check([("dgrad_sr", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2064), short), ("dgrad", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2064), long_),
@@ -257,6 +270,11 @@ def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_for():
     assert all(regw(op, s) for s in T.REGW_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
     assert all(regw("fwd", s) for s in T.REGW_RING_FORWARD)
     assert all(regw(op, s) for s in T.REGW_RING_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
+    def point(op, s):
+        B, H, W, C, stride, n = s
+        return launches.calls([(op, (LINEAR if H * W == 1 else CONV, B, H, W, C, 1, 1, stride, 0, n))])[0][0].kernel.startswith("hq_point_kernel")
+    assert all(point(op, s) for s in T.POINT_FORWARD for op in ("dynamic_fwd", "fwd"))
+    assert all(point(op, s) for s in T.POINT_BACKWARD for op in ("dynamic_dgrad", "dgrad", "dgrad_sr"))
     assert not any(regw(op, s) for s in T.REGW_PAST + T.REGW_ONE_ROUND for op in ("dynamic_fwd", "fwd", "dgrad", "dgrad_sr"))
     for L in T.RING_BACKWARD + T.RING_OTHER:
         check([(op, tuple(L)[1:], "hq_frame_kernel" if L.R == 3 and L.pad == 1 else "hq_ring_kernel") for op in ("dgrad", "dgrad_sr", "dynamic_dgrad")])

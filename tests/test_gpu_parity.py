@@ -433,6 +433,29 @@ def test_weights_in_registers_with_a_wrapping_ring(H, hq, s):
             g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
+# Short reductions: pixels off the block of 32, odd numbers of 16 reduced and output channels, the shortest and longest reduction, channels
+# split between workgroups by the LDS and for want of pixels, strides on sides they do not divide.
+POINT_FORWARD = [(1, 129, 129, 16, 1, 16), (1, 129, 131, 48, 1, 80), (5, 58, 57, 176, 1, 48), (3, 161, 160, 160, 3, 240), (4, 129, 131, 48, 2, 64), (1, 130, 127, 112, 1, 32),
+                 (2051, 1, 1, 192, 1, 1040), (1031, 1, 1, 80, 1, 2064), (16651, 1, 1, 128, 1, 64), (70001, 1, 1, 32, 1, 48)]
+POINT_BACKWARD = [(5, 58, 57, 32, 1, 192), (1, 131, 129, 240, 1, 144), (1, 129, 129, 48, 1, 16), (16651, 1, 1, 64, 1, 80), (2051, 1, 1, 1040, 1, 176)]
+
+
+@pytest.mark.parametrize("s", POINT_FORWARD + POINT_BACKWARD, ids=lambda s: "b%d_%dx%d_c%d_s%d_n%d" % s)
+def test_short_reductions_straight_from_memory(H, hq, s):
+    B, Hh, Ww, c, stride, n = s
+    L = wl.linear("point", B, c, n) if Hh * Ww == 1 else wl.LayerShape("point", wl.CONV, B, Hh, Ww, c, 1, 1, stride, 0, n)
+    y_track, g_track = H.TensorTrack(0.9, False), H.TensorTrack(0.9, True)
+    Wdev = None
+    for t in range(3):                                       # dynamic, nearest, stochastic
+        X, W, dY = rand_layer_inputs(L, 99 + t, x_asym=True, g_asym=True)
+        if Wdev is None:
+            W0, Wdev = W, H.DevWeights(L, W)
+        if s in POINT_FORWARD and t < 2:
+            y_track.step(L, "fwd", X, W0, H.DevTensor(X), Wdev)
+        if s in POINT_BACKWARD:
+            g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
+
+
 # Whole 128-byte lines per stage: pixels and channels off the 128 x 128 tile, mirrored taps under every padding, strides, filters that
 # are not square, the shortest reduction, bands of eight pixel tiles with a short last one.
 RING_SHAPES = [wl.conv("ring_n144", 34, 13, 128, 144, 3), wl.conv("ring_both_ways", 26, 14, 256, 256, 3), wl.conv("ring_s2", 40, 29, 128, 272, 3, stride=2),
