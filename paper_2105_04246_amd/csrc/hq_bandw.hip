@@ -1,7 +1,7 @@
 // 3x3 stride-1 convolution with many channels (C a multiple of 64 from 128 up, Cout a multiple of
 // 128) on int8 MFMA with the fused in-hindsight epilogue: forward and, with mirrored taps, the input
-// gradient of the layers of ResNet stages 2 to 4 (paper Sec. 3.1; Sec. 3.2 static quantization;
-// Sec. 4 steps 1 and 2).
+// gradient (paper Sec. 3.1; Sec. 3.2 static quantization; Sec. 4 steps 1 and 2), on images wider than the framed tiles of
+// hq_frame_kernel take, about 125 to 256 pixels.
 //
 // The general gather kernel fetches every input byte once per tap: at a 128x128 tile that is 64
 // bytes through the vector memory path per clock of matrix work, which is all that path delivers.

@@ -11,14 +11,14 @@
 // are added through LDS once), a stage is 8 MFMAs and about 40 other instructions, dealt out between the MFMAs: fragments of the
 // next k-step are read, the loads of the stage after next are worked out and requested while one is carried out.
 //
-// Measured (with the kernels before / with this one): 3x3 on 128 x 8 x 8 x 512 -> 512 43.6 / 23.9 us, 128 x 16 x 16 x 256 -> 256
-// 28.0 / 24.1, 256 x 7 x 7 x 512 -> 512 48.3 / 37.2, stride 2 on 256 x 28 x 28 x 128 -> 256 30.2 / 26.1, 5x5 on
-// 64 x 28 x 28 x 128 -> 128 49.6 / 28.7, linear 8192 x 4096 -> 4096 189 / 149 (1.84 POP/s).  What bounds it now (counters of
+// Measured (with the kernels before / with this one): 3x3 stride 2 on 256 x 28 x 28 x 128 -> 256 30.2 / 26.1 us, 5x5 on
+// 64 x 28 x 28 x 128 -> 128 49.6 / 28.7, linear 8192 x 4096 -> 4096 189 / 149 (1.84 POP/s); 3x3 of stride 1 and padding 1 has a kernel of its
+// own (256 x 7 x 7 x 512 -> 512 37.2 us here, 32.4 there).  What bounds it now (counters of
 // 4096 x 4096 x 4096, 79 us under collection): of 160 K cycles the matrix pipes are busy for 41 %, the LDS for 23 % without a conflict, and
 // the path from L2 brings 28 bytes a clock of the 50 that loads alone reach; what is left is a wavefront's 14 other instructions
 // per MFMA, in order, and its wait at the stage's barrier.  On random bytes the clock is 2.0 GHz: with all operands 0 the same cycles
 // take 62 us.  Three or four stages with one workgroup per compute unit were slower wherever there is more than one tile for it
-// (3x3, 256 x 14 x 14 x 256: 55 us against 44), and four wavefronts with all k-steps each where there is one (8 x 8 x 512: 29 us
+// (3x3 on 256 x 14 x 14 x 256: 55 us against 44), and four wavefronts with all k-steps each where there is one (8 x 8 x 512: 29 us
 // against 25).
 #include "hq_device.h"
 #include "hq_internal.h"
