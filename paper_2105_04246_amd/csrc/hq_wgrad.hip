@@ -21,6 +21,7 @@
 
 namespace {
 
+constexpr int WP_THREADS = 512;
 constexpr int MB = 64;             // pixels staged per step (two MFMA k-steps of 32)
 
 struct WgradArgs {
@@ -62,8 +63,8 @@ __device__ inline v4i load16(const int8_t *p, int nbytes, bool aligned16)
 // image with the zero-point code.
 // ALIGNED: rows of both operands are whole 16-byte chunks (and the pixel decode fits hq_magic_div): loads without a branch, lanes without
 // a source read the tensor's first bytes, and what they hold is replaced when it is stored to LDS.  With a branch per load
-// and per alignment a stage of 8 MFMAs was some 400 instructions: 3x3 stride 2, 256 x 28 x 28 x 128 -> 256 58.0 us, now 53.5; 1x1,
-// 128 x 56 x 56 x 32 -> 192 30.2, now 28.8; linear 8192 x 1024 -> 1024 47.4, now 43.6.
+// and per alignment a stage of 8 MFMAs was some 400 instructions: 3x3 stride 2, 256 x 28 x 28 x 128 -> 256 58.0 us, now 53.5;
+// linear 8192 x 1024 -> 1024 47.4, now 43.6.
 template <int TN, int TK, bool PACKED, bool PACKED3 = false, bool ALIGNED = false>
 __global__ __launch_bounds__(HQ_THREADS) void hq_wgrad_kernel(const WgradArgs a)
 {
@@ -592,6 +593,124 @@ __global__ __launch_bounds__(HQ_THREADS, 2) void hq_wgrad_stem_kernel(const Wste
 }
 
 // ---------------------------------------------------------------------------------------
+// 1x1 and linear layers of a few blocks of 32 x 32 weights (channel counts multiples of 32, unit stride): a stream of pixels.  All of G_W fits
+// one wavefront's accumulators, so every wavefront works alone: 32 pixels of both operands, two pieces of memory, go straight into its own LDS (two
+// buffers, the next pixels on their way while these are multiplied) and are read transposed; a pixel is fetched once, and there is no
+// barrier before the end, where a workgroup puts its sums together in LDS and adds them to the accumulator as whole lines.
+// Whole call, 64 x 64 tiles behind a barrier per 64 pixels / this (us): 401,408 pixels 32 -> 192 (90 MB: 16 at the rate of a copy; about 5 are the
+// clearing and the scaling) 29.0 / 22.5, 192 -> 32 29.5 / 21.8, 64 -> 64 27.4 / 16.3; 1,254,400 32 -> 32 50.6 / 19.1; 25,088 64 -> 64 19.0 / 9.1.
+template <int CT, int NT>
+__global__ __launch_bounds__(WP_THREADS, 2) void hq_wgrad_point_kernel(const WgradArgs a)
+{
+    constexpr int C = 32 * CT, N = 32 * NT, BUF = 32 * (C + N), WAVES = WP_THREADS / 64, WORDS = C * N + C + N;
+    extern __shared__ __attribute__((aligned(16))) int8_t wp_lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int all = (a.M + 31) / 32;
+    const int begin = (int)((long)all * blockIdx.x / gridDim.x), end = (int)((long)all * (blockIdx.x + 1) / gridDim.x);
+    int8_t *mine = wp_lds + 2 * BUF * wave;
+    const unsigned lds0 = hq_lds_address(mine);
+    // pixels past the last are zeros in both operands
+    auto load = [&](int buf, int block) __attribute__((always_inline)) {
+        const int left = a.M - 32 * block;
+#pragma unroll
+        for (int j = 0; j < CT + NT; j++) {
+            const bool x = j < CT;
+            const int at = 1024 * (x ? j : j - CT) + 16 * lane;
+            const int8_t *src = (x ? a.X + (size_t)block * (32 * C) : a.G + (size_t)block * (32 * N)) + at;
+            if (left < 32 && at / (x ? C : N) >= left) src = reinterpret_cast<const int8_t *>(hq_fill_rows.w[0]);
+            hq_lds_load16(src, lds0 + BUF * buf + 1024 * j);
+        }
+    };
+    v16i acc[NT][CT];
+    int gs[NT], xs[CT];
+#pragma unroll
+    for (int n = 0; n < NT; n++)
+#pragma unroll
+        for (int c = 0; c < CT; c++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) acc[n][c][e] = 0;
+#pragma unroll
+    for (int n = 0; n < NT; n++) gs[n] = 0;
+#pragma unroll
+    for (int c = 0; c < CT; c++) xs[c] = 0;
+    const bool do_gsum = a.xq->zero_point != 0, do_xsum = a.gq->zero_point != 0;      // (a sum is only multiplied by the other's zero point)
+    int block = begin + wave, buf = 0;
+    if (block < end) load(0, block);
+    for (; block < end; block += WAVES, buf ^= 1) {
+        if (block + WAVES < end) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the buffer's last reads are done
+            load(buf ^ 1, block + WAVES);
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(CT + NT) : "memory");
+        } else {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        }
+        const int8_t *xb = mine + BUF * buf, *gb = xb + 32 * C;
+        v4i xf[CT], gf[NT];
+#pragma unroll
+        for (int c = 0; c < CT; c++) xf[c] = hq_read_frag_tr<C>(xb + 32 * c, lane);
+#pragma unroll
+        for (int n = 0; n < NT; n++) gf[n] = hq_read_frag_tr<N>(gb + 32 * n, lane);
+#pragma unroll
+        for (int n = 0; n < NT; n++)
+#pragma unroll
+            for (int c = 0; c < CT; c++) acc[n][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(gf[n], xf[c], acc[n][c], 0, 0, 0);
+        if (do_gsum)
+#pragma unroll
+            for (int n = 0; n < NT; n++)
+#pragma unroll
+                for (int d = 0; d < 4; d++) gs[n] = __builtin_amdgcn_sdot4(gf[n][d], 0x01010101, gs[n], false);
+        if (do_xsum)
+#pragma unroll
+            for (int c = 0; c < CT; c++)
+#pragma unroll
+                for (int d = 0; d < 4; d++) xs[c] = __builtin_amdgcn_sdot4(xf[c][d], 0x01010101, xs[c], false);
+    }
+
+    // ---- the wavefronts' sums: [N][C], [N], [C] in LDS, over the buffers.  Lane l holds column l % 32 of the input block and output
+    // channels 8 * (e / 4) + 4 * (l / 32) + e % 4.
+    __syncthreads();
+    int *sum = reinterpret_cast<int *>(wp_lds);
+    for (int i = tid; i < WORDS; i += WP_THREADS) sum[i] = 0;
+    __syncthreads();
+    const int half = lane >> 5, r32 = lane & 31;
+#pragma unroll
+    for (int n = 0; n < NT; n++) {
+#pragma unroll
+        for (int c = 0; c < CT; c++)
+#pragma unroll
+            for (int e = 0; e < 16; e++) atomicAdd(sum + (32 * n + 8 * (e >> 2) + 4 * half + (e & 3)) * C + 32 * c + r32, acc[n][c][e]);
+        if (do_gsum) atomicAdd(sum + N * C + 32 * n + r32, gs[n]);
+    }
+    if (do_xsum)
+#pragma unroll
+        for (int c = 0; c < CT; c++) atomicAdd(sum + N * C + N + 32 * c + r32, xs[c]);
+    __syncthreads();
+    // (every workgroup starts elsewhere: all add to the same lines)
+    constexpr int chunks = (C * N + WP_THREADS - 1) / WP_THREADS;
+    int q = (int)(blockIdx.x % (unsigned)chunks) * WP_THREADS + tid;
+    for (int k = 0; k < chunks; k++) {
+        const int v = q < C * N ? sum[q] : 0;
+        if (v != 0) atomicAdd(a.acc + q, v);
+        q += WP_THREADS;
+        if (q >= chunks * WP_THREADS) q -= chunks * WP_THREADS;
+    }
+    if (do_gsum && tid < N && sum[C * N + tid] != 0) atomicAdd(a.gsum + tid, sum[C * N + tid]);
+    if (do_xsum && tid < C && sum[C * N + N + tid] != 0) atomicAdd(a.xsum + tid, sum[C * N + N + tid]);
+}
+
+template <int CT, int NT> bool wp_launch(const WgradArgs &a, int blocks, hipStream_t stream)
+{
+    constexpr int C = 32 * CT, N = 32 * NT;
+    constexpr size_t lds = std::max((size_t)(WP_THREADS / 64) * 2 * 32 * (C + N), 4 * (size_t)(C * N + C + N));
+    static_assert(lds <= 156 * 1024 && C <= WP_THREADS && N <= WP_THREADS, "the buffers fit, a thread to a column sum");
+    static std::atomic<unsigned long long> allowed{0};
+    auto kern = hq_wgrad_point_kernel<CT, NT>;
+    if (!hq_allow_lds(kern, lds, allowed)) return false;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(WP_THREADS), lds, stream, a);
+    return true;
+}
+
+// ---------------------------------------------------------------------------------------
 __global__ void zero_kernel(int32_t *p, size_t n)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
@@ -716,6 +835,34 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
                                xq, gq, (unsigned)a.M, a.N, (int)K, 0, dW, dW_acc, ra);
             return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
         }
+    }
+
+    // 1x1 and linear layers whose G_W is at most eight blocks of 32 x 32, a pixel at most 224 bytes (hq_wgrad_point_kernel); for six blocks and more from
+    // 16384 pixels on (10,989 x 32 -> 224 9.2 us in tiles, 11.0; 16,384 x 192 -> 32 10.1 / 10.0; 20,480 x 128 -> 64 12.4 / 11.3; 61,440 x 256 -> 32,
+    // 288 bytes, 13.0 / 14.4).
+    const int cb = a.C / 32, nb = a.N / 32;
+    if (p->R == 1 && p->S == 1 && p->stride == 1 && p->pad == 0 && a.C % 32 == 0 && a.N % 32 == 0 && cb * nb <= 8 && cb + nb <= 7 && (cb * nb < 6 || a.M >= 16384) &&
+        ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(dY)) & 15) == 0 && a.M < (1 << 30)) {
+        const size_t zwords = sums_bytes / 4;
+        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((zwords + 255) / 256 > 1024 ? 1024 : (zwords + 255) / 256)), dim3(256), 0, stream, a.acc, zwords);
+        // Half the compute units bring what memory gives, and every workgroup's sums queue at the same lines: 401,408 x 64 -> 64 16.3 us
+        // in 128 workgroups, 17.8 in 192, 19.1 in 256; a wavefront gets four blocks of pixels, two where there are few (100,352 x 32 -> 192 13.0,
+        // with one 16.3).
+        const int all = (a.M + 31) / 32, blocks = std::max(1, std::min(128, std::max(all / 32, std::min(all / 16, 64))));
+        bool ok = false;
+        switch (16 * cb + nb) {
+#define WP(c, n) case 16 * c + n: ok = wp_launch<c, n>(a, blocks, stream); break
+        WP(1, 1); WP(1, 2); WP(1, 3); WP(1, 4); WP(1, 5); WP(1, 6); WP(2, 1); WP(2, 2);
+        WP(2, 3); WP(2, 4); WP(3, 1); WP(3, 2); WP(4, 1); WP(4, 2); WP(5, 1); WP(6, 1);
+#undef WP
+        }
+        if (!ok) return HQ_E_HIP;
+        const size_t total = (size_t)a.N * K;
+        const unsigned fb = (unsigned)((total + 255) / 256);
+        ra.first = (int)fb;
+        hipLaunchKernelGGL(wgrad_finalize_kernel, dim3(fb + (unsigned)ra.n), dim3(256), 0, stream, a.acc, a.gsum, a.xsum,
+                           xq, gq, (unsigned)a.M, a.N, (int)K, 0, dW, dW_acc, ra);
+        return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
     }
 
     const bool big = a.N > 64 && a.C > 64, packed = a.C < 16;

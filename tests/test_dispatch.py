@@ -98,6 +98,16 @@ def test_short_reductions_split_channels_for_want_of_pixels():
     assert blocks(401408, 32, 192) == 512 and blocks(8192, 192, 4096) == 512 and blocks(8192, 64, 512) == 256 and blocks(70000, 128, 512) == 512
 
 
+def test_weight_gradients_of_few_blocks_are_streamed():
+    import test_gpu_parity as T
+    point, tile = "hq_wgrad_point_kernel", "hq_wgrad_kernel"
+    lin = lambda m, c, n: (LINEAR, m, 1, 1, c, 1, 1, 1, 0, n)
+    work = [(tuple(L)[1:], point) for L in T.POINT_WGRAD] + [(lin(16383, 32, 192), tile), (lin(40000, 32, 224), tile), (lin(40000, 96, 96), tile),
+            (lin(40000, 48, 64), tile), (conv(60, 56, 64, 1, 2, 64), tile), (conv(128, 56, 32, 1, 1, 192), point)]
+    for (p, want), got in zip(work, launches.calls([("wgrad", p) for p, _ in work])):
+        assert [g.kernel.split("<")[0] for g in got] == ["zero_kernel", want, "wgrad_finalize_kernel"], (p, got)
+
+
 def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
     long_, short = "hq_gemm_kernel<128, 128, 2, 2, 128", "hq_gemm_kernel<128, 128, 2, 2, 64"
     check([("dgrad_sr", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2064), short), ("dgrad", (LINEAR, 3255, 1, 1, 3624, 1, 1, 1, 0, 2064), long_),

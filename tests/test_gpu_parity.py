@@ -561,6 +561,19 @@ def test_framed_weight_gradients(H, hq, L, g_asym):
     test_weight_gradient_lines(H, hq, L, g_asym)
 
 
+# Weight gradients of few blocks of 32 x 32 weights under one tap: a last block of one pixel, of 31, none; wavefronts without a block; every
+# shape of G_W that the kernel is built for at its ends.
+POINT_WGRAD = [wl.linear("pw_%d_%d_%d" % s, *s) for s in ((8193, 32, 32), (8223, 32, 160), (9000, 64, 64), (16385, 32, 192), (16415, 192, 32), (20003, 64, 128),
+                                                          (16384, 128, 64), (16390, 96, 64), (16390, 64, 96), (9001, 160, 32), (40003, 32, 64))] + [
+    wl.conv("pw_conv", 11, 28, 64, 32, 1, pad=0), wl.conv("pw_conv_odd", 3, 57, 32, 96, 1, pad=0)]
+
+
+@pytest.mark.parametrize("L", POINT_WGRAD, ids=[l.name for l in POINT_WGRAD])
+@pytest.mark.parametrize("g_asym", [False, True])
+def test_streamed_weight_gradients(H, hq, L, g_asym):
+    test_weight_gradient_lines(H, hq, L, g_asym)
+
+
 # First layers with staged input rows: odd strides read odd pixels from a second copy, at most four filter rows share the k-steps of
 # a band between two wavefronts; bands of one k-step, images of one band, last bands with fewer rows, every filter row in use.
 STEM_WGRAD = [wl.LayerShape("stem_wgrad", wl.CONV, B, Hh, Ww, C, R, S, st, pad, N)
