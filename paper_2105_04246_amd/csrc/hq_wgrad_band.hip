@@ -285,6 +285,9 @@ __global__ __launch_bounds__(WB_THREADS) void hq_wgrad_band_kernel(const WbandAr
         return v4i{acc[k >> 2][4 * (k & 3)], acc[k >> 2][4 * (k & 3) + 1], acc[k >> 2][4 * (k & 3) + 2], acc[k >> 2][4 * (k & 3) + 3]};
     };
     int *csum = reinterpret_cast<int *>(smem + EXCHANGE);            // [GROUPS][SUMS]
+    // A run shorter than a chunk has not waited for the second set of loads that was requested for it, which may land where the sums
+    // meet (the barrier does not wait for them); every other run has none under way.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (do_gsum) {
         const int sm = gsv + __shfl_xor(gsv, 32);
