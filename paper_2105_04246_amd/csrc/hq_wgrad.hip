@@ -741,13 +741,13 @@ size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
 } // namespace
 
-// Workspace: [Cout][K] integer sums, [Cout] and [K] column sums, then the band kernel's partial sums.
+// Workspace: [Cout][K] integer sums, [Cout] and [K] column sums; or the band kernel's partial sums in their place.
 size_t hq_wgrad_workspace_bytes(const hq_problem *p)
 {
     const size_t K = (size_t)p->R * p->S * p->C;
     if (p->kind == HQ_DEPTHWISE) return align16(4 * K) + align16(4 * (size_t)p->C) + align16(4 * K);
-    return align16(4 * (size_t)p->Cout * K) + align16(4 * (size_t)p->Cout) + align16(4 * K) +
-           hq_wgrad_band_bytes(p);
+    if (const size_t band = hq_wgrad_band_bytes(p)) return band;
+    return align16(4 * (size_t)p->Cout * K) + align16(4 * (size_t)p->Cout) + align16(4 * K);
 }
 
 int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY,
@@ -775,7 +775,7 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
 
     const int rc = hq_try_launch_wgrad_small(p, X, xq, dY, gq, dW, dW_acc, stream, ride);
     if (rc != HQ_E_BADSHAPE) return rc;
-    const int rc_band = hq_try_launch_wgrad_band(p, X, xq, dY, gq, dW, dW_acc, w + sums_bytes, stream, ride);
+    const int rc_band = hq_try_launch_wgrad_band(p, X, xq, dY, gq, dW, dW_acc, ws, stream, ride);
     if (rc_band != HQ_E_BADSHAPE) return rc_band;
 
     // first layers: input rows staged in LDS (hq_wgrad_stem_kernel)

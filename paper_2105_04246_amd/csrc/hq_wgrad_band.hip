@@ -47,7 +47,7 @@ constexpr int GLOADS = L / GLOAD / WB_WAVES;  // loads of the gradient per wavef
 constexpr int TAIL = L + 64;                  // rows of the ring's start that are repeated behind its end
 constexpr unsigned GBYTES = 3 * L * GROW;     // the three buffers of the gradient
 constexpr int SLOT_V4 = 2 * 9 * 4 * 64;       // 16-byte words of one workgroup's partial sums
-constexpr int SUMS = 64 + 9 * 32;             // a workgroup's column sums: dY [64], input [9][32]
+constexpr int SUMS = 64 + 9 * 32;             // column sums that a workgroup may form: dY [64], input [9][32]
 constexpr int EXCHANGE = WB_WAVES * 6 * 1024; // LDS bytes in which the groups' sums meet
 static_assert(L == XLOAD * WB_WAVES && GLOADS * GLOAD * WB_WAVES == L, "one load of the input per wavefront and chunk");
 
@@ -66,7 +66,7 @@ struct WbandArgs {
     const int8_t *X, *G;
     const hq_qparams *xq, *gq;
     int32_t *partial;              // [slot][SLOT_V4] 16-byte words: a workgroup's 64 x 9 x 32 sums
-    int32_t *sums;                 // [slot][SUMS]: column sums of dY and of the input taps
+    int32_t *gsums, *xsums;        // [run][N], [run][9][C]: column sums of dY and of the input taps
     int M, H, W, C, N;             // pixels of the batch; image, channels of input and gradient
     int PW;                        // positions of a row: W + 1
     WbandAdvance gadv, xadv;       // from one load to the next
@@ -308,20 +308,21 @@ __global__ __launch_bounds__(WB_THREADS) void hq_wgrad_band_kernel(const WbandAr
 #pragma unroll
     for (int k = 0; k < 6; k++) pout[(6 * grp + k) * 64] = (grp ? quad(6 + k) : quad(k)) + xch[(wave * 6 + k) * 64 + lane];
     // (what was not formed is neither read by the finalize kernel)
-    int *sp = a.sums + slot * SUMS;
     if ((cp == 0 && zx != 0) || xsums)
         for (int i = tid; i < SUMS; i += WB_THREADS) {
             int sm = 0;
 #pragma unroll
             for (int g = 0; g < GROUPS; g++) sm += csum[g * SUMS + i];
-            sp[i] = sm;
+            const int x = i - 64;
+            if (x < 0) { if (cp == 0) a.gsums[(size_t)split * a.N + np * 64 + i] = sm; }
+            else if (xsums) a.xsums[((size_t)split * 9 + (x >> 5)) * a.C + cp * 32 + (x & 31)] = sm;
         }
 }
 
 // Adds the workgroups' partial sums (64 threads along C, TY taking every TY-th slot), removes the zero points and scales.
 // One thread owns 4 consecutive output channels of one (tap, c): the 16 bytes a lane of the band kernel stored.
 template <int TY>
-__global__ __launch_bounds__(64 * TY) void wband_finalize_kernel(const int32_t *partial, const int32_t *sums,
+__global__ __launch_bounds__(64 * TY) void wband_finalize_kernel(const int32_t *partial, const int32_t *gsums, const int32_t *xsums,
                                                               const hq_qparams *xq, const hq_qparams *gq, unsigned M,
                                                               int N, int C, int splits, float *dW, int32_t *dW_acc,
                                                               const HqRideAlong ride)
@@ -336,20 +337,19 @@ __global__ __launch_bounds__(64 * TY) void wband_finalize_kernel(const int32_t *
     const int cp = c / 32, cc = c & 31, np = n0 / 64, i = (n0 >> 5) & 1, rq = (n0 >> 3) & 3, lh = (n0 >> 2) & 1;
     const v4i *src = reinterpret_cast<const v4i *>(partial) + (size_t)(np * cparts + cp) * SLOT_V4 +
                      ((i * 9 + tap) * 4 + rq) * 64 + lh * 32 + cc;
-    const int *xsrc = sums + (size_t)cp * SUMS + 64 + tap * 32 + cc;          // workgroups with np == 0
-    const int *gsrc = sums + (size_t)(np * cparts) * SUMS + (n0 & 63);              // workgroups with cp == 0
+    const int *xsrc = xsums + (size_t)tap * C + c, *gsrc = gsums + n0;
     // a column sum is only ever multiplied by the other operand's zero point: with that at 0 it is neither formed
     // by the band kernel nor read here (uniform branches)
     const bool need_xs = gq->zero_point != 0, need_gs = xq->zero_point != 0;
     v4i gs = {0, 0, 0, 0};                                         // (the same four for the whole workgroup, whose threads share the slots)
     if (need_gs)
-        for (int s = threadIdx.x; s < splits; s += 64 * TY) gs += *reinterpret_cast<const v4i *>(gsrc + (size_t)s * parts * SUMS);
+        for (int s = threadIdx.x; s < splits; s += 64 * TY) gs += *reinterpret_cast<const v4i *>(gsrc + (size_t)s * N);
     v4i sum = {0, 0, 0, 0};
     int xs = 0;
 #pragma unroll 4
     for (int s = ty; s < splits; s += TY) sum += src[(size_t)s * parts * SLOT_V4];
     if (need_xs)
-        for (int s = ty; s < splits; s += TY) xs += xsrc[(size_t)s * parts * SUMS];
+        for (int s = ty; s < splits; s += TY) xs += xsrc[(size_t)s * 9 * C];
     if (need_gs) {
 #pragma unroll
         for (int e = 0; e < 4; e++) gs[e] = hq_wave_reduce(gs[e], HqAdd());
@@ -378,12 +378,14 @@ __global__ __launch_bounds__(64 * TY) void wband_finalize_kernel(const int32_t *
     }
 }
 
-// Geometry of the band kernel for one layer (host, pure); covered == false: the tile kernel takes it.
+// Geometry of the band kernel for one layer (host, pure); covered == false: the tile kernel takes it.  Its workspace is one slot per run and
+// block of G_W and nothing else: up to 256 slots (18.9 MB and the column sums) while blocks are split, and with one run for every block the
+// size of G_W and its column sums, what the tile kernel's accumulator takes, so that a bounded workspace holds the same layers for both.
 struct WbandPlan {
     bool covered;
     int units, per_block, splits, parts, lead;
     unsigned ring;
-    size_t lds, partial_bytes, sums_bytes;
+    size_t lds, partial_bytes, gsums_bytes, xsums_bytes;
 };
 
 WbandPlan wband_plan(const hq_problem *p)
@@ -406,7 +408,8 @@ WbandPlan wband_plan(const hq_problem *p)
     pl.splits = (pl.units + pl.per_block - 1) / pl.per_block;
     pl.per_block = (pl.units + pl.splits - 1) / pl.splits;
     pl.partial_bytes = (size_t)pl.parts * pl.splits * SLOT_V4 * 16;
-    pl.sums_bytes = (size_t)pl.parts * pl.splits * SUMS * 4;
+    pl.gsums_bytes = (size_t)pl.splits * p->Cout * 4;
+    pl.xsums_bytes = (size_t)pl.splits * 9 * p->C * 4;
     pl.covered = true;
     return pl;
 }
@@ -416,7 +419,7 @@ WbandPlan wband_plan(const hq_problem *p)
 size_t hq_wgrad_band_bytes(const hq_problem *p)
 {
     const WbandPlan pl = wband_plan(p);
-    return pl.partial_bytes + pl.sums_bytes;
+    return pl.partial_bytes + pl.gsums_bytes + pl.xsums_bytes;
 }
 
 int hq_try_launch_wgrad_band(const hq_problem *p, const int8_t *X, const hq_qparams *xq, const int8_t *dY, const hq_qparams *gq,
@@ -428,7 +431,8 @@ int hq_try_launch_wgrad_band(const hq_problem *p, const int8_t *X, const hq_qpar
     a.X = X; a.G = dY; a.xq = xq; a.gq = gq;
     // every workgroup stores its sums to a slot of its own: nothing to zero, no atomics
     a.partial = static_cast<int32_t *>(ws);
-    a.sums = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + pl.partial_bytes);
+    a.gsums = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + pl.partial_bytes);
+    a.xsums = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + pl.partial_bytes + pl.gsums_bytes);
     a.M = p->B * p->H * p->W; a.H = p->H; a.W = p->W; a.C = p->C; a.N = p->Cout;
     a.PW = p->W + 1;
     a.by_image = wband_div((unsigned)(p->H + 1) * (unsigned)a.PW); a.by_row = wband_div((unsigned)a.PW);
@@ -451,7 +455,7 @@ int hq_try_launch_wgrad_band(const hq_problem *p, const int8_t *X, const hq_qpar
     ra.first = (int)(quads / 64);
     const dim3 fgrid((unsigned)(quads / 64) + (unsigned)ra.n);
     auto finalize = [&](auto kernel, int ty) {
-        hipLaunchKernelGGL(kernel, fgrid, dim3(64 * ty), 0, stream, a.partial, a.sums, xq, gq, (unsigned)a.M, a.N, a.C, pl.splits, dW, dW_acc, ra);
+        hipLaunchKernelGGL(kernel, fgrid, dim3(64 * ty), 0, stream, a.partial, a.gsums, a.xsums, xq, gq, (unsigned)a.M, a.N, a.C, pl.splits, dW, dW_acc, ra);
     };
     if (pl.splits >= 48) finalize(wband_finalize_kernel<16>, 16);
     else if (pl.splits >= 12) finalize(wband_finalize_kernel<4>, 4);

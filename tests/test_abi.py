@@ -69,6 +69,25 @@ def test_struct_views_match_header_sizes():
     assert ctypes.sizeof(hq.hq_problem) == 40
 
 
+def test_workspaces_of_framed_weight_gradients_hold_the_sums_once():
+    """One set of sums (a 32-bit word per weight, output channel and weight column) for every run of pixels: one run is what the tile
+    kernel's accumulator takes, and the runs of split blocks have 256 slots of 73,728 bytes at most, their column sums beside them."""
+    import random
+    import paper_2105_04246_amd as hq
+    rng = random.Random(3)
+    layer = lambda B, H, W, c, n: hq.problem(hq.HQ_CONV2D, B, H, W, c, 3, 3, 1, 1, n)
+    size = lambda *s: hq.hq_workspace_bytes(hq.HQ_ENTRY_WGRAD, layer(*s))
+    # layers that need their accumulator alone fit the static workspace, on images of any width
+    for c, n in ((1024, 1024), (448, 4096), (4096, 448), (1344, 1344)):
+        assert 36 * c * n + 4 * n + 36 * c <= hq.HQ_STATIC_SCRATCH_BYTES
+        for B, H, W in ((1, 8, 200), (1, 130, 130), (1, 2, 130), (3, 40, 400), (8, 14, 14), (2, 3, 600)):
+            assert 0 < size(B, H, W, c, n) <= hq.HQ_STATIC_SCRATCH_BYTES, (B, H, W, c, n)
+    for _ in range(300):
+        c, n = 64 * rng.randint(1, 16), 64 * rng.randint(1, 16)
+        B, H, W = rng.randint(1, 40), rng.randint(1, 60), rng.randint(1, 600)
+        assert 0 < size(B, H, W, c, n) <= max(36 * c * n + 4 * n + 36 * c, 20 << 20), (B, H, W, c, n)
+
+
 def test_host_side_argument_checks_need_no_gpu():
     """Shape / pointer validation happens before anything touches the device."""
     import paper_2105_04246_amd as hq

@@ -548,13 +548,14 @@ def test_tile_weight_gradients(H, hq, L, g_asym):
 
 
 # 3x3 weight gradients over framed images: runs of one unit to many with every remainder, images smaller than a step and wider than a
-# chunk (the widest the ring takes, and one more), one row, one column, one pixel, an odd number of blocks.  The last two: runs of two units
-# and a last one of one, shorter than a chunk, whose second set of loads only the wait in front of the sums' exchange covers.
+# chunk (the widest the ring takes, and one more), one row, one column, one pixel, an odd number of blocks.  The last three: runs of two units
+# and a last one of one, shorter than a chunk, whose second set of loads only the wait in front of the sums' exchange covers; and one run for
+# all blocks.
 BAND_WGRAD = [wl.LayerShape("band_wgrad", wl.CONV, B, Hh, Ww, C, 3, 3, 1, 1, N)
               for B, Hh, Ww, C, N in ((1, 24, 24, 320, 256), (40, 4, 4, 320, 256), (600, 1, 1, 320, 256), (300, 2, 1, 256, 320), (1, 2, 570, 320, 256),
                                       (1, 2, 571, 320, 256), (1, 1, 520, 320, 256), (1, 570, 1, 320, 256), (9, 7, 9, 448, 192), (57, 3, 5, 320, 256),
                                       (2, 61, 70, 64, 64), (43, 14, 14, 64, 128), (11, 29, 27, 128, 64), (1, 40, 250, 64, 64), (129, 9, 8, 64, 64),
-                                      (42, 14, 14, 64, 64), (19, 35, 35, 64, 64))]
+                                      (42, 14, 14, 64, 64), (19, 35, 35, 64, 64), (3, 14, 15, 512, 1024))]
 
 
 @pytest.mark.parametrize("L", BAND_WGRAD, ids=["b%d_%dx%d_c%d_n%d" % (l.B, l.H, l.W, l.C, l.Cout) for l in BAND_WGRAD])

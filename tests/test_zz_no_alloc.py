@@ -61,6 +61,8 @@ def test_static_weight_gradient_matches_the_workspace_one_on_two_calls_in_a_row(
     # the banded kernel (per-workgroup partial sums in the scratch), larger first, then a ragged smaller one
     _run_both(wl.conv("band_big", 16, 28, 128, 128, 3), 2)
     _run_both(wl.conv("band_small", 5, 14, 64, 64, 3), 3)
+    # ... and one run whose slot is nearly all of the scratch
+    _run_both(wl.LayerShape("band_one_run", wl.CONV, 1, 2, 130, 448, 3, 3, 1, 1, 4096), 7)
     # linear and depthwise layers take the same entry point
     _run_both(wl.linear("fc", 96, 512, 200), 4)
     _run_both(wl.depthwise("dw", 4, 28, 96), 5)
