@@ -15,7 +15,6 @@
 #include "hq_internal.h"
 
 #include <algorithm>
-#include <climits>
 #include <type_traits>
 
 namespace {
@@ -76,7 +75,9 @@ __global__ __launch_bounds__(PT_THREADS, 4) void hq_point_kernel(const PointArgs
 #pragma unroll
         for (int ks = 0; ks < KS; ks++) af[ks] = *reinterpret_cast<const v4i *>(p + min(32 * ks + 16 * half, a.K - 16));
     };
-    constexpr bool AHEAD = MODE != 2 || KS < 5;                          // (the random bits leave no registers for it)
+    // (beside the random bits 9 and 23 registers would spill.  Without them one does under 161 to 192 channels, and the next pixels on their way are
+    // worth it: 100,352 x 192 -> 32 5.9 us, 6.2 without)
+    constexpr bool AHEAD = MODE != 2 || KS < 5;
     v4i afA[KS], afB[AHEAD ? KS : 1];
     int block = begin + wave;
     if (block < end) fetch(block, afA);
@@ -216,15 +217,25 @@ int hq_try_launch_point(const hq_problem *p, int dgrad, const int8_t *A, const h
     // split, down to two blocks of 32, and the pixels dealt to as many workgroups as take least by this estimate: a wavefront's tiles one
     // after the other (5 units each) or the compute unit's on its four vector ALUs (2 wavefronts a unit), and 5 units to start a workgroup.
     // 8192 x 64 x 512: 10.5 us undivided, 4.8; 8192 x 128 x 1024 14.2, 7.6; 70000 x 128 x 512 24.9 in 274 workgroups, 21.6 in 512.
+    // With stochastic rounding the vector ALUs bound every size: a tile is then mostly their work (3 units of latency), a SIMD's share comes in
+    // whole blocks (every fourth of the workgroup's), one workgroup to a compute unit does not keep them busy, another number of workgroups for the
+    // same split has to save an eighth, and channels are split under any number of pixels (100,244 x 64 x 944 90.0 us undivided, 72.9 in five parts).
+    // Against the fastest of up to 60 splits each, 376 calls drawn at random: 4.9 % more time with rounding to nearest (a third at worst), 1.8 %
+    // with stochastic rounding (18 % at worst; by the estimate for rounding to nearest 8.5 % and 45 %).
     const int least = (blocks + most - 1) / most;
-    long best = LONG_MAX;
-    for (int nparts = least; nparts == least || (all < PT_MANY && nparts <= (blocks + 1) / 2); nparts++)
+    double best = 0.0;
+    for (int nper = std::min(most, blocks); nper >= 1; nper--) {         // (at most 69 steps)
+        const int nparts = (blocks + nper - 1) / nper;
+        if ((blocks + nparts - 1) / nparts != nper) continue;            // (as many parts as with fewer blocks each)
+        if (nparts != least && (nper < 2 || (mode != 2 && all >= PT_MANY))) continue;
         for (int want : {(all + PT_WAVES - 1) / PT_WAVES, 256 / nparts, 512 / nparts}) {
-            const int nper = (blocks + nparts - 1) / nparts, runs = std::max(1, std::min({want, 512 / nparts, all}));
-            const long share = (all + runs - 1) / runs, rounds = (runs * nparts + 255) / 256, serial = (share + PT_WAVES - 1) / PT_WAVES * nper;
-            const long cost = std::max(5 * serial, rounds * share * nper / 2) + 5 * rounds;
-            if (cost < best) { best = cost; a.nparts = (blocks + nper - 1) / nper; a.nper = nper; a.runs = runs; }
+            const int runs = std::max(1, std::min({want, 512 / nparts, all}));
+            const long share = (all + runs - 1) / runs, rounds = ((long)runs * nparts + 255) / 256, serial = (share + PT_WAVES - 1) / PT_WAVES * nper;
+            const double load = 0.5 * (double)(rounds * nper) * (double)(mode == 2 ? (share + 3) / 4 * 4 : share);
+            const double cost = std::max(mode == 2 ? 3.0 * serial : 5.0 * serial, mode == 2 && rounds == 1 ? 1.15 * load : load) + 5.0 * rounds;
+            if (a.nper == 0 || (mode == 2 && nper == a.nper ? 1.125 : 1.0) * cost < best) { best = cost; a.nparts = nparts; a.nper = nper; a.runs = runs; }
         }
+    }
     const size_t lds = (size_t)a.nper * (1024 * ks + 128);
     a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
     switch (ks) {

@@ -1,5 +1,8 @@
 """The lines of the dispatch rules: which kernel takes a call on either side of each (no GPU: see launches.py).  The
 figures behind the lines stand beside the rules."""
+import subprocess
+import sys
+
 import launches
 
 LINEAR, CONV, DEPTHWISE = 0, 1, 2
@@ -96,6 +99,24 @@ def test_short_reductions_split_channels_for_want_of_pixels():
     def blocks(*c):
         return launches.calls([("fwd", (LINEAR, c[0], 1, 1, c[1], 1, 1, 1, 0, c[2]))])[0][0].blocks
     assert blocks(401408, 32, 192) == 512 and blocks(8192, 192, 4096) == 512 and blocks(8192, 64, 512) == 256 and blocks(70000, 128, 512) == 512
+    # stochastic rounding: channels split under any number of pixels
+    layer = (LINEAR, 100244, 1, 1, 944, 1, 1, 1, 0, 64)
+    assert [c[0].lds for c in launches.calls([("dgrad", layer), ("dgrad_sr", layer)])] == [30 * 2176, 6 * 2176]
+
+
+def test_short_reductions_take_the_host_no_longer_for_more_channels():
+    """The split is found among the numbers of 32-channel blocks that a workgroup's LDS holds, whatever the layer's number of channels."""
+    code = """import sys, time, ctypes; rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL); sys.path.insert(0, sys.argv[2])
+import paper_2105_04246_amd as hq
+def least(n):
+    p, best = hq.problem(hq.HQ_LINEAR, 2000, 1, 1, 16, 1, 1, 1, 0, n), 1.0
+    for _ in range(50):
+        rec.recorder_reset(0); t = time.perf_counter(); hq.hq_gemm_fwd(p, *[0x10000] * 9, 0); best = min(best, time.perf_counter() - t)
+    return best
+print(least(1 << 20) / least(1 << 10))"""
+    r = subprocess.run([sys.executable, "-c", code, launches.recorder(), launches.ROOT], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert float(r.stdout) < 5, r.stdout                    # (50 when every split of the channels is tried)
 
 
 def test_weight_gradients_of_few_blocks_are_streamed():
