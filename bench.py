@@ -188,7 +188,7 @@ def kernel_family(wl, L, op):
         return "hq_ring_kernel"
     if k3 and cin == 64:
         return "hq_regw_kernel"
-    if taps == 1 and L.pad == 0 and not strided and cin % 16 == 0 and cout % 16 == 0 and cin <= 192 and not (cin in (112, 128) and cout >= 256 and up(pixels, 32) < 2048):
+    if taps == 1 and L.pad == 0 and not strided and cin % 16 == 0 and cout % 16 == 0 and cin <= 192 and not (cin == 128 and cout >= 256 and 340 < tiles <= 1024):
         return "hq_point_kernel"
     return "hq_gemm_kernel"
 

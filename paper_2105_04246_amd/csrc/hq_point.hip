@@ -209,9 +209,14 @@ int hq_try_launch_point(const hq_problem *p, int dgrad, const int8_t *A, const h
     const int mode = out32 ? 0 : sr_seed ? 2 : 1;
     const int ks = (K + 31) / 32, blocks = (N + 31) / 32, most = PT_LDS / (1024 * ks + 128);
     const int all = (int)((M + 31) / 32);
-    // 112 and 128 channels are one whole stage of the general kernel: up to PT_MANY blocks and for many channels it is as fast or faster
-    // (30000 x 128 x 384 9.9 us against 9.3 to 10.8, 13626 x 128 x 736 9.5 / 10.0); beyond it is not (63257 x 128 x 928 33.7 / 28.8).
-    if (K > 96 && K <= 128 && N >= 256 && all < PT_MANY && mode != 0) return HQ_E_BADSHAPE;
+    // 128 channels are two whole stages of the general kernel.  Where all of its 128 x 128 tiles are resident at once, four to a compute unit, and are
+    // more than a round and a third, the two are level (general / this, us: 12,000 x 512 7.6 / 7.5, 24,000 x 256 7.6 / 7.6, 16,000 x 512 7.9 / 7.4, 24,000 x
+    // 384 9.4 / 9.4, 11,729 x 864 9.4 / 9.6, 32,000 x 384 9.8 / 10.5, 12,000 x 928 9.7 / 10.7, 34,932 x 352 11.6 / 12.1, 16,805 x 768 11.3 / 10.9, 32,000 x 512 12.1 /
+    // 11.1) and it stays there.  With fewer or more tiles this kernel is ahead (12,000 x 256 6.5 / 5.5, 7010 x 752 7.8 / 7.2; 45,184 x 400 16.4 / 15.9,
+    // 24,021 x 1664 23.7 / 22.2, 63,257 x 928 33.7 / 29.0; 47 layers 0.90 of the time, one 3 % slower), and so it is with 112 channels (9852 x 288 6.7 / 5.3,
+    // 6294 x 1888 10.0 / 9.7, 27,522 x 1088 20.2 / 15.9; 32 layers 0.83) and under stochastic rounding (24,000 x 512 15.7 / 14.7; 64 layers 0.88, one 4 % slower).
+    const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
+    if (K == 128 && N >= 256 && mode == 1 && tiles > 340 && tiles <= 1024) return HQ_E_BADSHAPE;
     // Where there are blocks of pixels for every wavefront a workgroup takes all the channels whose weights fit: split between workgroups the
     // lines of an output would be written in parts (401,408 x 32 x 192: 24 us in one part, 39 in three).  With fewer blocks the channels are
     // split, down to two blocks of 32, and the pixels dealt to as many workgroups as take least by this estimate: a wavefront's tiles one

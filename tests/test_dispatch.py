@@ -93,8 +93,12 @@ def test_short_reductions_split_channels_for_want_of_pixels():
     check([("fwd", (LINEAR, 40000, 1, 1, 192, 1, 1, 1, 0, 256), point), ("fwd", (LINEAR, 40000, 1, 1, 208, 1, 1, 1, 0, 256), tile),
            ("fwd", (LINEAR, 40000, 1, 1, 184, 1, 1, 1, 0, 256), tile), ("fwd", (LINEAR, 40000, 1, 1, 192, 1, 1, 1, 0, 248), tile),      # off 16
            ("fwd", (LINEAR, 40000, 1, 1, 128, 1, 1, 1, 0, 256), tile), ("dynamic_fwd", (LINEAR, 40000, 1, 1, 128, 1, 1, 1, 0, 256), point),
-           ("fwd", (LINEAR, 65504, 1, 1, 128, 1, 1, 1, 0, 256), tile), ("fwd", (LINEAR, 65505, 1, 1, 128, 1, 1, 1, 0, 256), point),
+           # 128 channels: the general kernel's tiles are all resident, and more than a round and a third
+           ("fwd", (LINEAR, 21760, 1, 1, 128, 1, 1, 1, 0, 256), point), ("fwd", (LINEAR, 21761, 1, 1, 128, 1, 1, 1, 0, 256), tile),
+           ("fwd", (LINEAR, 65536, 1, 1, 128, 1, 1, 1, 0, 256), tile), ("fwd", (LINEAR, 65537, 1, 1, 128, 1, 1, 1, 0, 256), point),
+           ("dgrad", (LINEAR, 40000, 1, 1, 256, 1, 1, 1, 0, 128), tile), ("dgrad_sr", (LINEAR, 40000, 1, 1, 256, 1, 1, 1, 0, 128), point),
            ("fwd", (LINEAR, 40000, 1, 1, 128, 1, 1, 1, 0, 240), point), ("fwd", (LINEAR, 40000, 1, 1, 96, 1, 1, 1, 0, 256), point),
+           ("fwd", (LINEAR, 40000, 1, 1, 112, 1, 1, 1, 0, 256), point),
            ("fwd", conv(64, 57, 64, 1, 2, 64), point)])
     def blocks(*c):
         return launches.calls([("fwd", (LINEAR, c[0], 1, 1, c[1], 1, 1, 1, 0, c[2]))])[0][0].blocks
