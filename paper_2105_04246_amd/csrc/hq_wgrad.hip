@@ -837,11 +837,13 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
         }
     }
 
-    // 1x1 and linear layers whose G_W is at most eight blocks of 32 x 32, a pixel at most 224 bytes (hq_wgrad_point_kernel); for six blocks and more from
-    // 16384 pixels on (10,989 x 32 -> 224 9.2 us in tiles, 11.0; 16,384 x 192 -> 32 10.1 / 10.0; 20,480 x 128 -> 64 12.4 / 11.3; 61,440 x 256 -> 32,
-    // 288 bytes, 13.0 / 14.4).
+    // 1x1 and linear layers whose G_W is at most eight blocks of 32 x 32 (hq_wgrad_point_kernel), of six and more from the number of pixels on at which the
+    // longer end is paid for.  In tiles / here, us: 2 x 3 and 2 x 4 blocks or six in a row 16,384 pixels (192 -> 32 10.5 / 10.1, 32 -> 192 10.3 / 10.5, 64 -> 128 16.1 /
+    // 11.4), seven 65,536 (32 -> 224 13.6 / 13.5, 401,408 30.9 / 24.4; 32,768 11.1 / 11.8, 10,989 9.2 / 11.0), eight 100,000 (100,352 x 256 -> 32 16.7 / 15.7,
+    // 401,408 32.7 / 26.6; 65,536 13.7 / 14.7).
     const int cb = a.C / 32, nb = a.N / 32;
-    if (p->R == 1 && p->S == 1 && p->stride == 1 && p->pad == 0 && a.C % 32 == 0 && a.N % 32 == 0 && cb * nb <= 8 && cb + nb <= 7 && (cb * nb < 6 || a.M >= 16384) &&
+    const int least = cb * nb < 6 ? 0 : cb + nb <= 7 ? 16384 : cb + nb == 8 ? 65536 : 100000;
+    if (p->R == 1 && p->S == 1 && p->stride == 1 && p->pad == 0 && a.C % 32 == 0 && a.N % 32 == 0 && cb * nb <= 8 && a.M >= least &&
         ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(dY)) & 15) == 0 && a.M < (1 << 30)) {
         const size_t zwords = sums_bytes / 4;
         hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((zwords + 255) / 256 > 1024 ? 1024 : (zwords + 255) / 256)), dim3(256), 0, stream, a.acc, zwords);
@@ -853,7 +855,8 @@ int hq_launch_wgrad(const hq_problem *p, const int8_t *X, const hq_qparams *xq, 
         switch (16 * cb + nb) {
 #define WP(c, n) case 16 * c + n: ok = wp_launch<c, n>(a, blocks, stream); break
         WP(1, 1); WP(1, 2); WP(1, 3); WP(1, 4); WP(1, 5); WP(1, 6); WP(2, 1); WP(2, 2);
-        WP(2, 3); WP(2, 4); WP(3, 1); WP(3, 2); WP(4, 1); WP(4, 2); WP(5, 1); WP(6, 1);
+        WP(1, 7); WP(1, 8); WP(2, 3); WP(2, 4); WP(3, 1); WP(3, 2); WP(4, 1); WP(4, 2);
+        WP(5, 1); WP(6, 1); WP(7, 1); WP(8, 1);
 #undef WP
         }
         if (!ok) return HQ_E_HIP;

@@ -127,7 +127,7 @@ def test_weight_gradients_of_few_blocks_are_streamed():
     import test_gpu_parity as T
     point, tile = "hq_wgrad_point_kernel", "hq_wgrad_kernel"
     lin = lambda m, c, n: (LINEAR, m, 1, 1, c, 1, 1, 1, 0, n)
-    work = [(tuple(L)[1:], point) for L in T.POINT_WGRAD] + [(lin(16383, 32, 192), tile), (lin(40000, 32, 224), tile), (lin(40000, 96, 96), tile),
+    work = [(tuple(L)[1:], point) for L in T.POINT_WGRAD] + [(lin(16383, 32, 192), tile), (lin(40000, 32, 224), tile), (lin(65535, 224, 32), tile), (lin(99999, 32, 256), tile), (lin(200000, 32, 288), tile), (lin(40000, 96, 96), tile),
             (lin(40000, 48, 64), tile), (conv(60, 56, 64, 1, 2, 64), tile), (conv(128, 56, 32, 1, 1, 192), point)]
     for (p, want), got in zip(work, launches.calls([("wgrad", p) for p, _ in work])):
         assert [g.kernel.split("<")[0] for g in got] == ["zero_kernel", want, "wgrad_finalize_kernel"], (p, got)

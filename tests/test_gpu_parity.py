@@ -567,7 +567,8 @@ def test_framed_weight_gradients(H, hq, L, g_asym):
 # Weight gradients of few blocks of 32 x 32 weights under one tap: a last block of one pixel, of 31, none; wavefronts without a block; every
 # shape of G_W that the kernel is built for at its ends.
 POINT_WGRAD = [wl.linear("pw_%d_%d_%d" % s, *s) for s in ((8193, 32, 32), (8223, 32, 160), (9000, 64, 64), (16385, 32, 192), (16415, 192, 32), (20003, 64, 128),
-                                                          (16384, 128, 64), (16390, 96, 64), (16390, 64, 96), (9001, 160, 32), (40003, 32, 64))] + [
+                                                          (16384, 128, 64), (16390, 96, 64), (16390, 64, 96), (9001, 160, 32), (40003, 32, 64),
+                                                          (65551, 32, 224), (65536, 224, 32), (100001, 32, 256), (100000, 256, 32))] + [
     wl.conv("pw_conv", 11, 28, 64, 32, 1, pad=0), wl.conv("pw_conv_odd", 3, 57, 32, 96, 1, pad=0)]
 
 
