@@ -14,7 +14,7 @@
 // one barrier per stage, 12 to 48 MFMAs of a wavefront apart.  A workgroup with another tile requests its first stages before it
 // quantizes this one.
 //
-// Measured (before, with hq_ring_kernel or hq_bandw_kernel / now): 3x3 on 256 x 28 x 28 x 128 -> 128 50.3 / 38.7 us, batch 128 27.9 / 20.4, with
+// Measured (before, with hq_ring_kernel or row tiles / now): 3x3 on 256 x 28 x 28 x 128 -> 128 50.3 / 38.7 us, batch 128 27.9 / 20.4, with
 // stochastic rounding 33.6 / 27.9, 256 x 14 x 14 x 256 -> 256 42.7 / 31.0, 256 x 7 x 7 x 512 -> 512 38.4 / 32.4, 128 x 16 x 16 x 256 -> 256 25.1 /
 // 22.5, 64 x 14 x 14 x 384 -> 384 29.7 / 21.3, 5 x 93 x 93 x 320 -> 320 90.9 / 49.7; 207 calls of 70 layers drawn at random 0.80 of the time.
 // What bounds it now (256 x 14 x 14 x 256, tiles of 448): 6.2 K cycles until the first stage has arrived, 39.9 K of stages with 32.3 K of

@@ -146,8 +146,8 @@ def test_stochastic_rounding_takes_long_stages_while_all_tiles_are_resident():
            ("dgrad_sr", (LINEAR, 900, 1, 1, 4000, 1, 1, 1, 0, 360), short), ("dgrad_sr", (LINEAR, 900, 1, 1, 4000, 1, 1, 1, 0, 436), long_)])
 
 
-def test_whole_lines_per_stage_between_split_reductions_and_row_tiles():
-    ring, ks, bandw, tile, frame = "hq_ring_kernel", "hq_ksplit_kernel", "hq_bandw_kernel", "hq_gemm_kernel", "hq_frame_kernel"
+def test_whole_lines_per_stage_between_split_reductions_and_framed_tiles():
+    ring, ks, tile, frame = "hq_ring_kernel", "hq_ksplit_kernel", "hq_gemm_kernel", "hq_frame_kernel"
     check([("fwd", conv(26, 14, 256, 3, 1, 256), frame), ("dgrad", conv(26, 14, 256, 3, 1, 256), frame), ("dgrad_sr", conv(26, 14, 256, 3, 1, 256), frame),
            ("dynamic_fwd", conv(26, 14, 256, 3, 1, 256), frame), ("fwd", conv(128, 4, 512, 3, 1, 512), ks),
            ("fwd", conv(257, 16, 128, 5, 1, 128), ring), ("fwd", conv(257, 32, 128, 3, 2, 128), ring),           # not the framed tiles' layers
@@ -162,7 +162,8 @@ def test_whole_lines_per_stage_between_split_reductions_and_row_tiles():
            ("dgrad", conv(40, 16, 128, 3, 1, 128, 2), ring), ("fwd", (CONV, 20, 17, 19, 128, 5, 3, 1, 1, 160), ring),
            # the patch of a tile on wide images does not fit
            ("fwd", (CONV, 1, 70, 125, 128, 3, 3, 1, 1, 128), frame), ("fwd", (CONV, 1, 70, 126, 128, 3, 3, 1, 1, 128), ring),
-           ("fwd", (CONV, 1, 70, 125, 192, 3, 3, 1, 1, 128), frame), ("fwd", (CONV, 1, 70, 126, 192, 3, 3, 1, 1, 128), bandw)])
+           ("fwd", (CONV, 1, 70, 125, 192, 3, 3, 1, 1, 128), frame), ("fwd", (CONV, 1, 70, 126, 192, 3, 3, 1, 1, 128), tile),
+           ("fwd", (CONV, 400, 1, 93, 192, 3, 3, 1, 1, 192), frame), ("dgrad_sr", (CONV, 400, 1, 94, 192, 3, 3, 1, 1, 192), tile)])
 
 
 def test_framed_tiles_are_the_largest_that_fill_their_rounds():
@@ -316,7 +317,7 @@ def test_shapes_of_the_gpu_tests_reach_the_kernels_they_are_for():
     check([(op, tuple(L)[1:], "hq_frame_kernel") for L in T.FRAME_SHAPES for op in ("fwd", "dynamic_fwd")])
     check([(op, tuple(L)[1:], "hq_frame_kernel") for L in T.FRAME_SHAPES if L.Cout % 64 == 0 for op in ("dgrad", "dgrad_sr", "dynamic_dgrad")])
     assert {launches.calls([("fwd", tuple(L)[1:])])[0][0].kernel[16:23] for L in T.FRAME_SHAPES} == {"1, 1, 1", "1, 2, 1", "1, 2, 2", "1, 3, 3", "1, 4, 3", "1, 4, 4"}
-    check([(op, tuple(L)[1:], "hq_bandw_kernel") for L in T.WIDE_ROW_TILES for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")])
+    check([(op, tuple(L)[1:], "hq_gemm_kernel") for L in T.WIDE_IMAGES for op in ("fwd", "dgrad", "dgrad_sr", "dynamic_fwd")])
     check([("dgrad", tuple(L)[1:], "hq_ring_kernel") for L in T.RING_ONE_TAP])
     one, four = "hq_wgrad_small_kernel<1, 1, 4, 4>", "hq_wgrad_small_kernel<2, 2, 4, 2>"
     want = {"ws_1px": one, "ws_32_2145": one, "ws_32_300px": one, "ws_32_2304": one, "ws_64": four, "ws_64_256px": four, "past_ws_64": "zero_kernel",

@@ -72,8 +72,8 @@ SMALL = [
     wl.conv("band_multi_tile", 128, 36, 64, 64, 3),  # 4 bands per image of 9 rows: two tiles per band, second ragged
     wl.conv("wband_14", 3, 14, 64, 64, 3),           # weight-gradient band = one whole image, 28 pixels of padding
     wl.depthwise("dw_strips", 3, 40, 48),            # depthwise strips with a ragged last strip
-    wl.conv("bandw_multi_img", 3, 10, 128, 192, 3),  # streamed-weights path: tiles of two whole images (last one short), ragged channel chunk
-    wl.conv("bandw_rows", 2, 30, 192, 128, 3),       # ... tiles of rows, last tile of an image short; wgrad blocks 3 x 2
+    wl.conv("c3x3_128_192", 3, 10, 128, 192, 3),     # 128 and more channels on both sides, small images
+    wl.conv("c3x3_192_128", 2, 30, 192, 128, 3),     # ... larger ones, wgrad blocks 6 x 2
     wl.conv("first_layer", 2, 23, 4, 48, 7, stride=2),   # 4-channel first layer: direct kernel, ragged channel block, odd size
     wl.conv("first_layer_c8", 2, 19, 8, 32, 3),      # 8-channel first layer: packed weight gradient, general forward
     wl.conv("c5x5_s3", 2, 17, 16, 32, 5, stride=3),  # stride 3: nine pixel classes in the input gradient
@@ -252,7 +252,7 @@ def random_shapes(n, seed):
 def random_fast_path_shapes(n, seed):
     """Seeded random geometry for the shapes the specialised kernels take: 3x3 with 64 input channels
     (weights in LDS, bands and tiles of all lengths), 1x1 with 32 / 192, 3x3 with 128+ channels on both
-    sides (streamed weights), 4-channel first layers, depthwise strips, and the banded weight gradient."""
+    sides, 4-channel first layers, depthwise strips, and the banded weight gradient."""
     g = np.random.default_rng(seed)
     shapes = []
     while len(shapes) < n:
@@ -266,8 +266,8 @@ def random_fast_path_shapes(n, seed):
         elif fam == 1:    # weights-resident 1x1
             L = wl.LayerShape("fp%d_band1" % i, wl.CONV, B, Hh, Ww, int(g.choice([32, 192])), 1, 1, int(g.choice([1, 1, 2])), 0,
                               16 * int(g.integers(1, 14)))
-        elif fam == 2:    # streamed weights
-            L = wl.LayerShape("fp%d_bandw" % i, wl.CONV, B, Hh, Ww, 64 * int(g.integers(2, 5)), 3, 3, 1, 1, 16 * int(g.integers(8, 17)))
+        elif fam == 2:    # 128 and more channels on both sides
+            L = wl.LayerShape("fp%d_wide3" % i, wl.CONV, B, Hh, Ww, 64 * int(g.integers(2, 5)), 3, 3, 1, 1, 16 * int(g.integers(8, 17)))
         elif fam == 3:    # first layer
             S = int(g.integers(1, 9))
             R = int(g.integers(1, 8))
@@ -335,7 +335,7 @@ SMALL_LAUNCHES = [
     wl.conv("ks_s4_no_tap", 2, 18, 32, 16, 1, stride=4, pad=0), wl.LayerShape("ks_8x8", wl.CONV, 1, 12, 12, 16, 8, 8, 1, 3, 16),
     wl.linear("ks_word", 70, 100, 52), wl.linear("ks_word_64", 3000, 100, 260), wl.conv("ks_word_s2_n20", 2, 150, 20, 8, 3, stride=2),
     wl.conv("ks_word_s2_n100", 8, 50, 100, 36, 3, stride=2), wl.LayerShape("word_s5", wl.CONV, 2, 23, 23, 20, 3, 3, 5, 1, 12),
-    wl.conv("past_band", 12, 24, 64, 64, 3), wl.conv("past_bandw", 9, 28, 128, 192, 3), wl.linear("past_gather", 4200, 272, 520),
+    wl.conv("past_band", 12, 24, 64, 64, 3), wl.conv("past_c3x3_128_192", 9, 28, 128, 192, 3), wl.linear("past_gather", 4200, 272, 520),
     wl.LayerShape("ks_9x9", wl.CONV, 1, 14, 14, 16, 9, 9, 1, 4, 32), wl.LayerShape("ks_9x8", wl.CONV, 4, 14, 14, 64, 9, 8, 1, 4, 64),
     wl.LayerShape("ks_11x11_s2", wl.CONV, 2, 23, 21, 32, 11, 11, 2, 5, 48), wl.LayerShape("ks_word_9x8", wl.CONV, 3, 13, 17, 20, 9, 8, 1, 4, 36),
     wl.LayerShape("ks_word_11x11_s3", wl.CONV, 2, 19, 22, 12, 11, 11, 3, 5, 20), wl.LayerShape("past_9x9", wl.CONV, 20, 14, 14, 16, 9, 9, 1, 4, 260),
@@ -526,12 +526,13 @@ def test_framed_tiles(H, hq, L):
             g_track.step(L, "dgrad", dY, W0, H.DevTensor(dY), Wdev, seed=5 if t == 2 else None)
 
 
-# Images too wide for a framed tile's patch, channels off 128: row tiles.
-WIDE_ROW_TILES = [wl.LayerShape("wide_row_tiles", wl.CONV, 1, 66, 130, 192, 3, 3, 1, 1, 192)]
+# Images too wide for a framed tile's patch, channels off 128: the general kernel, on both sides of its widest tile, rows of odd number, one row.
+WIDE_IMAGES = [wl.LayerShape("wide_images", wl.CONV, B, Hh, Ww, C, 3, 3, 1, 1, N)
+               for B, Hh, Ww, C, N in ((1, 66, 130, 192, 192), (3, 23, 127, 192, 320), (2, 19, 251, 320, 192), (90, 1, 126, 192, 192))]
 
 
-@pytest.mark.parametrize("L", WIDE_ROW_TILES, ids=[l.name for l in WIDE_ROW_TILES])
-def test_wide_row_tiles(H, hq, L):
+@pytest.mark.parametrize("L", WIDE_IMAGES, ids=["b%d_%dx%d_c%d_n%d" % (l.B, l.H, l.W, l.C, l.Cout) for l in WIDE_IMAGES])
+def test_images_wider_than_framed_tiles(H, hq, L):
     test_framed_tiles(H, hq, L)
 
 
@@ -910,9 +911,9 @@ SR_SHAPES = [wl.conv("sr_c64", 2, 20, 64, 64, 3),                 # weights-resi
              wl.conv("sr_band_1x1", 2, 20, 192, 32, 1),           # ... 1x1, three column chunks (reduction over 32)
              wl.conv("sr_band_1x1_c192", 2, 20, 32, 192, 1),      # ... 1x1, reduction over 192
              wl.conv("sr_n64", 2, 20, 64, 48, 3),                 # general kernel, 256 x 64 tiles
-             wl.conv("sr_c128", 2, 14, 128, 128, 3),              # streamed-weights kernel
-             wl.conv("sr_bandw_rows", 2, 30, 128, 192, 3),        # ... tiles of rows, last one short; dX has 128 channels
-             wl.conv("sr_bandw_imgs", 3, 10, 192, 128, 3),        # ... tiles of whole images, ragged channel chunk
+             wl.conv("sr_c128", 2, 14, 128, 128, 3),              # 128 and more channels on both sides
+             wl.conv("sr_c3x3_128_192", 2, 30, 128, 192, 3),      # ... off 128 on one
+             wl.conv("sr_c3x3_192_128", 3, 10, 192, 128, 3),      # ... on the reduced one
              wl.conv("sr_c128_s2", 2, 14, 128, 128, 3, stride=2), # general kernel, 128 x 128 tiles
              wl.conv("sr_s2", 2, 12, 32, 48, 3, stride=2),        # strided classes
              wl.conv("sr_c24", 1, 9, 24, 40, 3),                  # 4-byte reduction path, ragged column groups
@@ -1233,7 +1234,7 @@ def test_wgrad_with_range_updates_riding_along(H, hq, L):
 
 
 NARROW = [wl.conv("nb_band", 2, 20, 64, 64, 3), wl.conv("nb_gemm", 2, 9, 24, 40, 3),
-          wl.conv("nb_bandw", 1, 12, 128, 128, 3), wl.conv("nb_first", 2, 23, 4, 48, 7, stride=2),
+          wl.conv("nb_c3x3_128", 1, 12, 128, 128, 3), wl.conv("nb_first", 2, 23, 4, 48, 7, stride=2),
           wl.depthwise("nb_dw", 2, 13, 48), wl.linear("nb_lin", 300, 72, 80)]
 
 
@@ -1266,7 +1267,7 @@ def _const_tensor(shape, code, scale, zp):
 
 
 @pytest.mark.parametrize("L", [wl.conv("deg_band", 2, 20, 64, 64, 3), wl.conv("deg_gemm", 2, 9, 24, 40, 3),
-                               wl.conv("deg_bandw", 1, 12, 128, 128, 3), wl.depthwise("deg_dw", 1, 10, 32),
+                               wl.conv("deg_c3x3_128", 1, 12, 128, 128, 3), wl.depthwise("deg_dw", 1, 10, 32),
                                wl.linear("deg_lin1", 1, 4, 4)], ids=lambda l: l.name)
 def test_degenerate_tensors(H, hq, L):
     """All-zero tensors (the range collapses to a point and the quantizer falls back to scale 1),
