@@ -212,7 +212,10 @@ int hq_try_launch_wgrad_small(const hq_problem *p, const int8_t *X, const hq_qpa
     // worth; beyond, the split-K kernels (a 7 x 7 x 512 layer at batch 32 23 -> 9 us, 8192 pixels under 36 tiles 16 -> 12,
     // 12544 pixels under 128 tiles 22 -> 31).  Rows off 16 bytes are read by words and reach that point earlier.
     // The time here grows with the pixels alone (8.2 us for 4700, 9.2 for 6000, 11.2 for 8000), that of the split-K kernels with
-    // the work: small gradients turn over earlier (3x3 16 -> 16 at 8000 pixels 11.1 us against 9.4, 64 -> 64 11.3 against 11.9).
+    // the work: small gradients turn over earlier (3x3 16 -> 16 at 8000 pixels 11.1 us against 9.4).  3x3 layers of unit stride whose channels are multiples
+    // of 64, against the framed kernel, at 8192 pixels: 64 -> 64 11.5 / 12.9, 64 -> 256 13.2 / 15.8, 128 -> 128 15.2 / 15.6, 64 -> 448 16.9 / 18.4; at 9016 128 -> 128
+    // 17.1 / 15.7, 64 -> 256 14.3 / 15.9.  Of 594 such layers those past 200 tiles and 6300 pixels are on the wrong side, by up to 9 % (192 -> 128 at 8192
+    // 19.1 / 17.6).
     // And every XCD reads all pixels it has a tile of, of whole 128-byte lines (with 256 channels half of them: eight tiles of
     // 32 channels, one per XCD): once they do not fit its L2 the time jumps (3x3 stride 2, 128 -> 64: 4.0 MB 10.1 us, 4.2 MB 15.9
     // against 13.1; but 96 -> 128, where the split-K kernel needs two tiles, 17.1 against 22.5).
