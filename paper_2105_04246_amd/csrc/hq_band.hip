@@ -1,7 +1,7 @@
-// Weights-resident implicit-GEMM convolution for gfx950: the fast path of hq_gemm_fwd /
-// hq_gemm_dgrad (and of pass 1 of the dynamic baseline) for layers whose quantized weights fit
-// in LDS next to two input patches (paper Sec. 3.1 forward / backward linear op; Sec. 3.2 and
-// Sec. 4 for what the epilogue does).
+// Weights-resident implicit-GEMM convolution for gfx950: the path of hq_gemm_fwd / hq_gemm_dgrad (and of pass 1 of
+// the dynamic baseline) for 3x3 layers with 64 reduced channels whose weights fit in LDS next to two input
+// patches, under the strides, paddings and channel counts that hq_regw_kernel does not take (paper Sec. 3.1
+// forward / backward linear op; Sec. 3.2 and Sec. 4 for what the epilogue does).
 //
 // Mapping to the machine
 //   * One workgroup of 8 wavefronts per CU owns a band of output rows of one image and walks
@@ -63,15 +63,15 @@ struct BandArgs {
 constexpr int BAND_THREADS = 512;  // two groups of four wavefronts, which alternate matrix-core phase and epilogue phase in lockstep, half a step apart
 constexpr int BM = 256;            // output pixels per tile: 4 wavefronts x 2 MFMA row blocks
 
-template <int C> __device__ inline int wswz(int i)
-{
-    return (C % 128 == 0) ? (i & 7) : (C % 64 == 0) ? ((i >> 2) & 3) : ((i >> 3) & 1);
-}
+constexpr int C = 64, KSZ = 3;      // reduced channels, sides of the filter
+constexpr int NT = 2;              // 32-channel blocks of a column tile
+
+__device__ inline int wswz(int i) { return (i >> 2) & 3; }
 
 // PR: patch rows prefetched per tile (>= PRmax), PJ: 16-byte column chunks per thread and row.
 // MODE: 0 = 32-bit outputs (first pass of the dynamic baseline), 1 = fused requantization with
 // round-half-even, 2 = fused with stochastic rounding (input gradients).
-template <int C, int KSZ, int NT, int PR, int PJ, int MODE>
+template <int PR, int PJ, int MODE>
 __global__ __launch_bounds__(BAND_THREADS, 1) void hq_band_kernel(const BandArgs a)
 {
     constexpr bool FUSED = MODE != 0, SR = MODE == 2;
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(BAND_THREADS, 1) void hq_band_kernel(const BandArgs
             const int lin = base + tid + BAND_THREADS * k, idx = rotated(lin);
             const int cq = idx % NCH, t = (idx / NCH) % TAPS, row = idx / (NCH * TAPS);
             if (lin < wchunks)
-                *reinterpret_cast<v4i *>(Wl + row * WROW + t * C + 16 * (cq ^ wswz<C>(row & 31))) = wv[k];
+                *reinterpret_cast<v4i *>(Wl + row * WROW + t * C + 16 * (cq ^ wswz(row & 31))) = wv[k];
         }
     };
     v4i wv0[WB];
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(BAND_THREADS, 1) void hq_band_kernel(const BandArgs
     for (int j = 0; j < NT; j++)
 #pragma unroll
         for (int ks = 0; ks < KS; ks++)
-            wbase[j][ks] = (j * 32 + (lane & 31)) * WROW + 16 * ((ks * 2 + (lane >> 5)) ^ wswz<C>(lane & 31));
+            wbase[j][ks] = (j * 32 + (lane & 31)) * WROW + 16 * ((ks * 2 + (lane >> 5)) ^ wswz(lane & 31));
 
     int mn = INT_MAX, mx = INT_MIN;
     unsigned nlo = 0, nhi = 0;
@@ -391,22 +391,22 @@ __global__ __launch_bounds__(BAND_THREADS, 1) void hq_band_kernel(const BandArgs
 
 constexpr size_t BAND_LDS_MAX = 160 * 1024;
 
-template <int C, int KSZ, int NT, int PR, int PJ, int MODE>
+template <int PR, int PJ, int MODE>
 int launch_band_mode(const BandArgs &a, int blocks, size_t lds, hipStream_t s)
 {
     static std::atomic<unsigned long long> allowed{0};
-    auto kern = hq_band_kernel<C, KSZ, NT, PR, PJ, MODE>;
+    auto kern = hq_band_kernel<PR, PJ, MODE>;
     if (!hq_allow_lds(kern, BAND_LDS_MAX, allowed)) return HQ_E_HIP;
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(BAND_THREADS), lds, s, a);
     return hipGetLastError() == hipSuccess ? HQ_OK : HQ_E_HIP;
 }
 
-template <int C, int KSZ, int NT, int PR, int PJ>
+template <int PR, int PJ>
 int launch_band(const BandArgs &a, int blocks, size_t lds, hipStream_t s)
 {
-    if (a.out32) return launch_band_mode<C, KSZ, NT, PR, PJ, 0>(a, blocks, lds, s);
-    if (!a.sr_on) return launch_band_mode<C, KSZ, NT, PR, PJ, 1>(a, blocks, lds, s);
-    return launch_band_mode<C, KSZ, NT, PR, PJ, 2>(a, blocks, lds, s);
+    if (a.out32) return launch_band_mode<PR, PJ, 0>(a, blocks, lds, s);
+    if (!a.sr_on) return launch_band_mode<PR, PJ, 1>(a, blocks, lds, s);
+    return launch_band_mode<PR, PJ, 2>(a, blocks, lds, s);
 }
 
 } // namespace
@@ -417,7 +417,7 @@ int hq_try_launch_band(const hq_problem *p, int dgrad, const int8_t *A, const hq
                        const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
                        int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream, const uint64_t *sr_seed)
 {
-    if (p->kind != HQ_CONV2D || p->R != p->S) return HQ_E_BADSHAPE;
+    if (p->kind != HQ_CONV2D || p->R != KSZ || p->S != KSZ || (dgrad ? p->Cout : p->C) != C) return HQ_E_BADSHAPE;
     if (dgrad && p->stride != 1) return HQ_E_BADSHAPE;
     if (sr_seed && out32) return HQ_E_BADARG;
     const int OH = (p->H + 2 * p->pad - p->R) / p->stride + 1, OW = (p->W + 2 * p->pad - p->S) / p->stride + 1;
@@ -426,21 +426,18 @@ int hq_try_launch_band(const hq_problem *p, int dgrad, const int8_t *A, const hq
     a.out8 = out8; a.out32 = out32; a.outq = outq; a.st = st;
     a.sr_on = sr_seed != nullptr;
     a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
-    int C;
     if (!dgrad) {
-        C = p->C; a.N = p->Cout; a.Hs = p->H; a.Ws = p->W; a.Ho = OH; a.Wo = OW;
+        a.N = p->Cout; a.Hs = p->H; a.Ws = p->W; a.Ho = OH; a.Wo = OW;
         a.stride = p->stride; a.pad = p->pad; a.flip = 0;
     } else {
-        C = p->Cout; a.N = p->C; a.Hs = OH; a.Ws = OW; a.Ho = p->H; a.Wo = p->W;
-        a.stride = 1; a.pad = p->R - 1 - p->pad; a.flip = 1;
+        a.N = p->C; a.Hs = OH; a.Ws = OW; a.Ho = p->H; a.Wo = p->W;
+        a.stride = 1; a.pad = KSZ - 1 - p->pad; a.flip = 1;
     }
-    const int KSZ = p->R;
-    if (C != 64 || KSZ != 3) return HQ_E_BADSHAPE;
-    const int NT = 2, PJ = ((a.Wo - 1) * a.stride + KSZ) * 4 > 256 ? 2 : 1;                 // patch rows of up to 64 / 128 pixels
+    a.PW = (a.Wo - 1) * a.stride + KSZ;
+    const int PJ = a.PW * 4 > 256 ? 2 : 1;                 // patch rows of up to 64 / 128 pixels
     if ((a.N % 16) != 0 || a.Ho * a.Wo >= 65536) return HQ_E_BADSHAPE;
     const int BN = 32 * NT;
     a.npad = (a.N + BN - 1) / BN * BN;
-    a.PW = (a.Wo - 1) * a.stride + KSZ;
     if (a.PW * (C / 16) > 256 * PJ) return HQ_E_BADSHAPE;
 
     // bands: one workgroup per CU
@@ -469,8 +466,8 @@ int hq_try_launch_band(const hq_problem *p, int dgrad, const int8_t *A, const hq
     a.magic_Wo = hq_magic32((unsigned)a.Wo);
     a.count = (unsigned long long)p->B * a.Ho * a.Wo * a.N;
     const int blocks = p->B * a.bands_per_image;
-    if (PJ == 2) return prmax <= 6 ? launch_band<64, 3, 2, 6, 2>(a, blocks, lds, stream) : HQ_E_BADSHAPE;
-    if (prmax <= 8) return launch_band<64, 3, 2, 8, 1>(a, blocks, lds, stream);
-    if (prmax <= 12) return launch_band<64, 3, 2, 12, 1>(a, blocks, lds, stream);
+    if (PJ == 2) return prmax <= 6 ? launch_band<6, 2>(a, blocks, lds, stream) : HQ_E_BADSHAPE;
+    if (prmax <= 8) return launch_band<8, 1>(a, blocks, lds, stream);
+    if (prmax <= 12) return launch_band<12, 1>(a, blocks, lds, stream);
     return HQ_E_BADSHAPE;
 }
