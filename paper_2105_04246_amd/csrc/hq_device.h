@@ -16,6 +16,75 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 __host__ __device__ inline unsigned hq_magic32(unsigned d) { return (unsigned)(((1ull << 32) + d - 1) / d); }
 __device__ inline unsigned hq_magic_div(unsigned x, unsigned magic) { return magic ? __umulhi(x, magic) : x; }
 
+// x / d by multiplication for every x < 2^31 and 1 <= d < 2^31 (Granlund and Montgomery): m = ceil(2^(31 + l) / d) with
+// 2^(l - 1) < d <= 2^l, s = l - 1.  d = 1 is m = 0, "no division"; hq_quot2 is for divisors that are at least 2.
+struct HqDivisor { unsigned m, s; };
+inline HqDivisor hq_divisor(unsigned d)
+{
+    unsigned l = 1;
+    while ((1ull << l) < d) l++;
+    return d < 2 ? HqDivisor{0, 0} : HqDivisor{(unsigned)(((1ull << (31 + l)) + d - 1) / d), l - 1};
+}
+__device__ inline unsigned hq_quot2(unsigned x, HqDivisor d) { return __umulhi(x, d.m) >> d.s; }
+__device__ inline unsigned hq_quot(unsigned x, HqDivisor d) { return d.m ? hq_quot2(x, d) : x; }
+
+// ---------------------------------------------------------------------------------------
+// Framed images: positions of rows of W + 1 and of images of H + 1 rows.  The extra column is the right border of its row and the left
+// border of the next one, the extra row the lower border of its image and the upper border of the next one, so that every tap of a
+// 3x3 filter is one distance in positions for all pixels.  A lane that walks such positions keeps pixel, row and column; the pixel counts as if
+// the frame were not there, so that it is right where row and column lie inside the image.
+// ---------------------------------------------------------------------------------------
+struct HqFrame {
+    int M, H, W;                   // pixels of the batch; image
+    int PW;                        // positions of a row: W + 1
+    HqDivisor image, row;          // (H + 1) * PW and PW
+};
+struct HqFramePlace { int p, y, x; };                        // pixel, row, column; of a distance: that many positions as such
+
+inline HqFrame hq_frame(int B, int H, int W)
+{
+    return HqFrame{B * H * W, H, W, W + 1, hq_divisor((unsigned)(H + 1) * (unsigned)(W + 1)), hq_divisor((unsigned)W + 1)};
+}
+inline HqFramePlace hq_frame_distance(const HqFrame &f, int k)
+{
+    const int image = (f.H + 1) * f.PW, y = k % image / f.PW, x = k % image % f.PW;
+    return HqFramePlace{(k / image * f.H + y) * f.W + x, y, x};
+}
+__device__ inline HqFramePlace hq_frame_place(const HqFrame &f, unsigned k)                 // of position k
+{
+    const unsigned image = (unsigned)(f.H + 1) * (unsigned)f.PW, b = hq_quot2(k, f.image), rem = k - b * image;
+    HqFramePlace t;
+    t.y = (int)hq_quot2(rem, f.row);
+    t.x = (int)(rem - (unsigned)t.y * (unsigned)f.PW);
+    t.p = ((int)b * f.H + t.y) * f.W + t.x;
+    return t;
+}
+__device__ inline void hq_frame_back(const HqFrame &f, HqFramePlace &t)                     // PW + 1 positions: what the first tap meets
+{
+    t.p -= f.W + 1; t.y--; t.x--;
+    if (t.x < 0) { t.x += f.PW; t.y--; t.p++; }
+    if (t.y < 0) { t.y += f.H + 1; t.p += f.W; }
+}
+__device__ inline void hq_frame_advance(const HqFrame &f, const HqFramePlace &d, HqFramePlace &t)
+{
+    t.x += d.x; t.y += d.y; t.p += d.p;
+    const bool cx = t.x >= f.PW;
+    t.x -= cx ? f.PW : 0; t.y += cx; t.p -= cx;
+    const bool cy = t.y > f.H;
+    t.y -= cy ? f.H + 1 : 0; t.p -= cy ? f.W : 0;
+}
+__device__ inline bool hq_frame_inside(const HqFrame &f, const HqFramePlace &t)
+{
+    return ((unsigned)t.p < (unsigned)f.M) & (t.y < f.H) & (t.x < f.W);
+}
+// base + offset where `in`, otherwise `fill`: selected, not branched around.
+__device__ inline const int8_t *hq_source(bool in, const int8_t *base, unsigned long long offset, const void *fill)
+{
+    unsigned long long p = (unsigned long long)(uintptr_t)base + offset;
+    asm("" : "+v"(p));
+    return reinterpret_cast<const int8_t *>((uintptr_t)(in ? p : (unsigned long long)(uintptr_t)fill));
+}
+
 // ---------------------------------------------------------------------------------------
 // 3-byte pixels (RGB inputs): a lane's 4-byte word of the reduction starts at any byte address and
 // can hold bytes of two taps.  Words are loaded unaligned and the unwanted bytes replaced under a

@@ -50,7 +50,7 @@ struct FrameArgs {
     int w0, wr, wc;                // weight tap = w0 + wr * tap row + wc * tap column (mirrored: from the last one down)
     unsigned wrow;                 // bytes per weight row
     unsigned magic_W, magic_H;
-    unsigned image_m, image_s, row_m, row_s;       // k / d = umulhi(k, m) >> s
+    HqDivisor by_image, by_row;    // image and PW
     int m_tiles, n_tiles;
     HqSr sr;
 };
@@ -109,12 +109,10 @@ __global__ __launch_bounds__(FR_THREADS) void hq_frame_kernel(const FrameArgs a)
         for (int k = 0; k < KA; k++) {
             const int block = wave + NW * k < a.blocks ? wave + NW * k : wave;
             const unsigned q = (unsigned)(p0 + 16 * block + (lane >> 2) + a.image - a.PW - 1);
-            const unsigned b1 = __umulhi(q, a.image_m) >> a.image_s, rem = q - b1 * (unsigned)a.image;
-            const unsigned y = __umulhi(rem, a.row_m) >> a.row_s, x = rem - y * (unsigned)a.PW;
+            const unsigned b1 = hq_quot2(q, a.by_image), rem = q - b1 * (unsigned)a.image;
+            const unsigned y = hq_quot2(rem, a.by_row), x = rem - y * (unsigned)a.PW;
             const bool in = (b1 - 1u < (unsigned)a.B) & (y < (unsigned)a.H) & (x < (unsigned)a.W);
-            unsigned long long p = (unsigned long long)(uintptr_t)a.A + (unsigned long long)(((b1 - 1u) * (unsigned)a.H + y) * (unsigned)a.W + x) * (unsigned)a.Cs + swizzled;
-            asm("" : "+v"(p));                                          // (selected, not branched around)
-            src[k] = reinterpret_cast<const int8_t *>((uintptr_t)(in ? p : (unsigned long long)(uintptr_t)hq_fill_rows.w[za & 0xff]));
+            src[k] = hq_source(in, a.A, (unsigned long long)(((b1 - 1u) * (unsigned)a.H + y) * (unsigned)a.W + x) * (unsigned)a.Cs + swizzled, hq_fill_rows.w[za & 0xff]);
             ok |= in ? 1u << k : 0u;
             load_patch(k);
         }
@@ -331,13 +329,7 @@ int hq_try_launch_frame(const hq_problem *p, int dgrad, const int8_t *A, const h
     a.w0 = dgrad ? 8 : 0; a.wr = dgrad ? -3 : 3; a.wc = dgrad ? -1 : 1;
     a.wrow = 9u * (unsigned)a.Cs;
     a.magic_W = hq_magic32((unsigned)a.W); a.magic_H = hq_magic32((unsigned)a.H);
-    auto divisor = [](unsigned d, unsigned &m, unsigned &s) {          // for k < 2^31, d >= 2
-        unsigned l = 1;
-        while ((1ull << l) < d) l++;
-        m = (unsigned)(((1ull << (31 + l)) + d - 1) / d); s = l - 1;
-    };
-    divisor((unsigned)a.image, a.image_m, a.image_s);
-    divisor((unsigned)a.PW, a.row_m, a.row_s);
+    a.by_image = hq_divisor((unsigned)a.image); a.by_row = hq_divisor((unsigned)a.PW);
     a.n_tiles = (a.N + FR_BN - 1) / FR_BN;
     if (sr_seed && out32) return HQ_E_BADARG;
     // The tile (64 s pixels) whose rounds of 256, one workgroup to a compute unit, take the fewest cycles: those of a stage and of a tile's end

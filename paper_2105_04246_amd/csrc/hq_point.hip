@@ -23,7 +23,6 @@ constexpr int PT_THREADS = 512, PT_WAVES = PT_THREADS / 64;
 constexpr int PT_MANY = 2048;                                            // blocks of 32 pixels that fill the chip (256 units, 8 wavefronts)
 constexpr int PT_LDS = 78 * 1024;                                        // two workgroups on a compute unit
 
-struct PointDivisor { unsigned m, s; };                                 // k / d = umulhi(k, m) >> s for k < 2^31; m = 0: d = 1
 struct PointArgs {
     const int8_t *A, *Bw;
     const int32_t *bsum;
@@ -36,7 +35,7 @@ struct PointArgs {
     int M, N, K;
     int nper, nparts, runs;        // blocks of 32 channels of a workgroup; such parts; workgroups per part
     int stride, H, W, OW, image;   // of a strided layer: source rows and columns, output columns and pixels of an image
-    PointDivisor per_image, line;  // by image and OW
+    HqDivisor per_image, line;     // image and OW
     HqSr sr;
 };
 
@@ -62,13 +61,12 @@ __global__ __launch_bounds__(PT_THREADS, 4) void hq_point_kernel(const PointArgs
         hq_global_to_lds16(n < a.N && k < a.K ? src : reinterpret_cast<const int8_t *>(hq_fill_rows.w[0]), smem + 1024 * f);
     }
 
-    auto over = [](unsigned k, PointDivisor d) __attribute__((always_inline)) { return d.m ? __umulhi(k, d.m) >> d.s : k; };
     // ---- a block of 32 pixels: lane's pixel, 16 channels of every 32.  What is read for channels past the last (K an odd number of 16)
     // meets weights of 0; pixels past the last repeat it.
     auto fetch = [&](int block, v4i (&af)[KS]) __attribute__((always_inline)) {
         unsigned m = (unsigned)min(32 * block + r32, a.M - 1);
         if (a.stride > 1) {
-            const unsigned b = over(m, a.per_image), rem = m - b * (unsigned)a.image, y = over(rem, a.line);
+            const unsigned b = hq_quot(m, a.per_image), rem = m - b * (unsigned)a.image, y = hq_quot(rem, a.line);
             m = (b * (unsigned)a.H + y * (unsigned)a.stride) * (unsigned)a.W + (rem - y * (unsigned)a.OW) * (unsigned)a.stride;
         }
         const int8_t *p = a.A + (size_t)m * a.K;
@@ -199,13 +197,8 @@ int hq_try_launch_point(const hq_problem *p, int dgrad, const int8_t *A, const h
     a.A = A; a.Bw = Bw; a.bsum = bsum; a.aq = aq; a.bq = bq; a.range = range;
     a.out8 = out8; a.out32 = out32; a.outq = outq; a.st = st;
     a.M = (int)M; a.N = N; a.K = K;
-    auto divisor = [](unsigned d) {
-        unsigned l = 1;
-        while ((1ull << l) < d) l++;
-        return d < 2 ? PointDivisor{0, 0} : PointDivisor{(unsigned)(((1ull << (31 + l)) + d - 1) / d), l - 1};
-    };
     a.stride = p->stride; a.H = p->H; a.W = p->W; a.OW = OW; a.image = OH * OW;
-    a.per_image = divisor((unsigned)a.image); a.line = divisor((unsigned)OW);
+    a.per_image = hq_divisor((unsigned)a.image); a.line = hq_divisor((unsigned)OW);
     const int mode = out32 ? 0 : sr_seed ? 2 : 1;
     const int ks = (K + 31) / 32, blocks = (N + 31) / 32, most = PT_LDS / (1024 * ks + 128);
     const int all = (int)((M + 31) / 32);

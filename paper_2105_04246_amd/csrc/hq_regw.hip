@@ -33,8 +33,6 @@ constexpr int RW_RING = 1792;                                            // posi
 constexpr int RW_PLANE = (RW_RING + RW_BLOCK) * 16;                     // bytes of a plane: 16 channels of every position
 constexpr int RW_WEIGHTS = 64 * 9 * 64;
 
-struct RegwDivisor { unsigned m, s; };                                  // k / d = umulhi(k, m) >> s for k < 2^31; m = 0: d = 1
-struct RegwAdvance { int p, y, x; };                                    // a number of pixels as positions, rows and columns, or of positions as pixels ...
 struct RegwArgs {
     const int8_t *A, *Bw;
     const int32_t *bsum;
@@ -44,11 +42,12 @@ struct RegwArgs {
     int32_t *out32;
     hq_qparams *outq;
     hq_stats *st;
-    int M, N, H, W, PW;            // output pixels, channels; image; positions of a row: W + 1
+    HqFrame frame;
+    int N;                         // output channels
     int flip;
     int units, nparts, runs;       // units; blocks of 64 channels; workgroups per channel block
-    RegwDivisor image, line, fimage, fline;          // H * W and W; (H + 1) * PW and PW
-    RegwAdvance unit, loads;       // a unit's pixels; 256 positions
+    HqDivisor image, line;         // H * W and W
+    HqFramePlace unit, loads;      // a unit's pixels as positions (p), rows and columns; four blocks of positions
     HqSr sr;
 };
 
@@ -80,49 +79,33 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
 
     // ---- input: 16 channels of 64 positions per load; a wavefront loads two planes of every fourth block.
     // The ring's place 0 is the first position under the run's first pixel, PW + 1 before the pixel's own.
-    auto over = [](unsigned k, RegwDivisor d) __attribute__((always_inline)) { return d.m ? __umulhi(k, d.m) >> d.s : k; };
+    const HqFrame &f = a.frame;
     auto position = [&](unsigned k, int &y, int &x) __attribute__((always_inline)) {   // of a pixel
-        const unsigned b = over(k, a.image), rem = k - b * (unsigned)(a.H * a.W);
-        y = (int)over(rem, a.line);
-        x = (int)(rem - (unsigned)y * (unsigned)a.W);
-        return ((int)b * (a.H + 1) + y) * a.PW + x;
+        const unsigned b = hq_quot(k, a.image), rem = k - b * (unsigned)(f.H * f.W);
+        y = (int)hq_quot(rem, a.line);
+        x = (int)(rem - (unsigned)y * (unsigned)f.W);
+        return ((int)b * (f.H + 1) + y) * f.PW + x;
     };
     int y0, x0, oy, ox;
     const int origin = position((unsigned)(u_begin * RW_UNIT), y0, x0);
     unsigned place = (unsigned)(position((unsigned)(u_begin * RW_UNIT + 32 * wave + r32), oy, ox) - origin);     // of the lane's pixel's first tap
     auto needed = [&](int u) __attribute__((always_inline)) {           // blocks up to the unit's last position
         int y, x;
-        return (unsigned)(position((unsigned)(min((u + 1) * RW_UNIT, a.M) - 1), y, x) + 2 * a.PW + 2 - origin) / RW_BLOCK + 1;
+        return (unsigned)(position((unsigned)(min((u + 1) * RW_UNIT, f.M) - 1), y, x) + 2 * f.PW + 2 - origin) / RW_BLOCK + 1;
     };
-    // pixel (as if the frame were not there, so that it is right where row and column lie inside the image), row and column of the lane's
-    // next position to load
-    int lp, ly, lx;
-    {
-        const unsigned k = (unsigned)(origin + RW_BLOCK * (wave & 3) + lane);
-        const unsigned b = over(k, a.fimage), rem = k - b * (unsigned)((a.H + 1) * a.PW);
-        ly = (int)over(rem, a.fline);
-        lx = (int)(rem - (unsigned)ly * (unsigned)a.PW);
-        lp = ((int)b * a.H + ly) * a.W + lx - (a.W + 1);
-        ly--; lx--;
-        if (lx < 0) { lx += a.PW; ly--; lp++; }
-        if (ly < 0) { ly += a.H + 1; lp += a.W; }
-    }
+    // the lane's next position to load
+    HqFramePlace next = hq_frame_place(f, (unsigned)(origin + RW_BLOCK * (wave & 3) + lane));
+    hq_frame_back(f, next);
     const int za = __builtin_amdgcn_readfirstlane(a.aq->zero_point);
     const int8_t *input = a.A + 32 * (wave >> 2);
     const int8_t *src;
     bool pending = true;                                                 // `src` has been used
     int second;                                                          // the other plane's distance: a position outside an image has one row of fill
     auto prepare = [&]() __attribute__((always_inline)) {
-        const bool there = ((unsigned)lp < (unsigned)a.M) & (ly < a.H) & (lx < a.W);
-        unsigned long long p = (unsigned long long)(uintptr_t)input + (unsigned long long)(unsigned)lp * 64u;
-        asm("" : "+v"(p));                                              // (selected, not branched around)
-        src = reinterpret_cast<const int8_t *>((uintptr_t)(there ? p : (unsigned long long)(uintptr_t)hq_fill_rows.w[za & 0xff]));
+        const bool there = hq_frame_inside(f, next);
+        src = hq_source(there, input, (unsigned long long)(unsigned)next.p * 64u, hq_fill_rows.w[za & 0xff]);
         second = there ? 16 : 0;
-        lx += a.loads.x; ly += a.loads.y; lp += a.loads.p;
-        const bool cx = lx >= a.PW;
-        lx -= cx ? a.PW : 0; ly += cx; lp -= cx;
-        const bool cy = ly > a.H;
-        ly -= cy ? a.H + 1 : 0; lp -= cy ? a.W : 0;
+        hq_frame_advance(f, a.loads, next);
         pending = false;
     };
     unsigned block = wave & 3;                                           // the wavefront's next
@@ -187,14 +170,14 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
         auto rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
             for (int r = 0; r < 3; r++) {
-                const unsigned k = place + (unsigned)(r * a.PW);
+                const unsigned k = place + (unsigned)(r * f.PW);
                 row[r] = mine + 16 * min(k, k - RW_RING);               // (k < 2 * RW_RING)
             }
             ox += a.unit.x; oy += a.unit.y; place += (unsigned)a.unit.p;
-            const bool cx = ox >= a.W;
-            ox -= cx ? a.W : 0; oy += cx; place += cx;
-            const bool cy = oy >= a.H;
-            oy -= cy ? a.H : 0; place += cy ? (unsigned)a.PW : 0u;
+            const bool cx = ox >= f.W;
+            ox -= cx ? f.W : 0; oy += cx; place += cx;
+            const bool cy = oy >= f.H;
+            oy -= cy ? f.H : 0; place += cy ? (unsigned)f.PW : 0u;
             place = min(place, place - RW_RING);
         };
         auto fetch = [&](int t) __attribute__((always_inline)) {
@@ -240,7 +223,7 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
         // channels of one pixel a lane it would touch 64 lines, a quarter of each: 44 us against 30 for 128 x 56 x 56 x 64).
         auto finish32 = [&]() __attribute__((always_inline)) {
             const unsigned mine32 = (unsigned)(4 * half * a.N + r32);
-            const bool whole = first + 32 <= a.M;
+            const bool whole = first + 32 <= f.M;
 #pragma unroll
             for (int nb = 0; nb < 2; nb++) {
                 int c[16];
@@ -252,18 +235,18 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
                 for (int e = 0; e < 16; e++) {
                     asm("" : "+s"(out));                                // (a uniform address and the lane's part, not 16 addresses)
                     if (whole) out[mine32] = c[e];
-                    else if (first + 8 * (e >> 2) + (e & 3) + 4 * half < a.M) { out[mine32] = c[e]; mn = min(mn, c[e]); mx = max(mx, c[e]); }
+                    else if (first + 8 * (e >> 2) + (e & 3) + 4 * half < f.M) { out[mine32] = c[e]; mn = min(mn, c[e]); mx = max(mx, c[e]); }
                     out += e % 4 == 3 ? 5 * a.N : a.N;
                 }
             }
         };
         // Returns whether all the wavefront's stores were issued.
         auto finish = [&]() __attribute__((always_inline)) {
-            const bool whole = first + 32 <= a.M;
+            const bool whole = first + 32 <= f.M;
             const int pixel = first + r32;
             if constexpr (MODE == 0) {
                 finish32();
-            } else if (pixel < a.M) {
+            } else if (pixel < f.M) {
 #pragma unroll
                 for (int nb = 0; nb < 2; nb++) {
                     int c[16];
@@ -300,7 +283,7 @@ __global__ __launch_bounds__(RW_THREADS, 2) void hq_regw_kernel(const RegwArgs a
     hq_block_stats_commit_n<RW_THREADS>(mn, mx, nlo, nhi, a.st, red);
     if (blockIdx.x == 0 && tid == 0) {
         a.st->acc_scale = acc_scale;
-        atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)a.M * (unsigned long long)a.N);
+        atomicAdd((unsigned long long *)&a.st->count, (unsigned long long)f.M * (unsigned long long)a.N);
         if (MODE != 0) *a.outq = a.range->qp;
     }
 }
@@ -321,27 +304,20 @@ int hq_try_launch_regw(const hq_problem *p, int dgrad, const int8_t *A, const hq
     const int lines = (2 * RW_UNIT - 2) / W + 1, images = (2 * RW_UNIT - 2) / (H * W) + 1;
     if (2 * RW_UNIT + lines + images * (W + 1) + 2 * (W + 1) + 2 + RW_BLOCK > RW_RING) return HQ_E_BADSHAPE;
     RegwArgs a = {};
-    a.PW = W + 1;
+    a.frame = hq_frame(p->B, H, W);
     a.A = A; a.Bw = Bw; a.bsum = bsum; a.aq = aq; a.bq = bq; a.range = range;
     a.out8 = out8; a.out32 = out32; a.outq = outq; a.st = st;
-    a.M = (int)M; a.N = N; a.H = H; a.W = W; a.flip = dgrad;
+    a.N = N; a.flip = dgrad;
     a.units = (int)((M + RW_UNIT - 1) / RW_UNIT);
     a.nparts = N / 64;
     a.runs = 256 / a.nparts;
     if (a.runs < 1) a.runs = 1;
     if (a.runs > a.units) a.runs = a.units;
-    auto divisor = [](unsigned d) {
-        unsigned l = 1;
-        while ((1ull << l) < d) l++;
-        return d < 2 ? RegwDivisor{0, 0} : RegwDivisor{(unsigned)(((1ull << (31 + l)) + d - 1) / d), l - 1};
-    };
-    const int image = H * W, fimage = (H + 1) * a.PW, step = 4 * RW_BLOCK;
-    a.image = divisor((unsigned)image); a.line = divisor((unsigned)W);
-    a.fimage = divisor((unsigned)fimage); a.fline = divisor((unsigned)a.PW);
+    const int image = H * W;
+    a.image = hq_divisor((unsigned)image); a.line = hq_divisor((unsigned)W);
     a.unit.y = RW_UNIT % image / W; a.unit.x = RW_UNIT % image % W;
-    a.unit.p = RW_UNIT / image * fimage + a.unit.y * a.PW + a.unit.x;
-    a.loads.y = step % fimage / a.PW; a.loads.x = step % fimage % a.PW;
-    a.loads.p = (step / fimage * H + a.loads.y) * W + a.loads.x;
+    a.unit.p = RW_UNIT / image * (H + 1) * (W + 1) + a.unit.y * (W + 1) + a.unit.x;
+    a.loads = hq_frame_distance(a.frame, 4 * RW_BLOCK);
     if (sr_seed && out32) return HQ_E_BADARG;
     a.sr = sr_seed ? HqSr{(unsigned)*sr_seed, (unsigned)(*sr_seed >> 32)} : HqSr{0, 0};
     const int mode = out32 ? 0 : sr_seed ? 2 : 1;

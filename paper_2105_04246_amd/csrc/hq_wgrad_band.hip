@@ -51,26 +51,14 @@ constexpr int SUMS = 64 + 9 * 32;             // column sums that a workgroup ma
 constexpr int EXCHANGE = WB_WAVES * 6 * 1024; // LDS bytes in which the groups' sums meet
 static_assert(L == XLOAD * WB_WAVES && GLOADS * GLOAD * WB_WAVES == L, "one load of the input per wavefront and chunk");
 
-// k / d by multiplication, for 2 <= d < 2^31 and k < 2^31: m = ceil(2^(31 + l) / d) with 2^(l - 1) < d <= 2^l, s = l - 1.
-struct WbandDiv { unsigned m, s; };
-WbandDiv wband_div(unsigned d)
-{
-    unsigned l = 1;
-    while ((1ull << l) < d) l++;
-    return WbandDiv{(unsigned)(((1ull << (31 + l)) + d - 1) / d), l - 1};
-}
-__device__ inline unsigned wband_quot(unsigned k, WbandDiv d) { return __umulhi(k, d.m) >> d.s; }
-
-struct WbandAdvance { int p, y, x; };                        // a number of positions as pixels, rows and columns
 struct WbandArgs {
     const int8_t *X, *G;
     const hq_qparams *xq, *gq;
     int32_t *partial;              // [slot][SLOT_V4] 16-byte words: a workgroup's 64 x 9 x 32 sums
     int32_t *gsums, *xsums;        // [run][N], [run][9][C]: column sums of dY and of the input taps
-    int M, H, W, C, N;             // pixels of the batch; image, channels of input and gradient
-    int PW;                        // positions of a row: W + 1
-    WbandAdvance gadv, xadv;       // from one load to the next
-    WbandDiv by_image, by_row;     // (H + 1) * PW and PW as divisors
+    HqFrame frame;
+    int C, N;                      // channels of input and gradient
+    HqFramePlace gstep, xstep;     // from one load to the next
     int units, per_block, splits;  // runs are cut at units of two steps of every group
     int cparts, nparts;            // C / 32, N / 64
     int lead;                      // chunks by which the input is ahead of the gradient: those of 2 * PW + 2 positions and a read's overhang
@@ -104,29 +92,10 @@ __global__ __launch_bounds__(WB_THREADS) void hq_wgrad_band_kernel(const WbandAr
     // ---- loads: a wavefront brings 16 positions x 64 channels of dY, 1 KB of the input; lane l lands at 16 * l
     const int grow = lane >> 2, xrow = lane / (XROW / 16);
     const int gchunk = 16 * ((lane & 3) ^ (grow & 4 ? 2 : 0)), xchunk = 16 * (lane & 1);
-    // pixel, row and column of the lane's next position: of the gradient, and of the input, PW + 1 positions before (the pixel counts
-    // as if the frame were not there, so that it is right where row and column lie inside the image)
-    const unsigned image = (unsigned)(a.H + 1) * (unsigned)a.PW;
-    auto locate = [&](unsigned k, int &p, int &y, int &x) __attribute__((always_inline)) {
-        const unsigned b = wband_quot(k, a.by_image), rem = k - b * image;
-        y = (int)wband_quot(rem, a.by_row);
-        x = (int)(rem - (unsigned)y * (unsigned)a.PW);
-        p = ((int)b * a.H + y) * a.W + x;
-    };
-    int gp, gy, gx, xp, xy, xx;
-    locate(begin + (unsigned)(GLOAD * wave + grow), gp, gy, gx);
-    locate(begin + (unsigned)(XLOAD * wave + xrow), xp, xy, xx);
-    xp -= a.W + 1; xy--; xx--;
-    if (xx < 0) { xx += a.PW; xy--; xp++; }
-    if (xy < 0) { xy += a.H + 1; xp += a.W; }
-    auto advance = [&](const WbandAdvance &d, int &p, int &y, int &x) __attribute__((always_inline)) {
-        x += d.x; y += d.y; p += d.p;
-        const bool cx = x >= a.PW;
-        x -= cx ? a.PW : 0; y += cx; p -= cx;
-        const bool cy = y > a.H;
-        y -= cy ? a.H + 1 : 0; p -= cy ? a.W : 0;
-    };
-    auto inside = [&](int p, int y, int x) __attribute__((always_inline)) { return ((unsigned)p < (unsigned)a.M) & (y < a.H) & (x < a.W); };
+    // the lane's next position, of the gradient and of the input, PW + 1 positions before
+    HqFramePlace gpl = hq_frame_place(a.frame, begin + (unsigned)(GLOAD * wave + grow));
+    HqFramePlace xpl = hq_frame_place(a.frame, begin + (unsigned)(XLOAD * wave + xrow));
+    hq_frame_back(a.frame, xpl);
     const unsigned gbase = a.ring + TAIL * XROW, mbase = gbase + GBYTES;
     const int zx = __builtin_amdgcn_readfirstlane(a.xq->zero_point);
     const int8_t *xfill = reinterpret_cast<const int8_t *>(hq_fill_rows.w[zx & 0xff]), *gfill = reinterpret_cast<const int8_t *>(hq_fill_rows.w[0]);
@@ -139,19 +108,14 @@ __global__ __launch_bounds__(WB_THREADS) void hq_wgrad_band_kernel(const WbandAr
     // request theirs at once, that arithmetic would hold up the MFMAs.
     const int8_t *xsrc, *gsrc[GLOADS];
     bool gin[GLOADS];
-    auto source = [&](bool in, const int8_t *base, unsigned pixel, unsigned channels, unsigned chunk16, const int8_t *fill) __attribute__((always_inline)) {
-        unsigned long long p = (unsigned long long)(uintptr_t)base + ((unsigned long long)pixel * channels + chunk16);
-        asm("" : "+v"(p));                                              // (selected, not branched around)
-        return reinterpret_cast<const int8_t *>((uintptr_t)(in ? p : (unsigned long long)(uintptr_t)fill));
-    };
     auto prepare_x = [&]() __attribute__((always_inline)) {
-        xsrc = source(inside(xp, xy, xx), Xc, (unsigned)xp, (unsigned)a.C, (unsigned)xchunk, xfill);
-        advance(a.xadv, xp, xy, xx);
+        xsrc = hq_source(hq_frame_inside(a.frame, xpl), Xc, (unsigned long long)(unsigned)xpl.p * (unsigned)a.C + (unsigned)xchunk, xfill);
+        hq_frame_advance(a.frame, a.xstep, xpl);
     };
     auto prepare_g = [&](int i) __attribute__((always_inline)) {
-        gin[i] = inside(gp, gy, gx);
-        gsrc[i] = source(gin[i], Gn, (unsigned)gp, (unsigned)a.N, (unsigned)gchunk, gfill);
-        advance(a.gadv, gp, gy, gx);
+        gin[i] = hq_frame_inside(a.frame, gpl);
+        gsrc[i] = hq_source(gin[i], Gn, (unsigned long long)(unsigned)gpl.p * (unsigned)a.N + (unsigned)gchunk, gfill);
+        hq_frame_advance(a.frame, a.gstep, gpl);
     };
     auto load_x = [&]() __attribute__((always_inline)) {
         hq_lds_load16(xsrc, xdst);
@@ -193,7 +157,7 @@ __global__ __launch_bounds__(WB_THREADS) void hq_wgrad_band_kernel(const WbandAr
     // (rows of 64 bytes: their halves are swapped by bit 2 of the row's number, which steps of 8 positions and the rings' lengths leave
     // alone).  The step's place in the ring is the same for all lanes; a lane is at most 39 rows behind it, hence the ring's tail.
     const int j16 = lane & 15, half = lane >> 5, row = 16 * half + (j16 >> 1), fcol = 16 * ((lane >> 4) & 1) + 8 * (j16 & 1);
-    const int xfirst = 32 * grp + fr * a.PW;
+    const int xfirst = 32 * grp + fr * a.frame.PW;
     const unsigned xlane = row * XROW + fcol;
     const unsigned glane = gbase + (32 * grp + row) * 64 + 32u * ((unsigned)nblk ^ ((unsigned)row >> 2 & 1)) + fcol;
     unsigned xat = (unsigned)xfirst * XROW, gat = 0, mat = 0;           // the chunk's places in the ring and in the buffers
@@ -394,7 +358,7 @@ WbandPlan wband_plan(const hq_problem *p)
     if (p->kind != HQ_CONV2D || p->R != 3 || p->S != 3 || p->stride != 1 || p->pad != 1) return pl;
     if (p->C % 64 != 0 || p->Cout % 64 != 0) return pl;
     const unsigned long long positions = (unsigned long long)p->B * (p->H + 1) * (p->W + 1);
-    if (positions >= 1ull << 30) return pl;                           // (wband_quot, with room for what is requested past the end)
+    if (positions >= 1ull << 30) return pl;                           // (hq_quot2, with room for what is requested past the end)
     pl.lead = (2 * (p->W + 1) + 10 + L - 1) / L;
     pl.ring = (unsigned)(pl.lead + 3) * L * XROW;
     pl.lds = std::max((size_t)pl.ring + TAIL * XROW + GBYTES + 3 * L, (size_t)EXCHANGE + GROUPS * SUMS * 4);
@@ -433,20 +397,12 @@ int hq_try_launch_wgrad_band(const hq_problem *p, const int8_t *X, const hq_qpar
     a.partial = static_cast<int32_t *>(ws);
     a.gsums = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + pl.partial_bytes);
     a.xsums = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + pl.partial_bytes + pl.gsums_bytes);
-    a.M = p->B * p->H * p->W; a.H = p->H; a.W = p->W; a.C = p->C; a.N = p->Cout;
-    a.PW = p->W + 1;
-    a.by_image = wband_div((unsigned)(p->H + 1) * (unsigned)a.PW); a.by_row = wband_div((unsigned)a.PW);
+    a.frame = hq_frame(p->B, p->H, p->W);
+    a.C = p->C; a.N = p->Cout;
     a.units = pl.units; a.per_block = pl.per_block; a.splits = pl.splits;
     a.cparts = p->C / 32; a.nparts = p->Cout / 64;
     a.lead = pl.lead; a.ring = pl.ring;
-    const int image = (p->H + 1) * a.PW;
-    auto advance = [&](int k) {
-        WbandAdvance d;
-        d.y = k % image / a.PW; d.x = k % image % a.PW;
-        d.p = (k / image * p->H + d.y) * p->W + d.x;
-        return d;
-    };
-    a.gadv = advance(GLOAD * WB_WAVES); a.xadv = advance(L);
+    a.gstep = hq_frame_distance(a.frame, GLOAD * WB_WAVES); a.xstep = hq_frame_distance(a.frame, L);
     static std::atomic<unsigned long long> allowed{0};
     if (!hq_allow_lds(hq_wgrad_band_kernel, 160 * 1024, allowed)) return HQ_E_HIP;
     hipLaunchKernelGGL(hq_wgrad_band_kernel, dim3((unsigned)(pl.parts * pl.splits)), dim3(WB_THREADS), pl.lds, stream, a);
@@ -455,7 +411,7 @@ int hq_try_launch_wgrad_band(const hq_problem *p, const int8_t *X, const hq_qpar
     ra.first = (int)(quads / 64);
     const dim3 fgrid((unsigned)(quads / 64) + (unsigned)ra.n);
     auto finalize = [&](auto kernel, int ty) {
-        hipLaunchKernelGGL(kernel, fgrid, dim3(64 * ty), 0, stream, a.partial, a.gsums, a.xsums, xq, gq, (unsigned)a.M, a.N, a.C, pl.splits, dW, dW_acc, ra);
+        hipLaunchKernelGGL(kernel, fgrid, dim3(64 * ty), 0, stream, a.partial, a.gsums, a.xsums, xq, gq, (unsigned)a.frame.M, a.N, a.C, pl.splits, dW, dW_acc, ra);
     };
     if (pl.splits >= 48) finalize(wband_finalize_kernel<16>, 16);
     else if (pl.splits >= 12) finalize(wband_finalize_kernel<4>, 4);
