@@ -58,7 +58,7 @@ int hq_try_launch_direct(const hq_problem *p, int dgrad, const int8_t *A, const 
                          const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8,
                          int32_t *out32, hq_qparams *outq, hq_stats *st, hipStream_t stream);
 
-// 3x3 stride-1 layers of 128 or more channels on both sides, the reduced ones a multiple of 64, on images up to about 125 pixels wide;
+// 3x3 stride-1 layers of 128 or more channels on both sides, the reduced ones a multiple of 64, on images up to about 125 pixels wide (one row: 93);
 // HQ_E_BADSHAPE: not covered.  sr_seed as for hq_launch_gemm.
 int hq_try_launch_frame(const hq_problem *p, int dgrad, const int8_t *A, const hq_qparams *aq, const int8_t *Bw,
                         const hq_qparams *bq, const int32_t *bsum, const hq_range *range, int8_t *out8, int32_t *out32,

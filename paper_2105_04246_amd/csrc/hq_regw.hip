@@ -13,7 +13,8 @@
 // multiplied (the run's first pixel starts the ring; a position outside the images loads a row of the zero point).  The ring is four
 // planes of 16 channels: a fragment's 32 positions are 512 consecutive bytes, without bank conflicts, and the taps of a filter row and the
 // halves of the channels are immediate offsets from one address per filter row.  What the framed stream costs in positions (a unit
-// of 3 x 3 images has 455) it costs only in loads: the matrix work is on pixels.  The ring holds two units of images up to 403 wide.
+// of 3 x 3 images has 455) it costs only in loads: the matrix work is on pixels.  The ring holds two units of images up to 403 wide that have
+// more than 510 pixels; every further image in two units is another extra row (one-row images: up to 241 wide, and 256 to 302).
 //
 // Before, patches of padded rows were copied through registers into two buffers, 1,000 of 4,950 clocks of a unit, for images up
 // to 121 wide.  Measured, before -> now (us): 256 x 56 x 56 x 64 40.5 -> 38.3, 128 x 56 x 56 x 64 24.8 -> 23.2, 16 x 56 x 56 x 64 7.8 -> 7.2,
